@@ -3,27 +3,26 @@
 // matrix, so the weights are read once per prompt chunk instead of once per 64 rows.  Included by la_mfma.hip (it needs
 // the model's packed weight streams).
 //
-// Per layer: pf_prep (row factors of the norm, x * gain as half-precision MFMA operand fragments) -> pf_gemm QKV
-// (epilogue: row factor, RoPE, K and V rows into the cache, q as operand fragments) -> pf_attn (causal flash attention
-// of every 16-row tile over the cache) -> pf_gemm O (x += ...) -> pf_prep -> pf_gemm gate/up (epilogue: SwiGLU into operand
-// fragments) -> pf_gemm down (x += ...).  The arithmetic is the block kernel's (half-precision operands, f32
-// accumulation, the cache's 16-bit type in the attention); only the order of the sums differs.
+// Per layer: pf_norm (the residual stream takes in the down projection of the layer before; sums of squares and x * gain as
+// half-precision MFMA operand fragments) -> pf_tile QKV (epilogue: row factor, RoPE, K and V rows into the cache, q as
+// operand fragments) -> pf_attn (causal flash attention over the cache) -> pf_tile O (products of the contraction's
+// slices) -> pf_norm -> pf_tile gate/up (epilogue: SwiGLU into operand fragments) -> pf_tile down.  The arithmetic is the
+// block kernel's (half-precision operands, f32 accumulation, the cache's 16-bit type in the attention); only the order
+// of the sums differs.
 //
-// pf_gemm: one wave computes 64 rows x 128 columns (4 x 8 MFMA tiles, 128 accumulator registers) straight from
-// memory: the activation operand is stored as MFMA fragments [k-tile][row tile][lane][8 halves] by its producer and a
-// weight fragment is the 1 KB block of the per-CU streams the block kernel reads, so both operands are single 16-byte
-// loads per lane and there is no LDS stage; the four waves of a workgroup share their rows (the A fragments hit L1) and
-// take adjacent column groups.  Next k-tile's twelve fragments are requested before the current ones are multiplied.
+// Both operands of the products are MFMA fragments of 1 KB: the activations are stored as [k-tile][row tile][lane][8
+// halves] by their producers, and a weight fragment is the 1 KB block of the per-CU streams the block kernel reads.
 #pragma once
 
 namespace la {
 
-constexpr int PF_ROWS = 1024;  // rows of one prompt chunk (buffers are sized for it)
-constexpr int PF_MIN = 128;    // shorter prompts go through the block kernel
-constexpr int PF_NS = 4;       // k-tiles a wave of the matrix product keeps in flight: all operands in registers
-constexpr int PF_NS_LDS = 4;   // ... weight fragments through LDS (a step takes half the memory latency at four, measured)
+constexpr int PF_ROWS = 1024;   // rows of one prompt chunk (buffers are sized for it)
+constexpr int PF_MIN = 128;     // shorter prompts go through the block kernel
+constexpr int PF_CHUNKS = 32;   // partial sums of squares per row (column chunks of pf_norm_kernel)
+constexpr int PF_PART_ROWS = 2048;  // rows of all slices' products together
+constexpr int PF_MAX_SPLIT = 8; // most slices of a contraction
 
-enum PfMode { PF_QKV = 0, PF_RESID = 1, PF_GATEUP = 2 };
+enum PfMode { PF_QKV = 0, PF_PART = 1, PF_GATEUP = 2 };
 
 struct PfGemm {
   const uint8_t *wstream;
@@ -32,12 +31,14 @@ struct PfGemm {
   int G, NW;       // workgroups and MFMA waves the streams were packed for
   int n_prev, prev_ntiles[3], prev_KT[3];
   int ntiles, KT;
+  int S;              // slices of the contraction (PART; else 1)
   const uint16_t *A;  // operand fragments [KT][RT][64][8]
-  int RT, M;          // row tiles of the chunk (buffers hold RT4 = RT rounded up to 4), rows
+  int RT, M;          // row tiles the buffers are laid out for, rows
   // epilogues
-  float *x;           // RESID: residual stream [M][d], updated in place
+  float *part;        // PART: products of slice s [S][M][d]
   int d;
-  const float *rs;    // QKV, GATEUP: row factors of the norm
+  const float *ss;    // QKV, GATEUP: partial sums of squares of the norm's input [M][PF_CHUNKS]
+  float inv_d, eps;
   const float *cs;    // QKV: cos, sin [M][dh/2][2]
   uint16_t *Kc, *Vc;  // QKV: this layer's cache
   uint16_t *Q;        // QKV: q fragments [Hq][RT][dh/32][64][8]
@@ -50,8 +51,11 @@ struct PfGemm {
 // tile t0 + j.  Every store is then an 8- or 16-byte vector (the cache's V layout aside), and the partner of a RoPE
 // pair or of a gate channel (8 columns further) sits 32 lanes further.
 template <int MODE, int NTW>
-__device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[4][NTW], int r0, int t0, int lane) {
+__device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[4][NTW], int r0, int t0, int lane, int slice, LDS_AS const float *rf) {
   const int q4 = lane >> 4, c16 = lane & 15;
+  float rsm[4];  // row factors of the norm
+#pragma unroll
+  for (int m = 0; m < 4; ++m) rsm[m] = MODE == PF_PART ? 0.f : rf[16 * m + c16];
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     const int t = t0 + j;
@@ -60,13 +64,10 @@ __device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[
     for (int m = 0; m < 4; ++m) {
       const int row = 16 * (r0 + m) + c16;
       const f32x4 v = acc[m][j];
-      if (MODE == PF_RESID) {
-        if (row < p.M) {
-          f32x4 *xp = reinterpret_cast<f32x4 *>(p.x + (size_t)row * p.d + 16 * t + 4 * q4);
-          *xp = *xp + v;
-        }
+      if (MODE == PF_PART) {
+        if (row < p.M) *reinterpret_cast<f32x4 *>(p.part + ((size_t)slice * p.M + row) * p.d + 16 * t + 4 * q4) = v;
       } else {
-        const float rsf = row < p.M ? p.rs[row] : 0.f;
+        const float rsf = rsm[m];
         f32x4 other;
 #pragma unroll
         for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(v[i], 32, 64);
@@ -121,44 +122,96 @@ __device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[
   }
 }
 
-// NTW: column tiles per wave (8: 128 columns, for the wide matrices; 4: 64 columns, so that the 4096-column matrices
-// still give every CU a workgroup); NS: k-tiles in flight per wave (NS - 1 requested ahead of the one being multiplied).
-template <int MODE, int NTW, int NS>
-__global__ __launch_bounds__(256) void pf_gemm_kernel(PfGemm p) {
+template <int N>
+__device__ __forceinline__ void pf_wait_lds_reads() {  // at most N LDS operations of this wave outstanding
+  asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// One product.  A workgroup computes a tile of 64 WM rows x 16 WN NTW columns, a wave 64 rows x 16 NTW columns of it; the
+// fragments of a k-tile (32 deep) come in once per workgroup with direct-to-LDS loads, into a ring of NS stages.
+// Bound: the matrix cores, if the operands get there: a wave reads 4 + NTW fragments of LDS for 4 NTW products (16 cycles
+// each, four waves' reads sharing 128 bytes a cycle), so small tiles are LDS-bound, and a workgroup takes 4 WM + WN NTW KB
+// a k-tile through its CU's 64 bytes a cycle.  256 rows x 224 columns (8 waves, one workgroup per CU) needs 79 % of the
+// LDS cycles and 54 % of the load cycles that its products take, and cuts the 28672 columns of the 7B shape's gate/up
+// into whole rounds of 256 CUs; smaller tiles are for the narrower matrices and fewer rows (pf_choose).  One workgroup
+// barrier per k-tile: past it every wave's part of the next stage is in, and nobody reads the stage any more that the
+// next requests overwrite (its fragments are in registers, one k-tile ahead of the products).
+// Measured (1023 rows, 7B shape, before: 64 x 64 per wave, activations from L2 into registers): gate/up 257 -> 205 us
+// (1170 TFLOP/s, what a large library product reaches on this card), QKV 92 -> 65, O 51 -> 42, down 147 -> 117.
+template <int MODE, int WM, int WN, int NTW, int NS>
+__device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf_lds) {
+  constexpr int NWV = WM * WN;                 // waves
+  constexpr int RTB = 4 * WM, CTB = WN * NTW;  // row and column tiles of the workgroup
+  constexpr int F = RTB + CTB;                 // fragments of a k-tile
+  constexpr int LPW = (F + NWV - 1) / NWV;     // ... a wave brings (the last one several times if they do not divide)
+  static_assert((NS - 1) * LPW <= 63, "load counter");
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int q4 = lane >> 4, c16 = lane & 15;
-  // Workgroup -> (row group, column group): workgroup b runs on XCD b % 8; all row groups of a column group get the same
-  // XCD and consecutive turns there, so a weight fragment comes from memory once and the other row groups find it in that
-  // XCD's L2 (the other order read every weight once per row group: 16 times for a 1024-token prompt).
-  const int n_cg = (p.ntiles + NTW - 1) / NTW, n_cg4 = (n_cg + 3) / 4, RG = p.RT / 4;
-  const int xcd = (int)blockIdx.x % 8, turn = (int)blockIdx.x / 8;
-  const int rb = turn % RG, cg4 = (turn / RG) * 8 + xcd;
-  const int cg = cg4 * 4 + wave;
-  if (cg >= n_cg) return;
-  const int r0 = rb * 4;  // first row tile
-  // weight fragments of column tile t0 + j, k-tile kt: base_j + (before[kt % NW] + kt / NW) * nt_j KB
-  const uint8_t *wb[NTW];
-  unsigned wnt[NTW];
-  const int t0 = cg * NTW;
+  const int wm = wave % WM, wn = wave / WM;
+  const int n_cg = (p.ntiles + CTB - 1) / CTB, RB = (p.RT + RTB - 1) / RTB;
+  const int xcd = (int)blockIdx.x % 8;
+  int turn = (int)blockIdx.x / 8;
+  const int rb = turn % RB;
+  turn /= RB;
+  const int slice = turn % p.S, cg = (turn / p.S) * 8 + xcd;
+  if (cg >= n_cg) return;  // (the whole workgroup)
+  const int row0 = p.KT * slice / p.S, row1 = p.KT * (slice + 1) / p.S, n_kt = row1 - row0;
+  const unsigned lds0 = (unsigned)(uintptr_t)pf_lds;
+  // what this wave brings of a k-tile: fragments wave * LPW ..; 0 .. RTB - 1 are the activations' row tiles
+  __amdgpu_buffer_rsrc_t rs[LPW];
+  unsigned of[LPW], mul_a[LPW], mul_b[LPW], dst[LPW];
 #pragma unroll
-  for (int j = 0; j < NTW; ++j) {
-    const int t = t0 + j < p.ntiles ? t0 + j : p.ntiles - 1;  // (a group past the last tile repeats it; its result is dropped)
-    const int c = t % p.G, lt = t / p.G;
-    unsigned off = p.frag0;
-    for (int i = 0; i < p.n_prev; ++i) off += (unsigned)((p.prev_ntiles[i] > c ? (p.prev_ntiles[i] - c + p.G - 1) / p.G : 0) * p.prev_KT[i]);
-    wnt[j] = (unsigned)((p.ntiles - c + p.G - 1) / p.G);
-    wb[j] = p.wstream + (size_t)c * p.cu_bytes + ((size_t)off + (unsigned)lt) * 1024u + (unsigned)lane * 16u;
+  for (int i = 0; i < LPW; ++i) {
+    int f = wave * LPW + i;
+    if (f >= F) f = F - 1;
+    dst[i] = lds0 + (unsigned)f * 1024u;
+    if (f < RTB) {
+      const int r = rb * RTB + f;
+      rs[i] = rsrc_of(p.A);
+      of[i] = uni((unsigned)(r < p.RT ? r : p.RT - 1) * 1024u);
+      mul_a[i] = uni((unsigned)p.RT * 1024u);
+      mul_b[i] = 0u;
+    } else {
+      const int tj = cg * CTB + f - RTB;
+      const int t = tj < p.ntiles ? tj : p.ntiles - 1;  // (a group past the last tile repeats it; its result is dropped)
+      const int c = uni(t % p.G), lt = uni(t / p.G);
+      unsigned off = p.frag0;
+      for (int q = 0; q < p.n_prev; ++q) off += (unsigned)((p.prev_ntiles[q] > c ? (p.prev_ntiles[q] - c + p.G - 1) / p.G : 0) * p.prev_KT[q]);
+      rs[i] = rsrc_of(p.wstream + (size_t)c * p.cu_bytes);
+      of[i] = uni((off + (unsigned)lt) * 1024u);
+      mul_a[i] = 0u;
+      mul_b[i] = uni((unsigned)((p.ntiles - c + p.G - 1) / p.G) * 1024u);
+    }
   }
-  const int nk_q = p.KT / p.NW, nk_r = p.KT % p.NW;  // wave w of the packing holds nk_q (+1 if w < nk_r) k-tiles
-  const uint8_t *ab = (const uint8_t *)p.A + ((size_t)r0 * 64 + (unsigned)lane) * 16u;
-  const size_t a_kt = (size_t)p.RT * 1024u;  // bytes from one k-tile's fragments to the next
-  auto load = [&](int kt, u32x4 (&a)[4], u32x4 (&b)[NTW]) {
-    const int w = kt % p.NW, i = kt / p.NW;
-    const unsigned row = (unsigned)(w * nk_q + (w < nk_r ? w : nk_r) + i);  // k-tiles of the waves in front of w, then its own
+  const unsigned voff = (unsigned)lane * 16u;
+  // k-tiles in the order the weights are stored: row r of a tile's stream is k-tile kt, kt = w, w + NW, ... for w = 0, 1, ...
+  int nx_row = row0, nx_kt = row0, nx_w = 0;
+  while (nx_kt >= (p.KT - nx_w + p.NW - 1) / p.NW) {
+    nx_kt -= (p.KT - nx_w + p.NW - 1) / p.NW;
+    ++nx_w;
+  }
+  nx_kt = nx_w + p.NW * nx_kt;
+  unsigned nx_slot = 0;
+  auto request = [&]() {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = *(const u32x4 *)(ab + (size_t)kt * a_kt + (unsigned)m * 1024u);
+    for (int i = 0; i < LPW; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[i], (LDS_AS void *)(uintptr_t)(dst[i] + nx_slot), 16, voff,
+                                               uni(of[i] + (unsigned)nx_kt * mul_a[i] + (unsigned)nx_row * mul_b[i]), 0, 0);
+    const bool more = nx_row + 1 < row1;  // (past the end the last one is requested again and never used)
+    const bool wrap = nx_kt + p.NW >= p.KT;
+    nx_kt = !more ? nx_kt : wrap ? nx_w + 1 : nx_kt + p.NW;
+    nx_w += more && wrap ? 1 : 0;
+    nx_row += more ? 1 : 0;
+    nx_slot = nx_slot + F * 1024u == NS * F * 1024u ? 0u : nx_slot + F * 1024u;
+  };
+  u32x4 fa[2][4], fb[2][NTW];
+  unsigned rd_slot = 0;
+  auto read = [&](u32x4 (&a)[4], u32x4 (&b)[NTW]) {
+    const unsigned base = lds0 + rd_slot + voff;
 #pragma unroll
-    for (int j = 0; j < NTW; ++j) b[j] = *(const u32x4 *)(wb[j] + (size_t)row * wnt[j] * 1024u);
+    for (int m = 0; m < 4; ++m) a[m] = *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(4 * wm + m) * 1024u);
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) b[j] = *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(RTB + wn * NTW + j) * 1024u);
+    rd_slot = rd_slot + F * 1024u == NS * F * 1024u ? 0u : rd_slot + F * 1024u;
   };
   f32x4 acc[4][NTW];
 #pragma unroll
@@ -167,162 +220,115 @@ __global__ __launch_bounds__(256) void pf_gemm_kernel(PfGemm p) {
     for (int j = 0; j < NTW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto mul = [&](const u32x4 (&a)[4], const u32x4 (&b)[NTW]) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int j = 0; j < NTW; ++j)
-        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[j]), __builtin_bit_cast(f16x8, a[m]), acc[m][j], 0, 0, 0);
-  };
-  // A window of NS k-tiles: stage s holds k-tile kt with kt % NS == s (all indices are constants after unrolling).
-  // The loop body has no branch (requests past the last k-tile repeat it and are never used): with a branch around a
-  // request the compiler cannot count the requests in flight and waits for all of them at every use.
-  u32x4 sa[NS][4], sb[NS][NTW];
-  const int last_kt = p.KT - 1, n_full = p.KT / NS * NS;
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s) load(s < last_kt ? s : last_kt, sa[s], sb[s]);
-  for (int kt0 = 0; kt0 < n_full; kt0 += NS) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int nx = kt0 + s + NS - 1;
-      load(nx < last_kt ? nx : last_kt, sa[(s + NS - 1) % NS], sb[(s + NS - 1) % NS]);
-      __builtin_amdgcn_sched_barrier(0);  // (the requests stay in front of the products: the scheduler would sink them to their uses)
-      mul(sa[s], sb[s]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  for (int kt = n_full; kt < p.KT; ++kt) {  // fewer than NS k-tiles left: one at a time
-    load(kt, sa[0], sb[0]);
-    mul(sa[0], sb[0]);
-  }
-  pf_epilogue<MODE, NTW>(p, acc, r0, t0, lane);
-}
-
-// The same product with the weight fragments shared through LDS: a workgroup's four waves take four consecutive 64-row
-// groups of ONE column group, so the NTW weight fragments of a k-tile are fetched once per workgroup (each wave brings
-// NTW / 4 of them with direct-to-LDS loads into a ring of NS stages) instead of once per wave; the activation fragments
-// stay per wave in registers.  What a CU takes in per k-tile drops from 4 x (4 + NTW) KB to 16 + NTW KB, which is what
-// bounded the first kernel.  One workgroup barrier per k-tile: past it every wave's part of the stage has landed and
-// every wave is done reading the stage that the next requests overwrite.  Needs KT to be a multiple of NS.
-template <int MODE, int NTW, int NS>
-__device__ __forceinline__ void pf_gemm_lds_body(const PfGemm &p, LDS_AS uint8_t *pf_lds) {  // (device-only types: not in the kernel's own body, which the host pass instantiates too)
-  static_assert(NTW % 4 == 0, "every wave brings the same number of weight fragments");
-  constexpr int BW = NTW / 4;       // weight fragments a wave brings per k-tile
-  constexpr int LPS = 4 + BW;       // this wave's requests per stage
-  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int n_cg = (p.ntiles + NTW - 1) / NTW, RB = (p.RT / 4 + 3) / 4;
-  const int xcd = (int)blockIdx.x % 8, turn = (int)blockIdx.x / 8;
-  const int rb = turn % RB, cg = (turn / RB) * 8 + xcd;
-  if (cg >= n_cg) return;  // (the whole workgroup)
-  const int rg = rb * 4 + wave;                       // this wave's 64-row group
-  const bool active = rg * 4 < p.RT;
-  const int r0 = active ? rg * 4 : p.RT - 4;          // (a wave without rows runs along on the last group and drops the result)
-  const int t0 = cg * NTW;
-  const unsigned lds0 = (unsigned)(uintptr_t)pf_lds;
-  // the weight fragments this wave brings: column tiles t0 + BW wave .. + BW - 1
-  __amdgpu_buffer_rsrc_t wr[BW];
-  unsigned wof[BW], wnt[BW];
-#pragma unroll
-  for (int jj = 0; jj < BW; ++jj) {
-    const int tj = t0 + BW * wave + jj;
-    const int t = tj < p.ntiles ? tj : p.ntiles - 1;
-    const int c = uni(t % p.G), lt = uni(t / p.G);
-    unsigned off = p.frag0;
-    for (int i = 0; i < p.n_prev; ++i) off += (unsigned)((p.prev_ntiles[i] > c ? (p.prev_ntiles[i] - c + p.G - 1) / p.G : 0) * p.prev_KT[i]);
-    wr[jj] = rsrc_of(p.wstream + (size_t)c * p.cu_bytes);
-    wof[jj] = uni((off + (unsigned)lt) * 1024u);
-    wnt[jj] = uni((unsigned)((p.ntiles - c + p.G - 1) / p.G) * 1024u);
-  }
-  const int nk_q = p.KT / p.NW, nk_r = p.KT % p.NW;
-  const uint8_t *ab = (const uint8_t *)p.A + ((size_t)r0 * 64 + (unsigned)lane) * 16u;
-  const size_t a_kt = (size_t)p.RT * 1024u;
-  const unsigned voff = (unsigned)lane * 16u;
-  auto request = [&](int kt, int slot, u32x4 (&a)[4]) {
-    const int w = kt % p.NW, i = kt / p.NW;
-    const unsigned row = (unsigned)(w * nk_q + (w < nk_r ? w : nk_r) + i);
-#pragma unroll
-    for (int jj = 0; jj < BW; ++jj)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr[jj], (LDS_AS void *)(uintptr_t)(lds0 + (unsigned)((slot * NTW + BW * wave + jj) * 1024)), 16, voff,
-                                               uni(wof[jj] + row * wnt[jj]), 0, 0);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = *(const u32x4 *)(ab + (size_t)kt * a_kt + (unsigned)m * 1024u);
-  };
-  f32x4 acc[4][NTW];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 sa[NS][4];
-  const int last_kt = p.KT - 1;
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s) request(s < last_kt ? s : last_kt, s, sa[s]);
-  for (int kt0 = 0; kt0 < p.KT; kt0 += NS) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      wait_vmcnt<(NS - 2) * LPS>();        // this wave's requests of stage s are in (the NS - 2 younger stages may be out)
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      __builtin_amdgcn_s_barrier();        // ... and everybody's; the stage before is read by nobody any more
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);  // (compiler fences: no LDS read moves across the barrier; no hardware wait for memory is wanted here)
-      const int nx = kt0 + s + NS - 1;
-      request(nx < last_kt ? nx : last_kt, (s + NS - 1) % NS, sa[(s + NS - 1) % NS]);
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4 b[NTW];
-#pragma unroll
-      for (int j = 0; j < NTW; ++j) b[j] = *(LDS_AS const u32x4 *)(uintptr_t)(lds0 + (unsigned)((s * NTW + j) * 1024) + voff);
+    for (int j = 0; j < NTW; ++j)
 #pragma unroll
       for (int m = 0; m < 4; ++m)
+        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[j]), __builtin_bit_cast(f16x8, a[m]), acc[m][j], 0, 0, 0);
+  };
+  auto turn_over = [&]() {  // everybody's next stage is in, and everybody has read the stage that the next request overwrites
+    wait_vmcnt<(NS - 2) * LPW>();
+    pf_wait_lds_reads<0>();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  };
 #pragma unroll
-        for (int j = 0; j < NTW; ++j)
-          acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[j]), __builtin_bit_cast(f16x8, sa[s][m]), acc[m][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+  for (int s = 0; s < NS; ++s) request();
+  // row factors of the norm into LDS, while the first stages are on their way
+  LDS_AS float *rf = (LDS_AS float *)(uintptr_t)(lds0 + NS * F * 1024u);
+  if (MODE != PF_PART && (int)threadIdx.x < 16 * RTB) {
+    const int row = 16 * rb * RTB + (int)threadIdx.x;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    if (row < p.M) {
+      const f32x4 *sp = reinterpret_cast<const f32x4 *>(p.ss + (size_t)row * PF_CHUNKS);
+#pragma unroll
+      for (int i = 0; i < PF_CHUNKS / 4; ++i) a += sp[i];
     }
+    rf[threadIdx.x] = row < p.M ? 1.0f / sqrtf(((a[0] + a[1]) + (a[2] + a[3])) * p.inv_d + p.eps) : 0.f;
   }
+  wait_vmcnt<(NS - 1) * LPW>();
+  pf_wait_lds_reads<0>();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  read(fa[0], fb[0]);
+  auto step = [&](int s) {
+    turn_over();
+    request();
+    __builtin_amdgcn_sched_barrier(0);
+    read(fa[s ^ 1], fb[s ^ 1]);
+    mul(fa[s], fb[s]);
+    // one fragment read per two products
+#pragma unroll
+    for (int i = 0; i < 4 + NTW; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4 * NTW - 2 * (4 + NTW) > 0 ? 4 * NTW - 2 * (4 + NTW) : 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int r = 0;
+  for (; r + 2 <= n_kt; r += 2) {
+    step(0);
+    step(1);
+  }
+  if (r < n_kt) mul(fa[0], fb[0]);
   wait_vmcnt<0>();  // (the requests past the last k-tile land before the LDS is given back)
-  if (active) pf_epilogue<MODE, NTW>(p, acc, r0, t0, lane);
+  const int r0 = rb * RTB + 4 * wm;
+  if (r0 < p.RT) pf_epilogue<MODE, NTW>(p, acc, r0, cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
 }
 
-template <int MODE, int NTW, int NS>
-__global__ __launch_bounds__(256) void pf_gemm_lds_kernel(PfGemm p) {
+template <int MODE, int WM, int WN, int NTW, int NS>
+__global__ __launch_bounds__(64 * WM * WN, 2) void pf_tile_kernel(PfGemm p) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t pf_lds[];
-  pf_gemm_lds_body<MODE, NTW, NS>(p, (LDS_AS uint8_t *)pf_lds);
+  pf_tile_body<MODE, WM, WN, NTW, NS>(p, (LDS_AS uint8_t *)pf_lds);
 }
 
-// Row factors rsqrt(mean x^2 + eps) and the operand fragments of x * gain; one workgroup per row.  Rows M .. 16 RT4 - 1
-// of the fragments are written as zeros (the matrix products read whole 64-row groups).
-__global__ __launch_bounds__(256) void pf_prep_kernel(const float *x, const float *gain, int M, int d, int RT, float eps, float *rs, uint16_t *A) {
-  const int row = blockIdx.x;
-  __shared__ float red[4];
+// The residual stream takes in the products of the projection before (x += the slices' products, added in slice order),
+// and the operand fragments of x * gain and the sums of squares for the next projection's row factors are formed in the
+// same pass: a workgroup takes 16 rows x one of PF_CHUNKS column chunks, a wave whole fragments of 16 rows x 32 columns.
+// S = 0: x as it is.  Rows M .. 16 RT - 1 of the fragments are written as zeros (the products read whole row blocks).
+template <int S>
+__global__ __launch_bounds__(256) void pf_norm_kernel(float *x, const float *part, const float *gain, int M, int d, int RT, float *ss, uint16_t *A) {
+  const int rt = blockIdx.x, chunk = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
+  const int KT = d >> 5, per = (KT + PF_CHUNKS - 1) / PF_CHUNKS, k1 = (chunk + 1) * per < KT ? (chunk + 1) * per : KT;
+  const int row = 16 * rt + c16;
+  __shared__ float red[4][16];
   float sq = 0.f;
-  for (int c0 = threadIdx.x * 8; c0 < d; c0 += 256 * 8) {
+  for (int kt = chunk * per + wave; kt < k1; kt += 4) {
+    const int col = 32 * kt + 8 * q4;
     u32x4 out = {0u, 0u, 0u, 0u};
     if (row < M) {
-      const float *xp = x + (size_t)row * d + c0;
-      float y[8];
+      f32x4 *xp = reinterpret_cast<f32x4 *>(x + (size_t)row * d + col);
+      f32x4 x0 = xp[0], x1 = xp[1];
+      if (S > 0) {
+        f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float v = xp[i];
-        sq += v * v;
-        y[i] = v * gain[c0 + i];
+        for (int s = 0; s < S; ++s) {
+          const f32x4 *pp = reinterpret_cast<const f32x4 *>(part + ((size_t)s * M + row) * d + col);
+          y0 += pp[0];
+          y1 += pp[1];
+        }
+        x0 += y0;
+        x1 += y1;
+        xp[0] = x0;
+        xp[1] = x1;
       }
-      out = u32x4{pack_f16(y[0], y[1]), pack_f16(y[2], y[3]), pack_f16(y[4], y[5]), pack_f16(y[6], y[7])};
-    }
-    *(u32x4 *)((uint8_t *)A + frag_piece(c0, row, RT)) = out;
-  }
+      const f32x4 *gp = reinterpret_cast<const f32x4 *>(gain + col);
+      const f32x4 g0 = gp[0], g1 = gp[1];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+      for (int i = 0; i < 4; ++i) sq += x0[i] * x0[i] + x1[i] * x1[i];
+      out = u32x4{pack_f16(x0[0] * g0[0], x0[1] * g0[1]), pack_f16(x0[2] * g0[2], x0[3] * g0[3]),
+                  pack_f16(x1[0] * g1[0], x1[1] * g1[1]), pack_f16(x1[2] * g1[2], x1[3] * g1[3])};
+    }
+    *(u32x4 *)((uint8_t *)A + (((size_t)kt * RT + rt) * 64 + lane) * 16) = out;
+  }
+  sq += __shfl_xor(sq, 16, 64);
+  sq += __shfl_xor(sq, 32, 64);
+  if (q4 == 0) red[wave][c16] = sq;
   __syncthreads();
-  if (threadIdx.x == 0 && row < M) rs[row] = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)d + eps);
-}
-
-// cos, sin of position L0 + row for every RoPE pair (double precision angles, as the block kernel's table)
-__global__ void pf_rope_kernel(float *cs, int M, int half, int L0, double theta) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= M * half) return;
-  const int row = e / half, i = e - row * half;
-  const double inv = exp2(-(double)i / (double)half * log2(theta));
-  double s, c;
-  sincos((double)(L0 + row) * inv, &s, &c);
-  cs[(size_t)e * 2] = (float)c;
-  cs[(size_t)e * 2 + 1] = (float)s;
+  if (threadIdx.x < 16 && 16 * rt + (int)threadIdx.x < M)
+    ss[(size_t)(16 * rt + threadIdx.x) * PF_CHUNKS + chunk] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
 // Causal attention of one 16-row tile of one q head per wave over cache rows 0 .. L0 + row (Section 4.4's plain causal
@@ -419,22 +425,140 @@ __global__ __launch_bounds__(256) void pf_attn_kernel(const uint16_t *Q, const u
   }
 }
 
-__global__ void pf_embed_kernel(const uint16_t *E, const int32_t *tok, int V, int d, int half, float *x) {
-  int t = tok[blockIdx.x];
+// x[row] = E[tok[row]] (eight elements per thread at a time), and cos, sin of position L0 + row for every RoPE pair (double
+// precision angles, as the block kernel's table); one workgroup per row.
+__global__ __launch_bounds__(256) void pf_embed_kernel(const uint16_t *E, const int32_t *tok, int V, int d, int f16, float *x, float *cs, int half, int L0,
+                                                       double theta) {
+  const int row = blockIdx.x;
+  int t = tok[row];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    const uint16_t b = E[(size_t)t * d + i];
-    x[(size_t)blockIdx.x * d + i] = half ? (float)__builtin_bit_cast(_Float16, b) : __uint_as_float((uint32_t)b << 16);
+  for (int i = threadIdx.x * 8; i < d; i += 256 * 8) {
+    const u32x4 e = *(const u32x4 *)(E + (size_t)t * d + i);
+    f32x4 y[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint16_t b = (uint16_t)(e[k >> 1] >> (16 * (k & 1)));
+      y[k >> 2][k & 3] = f16 ? (float)__builtin_bit_cast(_Float16, b) : __uint_as_float((uint32_t)b << 16);
+    }
+    f32x4 *xp = reinterpret_cast<f32x4 *>(x + (size_t)row * d + i);
+    xp[0] = y[0];
+    xp[1] = y[1];
+  }
+  for (int i = threadIdx.x; i < half; i += 256) {
+    const double inv = exp2(-(double)i / (double)half * log2(theta));
+    double s, c;
+    sincos((double)(L0 + row) * inv, &s, &c);
+    cs[((size_t)row * half + i) * 2] = (float)c;
+    cs[((size_t)row * half + i) * 2 + 1] = (float)s;
   }
 }
 
 // ---- host side ----------------------------------------------------------------------------------------
+// The tiles pf_choose picks from, and what a k-tile of them costs: of the two smallest, two workgroups fit a CU.
+struct PfTile {
+  int rows, cols;         // in 16 x 16 tiles
+  int per_cu;
+  float t_full, t_single;  // us per k-tile of a round that fills the chip, and of one with a workgroup per CU at most
+};
+// (from the products of the 7B shape at 77 .. 1023 rows, launch overhead included)
+constexpr PfTile PF_TILES[] = {
+    {16, 14, 1, 0.85f, 0.85f}, {16, 10, 1, 0.66f, 0.66f}, {16, 8, 1, 0.57f, 0.57f}, {8, 12, 1, 0.50f, 0.50f}, {8, 8, 2, 0.70f, 0.45f}, {8, 4, 2, 0.52f, 0.30f},
+};
+constexpr int PF_N_TILES = 6;
+
+template <int MODE, int WM, int WN, int NTW, int NS>
+static int pf_launch_tile(const PfGemm &p, hipStream_t s, bool prepare) {
+  constexpr int bytes = NS * (4 * WM + WN * NTW) * 1024 + WM * 256;
+  static_assert(bytes <= 160 * 1024, "LDS of one CU");
+  if (prepare) {
+    LA_HIP(hipFuncSetAttribute((const void *)pf_tile_kernel<MODE, WM, WN, NTW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    return LA_OK;
+  }
+  const int n_cg = ceil_div(p.ntiles, WN * NTW), RB = ceil_div(p.RT, 4 * WM);
+  pf_tile_kernel<MODE, WM, WN, NTW, NS><<<RB * p.S * ((n_cg + 7) / 8 * 8), 64 * WM * WN, bytes, s>>>(p);
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+template <int MODE>
+static int pf_launch_tile(int tile, const PfGemm &p, hipStream_t s, bool prepare) {
+  switch (tile) {
+  case 0: return pf_launch_tile<MODE, 4, 2, 7, 5>(p, s, prepare);
+  case 1: return pf_launch_tile<MODE, 4, 2, 5, 6>(p, s, prepare);
+  case 2: return pf_launch_tile<MODE, 4, 2, 4, 6>(p, s, prepare);
+  case 3: return pf_launch_tile<MODE, 2, 4, 3, 6>(p, s, prepare);
+  case 4: return pf_launch_tile<MODE, 2, 2, 4, 4>(p, s, prepare);
+  default: return pf_launch_tile<MODE, 2, 2, 2, 6>(p, s, prepare);
+  }
+}
+
+static_assert(PF_PART_ROWS >= PF_ROWS, "one slice of a whole chunk");
+
+// Tile and number of slices of the contraction by estimated time: whole rounds of the chip's CUs times the k-tiles of a
+// slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  The estimate picks the
+// fastest or within 5 % of it of the tiles that were measured at 77, 129, 200, 300, 400, 512, 700 and 1023 rows.  Only
+// the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
+// for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
+static void pf_choose(const PfGemm &p, int max_split, int cus, int &tile, int &S) {
+  float best = 0.f;
+  tile = -1;
+  for (int i = 0; i < PF_N_TILES; ++i)
+    for (int k = 1; k <= max_split; ++k) {
+      const PfTile &t = PF_TILES[i];
+      if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > PF_PART_ROWS)) break;
+      const int n = ceil_div(p.RT, t.rows) * ceil_div(p.ntiles, t.cols) * k, round = t.per_cu * cus, rest = n % round;
+      float us = (float)(n / round) * t.t_full + (rest == 0 ? 0.f : rest <= cus ? t.t_single : t.t_full);
+      us *= (float)ceil_div(p.KT, k);
+      if (max_split > 1) us += (float)k * (float)p.M * (float)p.d * 8.f / 4.5e6f;
+      if (tile < 0 || us < best) {
+        best = us;
+        tile = i;
+        S = k;
+      }
+    }
+}
+
+template <int MODE>
+static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int *S = nullptr) {
+  ProfScope ps(name, s);
+  int tile;
+  pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, cus, tile, p.S);
+  if (S) *S = p.S;
+  return pf_launch_tile<MODE>(tile, p, s, false);
+}
+
+static int pf_launch_norm(int S, float *x, const float *part, const float *gain, int M, int d, int RT, float *ss, uint16_t *A, hipStream_t s) {
+  ProfScope ps("pf_norm", s);
+  const dim3 grid(RT, PF_CHUNKS);
+  switch (S) {
+  case 0: pf_norm_kernel<0><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 1: pf_norm_kernel<1><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 2: pf_norm_kernel<2><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 3: pf_norm_kernel<3><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 4: pf_norm_kernel<4><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 5: pf_norm_kernel<5><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 6: pf_norm_kernel<6><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  case 7: pf_norm_kernel<7><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  default: pf_norm_kernel<8><<<grid, 256, 0, s>>>(x, part, gain, M, d, RT, ss, A); break;
+  }
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+
+template <int DH, bool F16>
+static int pf_launch_attn(const PfBuffers &b, const PfGemm &p, int M, int RT, int RTr, hipStream_t s) {
+  ProfScope ps("pf_attn", s);
+  pf_attn_kernel<DH, F16><<<ceil_div(RTr * p.Hq, 4), 256, 0, s>>>(b.Q, p.Kc, p.Vc, b.attn, M, RT, RTr, p.L0, p.Hq, p.Hkv);
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+
 static int pf_alloc(la_model *m, PfBuffers &b) {
   const la_model_desc &d = m->d;
   const size_t R = PF_ROWS;
   bool ok = true;
   ok = ok && (b.x = (float *)dalloc(R * d.d_model * 4));
-  ok = ok && (b.rs = (float *)dalloc(R * 4));
+  ok = ok && (b.part = (float *)dalloc((size_t)PF_PART_ROWS * d.d_model * 4));
+  ok = ok && (b.ss = (float *)dalloc(R * PF_CHUNKS * 4));
   ok = ok && (b.cs = (float *)dalloc(R * d.head_dim * 4));
   ok = ok && (b.A = (uint16_t *)dalloc(R * d.d_model * 2));
   ok = ok && (b.Q = (uint16_t *)dalloc(R * (size_t)m->qdim() * 2));
@@ -445,22 +569,12 @@ static int pf_alloc(la_model *m, PfBuffers &b) {
   LA_HIP(hipMemset(b.Q, 0, R * (size_t)m->qdim() * 2));
   LA_HIP(hipMemset(b.attn, 0, R * (size_t)m->qdim() * 2));
   LA_HIP(hipMemset(b.act, 0, R * (size_t)d.d_ffn * 2));
-  return LA_OK;
-}
-
-
-template <int MODE, int NTW>
-static int pf_launch_gemm(const PfGemm &p, hipStream_t s, const char *name) {
-  const int n_cg = (p.ntiles + NTW - 1) / NTW;
-  ProfScope ps(name, s);
-  if (p.KT % PF_NS_LDS == 0) {  // weight fragments shared through LDS
-    const int RB = (p.RT / 4 + 3) / 4;
-    pf_gemm_lds_kernel<MODE, NTW, PF_NS_LDS><<<RB * ((n_cg + 7) / 8 * 8), 256, PF_NS_LDS * NTW * 1024, s>>>(p);
-  } else {
-    const int n_cg4 = (n_cg + 3) / 4, row_groups = p.RT / 4;
-    pf_gemm_kernel<MODE, NTW, PF_NS><<<row_groups * ((n_cg4 + 7) / 8 * 8), 256, 0, s>>>(p);
+  for (int i = 0; i < PF_N_TILES; ++i) {
+    int rc = pf_launch_tile<PF_QKV>(i, PfGemm{}, nullptr, true);
+    if (!rc) rc = pf_launch_tile<PF_PART>(i, PfGemm{}, nullptr, true);
+    if (!rc) rc = pf_launch_tile<PF_GATEUP>(i, PfGemm{}, nullptr, true);
+    if (rc) return rc;
   }
-  LA_HIP(hipGetLastError());
   return LA_OK;
 }
 
@@ -481,13 +595,13 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
   const int RT = (M + 63) / 64 * 4, RTr = (M + 15) / 16, half = d.head_dim / 2, f16 = d.dtype == LA_F16;
   {
     ProfScope ps("pf_embed", s);
-    pf_embed_kernel<<<M, 256, 0, s>>>((const uint16_t *)m->embed, tok, d.vocab, d.d_model, f16, b.x);
-    pf_rope_kernel<<<ceil_div(M * half, 256), 256, 0, s>>>(b.cs, M, half, L0, (double)d.rope_theta);
+    pf_embed_kernel<<<M, 256, 0, s>>>((const uint16_t *)m->embed, tok, d.vocab, d.d_model, f16, b.x, b.cs, half, L0, (double)d.rope_theta);
   }
   LA_HIP(hipGetLastError());
   const GemmPlan *plans[4] = {&f->p_qkv, &f->p_o, &f->p_gu, &f->p_down};
+  int S_down = 0;  // slices of the products that x has not taken in yet
   for (int l = 0; l < d.n_layers; ++l) {
-    auto gemm_args = [&](int gi) {
+    auto gemm_args = [&](int gi, const uint16_t *A) {
       PfGemm p{};
       p.wstream = f->wstream;
       p.cu_bytes = f->cu_bytes;
@@ -501,11 +615,15 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
       }
       p.ntiles = plans[gi]->ntiles;
       p.KT = plans[gi]->KT;
+      p.A = A;
+      p.S = 1;
       p.RT = RT;
       p.M = M;
-      p.x = b.x;
+      p.part = b.part;
       p.d = d.d_model;
-      p.rs = b.rs;
+      p.ss = b.ss;
+      p.inv_d = 1.0f / (float)d.d_model;
+      p.eps = d.rms_eps;
       p.cs = b.cs;
       p.Kc = (uint16_t *)kv->K + (size_t)l * kv->layer_elems();
       p.Vc = (uint16_t *)kv->V + (size_t)l * kv->layer_elems();
@@ -518,39 +636,17 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
       p.act = b.act;
       return p;
     };
-    int rc;
-    {
-      ProfScope ps("pf_prep", s);
-      pf_prep_kernel<<<16 * RT, 256, 0, s>>>(b.x, m->layers[l].g_attn, M, d.d_model, RT, d.rms_eps, b.rs, b.A);
-    }
-    PfGemm p = gemm_args(0);
-    p.A = b.A;
-    if ((rc = pf_launch_gemm<PF_QKV, 4>(p, s, "pf_gemm_qkv"))) return rc;
-    {
-      ProfScope ps("pf_attn", s);
-      const int grid = ceil_div(RTr * d.n_q_heads, 4);
-      const uint16_t *Kc = p.Kc, *Vc = p.Vc;
-      if (d.head_dim == 128) {
-        if (f16) pf_attn_kernel<128, true><<<grid, 256, 0, s>>>(b.Q, Kc, Vc, b.attn, M, RT, RTr, L0, d.n_q_heads, d.n_kv_heads);
-        else pf_attn_kernel<128, false><<<grid, 256, 0, s>>>(b.Q, Kc, Vc, b.attn, M, RT, RTr, L0, d.n_q_heads, d.n_kv_heads);
-      } else {
-        if (f16) pf_attn_kernel<64, true><<<grid, 256, 0, s>>>(b.Q, Kc, Vc, b.attn, M, RT, RTr, L0, d.n_q_heads, d.n_kv_heads);
-        else pf_attn_kernel<64, false><<<grid, 256, 0, s>>>(b.Q, Kc, Vc, b.attn, M, RT, RTr, L0, d.n_q_heads, d.n_kv_heads);
-      }
-    }
-    p = gemm_args(1);
-    p.A = b.attn;
-    if ((rc = pf_launch_gemm<PF_RESID, 4>(p, s, "pf_gemm_o"))) return rc;
-    {
-      ProfScope ps("pf_prep", s);
-      pf_prep_kernel<<<16 * RT, 256, 0, s>>>(b.x, m->layers[l].g_mlp, M, d.d_model, RT, d.rms_eps, b.rs, b.A);
-    }
-    p = gemm_args(2);
-    p.A = b.A;
-    if ((rc = pf_launch_gemm<PF_GATEUP, 4>(p, s, "pf_gemm_gateup"))) return rc;
-    p = gemm_args(3);
-    p.A = b.act;
-    if ((rc = pf_launch_gemm<PF_RESID, 4>(p, s, "pf_gemm_down"))) return rc;
+    int rc, S_o = 0;
+    if ((rc = pf_launch_norm(S_down, b.x, b.part, m->layers[l].g_attn, M, d.d_model, RT, b.ss, b.A, s))) return rc;
+    PfGemm p = gemm_args(0, b.A);
+    if ((rc = pf_launch_gemm<PF_QKV>(p, s, "pf_gemm_qkv", f->n_wgs))) return rc;
+    if (d.head_dim == 128) rc = f16 ? pf_launch_attn<128, true>(b, p, M, RT, RTr, s) : pf_launch_attn<128, false>(b, p, M, RT, RTr, s);
+    else rc = f16 ? pf_launch_attn<64, true>(b, p, M, RT, RTr, s) : pf_launch_attn<64, false>(b, p, M, RT, RTr, s);
+    if (rc) return rc;
+    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(1, b.attn), s, "pf_gemm_o", f->n_wgs, &S_o))) return rc;
+    if ((rc = pf_launch_norm(S_o, b.x, b.part, m->layers[l].g_mlp, M, d.d_model, RT, b.ss, b.A, s))) return rc;
+    if ((rc = pf_launch_gemm<PF_GATEUP>(gemm_args(2, b.A), s, "pf_gemm_gateup", f->n_wgs))) return rc;
+    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(3, b.act), s, "pf_gemm_down", f->n_wgs, &S_down))) return rc;
   }
   LA_HIP(hipGetLastError());
   return LA_OK;

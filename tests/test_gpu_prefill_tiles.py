@@ -1,0 +1,108 @@
+"""The prompt pass at the sizes where its tiles, slices of the contraction, key blocks and chunks change,
+against a float64 torch model of two layers of the 7B width (and of the 64-channel heads)."""
+import math
+import zlib
+from dataclasses import replace
+
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+# max |got - want| over max |want| of a layer's cache rows: the bars of the prompt-pass parity tests (one storage
+# rounding of the rows on top of the hidden-state error of one layer)
+TOL = {"bf16": 2e-2, "f16": 2e-3}
+
+
+def _normal(name, size, std, dtype):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(zlib.crc32(name.encode()))
+    return torch.randn(size, generator=g, device="cuda").mul_(std).to(dtype)
+
+
+def _layer(sh, l, dtype):
+    import torch
+    d, F, q, kv = sh.d_model, sh.d_ffn, sh.q_dim, sh.kv_dim
+    size = {"wq": (d, q), "wk": (d, kv), "wv": (d, kv), "wo": (q, d), "wgate": (d, F), "wup": (d, F), "wdown": (F, d)}
+    w = {k: _normal(f"{l}/{k}", s, 0.02, dtype) for k, s in size.items()}
+    for k in ("g_attn", "g_mlp"):
+        w[k] = 1.0 + 0.1 * _normal(f"{l}/{k}", (d,), 1.0, torch.float32)
+    return w
+
+
+def _reference(sh, embed, tok, L0, old, dtype):
+    """K, V rows L0 .. of every layer in float64, all layers' weights made again."""
+    import torch
+    dev, f8 = "cuda", torch.float64
+    n, half, g = len(tok), sh.head_dim // 2, sh.n_q_heads // sh.n_kv_heads
+    pos = torch.arange(L0, L0 + n, device=dev, dtype=f8)
+    ang = pos[:, None, None] * torch.pow(torch.tensor(sh.rope_theta, dtype=f8, device=dev), -torch.arange(half, device=dev, dtype=f8) / half)
+    norm = lambda x, gain: x * torch.rsqrt(x.square().mean(1, keepdim=True) + sh.rms_eps) * gain.double()
+
+    def rope(y):
+        a, b = y[..., :half], y[..., half:]
+        return torch.cat([a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()], -1)
+
+    see = torch.ones((n, L0 + n), dtype=torch.bool, device=dev).tril(L0)
+    x, out = embed[tok.long()].double(), []
+    for l in range(sh.n_layers):
+        w = _layer(sh, l, dtype)
+        h = norm(x, w["g_attn"])
+        q = rope((h @ w["wq"].double()).view(n, sh.n_q_heads, sh.head_dim))
+        k = rope((h @ w["wk"].double()).view(n, sh.n_kv_heads, sh.head_dim))
+        v = (h @ w["wv"].double()).view(n, sh.n_kv_heads, sh.head_dim)
+        out.append((k, v))
+        if l + 1 == sh.n_layers:
+            break
+        ka, va = torch.cat([old[l][0].double(), k]), torch.cat([old[l][1].double(), v])
+        o = torch.empty_like(q)
+        for i in range(sh.n_q_heads):
+            s = q[:, i] @ ka[:, i // g].t() / math.sqrt(sh.head_dim)
+            o[:, i] = torch.softmax(s.masked_fill(~see, -math.inf), 1) @ va[:, i // g]
+        x = x + o.reshape(n, -1) @ w["wo"].double()
+        h = norm(x, w["g_mlp"])
+        x = x + (torch.nn.functional.silu(h @ w["wgate"].double()) * (h @ w["wup"].double())) @ w["wdown"].double()
+    return out
+
+
+@pytest.mark.parametrize("name,dtype,cases", [
+    ("mistral7b", "bf16", [(65, 0), (128, 1), (130, 37), (257, 0), (300, 31), (700, 5), (1023, 0), (1100, 32), (2200, 3)]),
+    ("mistral7b", "f16", [(193, 33), (1025, 0)]),
+    ("nemo12b", "bf16", [(400, 64), (1024, 0)]),
+    ("small64_bf16", "bf16", [(65, 7), (191, 0), (2049, 100)]),
+])
+def test_prompt_pass_sizes(name, dtype, cases):
+    import torch
+    from paper_2602_16760_amd import binding as B
+    sh = replace(synth.SHAPES[name], n_layers=2, dtype=dtype, vocab=512)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, td)
+    model = B.la_init_model(sh, embed)
+    try:
+        for l in range(sh.n_layers):
+            B.la_model_set_layer(model, l, _layer(sh, l, td))
+            torch.cuda.synchronize()
+        for n, L0 in cases:
+            print(f"{name} {dtype}: {n} tokens at {L0}", flush=True)
+            kv = B.la_kv_alloc(model, L0 + n)
+            try:
+                old = [tuple(_normal(f"{l}/{c}", (L0, sh.n_kv_heads, sh.head_dim), 1.0, td) for c in "kv") for l in range(sh.n_layers)]
+                if L0:
+                    for l in range(sh.n_layers):
+                        B.la_kv_fill(kv, l, 0, *old[l])
+                tok = torch.randint(0, sh.vocab, (n,), device="cuda", dtype=torch.int32, generator=torch.Generator(device="cuda").manual_seed(n))
+                B.la_prefill(model, kv, tok, L0)
+                assert B.la_kv_get_len(kv) == L0 + n
+                for l, want in enumerate(_reference(sh, embed, tok, L0, old, td)):
+                    got = [torch.empty((n, sh.n_kv_heads, sh.head_dim), dtype=td, device="cuda") for _ in "kv"]
+                    B.la_kv_read(kv, l, L0, n, *got)
+                    for c, a, b in zip("KV", got, want):
+                        e = ((a.double() - b).abs().max() / b.abs().max()).item()
+                        assert e <= TOL[dtype], f"{n} tokens at {L0}, layer {l} {c}: {e:.3e}"
+            finally:
+                torch.cuda.synchronize()
+                B.la_free_kv(kv)
+    finally:
+        torch.cuda.synchronize()
+        B.la_free_model(model)
