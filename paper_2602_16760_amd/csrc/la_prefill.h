@@ -21,6 +21,7 @@ constexpr int PF_MIN = 128;     // shorter prompts go through the block kernel
 constexpr int PF_CHUNKS = 32;   // partial sums of squares per row (column chunks of pf_norm_kernel)
 constexpr int PF_PART_ROWS = 2048;  // rows of all slices' products together
 constexpr int PF_MAX_SPLIT = 8; // most slices of a contraction
+constexpr int PF_KEYS = 64;     // keys of a block of the attention
 
 enum PfMode { PF_QKV = 0, PF_PART = 1, PF_GATEUP = 2 };
 
@@ -331,90 +332,162 @@ __global__ __launch_bounds__(256) void pf_norm_kernel(float *x, const float *par
     ss[(size_t)(16 * rt + threadIdx.x) * PF_CHUNKS + chunk] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-// Causal attention of one 16-row tile of one q head per wave over cache rows 0 .. L0 + row (Section 4.4's plain causal
-// mask); the same products and running softmax as the block kernel's attention, one key block of 32 at a time, the next
-// block's K requested when the scores are out of the matrix unit and its V after P V.  Output: operand fragments of the
-// O projection.
+// The value of the lane 32 (16) further, and the maximum over the lanes 16 and 32 apart, without the LDS.
+__device__ __forceinline__ float pf_max_q4(float v) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+
+// Two probabilities in the cache's 16-bit type (round to nearest even; no value is out of range).
+template <bool F16>
+__device__ __forceinline__ uint32_t pf_pack_p(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  if constexpr (F16) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
+  } else {
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), b2));
+  }
+}
+
+// Causal attention over cache rows 0 .. L0 + row (Section 4.4's plain causal mask).  A workgroup takes four consecutive
+// (row tile, q head) pairs of one kv head (the heads of a row tile are neighbours), a wave one of them; blocks of 64 keys of
+// K and V go through LDS once for all four.  The products and the running softmax are the block kernel's.  Output: operand
+// fragments of the O projection.
+// Bound: the vector instructions of the softmax beside the products (about 600 cycles of the former, 512 of the latter
+// per wave and 64 keys).  Four waves share a K/V block because a wave of its own took 16 KB from L2 for 32 keys and 16
+// rows, four times what its products take at 64 bytes a cycle; 64 keys at a time halve the maxima, the barriers and the
+// branches of 32 (26 -> 23 us and 70 -> 62 us at the two sizes below); a wave takes one tile and not two (36 us): two
+// tiles leave one workgroup per CU and the longest rows last.  The running maximum's lanes are compared without LDS
+// (v_permlane swaps), the sums stay per lane until the end, and the output is rescaled only when a maximum moved.
+// Measured per layer (7B shape): 1023 rows at 0 69 -> 23 us, 1024 rows at 1000 .. 3000 231 -> 62 us (mean).
 template <int DH, bool F16>
-__global__ __launch_bounds__(256) void pf_attn_kernel(const uint16_t *Q, const uint16_t *Kc, const uint16_t *Vc, uint16_t *out, int M, int RT, int RTr,
-                                                      int L0, int Hq, int Hkv) {  // RT: row tiles the fragment buffers are laid out for; RTr: tiles that hold rows
+__device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t *Q, const uint16_t *Kc, const uint16_t *Vc, uint16_t *out, int M, int RT, int RTr,
+                                             int L0, int Hq, int Hkv) {  // RT: row tiles the fragment buffers are laid out for; RTr: tiles that hold rows
   constexpr int KT = DH / 32, DT = DH / 16;
+  constexpr int NB = PF_KEYS / 32;                                  // the cache's 32-key blocks of a stage
+  constexpr int ROWB = DH * 2, HALF = PF_KEYS * ROWB, STAGE = 2 * HALF;  // a stage: K rows, then V blocks
+  constexpr int LPW = HALF / 1024 / 4;                              // requests of a wave per half stage
   using v8 = std::conditional_t<F16, f16x8, bf16x8>;
   auto mma = [](v8 x, v8 y, f32x4 c) {
     if constexpr (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(x, y, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
   };
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
-  // the longest rows first: tiles are dealt from the end of the chunk
-  const int task = blockIdx.x * 4 + wave;
-  if (task >= RTr * Hq) return;
-  const int rt = RTr - 1 - task / Hq, h = task % Hq, kvh = h / (Hq / Hkv);
-  const int row = 16 * rt + c16;          // this lane's query row (as a column of the transposed scores)
-  const int last = L0 + (row < M ? row : M - 1);  // last visible cache row
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
+  const int g = Hq / Hkv, n_tile = g * RTr, n_task = (n_tile + 3) / 4;
+  const int kvh = uni((int)blockIdx.x % Hkv), w0 = uni((n_task - 1 - (int)blockIdx.x / Hkv) * 4);  // (the longest rows first)
+  const unsigned lds0 = (unsigned)(uintptr_t)lds;
+  const int last_row = L0 + M - 1, last_tile = n_tile - 1;
+  auto blocks_of = [&](int rt) { return ((L0 + 16 * rt + 15 < last_row ? L0 + 16 * rt + 15 : last_row) / PF_KEYS) + 1; };  // blocks that hold a visible key
+  const int nkb = uni(blocks_of((w0 + 3 < last_tile ? w0 + 3 : last_tile) / g));
+  // K half: row-major [key][DH], the 16-byte pieces of a row permuted by the key so that sixteen keys' equal pieces lie in
+  // different banks; V half: the cache's own blocks.  The last block may reach past the cache's last 32-key block: those
+  // requests repeat it (no row of it is visible).
+  auto swz = [](int key) { return DH == 128 ? key & 15 : (key >> 1) & 7; };
+  __amdgpu_buffer_rsrc_t rk = rsrc_of(Kc), rv = rsrc_of(Vc);
+  constexpr int KPI = 1024 / ROWB, PPR = ROWB / 16;  // keys a K request brings, pieces per key
+  constexpr int RPB = 32 * ROWB / 1024;              // requests per 32-key block
+  const int top_block = last_row >> 5;
+  const unsigned k_lane = (unsigned)((lane / PPR) * Hkv * ROWB), v_lane = (unsigned)(c16 * 64 + q4 * 16);
+  int nx_kb = 0;
+  unsigned nx_slot = 0;
+  auto request = [&]() {
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const int n = wave * LPW + i;  // request of the half stage: part n % RPB of its 32-key block n / RPB
+      int blk = nx_kb * NB + n / RPB;
+      blk = blk < top_block ? blk : top_block;
+      const int key0 = (n % RPB) * KPI;
+      const unsigned k_off = k_lane + (unsigned)(((lane % PPR) ^ swz(key0 + lane / PPR)) * 16);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (LDS_AS void *)(uintptr_t)(lds0 + nx_slot + (unsigned)n * 1024u), 16, k_off,
+                                               uni((unsigned)((blk * 32 + key0) * Hkv + kvh) * (unsigned)ROWB), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (LDS_AS void *)(uintptr_t)(lds0 + nx_slot + (unsigned)HALF + (unsigned)n * 1024u), 16, v_lane,
+                                               uni((unsigned)(blk * Hkv + kvh) * (unsigned)(32 * ROWB) + (unsigned)(n % RPB) * 1024u), 0, 0);
+    }
+    nx_slot = nx_slot ? 0u : (unsigned)STAGE;
+    if (nx_kb + 1 < nkb) ++nx_kb;  // (past the end the last one is requested again and never used)
+  };
+  const int t0 = w0 + wave, t = t0 < last_tile ? t0 : last_tile;  // (a wave without a tile repeats the last one and drops it)
+  const int rt = t / g, h = kvh * g + t % g;
+  const int row = 16 * rt + c16, last = L0 + (row < M ? row : M - 1);  // this lane's query row (as a column of the scores), its last visible key
   v8 q[KT];
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) q[kt] = *(const v8 *)(Q + ((((size_t)h * RT + rt) * KT + kt) * 64 + lane) * 8);
+  request();
+  const int nkb_w = uni(blocks_of(rt)), full = uni((L0 + 16 * rt + 1) / PF_KEYS);  // blocks 0 .. full - 1 are visible to every row of the tile
   f32x4 o[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -1e30f, l_run = 0.f;
-  u32x4 ka[KT], kb2[KT], vt[DT];
-  auto load_k = [&](int kb) {
-    const uint16_t *kp = Kc + (((size_t)(kb * 32 + c16) * Hkv + kvh) * DH + 8 * q4);
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      ka[kt] = *(const u32x4 *)(kp + kt * 32);
-      kb2[kt] = *(const u32x4 *)(kp + (size_t)16 * Hkv * DH + kt * 32);
-    }
-  };
-  auto load_v = [&](int kb) {
-    const uint16_t *vp = Vc + ((((size_t)kb * Hkv + kvh) * DH + c16) * 32 + 8 * q4);
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vt[dt] = *(const u32x4 *)(vp + dt * 16 * 32);
-  };
-  const int nkb = ((L0 + 16 * rt + 15 < L0 + M - 1 ? L0 + 16 * rt + 15 : L0 + M - 1) >> 5) + 1;  // blocks that hold a visible key of the tile
-  load_k(0);
-  load_v(0);
+  constexpr float LOG2E = 1.4426950408889634f;
   for (int kb = 0; kb < nkb; ++kb) {
-    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+    wait_vmcnt<0>();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_barrier();  // everybody's part of the stage is in, and nobody reads the stage before any more
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    request();
+    if (kb < nkb_w) {
+      const unsigned base = lds0 + (unsigned)((kb & 1) * STAGE);
+      f32x4 sc[2 * NB];
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      sa = mma(__builtin_bit_cast(v8, ka[kt]), q[kt], sa);
-      sb = mma(__builtin_bit_cast(v8, kb2[kt]), q[kt], sb);
-    }
-    if (kb + 1 < nkb) load_k(kb + 1);
-    float sv[8], p[8], mx = -1e30f;
-    bool ok[8];
+      for (int n = 0; n < 2 * NB; ++n) sc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      sv[i] = i < 4 ? sa[i] : sb[i - 4];
-      const int key = kb * 32 + (i >> 2) * 16 + 4 * q4 + (i & 3);
-      ok[i] = key <= last;
-      if (ok[i]) mx = fmaxf(mx, sv[i]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float corr = __expf(m_run - m_new);
-    float ps = 0.f;
+      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      p[i] = ok[i] ? __expf(sv[i] - m_new) : 0.f;
-      ps += p[i];
-    }
-    ps += __shfl_xor(ps, 16, 64);
-    ps += __shfl_xor(ps, 32, 64);
-    l_run = l_run * corr + ps;
-    m_run = m_new;
-    const u32x4 pw = {pack_kv(F16, p[0], p[1]), pack_kv(F16, p[2], p[3]), pack_kv(F16, p[4], p[5]), pack_kv(F16, p[6], p[7])};
+        for (int n = 0; n < 2 * NB; ++n) {
+          const v8 kf = __builtin_bit_cast(v8, *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)((16 * n + c16) * ROWB + ((4 * kt + q4) ^ swz(c16)) * 16)));
+          sc[n] = mma(kf, q[kt], sc[n]);
+        }
+      if (kb >= full) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      o[dt] *= corr;
-      o[dt] = mma(__builtin_bit_cast(v8, vt[dt]), __builtin_bit_cast(v8, pw), o[dt]);
+        for (int n = 0; n < 2 * NB; ++n)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (kb * PF_KEYS + 16 * n + 4 * q4 + i > last) sc[n][i] = -INFINITY;
+      }
+      float mx = sc[0][0];
+#pragma unroll
+      for (int n = 0; n < 2 * NB; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, sc[n][i]);
+      mx = pf_max_q4(mx);
+      if (__any(mx > m_run)) {  // (otherwise the factor is one in every lane)
+        const float m_new = fmaxf(m_run, mx);
+        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * LOG2E);
+        m_run = m_new;
+        l_run *= corr;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      }
+      const float mb = m_run * LOG2E;
+      v8 pb[NB];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        float pr[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          pr[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[2 * n + (i >> 2)][i & 3], LOG2E, -mb));
+          l_run += pr[i];  // (this lane's keys; added over the lanes at the end)
+        }
+        pb[n] = __builtin_bit_cast(v8, u32x4{pf_pack_p<F16>(pr[0], pr[1]), pf_pack_p<F16>(pr[2], pr[3]), pf_pack_p<F16>(pr[4], pr[5]), pf_pack_p<F16>(pr[6], pr[7])});
+      }
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const v8 vf = __builtin_bit_cast(v8, *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(HALF + (n * DT + dt) * 1024) + (unsigned)lane * 16u));
+          o[dt] = mma(vf, pb[n], o[dt]);
+        }
     }
-    if (kb + 1 < nkb) load_v(kb + 1);
   }
-  if (row < M) {
+  wait_vmcnt<0>();  // (the request past the last block lands before the LDS is given back)
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (t0 <= last_tile && row < M) {
     const float inv = 1.0f / l_run;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
@@ -423,6 +496,13 @@ __global__ __launch_bounds__(256) void pf_attn_kernel(const uint16_t *Q, const u
           u32x2{pack_f16(o[dt][0] * inv, o[dt][1] * inv), pack_f16(o[dt][2] * inv, o[dt][3] * inv)};
     }
   }
+}
+
+template <int DH, bool F16>
+__global__ __launch_bounds__(256, 2) void pf_attn_kernel(const uint16_t *Q, const uint16_t *Kc, const uint16_t *Vc, uint16_t *out, int M, int RT, int RTr,
+                                                         int L0, int Hq, int Hkv) {
+  __shared__ __attribute__((aligned(1024))) uint8_t pf_kv[4 * PF_KEYS * DH * 2];
+  pf_attn_body<DH, F16>((LDS_AS uint8_t *)pf_kv, Q, Kc, Vc, out, M, RT, RTr, L0, Hq, Hkv);
 }
 
 // x[row] = E[tok[row]] (eight elements per thread at a time), and cos, sin of position L0 + row for every RoPE pair (double
@@ -547,7 +627,7 @@ static int pf_launch_norm(int S, float *x, const float *part, const float *gain,
 template <int DH, bool F16>
 static int pf_launch_attn(const PfBuffers &b, const PfGemm &p, int M, int RT, int RTr, hipStream_t s) {
   ProfScope ps("pf_attn", s);
-  pf_attn_kernel<DH, F16><<<ceil_div(RTr * p.Hq, 4), 256, 0, s>>>(b.Q, p.Kc, p.Vc, b.attn, M, RT, RTr, p.L0, p.Hq, p.Hkv);
+  pf_attn_kernel<DH, F16><<<p.Hkv * ceil_div(p.Hq / p.Hkv * RTr, 4), 256, 0, s>>>(b.Q, p.Kc, p.Vc, b.attn, M, RT, RTr, p.L0, p.Hq, p.Hkv);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }
