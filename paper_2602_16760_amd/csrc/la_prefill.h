@@ -34,7 +34,7 @@ struct PfGemm {
   unsigned frag0;  // fragment index of the layer inside a CU's region
   int G, NW;       // workgroups and MFMA waves the streams were packed for
   int n_prev, prev_ntiles[3], prev_KT[3];
-  int ntiles, KT;
+  int t_first, ntiles, KT;  // column tiles t_first .. ntiles - 1 are wanted
   int S;              // slices of the contraction (PART; else 1)
   const uint16_t *A;  // operand fragments [KT][RT][64][8]
   int RT, M;          // row tiles the buffers are laid out for, rows
@@ -151,7 +151,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   static_assert((NS - 1) * LPW <= 63, "load counter");
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int wm = wave % WM, wn = wave / WM;
-  const int n_cg = (p.ntiles + CTB - 1) / CTB, RB = (p.RT + RTB - 1) / RTB;
+  const int n_cg = (p.ntiles - p.t_first + CTB - 1) / CTB, RB = (p.RT + RTB - 1) / RTB;
   const int xcd = (int)blockIdx.x % 8;
   int turn = (int)blockIdx.x / 8;
   const int rb = turn % RB;
@@ -175,7 +175,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
       mul_a[i] = uni((unsigned)p.RT * 1024u);
       mul_b[i] = 0u;
     } else {
-      const int tj = cg * CTB + f - RTB;
+      const int tj = p.t_first + cg * CTB + f - RTB;
       const int t = tj < p.ntiles ? tj : p.ntiles - 1;  // (a group past the last tile repeats it; its result is dropped)
       const int c = uni(t % p.G), lt = uni(t / p.G);
       unsigned off = p.frag0;
@@ -279,7 +279,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   if (r < n_kt) mul(fa[0], fb[0]);
   wait_vmcnt<0>();  // (the requests past the last k-tile land before the LDS is given back)
   const int r0 = rb * RTB + 4 * wm;
-  if (r0 < p.RT) pf_epilogue<MODE, NTW>(p, acc, r0, cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
+  if (r0 < p.RT) pf_epilogue<MODE, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
 }
 
 template <int MODE, int WM, int WN, int NTW, int NS>
@@ -557,7 +557,7 @@ static int pf_launch_tile(const PfGemm &p, hipStream_t s, bool prepare) {
     LA_HIP(hipFuncSetAttribute((const void *)pf_tile_kernel<MODE, WM, WN, NTW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     return LA_OK;
   }
-  const int n_cg = ceil_div(p.ntiles, WN * NTW), RB = ceil_div(p.RT, 4 * WM);
+  const int n_cg = ceil_div(p.ntiles - p.t_first, WN * NTW), RB = ceil_div(p.RT, 4 * WM);
   pf_tile_kernel<MODE, WM, WN, NTW, NS><<<RB * p.S * ((n_cg + 7) / 8 * 8), 64 * WM * WN, bytes, s>>>(p);
   LA_HIP(hipGetLastError());
   return LA_OK;
@@ -588,7 +588,7 @@ static void pf_choose(const PfGemm &p, int max_split, int cus, int &tile, int &S
     for (int k = 1; k <= max_split; ++k) {
       const PfTile &t = PF_TILES[i];
       if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > PF_PART_ROWS)) break;
-      const int n = ceil_div(p.RT, t.rows) * ceil_div(p.ntiles, t.cols) * k, round = t.per_cu * cus, rest = n % round;
+      const int n = ceil_div(p.RT, t.rows) * ceil_div(p.ntiles - p.t_first, t.cols) * k, round = t.per_cu * cus, rest = n % round;
       float us = (float)(n / round) * t.t_full + (rest == 0 ? 0.f : rest <= cus ? t.t_single : t.t_full);
       us *= (float)ceil_div(p.KT, k);
       if (max_split > 1) us += (float)k * (float)p.M * (float)p.d * 8.f / 4.5e6f;
@@ -719,10 +719,13 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
       p.act = b.act;
       return p;
     };
+    const bool last = l + 1 == d.n_layers;  // its K and V rows are all that anybody reads: the pass ends with them
     int rc, S_o = 0;
     if ((rc = pf_launch_norm(S_down, b.x, b.part, m->layers[l].g_attn, M, d.d_model, RT, b.ss, b.A, s))) return rc;
     PfGemm p = gemm_args(0, b.A);
+    if (last) p.t_first = m->qdim() / 16;
     if ((rc = pf_launch_gemm<PF_QKV>(p, s, "pf_gemm_qkv", f->n_wgs))) return rc;
+    if (last) break;
     if (d.head_dim == 128) rc = f16 ? pf_launch_attn<128, true>(b, p, M, RT, RTr, s) : pf_launch_attn<128, false>(b, p, M, RT, RTr, s);
     else rc = f16 ? pf_launch_attn<64, true>(b, p, M, RT, RTr, s) : pf_launch_attn<64, false>(b, p, M, RT, RTr, s);
     if (rc) return rc;
