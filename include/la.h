@@ -202,7 +202,7 @@ int la_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_t 
 
 /* Prompt prefill (Section 4.1 step 1; Section 6.3 "Prefill"): runs the n tokens tok[0..n)
  * (device int32) at positions L0.. through every layer, writes cache rows L0..L0+n-1 and
- * sets L = L0 + n.  Prompts of 128 tokens or more on the matrix-core path run as one matrix
+ * sets L = L0 + n.  Prompts of more than LA_MAX_ROWS tokens on the matrix-core path run as one matrix
  * product per weight matrix and chunk of 2048 tokens (the weights are read once per chunk),
  * with a causal attention kernel over the cache; shorter prompts, and models on the plain
  * kernels, go through the block kernel in causal chunks of LA_MAX_ROWS rows.  Everything is

@@ -136,6 +136,7 @@ struct GemmPlan {
 };
 
 struct PfBuffers {  // the large-M prompt pass (la_prefill.h), allocated at its first use
+  uint8_t *base = nullptr;  // the one allocation; the rest are its parts
   float *x = nullptr, *part = nullptr, *ss = nullptr, *cs = nullptr;
   uint16_t *A = nullptr, *Q = nullptr, *attn = nullptr, *act = nullptr;
 };
@@ -206,7 +207,7 @@ void mfma_destroy(la_model *m) {
   void *ps[] = {f->wstream, f->ustream, f->xa, f->attn_a, f->act_a, f->qf, f->xa_u, f->rsq_u, f->rsq, f->un_part,
                 f->sync, f->dev_gains, f->zero_len, f->trace, f->att_part, f->att_cnt,
                 f->sched[0][0], f->sched[0][1], f->sched[1][0], f->sched[1][1], f->sched[2][0], f->sched[2][1],
-                f->pf.x, f->pf.part, f->pf.ss, f->pf.cs, f->pf.A, f->pf.Q, f->pf.attn, f->pf.act};
+                f->pf.base};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   delete f;

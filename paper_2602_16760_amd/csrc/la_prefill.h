@@ -20,7 +20,9 @@ namespace la {
 // of the contraction: 2048 tokens, four layers, 2.77 ms against 3.02 in chunks of 1024; 1100 tokens 1.89 against 2.05.  4096
 // rows gain nothing more (3000 tokens at 1000: 5.4 ms against 4.5, two rounds of which the second is nearly empty).
 constexpr int PF_ROWS = 2048;
-constexpr int PF_MIN = 128;     // shorter prompts go through the block kernel
+// Shorter prompts are one block of the block kernel (64 rows of the 7B shape, eight layers: 1.14 ms); two blocks read the
+// weights twice (77 tokens 1.92 ms, the products' 128-row tiles 1.24).
+constexpr int PF_MIN = LA_MAX_ROWS + 1;
 constexpr int PF_CHUNKS = 32;   // partial sums of squares per row (column chunks of pf_norm_kernel)
 constexpr int PF_PART_ROWS = 4096;  // rows of all slices' products together
 constexpr int PF_MAX_SPLIT = 8; // most slices of a contraction
@@ -635,29 +637,29 @@ static int pf_launch_attn(const PfBuffers &b, const PfGemm &p, int M, int RT, in
   return LA_OK;
 }
 
+// One allocation for all buffers (eight took 0.4 ms of the first prompt).  They need no clearing: what the products read of
+// rows past the prompt's end only reaches rows past its end.
 static int pf_alloc(la_model *m, PfBuffers &b) {
   const la_model_desc &d = m->d;
-  const size_t R = PF_ROWS;
-  bool ok = true;
-  ok = ok && (b.x = (float *)dalloc(R * d.d_model * 4));
-  ok = ok && (b.part = (float *)dalloc((size_t)PF_PART_ROWS * d.d_model * 4));
-  ok = ok && (b.ss = (float *)dalloc(R * PF_CHUNKS * 4));
-  ok = ok && (b.cs = (float *)dalloc(R * d.head_dim * 4));
-  ok = ok && (b.A = (uint16_t *)dalloc(R * d.d_model * 2));
-  ok = ok && (b.Q = (uint16_t *)dalloc(R * (size_t)m->qdim() * 2));
-  ok = ok && (b.attn = (uint16_t *)dalloc(R * (size_t)m->qdim() * 2));
-  ok = ok && (b.act = (uint16_t *)dalloc(R * (size_t)d.d_ffn * 2));
-  LA_REQUIRE(ok, LA_ENOMEM, "device allocation of the prefill buffers failed");
-  // the fragments of rows past the prompt's end are read by the matrix products: keep them finite
-  LA_HIP(hipMemset(b.Q, 0, R * (size_t)m->qdim() * 2));
-  LA_HIP(hipMemset(b.attn, 0, R * (size_t)m->qdim() * 2));
-  LA_HIP(hipMemset(b.act, 0, R * (size_t)d.d_ffn * 2));
+  const size_t R = PF_ROWS, dm = d.d_model, qd = m->qdim();
+  size_t total = 0;
+  auto place = [&](size_t bytes) {
+    const size_t at = total;
+    total += (bytes + 1023) / 1024 * 1024;
+    return at;
+  };
+  const size_t x = place(R * dm * 4), part = place(PF_PART_ROWS * dm * 4), ss = place(R * PF_CHUNKS * 4), cs = place(R * d.head_dim * 4),
+               A = place(R * dm * 2), Q = place(R * qd * 2), attn = place(R * qd * 2), act = place(R * (size_t)d.d_ffn * 2);
   for (int i = 0; i < PF_N_TILES; ++i) {
     int rc = pf_launch_tile<PF_QKV>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_PART>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_GATEUP>(i, PfGemm{}, nullptr, true);
     if (rc) return rc;
   }
+  uint8_t *p = (uint8_t *)dalloc(total);
+  LA_REQUIRE(p != nullptr, LA_ENOMEM, "device allocation of the prefill buffers (%zu bytes) failed", total);
+  b = PfBuffers{p, (float *)(p + x), (float *)(p + part), (float *)(p + ss), (float *)(p + cs),
+                (uint16_t *)(p + A), (uint16_t *)(p + Q), (uint16_t *)(p + attn), (uint16_t *)(p + act)};
   return LA_OK;
 }
 
@@ -670,7 +672,7 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
   MfmaModel *f = m->mf;
   const la_model_desc &d = m->d;
   LA_REQUIRE(f->use_r, LA_EINVAL, "the large-M prompt pass reads the register-streaming kernel's weight layout");
-  if (!f->pf.x) {
+  if (!f->pf.base) {
     int rc = pf_alloc(m, f->pf);
     if (rc) return rc;
   }
