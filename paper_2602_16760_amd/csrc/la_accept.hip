@@ -47,225 +47,298 @@ __host__ __device__ inline void block_layout(int W, int N, int G, int n_cand, in
     }
 }
 
-__device__ void build_block(la_step_state *st, int W, int N, int G) {
-  int Bp = st->Bp;
-  block_layout(W, N, G, st->n_cand, st->L, Bp, st->pos, st->vis);
-  for (int i = 0; i < Bp; ++i) st->tok[i] = st->c0;
-  for (int r = 0; r < N - 1; ++r)
-    for (int c = 0; c < W; ++c) st->tok[la_row_index(W, r, c)] = st->win[r * W + c];
-  for (int k = 0; k < st->n_cand; ++k)
-    for (int j = 1; j <= N - 1; ++j) st->tok[v_row_index(W, N, k, j)] = st->cand[k * (N - 1) + j - 1];
-}
-
-// Insert (key -> tup[0..N-2]).  Present: refresh its stamp.  Else take a free slot, else
-// replace the slot with the smallest stamp.
-__device__ void pool_insert(const PoolView &p, int key, const int32_t *tup) {
-  uint32_t now = *p.counter + 1u;
-  *p.counter = now;
-  if (p.G == 0 || key < 0 || key >= p.vocab) return;
-  int n1 = p.N - 1;
-  uint32_t *st = p.stamp + (size_t)key * p.G;
-  int32_t *tk = p.toks + (size_t)key * p.G * n1;
-  int free_slot = -1, old_slot = 0;
-  uint32_t old_stamp = 0xffffffffu;
-  for (int s = 0; s < p.G; ++s) {
-    uint32_t sv = st[s];
-    if (sv == 0u) {
-      if (free_slot < 0) free_slot = s;
-      continue;
-    }
-    bool same = true;
-    for (int j = 0; j < n1; ++j) same = same && (tk[s * n1 + j] == tup[j]);
-    if (same) {
-      st[s] = now;
-      return;
-    }
-    if (sv < old_stamp) {
-      old_stamp = sv;
-      old_slot = s;
-    }
+// The next block into *st, one row per lane (lane < 64): tokens from the window and the candidates in LDS.
+__device__ __forceinline__ void build_block(la_step_state *st, int W, int N, int n_cand, int t, int Bp, int c0, const int32_t *win, const int32_t *cand, int i) {
+  if (i >= Bp) return;
+  const int n1 = N - 1;
+  int pos = t, tok = c0;
+  uint64_t vis = 1ull << i;
+  const int w = i - 1, v = w - W * n1;  // index among the window rows, among the verification rows
+  if (i > 0 && v < 0) {
+    const int r = w / W, c = w - r * W;
+    uint64_t m = 1ull | (((2ull << c) - 1ull) << la_row_index(W, 0, 0));
+    for (int r2 = 1; r2 <= r; ++r2) m |= 1ull << la_row_index(W, r2, c);
+    pos = t + 1 + c + r;
+    vis = m;
+    tok = win[w];
+  } else if (i > 0 && v < n_cand * n1) {
+    const int k = v / n1, j = v - k * n1 + 1;
+    vis = 1ull | (((1ull << j) - 1ull) << v_row_index(W, N, k, 1));
+    pos = t + j;
+    tok = cand[v];
   }
-  int s = free_slot >= 0 ? free_slot : old_slot;
-  for (int j = 0; j < n1; ++j) tk[s * n1 + j] = tup[j];
-  st[s] = now;
+  st->pos[i] = pos;
+  st->vis[i] = vis;
+  st->tok[i] = tok;
 }
 
-// Candidates of `key`, most recently inserted first, into cand[k*(N-1)+j]; returns the count.
-__device__ int pool_lookup(const PoolView &p, int key, int32_t *cand) {
+// Candidates of `key` (its G slots: stamp and tuple of slot s in lane s), most recently inserted first, into cand[k*(N-1)+j]
+// (LDS and, where it is kept, the state); returns the count.  Stamps are distinct, so a slot's place is the number of
+// later ones.
+__device__ __forceinline__ int pool_lookup(const PoolView &p, int key, int32_t *cand, int32_t *state_cand, int lane) {
   if (p.G == 0 || key < 0 || key >= p.vocab) return 0;
-  int n1 = p.N - 1;
-  const uint32_t *st = p.stamp + (size_t)key * p.G;
-  const int32_t *tk = p.toks + (size_t)key * p.G * n1;
-  int n = 0;
-  uint32_t below = 0xffffffffu;  // stamps are distinct: walk them in descending order
-  for (;;) {
-    int best = -1;
-    uint32_t bs = 0u;
-    for (int s = 0; s < p.G; ++s) {
-      uint32_t sv = st[s];
-      if (sv != 0u && sv < below && sv > bs) {
-        bs = sv;
-        best = s;
-      }
+  const int n1 = p.N - 1;
+  const uint32_t sv = lane < p.G ? p.stamp[(size_t)key * p.G + lane] : 0u;
+  int place = 0;
+  for (int s = 0; s < p.G; ++s) place += (uint32_t)__shfl((int)sv, s, 64) > sv ? 1 : 0;
+  if (sv != 0u)
+    for (int j = 0; j < n1; ++j) {
+      const int32_t t = p.toks[((size_t)key * p.G + lane) * n1 + j];
+      cand[place * n1 + j] = t;
+      state_cand[place * n1 + j] = t;
     }
-    if (best < 0) break;
-    for (int j = 0; j < n1; ++j) cand[n * n1 + j] = tk[best * n1 + j];
-    below = bs;
-    ++n;
+  return __popcll(__ballot(sv != 0u));
+}
+
+// Inserts (win[c] -> tuple of column c) for c = 0 .. W - 1 in that order: a tuple that is present gets a new stamp, else a
+// free slot is taken, else the one with the smallest stamp.  A wave takes as many columns at once as it has lanes for their
+// slots, if their keys differ (lane: slot s of column c); columns that share a key go one at a time.
+__device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *win, const int32_t *newest, int W, int lane) {
+  const int G = p.G, n1 = p.N - 1;
+  const uint32_t now = *p.counter;
+  if (lane == 0) *p.counter = now + (uint32_t)W;
+  if (G == 0) return;
+  const int per = 64 / G;
+  for (int c0 = 0; c0 < W;) {
+    int n = W - c0 < per ? W - c0 : per;
+    // the first column of the batch whose key an earlier one of the batch has: the batch ends in front of it
+    bool again = false;
+    if (lane > 0 && lane < n)
+      for (int i = 0; i < lane; ++i) again = again || win[c0 + i] == win[c0 + lane];
+    const uint64_t rep = __ballot(again);
+    if (rep) n = __ffsll((long long)rep) - 1;
+    const int col = lane / G, s = lane - col * G, c = c0 + col;
+    const int key = col < n ? win[c] : -1;
+    const bool in = col < n && key >= 0 && key < p.vocab;
+    const size_t slot = in ? (size_t)key * G + s : 0;
+    const uint32_t sv = in ? p.stamp[slot] : 0u;
+    bool same = in && sv != 0u;
+    if (in)
+      for (int j = 0; j < n1; ++j) same = (p.toks[slot * n1 + j] == (j + 1 < n1 ? win[(j + 1) * W + c] : newest[c])) && same;
+    const uint64_t mine = ((G < 64 ? 1ull << G : 0ull) - 1ull) << (col * G < 64 ? col * G : 0);
+    const uint64_t hit = __ballot(same) & mine, empty = __ballot(in && sv == 0u) & mine;
+    bool oldest = true;
+    for (int i = 0; i < G; ++i) {
+      const uint32_t o = (uint32_t)__shfl((int)sv, col * G + i < 64 ? col * G + i : 63, 64);
+      oldest = oldest && (i == s || o > sv);
+    }
+    const bool take = in && (hit ? same : empty ? lane == __ffsll((long long)empty) - 1 : oldest);
+    if (take) {
+      p.stamp[slot] = now + (uint32_t)c + 1u;
+      if (!hit)
+        for (int j = 0; j < n1; ++j) p.toks[slot * n1 + j] = j + 1 < n1 ? win[(j + 1) * W + c] : newest[c];
+    }
+    __threadfence();  // (the next batch, and the lookup, read what this one stored)
+    c0 += n;
   }
-  return n;
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-__global__ void state_init_kernel(PoolView p, la_step_state *st, const int32_t *prompt, int P, int W, int N, int G,
-                                  int Bp, int seed_pool, int32_t *kv_L) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  *p.counter = 0u;
-  if (seed_pool)
-    for (int i = 0; i + N <= P; ++i) pool_insert(p, prompt[i], prompt + i + 1);
-  for (int r = 0; r < N - 1; ++r)
-    for (int c = 0; c < W; ++c) st->win[r * W + c] = prompt[(r + c) % P];
-  st->L = P - 1;
-  st->c0 = prompt[P - 1];
-  st->Bp = Bp;
-  st->steps = st->matched_steps = st->n_emitted = st->last_emitted = st->last_k = st->last_m = 0;
-  st->error = st->reserved = 0;
-  st->n_cand = (N >= 2) ? pool_lookup(p, st->c0, st->cand) : 0;
-  build_block(st, W, N, G);
-  *kv_L = P - 1;
+// Every N-gram of the prompt into the (empty) pool, as if inserted in order: a key ends up with its last G distinct tuples,
+// each with the stamp of its last insertion.  One wave per position; the last position of each key does the work: it walks
+// back over the prompt, 256 positions at a time, and collects tuples it has not seen until it has G.  (One thread inserting
+// one N-gram after the other waited for the pool's memory twice per token: 2.9 ms for 2048 tokens, now 9 us.)
+__global__ __launch_bounds__(256) void pool_seed_kernel(PoolView p, const int32_t *prompt, int n) {  // n = P - N + 1 N-grams
+  const int lane = threadIdx.x & 63, i = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), n1 = p.N - 1;
+  if (i >= n) return;
+  const int key = prompt[i];
+  if (key < 0 || key >= p.vocab) return;
+  for (int j0 = i + 1; j0 < n; j0 += 256) {  // a later position with this key?
+    bool found = false;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + 64 * u + lane;
+      found = found || (j < n && prompt[j] == key);
+    }
+    if (__any(found)) return;
+  }
+  int got = i, count = 1;  // lane s: position of the s-th tuple found
+  for (int j0 = i - 1; j0 >= 0 && count < p.G; j0 -= 256) {  // positions j0, j0 - 1, ...
+    bool at[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 - 64 * u - lane;
+      at[u] = j >= 0 && prompt[j < 0 ? 0 : j] == key;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      uint64_t m = __ballot(at[u]);
+      while (m != 0 && count < p.G) {
+        const int j = j0 - 64 * u - (__ffsll((long long)m) - 1);
+        m &= m - 1;
+        bool same = lane < count;
+        for (int t = 1; t <= n1; ++t) same = (prompt[got + t] == prompt[j + t]) && same;
+        if (!__any(same)) {
+          if (lane == count) got = j;
+          ++count;
+        }
+      }
+    }
+  }
+  if (lane < count) {
+    const size_t slot = (size_t)key * p.G + lane;
+    p.stamp[slot] = (uint32_t)got + 1u;
+    for (int t = 0; t < n1; ++t) p.toks[slot * n1 + t] = prompt[got + 1 + t];
+  }
 }
 
-__global__ void accept_kernel(PoolView p, la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total,
-                              int W, int N, int G, int32_t *kv_L, const int32_t *err) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  st->error = *err;  // what the launches before this one on the model raised (0: nothing)
-  int remaining = max_total - st->n_emitted;
+__global__ __launch_bounds__(64) void state_init_kernel(PoolView p, la_step_state *st, const int32_t *prompt, int P, int W, int N, int G,
+                                                        int Bp, uint32_t inserted, int32_t *kv_L) {
+  __shared__ int32_t win[LA_MAX_ROWS], cand[LA_MAX_ROWS];
+  const int lane = threadIdx.x, c0 = prompt[P - 1];
+  if (lane < W * (N - 1)) {
+    const int r = lane / W, c = lane - r * W;
+    win[lane] = st->win[lane] = prompt[(r + c) % P];
+  }
+  const int n_cand = N >= 2 ? pool_lookup(p, c0, cand, st->cand, lane) : 0;
+  __syncthreads();
+  build_block(st, W, N, n_cand, P - 1, Bp, c0, win, cand, lane);
+  if (lane == 0) {
+    *p.counter = inserted;
+    st->L = P - 1;
+    st->c0 = c0;
+    st->Bp = Bp;
+    st->steps = st->matched_steps = st->n_emitted = st->last_emitted = st->last_k = st->last_m = 0;
+    st->error = st->reserved = 0;
+    st->n_cand = n_cand;
+    *kv_L = P - 1;
+  }
+}
+
+// One wave: verification with a candidate per lane, harvest with a pool slot per lane, the next block with a row per lane;
+// what the step reads comes into LDS at once.  (One thread doing all of it took 23 us, most of it waiting for one word
+// after the other.)
+__global__ __launch_bounds__(64) void accept_kernel(PoolView p, la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total,
+                                                    int W, int N, int G, int32_t *kv_L, const int32_t *err) {
+  __shared__ int32_t id[LA_MAX_ROWS], win[LA_MAX_ROWS], cand[LA_MAX_ROWS], newest[LA_MAX_ROWS];
+  const int lane = threadIdx.x, n1 = N - 1, rows = 1 + (W + G) * n1;
+  if (lane < rows) id[lane] = ids[lane];
+  win[lane] = lane < W * n1 ? st->win[lane] : 0;
+  cand[lane] = st->cand[lane];
+  const int emitted_before = st->n_emitted, n_cand = st->n_cand, L0 = st->L, Bp = st->Bp;
+  const int error = *err;  // what the launches before this one on the model raised (0: nothing)
+  const int steps = st->steps, matched = st->matched_steps;
+  __syncthreads();
+  const int remaining = max_total - emitted_before;
   if (remaining <= 0) {  // budget spent: the step is a no-op
-    st->last_emitted = 0;
+    if (lane == 0) {
+      st->error = error;
+      st->last_emitted = 0;
+    }
     return;
   }
-  int n1 = N - 1;
-  int y0 = ids[0];
-  int best_k = 0, best_m = 0;
-  for (int k = 0; k < st->n_cand; ++k) {
-    const int32_t *cd = st->cand + k * n1;
-    int m = 0;
-    if (cd[0] == y0) {
-      m = 1;
-      while (m < n1 && cd[m] == ids[v_row_index(W, N, k, m)]) ++m;
-    }
-    if (m > best_m) {
-      best_m = m;
-      best_k = k;
-    }
+  // candidate `lane` matches m tokens; the longest match wins, the lowest candidate of equal ones
+  int m = 0;
+  if (lane < n_cand && cand[lane * n1] == id[0]) {
+    m = 1;
+    while (m < n1 && cand[lane * n1 + m] == id[v_row_index(W, N, lane, m)]) ++m;
   }
-  int e = best_m + 1;
-  if (e > remaining) e = remaining;
-  int base = st->n_emitted;
-  int last = y0;
-  emitted[base] = y0;
-  for (int j = 1; j < e; ++j) {
-    last = ids[v_row_index(W, N, best_k, j)];
-    emitted[base + j] = last;
+  int best = m * 64 + (63 - lane);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const int other = __shfl_xor(best, o, 64);
+    best = other > best ? other : best;
   }
-  st->n_emitted = base + e;
-  st->last_emitted = e;
-  st->last_k = best_k;
-  st->last_m = best_m;
-  st->steps += 1;
-  st->matched_steps += (best_m >= 1) ? 1 : 0;
-  // harvest: each window column yields one n-gram ending in the model's newest guess
+  const int best_m = best >> 6, best_k = best_m > 0 ? 63 - (best & 63) : 0;
+  const int e = best_m + 1 < remaining ? best_m + 1 : remaining;
+  if (lane < e) emitted[emitted_before + lane] = lane == 0 ? id[0] : id[v_row_index(W, N, best_k, lane)];
+  const int last = e == 1 ? id[0] : id[v_row_index(W, N, best_k, e - 1)];
+  // harvest: each window column yields one n-gram ending in the model's newest guess; then the columns move up
+  int n_next = 0;
   if (N >= 2) {
-    int32_t tup[LA_MAX_ROWS];
-    for (int c = 0; c < W; ++c) {
-      int nl = ids[la_row_index(W, N - 2, c)];
-      for (int r = 1; r < n1; ++r) tup[r - 1] = st->win[r * W + c];
-      tup[n1 - 1] = nl;
-      pool_insert(p, st->win[c], tup);
-    }
-    for (int c = 0; c < W; ++c) {
-      int nl = ids[la_row_index(W, N - 2, c)];
-      for (int r = 0; r + 1 < n1; ++r) st->win[r * W + c] = st->win[(r + 1) * W + c];
-      st->win[(n1 - 1) * W + c] = nl;
-    }
+    if (lane < W) newest[lane] = id[la_row_index(W, N - 2, lane)];
+    __syncthreads();
+    pool_harvest(p, win, newest, W, lane);
+    const int up = lane + W < W * n1 ? win[lane + W] : lane < W * n1 ? newest[lane - W * (n1 - 1)] : 0;
+    __syncthreads();
+    if (lane < W * n1) win[lane] = st->win[lane] = up;
+    n_next = pool_lookup(p, last, cand, st->cand, lane);
+    __syncthreads();
   }
-  st->L += e;
-  *kv_L = st->L;
-  st->c0 = last;
-  st->n_cand = (N >= 2) ? pool_lookup(p, last, st->cand) : 0;
-  build_block(st, W, N, G);
+  build_block(st, W, N, n_next, L0 + e, Bp, last, win, cand, lane);
+  if (lane == 0) {
+    st->error = error;
+    st->n_emitted = emitted_before + e;
+    st->last_emitted = e;
+    st->last_k = best_k;
+    st->last_m = best_m;
+    st->steps = steps + 1;
+    st->matched_steps = matched + (best_m >= 1 ? 1 : 0);
+    st->L = L0 + e;
+    *kv_L = L0 + e;
+    st->c0 = last;
+    st->n_cand = n_next;
+  }
 }
 
 // ---- Jacobi decoding (Section 4.2) --------------------------------------------------------------
 // The block's rows: row 0 = c0 at position L, row i = guess y_i at L + i (i < k) under the plain
 // causal mask; rows k.. carry nothing.  The guesses live in st->cand[0..k-1].
-__device__ void jacobi_build(la_step_state *st, int k) {
-  const int Bp = st->Bp, t = st->L;
-  for (int i = 0; i < Bp; ++i) {
-    if (i < k) {
-      st->tok[i] = i == 0 ? st->c0 : st->cand[i - 1];
-      st->pos[i] = t + i;
-      st->vis[i] = i == 63 ? ~0ull : ((1ull << (i + 1)) - 1ull);
-    } else {
-      st->tok[i] = 0;
-      st->pos[i] = t + k - 1;
-      st->vis[i] = 1ull << i;
-    }
-  }
+__device__ __forceinline__ void jacobi_build(la_step_state *st, int k, int t, int Bp, int c0, const int32_t *guess, int i) {
+  if (i >= Bp) return;
+  st->tok[i] = i >= k ? 0 : i == 0 ? c0 : guess[i - 1];
+  st->pos[i] = i < k ? t + i : t + k - 1;
+  st->vis[i] = i < k ? (2ull << i) - 1ull : 1ull << i;
 }
 
-__global__ void jacobi_init_kernel(la_step_state *st, const int32_t *prompt, int P, int k, int Bp, int32_t *kv_L) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  st->L = P - 1;
-  st->c0 = prompt[P - 1];
-  st->Bp = Bp;
-  st->n_cand = k;
-  st->steps = st->matched_steps = st->n_emitted = st->last_emitted = st->last_k = st->last_m = 0;
-  st->error = st->reserved = 0;
-  for (int i = 0; i < k; ++i) st->cand[i] = st->c0;  // every position starts from the last committed token
-  jacobi_build(st, k);
-  *kv_L = P - 1;
+__global__ __launch_bounds__(64) void jacobi_init_kernel(la_step_state *st, const int32_t *prompt, int P, int k, int Bp, int32_t *kv_L) {
+  __shared__ int32_t guess[LA_MAX_ROWS];
+  const int lane = threadIdx.x, c0 = prompt[P - 1];
+  guess[lane] = c0;  // every position starts from the last committed token
+  if (lane < k) st->cand[lane] = c0;
+  __syncthreads();
+  jacobi_build(st, k, P - 1, Bp, c0, guess, lane);
+  if (lane == 0) {
+    st->L = P - 1;
+    st->c0 = c0;
+    st->Bp = Bp;
+    st->n_cand = k;
+    st->steps = st->matched_steps = st->n_emitted = st->last_emitted = st->last_k = st->last_m = 0;
+    st->error = st->reserved = 0;
+    *kv_L = P - 1;
+  }
 }
 
 // One pass's greedy ids become the new guesses (ids[i] is the prediction for position L + i + 1).  The block has
 // converged when the pass returned its own input, and after k passes at the latest (pass j fixes guess j for good);
 // it then commits: the pass's cache rows L.. were computed from the final tokens, so they stay and L advances.
-__global__ void jacobi_accept_kernel(la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total, int k,
-                                     int32_t *kv_L, const int32_t *err) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  st->error = *err;
-  int remaining = max_total - st->n_emitted;
+// One wave, a guess per lane.
+__global__ __launch_bounds__(64) void jacobi_accept_kernel(la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total, int k,
+                                                           int32_t *kv_L, const int32_t *err) {
+  __shared__ int32_t guess[LA_MAX_ROWS];
+  const int lane = threadIdx.x;
+  const int id = lane < k ? ids[lane] : 0, old = lane < k ? st->cand[lane] : 0;
+  const int before = st->n_emitted, passes = st->last_k + 1, steps = st->steps, matched = st->matched_steps, L0 = st->L, Bp = st->Bp, c0 = st->c0;
+  const int error = *err;
+  const int remaining = max_total - before;
+  __syncthreads();
+  if (lane == 0) st->error = error;
   if (remaining <= 0) {
-    st->last_emitted = 0;
+    if (lane == 0) st->last_emitted = 0;
     return;
   }
-  bool same = true;
-  for (int i = 0; i < k; ++i) {
-    same = same && (ids[i] == st->cand[i]);
-    st->cand[i] = ids[i];
-  }
-  st->steps += 1;
-  st->last_k += 1;
-  if (!same && st->last_k < k) {
-    st->last_emitted = 0;
-    jacobi_build(st, k);
-    return;
-  }
-  int e = k < remaining ? k : remaining;
-  for (int i = 0; i < e; ++i) emitted[st->n_emitted + i] = st->cand[i];
-  st->n_emitted += e;
-  st->last_emitted = e;
-  st->last_m = st->last_k;
-  st->last_k = 0;
-  st->matched_steps += 1;
-  st->L += e;
-  *kv_L = st->L;
-  st->c0 = st->cand[e - 1];
-  for (int i = 0; i < k; ++i) st->cand[i] = st->c0;
-  jacobi_build(st, k);
+  const bool commit = !__any(id != old) || passes >= k;
+  const int e = k < remaining ? k : remaining;
+  const int last = __shfl(id, e - 1, 64);
+  guess[lane] = commit ? last : id;
+  if (lane < k) st->cand[lane] = guess[lane];
+  if (commit && lane < e) emitted[before + lane] = id;
+  __syncthreads();
+  jacobi_build(st, k, commit ? L0 + e : L0, Bp, commit ? last : c0, guess, lane);
+  if (lane != 0) return;
+  st->steps = steps + 1;
+  st->last_emitted = commit ? e : 0;
+  st->last_k = commit ? 0 : passes;
+  if (!commit) return;
+  st->n_emitted = before + e;
+  st->last_m = passes;
+  st->matched_steps = matched + 1;
+  st->L = L0 + e;
+  *kv_L = L0 + e;
+  st->c0 = last;
 }
 
 // Cache relocation: the accepted verification rows of candidate last_k move from block rows
@@ -358,9 +431,14 @@ extern "C" int la_state_init(la_pool *p, la_kv *kv, const la_lookahead_desc *d, 
     ProfScope ps("pool_clear", s);
     fill_u32_kernel<<<1024, 256, 0, s>>>(p->stamp, slots, 0u);
   }
+  const int grams = seed_pool && P >= d->N ? P - d->N + 1 : 0;
+  if (grams > 0 && d->G > 0) {
+    ProfScope ps("pool_seed", s);
+    pool_seed_kernel<<<ceil_div(grams, 4), 256, 0, s>>>(view(p), prompt, grams);
+  }
   {
     ProfScope ps("state_init", s);
-    state_init_kernel<<<1, 64, 0, s>>>(view(p), state, prompt, P, d->W, d->N, d->G, Bp, seed_pool, kv->L_dev);
+    state_init_kernel<<<1, 64, 0, s>>>(view(p), state, prompt, P, d->W, d->N, d->G, Bp, (uint32_t)grams, kv->L_dev);
   }
   LA_HIP(hipGetLastError());
   kv->L_bound = P - 1;
