@@ -189,7 +189,7 @@ extern "C" void la_free_model(la_model *m) {
     for (void *p : ps)
       if (p) (void)hipFree(p);
   }
-  void *ps[] = {m->embed, m->unembed, m->g_final, m->h, m->qkv, m->attn, m->gu, m->act, m->logits, m->rope_cs, m->err_dev,
+  void *ps[] = {m->embed, m->unembed, m->g_final, m->qkv, m->attn, m->act, m->logits, m->rope_cs, m->err_dev,
                 m->pf_hidden, m->pf_pos, m->pf_vis};
   for (void *p : ps)
     if (p) (void)hipFree(p);
@@ -232,10 +232,8 @@ extern "C" int la_init_model(const la_model_desc *desc, const la_layer_weights *
     ok = hipHostGetDevicePointer((void **)&m->err_map, m->err_host, 0) == hipSuccess;
   }
   if (!m->use_mfma) {
-    ok = ok && (m->h = (float *)dev_alloc(R * d.d_model * 4));
     ok = ok && (m->qkv = (float *)dev_alloc(R * m->nqkv() * 4));
     ok = ok && (m->attn = (float *)dev_alloc(R * m->qdim() * 4));
-    ok = ok && (m->gu = (float *)dev_alloc(R * 2 * (size_t)d.d_ffn * 4));
     ok = ok && (m->act = (float *)dev_alloc(R * (size_t)d.d_ffn * 4));
     if (unembed) ok = ok && (m->logits = (float *)dev_alloc(R * (size_t)d.vocab * 4));
   }

@@ -42,51 +42,132 @@ __device__ __forceinline__ float block_max(float v, float *red) {
   return t;
 }
 
-// out[b,:] = x[b,:] * rsqrt(mean(x[b,:]^2) + eps) * g
-__global__ void rmsnorm_kernel(const float *x, const float *g, float eps, int d, float *out) {
-  __shared__ float red[8];
-  const float *xr = x + (size_t)blockIdx.x * d;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) ss += xr[i] * xr[i];
-  ss = block_sum(ss, red);
-  float r = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)blockIdx.x * d + i] = xr[i] * r * g[i];
-}
+// C[M, N] (=|+=) A[M, K] W[K, N] with the fp32 matrix instruction (fp32 operands, products and sums), M <= 64.  A workgroup
+// takes 16 columns (WIDE: 64, GLU: 16 of the gate and the same 16 of up) and all rows; its eight waves share the
+// contraction, 16 deep at a time, and their sums are added in wave order.  Bound: the latency of the loads; these matrices
+// are small, so the columns are cut finely and the contraction is split where one thread per column walked it alone
+// (2 layers of the tiny shape, 17 rows: 256 x 512 28 us, 688 x 256 70 us; now 4 - 6 us a launch).
+//   gain != NULL: A is x * gain and the sums are multiplied by the row factor 1 / sqrt(mean x^2 + eps) of the norm.
+//   GLU: C[M, F] = silu(gate) * up.
+// A lane's four contraction indices of a turn are consecutive: the k-th matrix instruction of the turn takes the k-th of
+// them from every lane, in both operands alike.
+enum GemmKind { GEMM_16 = 0, GEMM_WIDE = 1, GEMM_GLU = 2 };
+typedef float f4 __attribute__((ext_vector_type(4)));
+constexpr int GEMM_WAVES = 8;
 
-// C[M,N] (=|+=) A[M,K] W[K,N].  One thread owns one column for 8 rows.
-template <typename T>
-__global__ void gemm_generic_kernel(const float *A, int lda, const T *W, int ldw, float *C, int ldc, int M,
-                                    int K, int N, int accumulate) {
-  constexpr int KT = 128, MR = 8;
-  __shared__ float As[MR][KT];
-  int n = blockIdx.x * blockDim.x + threadIdx.x;
-  int m0 = blockIdx.y * MR;
-  float acc[MR];
+template <typename T, int MT, int KIND>
+__global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const float *A, int lda, const float *gain, float eps, const T *W, int ldw,
+                                                                       float *C, int ldc, int M, int K, int N, int accumulate, int vec) {
+  constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1, HALF = GEMM_WAVES / 2;
+  extern __shared__ __attribute__((aligned(16))) float gemm_lds[];
+  f4 *part = reinterpret_cast<f4 *>(gemm_lds);                     // [wave of the lower half][MT][CT][lane]
+  float *sqs = gemm_lds + HALF * MT * CT * 64 * 4;           // [wave][16 MT] sums of squares
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
+  const int c0 = blockIdx.x * (KIND == GEMM_WIDE ? 64 : 16);
+  // (columns past the end read the last one; their results are dropped)
+  int col[CT];
 #pragma unroll
-  for (int i = 0; i < MR; ++i) acc[i] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += KT) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < MR * KT; e += blockDim.x) {
-      int i = e / KT, kk = e % KT;
-      As[i][kk] = (m0 + i < M && k0 + kk < K) ? A[(size_t)(m0 + i) * lda + k0 + kk] : 0.f;
-    }
-    __syncthreads();
-    if (n < N) {
-      int kmax = min(KT, K - k0);
-      for (int kk = 0; kk < kmax; ++kk) {
-        float w = load_as_float<T>(W + (size_t)(k0 + kk) * ldw + n);
-#pragma unroll
-        for (int i = 0; i < MR; ++i) acc[i] = fmaf(As[i][kk], w, acc[i]);
-      }
-    }
+  for (int ct = 0; ct < CT; ++ct) {
+    const int c = KIND == GEMM_WIDE ? c0 + 4 * c16 + ct : c0 + c16;
+    col[ct] = (c < N ? c : N - 1) + (KIND == GEMM_GLU && ct == 1 ? N : 0);
   }
-  if (n < N) {
+  f4 acc[MT][CT];
+  float sq[MT];
 #pragma unroll
-    for (int i = 0; i < MR; ++i)
-      if (m0 + i < M) {
-        float *c = C + (size_t)(m0 + i) * ldc + n;
-        *c = accumulate ? (*c + acc[i]) : acc[i];
+  for (int mt = 0; mt < MT; ++mt) {
+    sq[mt] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[mt][ct] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float *ar[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) ar[mt] = A + (size_t)(16 * mt + c16 < M ? 16 * mt + c16 : M - 1) * lda;  // (rows past the end repeat the last)
+  for (int k0 = wave * 16; k0 < K; k0 += 16 * GEMM_WAVES) {
+    const int k = k0 + 4 * q4;
+    f4 a[MT], b[CT];
+    float g[4];
+    if (k0 + 16 <= K) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const T *w = W + (size_t)(k + j) * ldw;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) b[ct][j] = load_as_float<T>(w + col[ct]);
+        g[j] = gain ? gain[k + j] : 1.f;
       }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        if (vec) {
+          a[mt] = *reinterpret_cast<const f4 *>(ar[mt] + k);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) a[mt][j] = ar[mt][k + j];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = k + j < K;
+        const int kk = in ? k + j : K - 1;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) b[ct][j] = in ? load_as_float<T>(W + (size_t)kk * ldw + col[ct]) : 0.f;
+        g[j] = gain ? gain[kk] : 1.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) a[mt][j] = in ? ar[mt][kk] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (gain) sq[mt] = fmaf(a[mt][j], a[mt][j], sq[mt]);
+        const float x = gain ? a[mt][j] * g[j] : a[mt][j];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[ct][j], acc[mt][ct], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+    if (gain) {
+      sq[mt] += __shfl_xor(sq[mt], 16, 64);
+      sq[mt] += __shfl_xor(sq[mt], 32, 64);
+      if (q4 == 0) sqs[wave * 16 * MT + 16 * mt + c16] = sq[mt];
+    }
+  // the upper half's sums go to the lower half first: four waves' sums fit the 64 KB a launch may ask for
+  f4 *mine = part + (size_t)(wave % HALF) * MT * CT * 64 + lane;
+  if (wave >= HALF)
+#pragma unroll
+    for (int n = 0; n < MT * CT; ++n) mine[n * 64] = acc[n / CT][n % CT];
+  __syncthreads();
+  if (wave < HALF)
+#pragma unroll
+    for (int n = 0; n < MT * CT; ++n) mine[n * 64] = acc[n / CT][n % CT] + mine[n * 64];
+  __syncthreads();
+  // a wave finishes a row tile's columns: the same lane layout as the products (column c16, rows 4 q4 + i)
+  for (int it = wave; it < MT * (KIND == GEMM_GLU ? 1 : CT); it += GEMM_WAVES) {
+    const int mt = KIND == GEMM_GLU ? it : it / CT, ct = KIND == GEMM_GLU ? 0 : it % CT;
+    f4 s = {0.f, 0.f, 0.f, 0.f}, u = s;
+#pragma unroll
+    for (int w = 0; w < HALF; ++w) {
+      s += part[((w * MT + mt) * CT + ct) * 64 + lane];
+      if (KIND == GEMM_GLU) u += part[((w * MT + mt) * CT + 1) * 64 + lane];
+    }
+    const int c = KIND == GEMM_WIDE ? c0 + 4 * c16 + ct : c0 + c16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 16 * mt + 4 * q4 + i;
+      if (row >= M || c >= N) continue;
+      float r = 1.f;
+      if (gain) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < GEMM_WAVES; ++w) t += sqs[w * 16 * MT + row];
+        r = 1.0f / sqrtf(t / (float)K + eps);
+      }
+      float v = s[i] * r;
+      if (KIND == GEMM_GLU) v = v / (1.0f + expf(-v)) * (u[i] * r);
+      float *cp = C + (size_t)row * ldc + c;
+      *cp = accumulate ? *cp + v : v;
+    }
   }
 }
 
@@ -126,16 +207,15 @@ __global__ void rope_kvwrite_kernel(float *qkv, int Hq, int Hkv, int dh, const f
     store_from_float<T>(Vc + (size_t)(L + b) * nkv + e, row[nq + nkv + e]);
 }
 
-// One workgroup per (row b, query head): online softmax over the visible keys in chunks
-// of blockDim.x keys.  Scores and probabilities in float.
+// One workgroup per (row b, query head): online softmax over the visible keys in chunks of blockDim.x keys, a key per
+// thread for the scores; for the output the threads form blockDim.x / dh groups of a channel each, which share the chunk's
+// keys and are added at the end in group order.  Scores and probabilities in float.  (With one thread per channel and the
+// rest idle, one key after the other, 64 keys of 64 channels took 22 us.)
 template <typename T>
-__global__ void attention_generic_kernel(const float *qkv, int Hq, int Hkv, int dh, const T *Kc, const T *Vc,
-                                         const int32_t *L_dev, int max_len, int Bp, const uint64_t *vis,
-                                         float *out) {
-  extern __shared__ float sm[];
-  float *qs = sm;            // [dh]
-  float *ps = sm + dh;       // [blockDim.x]
-  float *red = ps + blockDim.x;  // [8]
+__global__ __launch_bounds__(256) void attention_generic_kernel(const float *qkv, int Hq, int Hkv, int dh, const T *Kc, const T *Vc,
+                                                                const int32_t *L_dev, int max_len, int Bp, const uint64_t *vis,
+                                                                float *out) {
+  __shared__ float qs[256], ps[256], red[8];
   int b = blockIdx.x, hq = blockIdx.y;
   int L = *L_dev;
   if (L < 0 || L + Bp > max_len) return;
@@ -146,7 +226,8 @@ __global__ void attention_generic_kernel(const float *qkv, int Hq, int Hkv, int 
   __syncthreads();
   uint64_t vb = vis[b];
   float scale = 1.0f / sqrtf((float)dh);
-  float m_run = -INFINITY, l_run = 0.f, acc = 0.f;  // acc: output channel threadIdx.x (< dh)
+  const int groups = (int)blockDim.x / dh, gi = (int)threadIdx.x / dh, ch = (int)threadIdx.x - gi * dh;
+  float m_run = -INFINITY, l_run = 0.f, acc = 0.f;  // acc: output channel ch over this group's keys
   int total = L + Bp;
   for (int k0 = 0; k0 < total; k0 += blockDim.x) {
     int key = k0 + threadIdx.x;
@@ -154,9 +235,20 @@ __global__ void attention_generic_kernel(const float *qkv, int Hq, int Hkv, int 
     float s = -INFINITY;
     if (ok) {
       const T *kr = Kc + ((size_t)key * Hkv + kvh) * dh;
-      float d = 0.f;
-      for (int i = 0; i < dh; ++i) d = fmaf(qs[i], load_as_float<T>(kr + i), d);
-      s = d * scale;
+      float d0 = 0.f, d1 = 0.f;
+      int i = 0;
+      for (; i + 8 <= dh; i += 8) {
+        float kv[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) kv[j] = load_as_float<T>(kr + i + j);
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+          d0 = fmaf(qs[i + j], kv[j], d0);
+          d1 = fmaf(qs[i + j + 1], kv[j + 1], d1);
+        }
+      }
+      for (; i < dh; ++i) d0 = fmaf(qs[i], load_as_float<T>(kr + i), d0);
+      s = (d0 + d1) * scale;
     }
     float m_new = fmaxf(m_run, block_max(s, red));
     float p = ok ? expf(s - m_new) : 0.f;
@@ -166,25 +258,35 @@ __global__ void attention_generic_kernel(const float *qkv, int Hq, int Hkv, int 
     float psum = block_sum(p, red);  // contains the barriers that publish ps
     l_run = l_run * corr + psum;
     m_run = m_new;
-    if ((int)threadIdx.x < dh) {
+    if (gi < groups) {
       acc *= corr;
       int kmax = min((int)blockDim.x, total - k0);
-      for (int j = 0; j < kmax; ++j) {
-        float pj = ps[j];
-        if (pj != 0.f) acc = fmaf(pj, load_as_float<T>(Vc + ((size_t)(k0 + j) * Hkv + kvh) * dh + threadIdx.x), acc);
+      const T *vp = Vc + ((size_t)k0 * Hkv + kvh) * dh + ch;
+      int j = gi;
+      for (; j + 7 * groups < kmax; j += 8 * groups) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = load_as_float<T>(vp + (size_t)(j + u * groups) * nkv);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const float pj = ps[j + u * groups];
+          if (pj != 0.f) acc = fmaf(pj, v[u], acc);
+        }
+      }
+      for (; j < kmax; j += groups) {
+        const float pj = ps[j];
+        if (pj != 0.f) acc = fmaf(pj, load_as_float<T>(vp + (size_t)j * nkv), acc);
       }
     }
     __syncthreads();
   }
-  if ((int)threadIdx.x < dh) out[(size_t)b * nq + hq * dh + threadIdx.x] = acc / l_run;
-}
-
-__global__ void swiglu_kernel(const float *gu, int F, float *act) {
-  int b = blockIdx.y;
-  int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= F) return;
-  float g = gu[(size_t)b * 2 * F + f], u = gu[(size_t)b * 2 * F + F + f];
-  act[(size_t)b * F + f] = g / (1.0f + expf(-g)) * u;
+  ps[threadIdx.x] = gi < groups ? acc : 0.f;
+  __syncthreads();
+  if ((int)threadIdx.x < dh) {
+    float t = 0.f;
+    for (int u = 0; u < groups; ++u) t += ps[u * dh + threadIdx.x];
+    out[(size_t)b * nq + hq * dh + threadIdx.x] = t / l_run;
+  }
 }
 
 // Greedy choice per row with ties to the lowest index, plus the two largest values.
@@ -239,14 +341,31 @@ int launch_argmax_rows(const float *logits, int Bp, int V, int32_t *ids, float *
   return LA_OK;
 }
 
-template <typename T>
-static int gemm(const char *name, const float *A, int lda, const void *W, int ldw, float *C, int ldc, int M, int K,
-                int N, int accumulate, hipStream_t s) {
-  ProfScope p(name, s);
-  dim3 grid(ceil_div(N, 256), ceil_div(M, 8));
-  gemm_generic_kernel<T><<<grid, 256, 0, s>>>(A, lda, (const T *)W, ldw, C, ldc, M, K, N, accumulate);
+template <typename T, int KIND>
+static int gemm_kind(int MT, dim3 grid, hipStream_t s, const float *A, int lda, const float *gain, float eps, const T *W, int ldw, float *C, int ldc, int M,
+                     int K, int N, int accumulate, int vec) {
+  constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1;
+  const size_t lds = (size_t)GEMM_WAVES * MT * (CT * 32 * 4 + 16) * sizeof(float);
+  switch (MT) {
+  case 1: gemm_generic_kernel<T, 1, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  case 2: gemm_generic_kernel<T, 2, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  case 3: gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  default: gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  }
   LA_HIP(hipGetLastError());
   return LA_OK;
+}
+
+// N: columns of C (GLU: half the columns of W).  64 columns per workgroup once that alone gives every CU some.
+template <typename T>
+static int gemm(const char *name, const float *A, int lda, const float *gain, float eps, const void *W, int ldw, float *C, int ldc, int M, int K,
+                int N, int accumulate, bool glu, hipStream_t s) {
+  ProfScope p(name, s);
+  const int MT = ceil_div(M, 16), vec = ((uintptr_t)A | (size_t)lda * 4) % 16 == 0;
+  if (glu) return gemm_kind<T, GEMM_GLU>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
+  if (N >= 64 * 256 && MT <= 2)
+    return gemm_kind<T, GEMM_WIDE>(MT, ceil_div(N, 64), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
+  return gemm_kind<T, GEMM_16>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
 }
 
 template <typename T>
@@ -261,11 +380,7 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
     LA_REQUIRE(w.set, LA_EINVAL, "layer %d has no weights", l);
     T *Kc = (T *)kv->K + (size_t)l * kv->layer_elems();
     T *Vc = (T *)kv->V + (size_t)l * kv->layer_elems();
-    {
-      ProfScope p("rmsnorm", s);
-      rmsnorm_kernel<<<Bp, 256, 0, s>>>(hidden, w.g_attn, d.rms_eps, dm, m->h);
-    }
-    if ((rc = gemm<T>("gemm_qkv", m->h, dm, w.wqkv, nqkv, m->qkv, nqkv, Bp, dm, nqkv, 0, s))) return rc;
+    if ((rc = gemm<T>("gemm_qkv", hidden, dm, w.g_attn, d.rms_eps, w.wqkv, nqkv, m->qkv, nqkv, Bp, dm, nqkv, 0, false, s))) return rc;
     {
       ProfScope p("rope_kvwrite", s);
       rope_kvwrite_kernel<T><<<Bp, 256, 0, s>>>(m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, m->rope_cs, Kc, Vc,
@@ -273,22 +388,12 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
     }
     {
       ProfScope p("attention", s);
-      int threads = 256;
-      size_t sh = (d.head_dim + threads + 8) * sizeof(float);
-      attention_generic_kernel<T><<<dim3(Bp, d.n_q_heads), threads, sh, s>>>(
+      attention_generic_kernel<T><<<dim3(Bp, d.n_q_heads), 256, 0, s>>>(
           m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev, kv->max_len, Bp, vis, m->attn);
     }
-    if ((rc = gemm<T>("gemm_o", m->attn, qd, w.wo, dm, hidden, dm, Bp, qd, dm, 1, s))) return rc;
-    {
-      ProfScope p("rmsnorm", s);
-      rmsnorm_kernel<<<Bp, 256, 0, s>>>(hidden, w.g_mlp, d.rms_eps, dm, m->h);
-    }
-    if ((rc = gemm<T>("gemm_gateup", m->h, dm, w.wgu, 2 * F, m->gu, 2 * F, Bp, dm, 2 * F, 0, s))) return rc;
-    {
-      ProfScope p("swiglu", s);
-      swiglu_kernel<<<dim3(ceil_div(F, 256), Bp), 256, 0, s>>>(m->gu, F, m->act);
-    }
-    if ((rc = gemm<T>("gemm_down", m->act, F, w.wdown, dm, hidden, dm, Bp, F, dm, 1, s))) return rc;
+    if ((rc = gemm<T>("gemm_o", m->attn, qd, nullptr, 0.f, w.wo, dm, hidden, dm, Bp, qd, dm, 1, false, s))) return rc;
+    if ((rc = gemm<T>("gemm_gateup", hidden, dm, w.g_mlp, d.rms_eps, w.wgu, 2 * F, m->act, F, Bp, dm, F, 0, true, s))) return rc;
+    if ((rc = gemm<T>("gemm_down", m->act, F, nullptr, 0.f, w.wdown, dm, hidden, dm, Bp, F, dm, 1, false, s))) return rc;
     LA_HIP(hipGetLastError());
   }
   return LA_OK;
@@ -303,17 +408,12 @@ int generic_forward(la_model *m, int lb, int le, float *hidden, int Bp, const in
 
 int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2, hipStream_t s) {
   const la_model_desc &d = m->d;
-  {
-    ProfScope p("rmsnorm", s);
-    rmsnorm_kernel<<<Bp, 256, 0, s>>>(hidden, m->g_final, d.rms_eps, d.d_model, m->h);
-  }
   int rc;
-  if (d.dtype == LA_F32)
-    rc = gemm<float>("gemm_unembed", m->h, d.d_model, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, 0, s);
-  else if (d.dtype == LA_F16)
-    rc = gemm<_Float16>("gemm_unembed", m->h, d.d_model, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, 0, s);
-  else
-    rc = gemm<uint16_t>("gemm_unembed", m->h, d.d_model, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, 0, s);
+  auto head = [&](auto t) {
+    using T = decltype(t);
+    return gemm<T>("gemm_unembed", hidden, d.d_model, m->g_final, d.rms_eps, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, 0, false, s);
+  };
+  rc = d.dtype == LA_F32 ? head(float{}) : d.dtype == LA_F16 ? head(_Float16{}) : head(uint16_t{});
   if (rc) return rc;
   return launch_argmax_rows(m->logits, Bp, d.vocab, ids, top2, s);
 }

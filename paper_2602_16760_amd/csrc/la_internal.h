@@ -59,7 +59,7 @@ struct la_model {
   void *embed = nullptr, *unembed = nullptr;
   float *g_final = nullptr;
   // scratch of the generic path, sized for LA_MAX_ROWS rows
-  float *h = nullptr, *qkv = nullptr, *attn = nullptr, *gu = nullptr, *act = nullptr, *logits = nullptr;
+  float *qkv = nullptr, *attn = nullptr, *act = nullptr, *logits = nullptr;
   float *rope_cs = nullptr;  // [LA_MAX_ROWS][dh/2][2] cos, sin at each row's position
   // la_prefill's chunk: residual stream [LA_MAX_ROWS, d], positions and causal masks of its rows
   float *pf_hidden = nullptr;
