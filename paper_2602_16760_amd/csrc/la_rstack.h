@@ -580,9 +580,10 @@ __device__ __forceinline__ bool io_barrier(Io &io) {
   return io_wait_ge(io, K_IOBAR, io.bar_seq);
 }
 
-// Grid barrier, run by the IO waves (same counters and protocol as la_stack.h's grid_sync).
+// Grid barrier, run by the IO waves (same counters and protocol as la_stack.h's grid_sync), in two halves: what a wave works
+// out between them (the next phase's pointers, which need memory reads of their own) costs nothing while the others arrive.
 template <int NIO>
-__device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigned epoch) {
+__device__ __forceinline__ bool io_grid_arrive(const StackArgs &a, Io &io, unsigned epoch) {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   io_mark(io, 2);
   if (LA_TRACE_PTR(a) && io.v == 0 && io.lane == 0 && (blockIdx.x == 0 || blockIdx.x > 2)) {  // (timeline: when each workgroup ends a phase)
@@ -603,6 +604,13 @@ __device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigne
       unsigned t = __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (t + 1 == epoch * a.n_groups) __hip_atomic_store(rel, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+  }
+  return true;
+}
+template <int NIO>
+__device__ __forceinline__ bool io_grid_wait(const StackArgs &a, Io &io, unsigned epoch) {
+  if (io.v == 0 && io.lane == 0) {
+    unsigned *rel = a.sync + SYNC_STRIDE * 65;
     unsigned spins = 0;
     bool ok = true;
     while ((int)(__hip_atomic_load(rel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - epoch) < 0) {
@@ -619,6 +627,10 @@ __device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigne
   const bool ok = io_wait_ge(io, K_GPASS, epoch);
   io_mark(io, 8);
   return ok;
+}
+template <int NIO>
+__device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigned epoch) {
+  return io_grid_arrive<NIO>(a, io, epoch) && io_grid_wait<NIO>(a, io, epoch);
 }
 
 // The operand of one pass into the rings of the MFMA waves this IO wave serves (w = v, v + NIO,
@@ -831,17 +843,47 @@ __device__ __forceinline__ void row_factors_load(const Io &io, const float *rsq_
     }
   }
 }
+// Eight rows' values per lane -> two registers whose sixteen-lane groups hold a row each: the swaps add the lanes 32 and
+// 16 apart of two rows at a time.
+__device__ __forceinline__ float swap_add_32(float a, float b) {  // lanes 0..31: a + (a 32 lanes further), lanes 32..63: b likewise
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add_16(float a, float b) {  // ... the same with the 16-lane rows: even rows a, odd rows b
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// The sum over the lanes in every row of sixteen lanes, in every lane of it.
+__device__ __forceinline__ float row16_sum(float v) {
+  v = dpp_add<0x128>(v);  // row_ror:8
+  v = dpp_add<0x124>(v);  // row_ror:4
+  v = dpp_add<0x122>(v);  // row_ror:2
+  return dpp_add<0x121>(v);  // row_ror:1
+}
+// Four rows at a time, without LDS and without a branch between rows: with six ds_bpermute per row this took the IO waves
+// 2 us, and in the QKV phase (whose k-loop is short) the finished partial tiles waited for it.
 template <int MT, int NIO>
 __device__ __forceinline__ void row_factors_finish(const Io &io, int Bp, float inv_d, float eps, const RowStat<MT, NIO> &rs) {
   LDS_AS float *rs_lds = (LDS_AS float *)(uintptr_t)(io.misc + M_RS);
-#pragma unroll
-  for (int i = 0; i < RowStat<MT, NIO>::NR; ++i) {
-    const int row = io.v + NIO * i;
+  constexpr int NR = RowStat<MT, NIO>::NR;
+  auto lane_sum = [&](int i) {
     const f32x4 t = rs.t[i][0] + rs.t[i][1];
-    float s = (t[0] + t[1]) + (t[2] + t[3]);
+    return (t[0] + t[1]) + (t[2] + t[3]);
+  };
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (row < 16 * MT && io.lane == 0) rs_lds[row] = row < Bp ? 1.0f / sqrtf(s * inv_d + eps) : 0.f;
+  for (int i = 0; i < NR; i += 4) {
+    float s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = i + k < NR ? lane_sum(i + k < NR ? i + k : 0) : 0.f;
+    // 16-lane row g of the wave: values 0, 2, 1, 3
+    const float v = row16_sum(swap_add_16(swap_add_32(s[0], s[1]), swap_add_32(s[2], s[3])));
+    const int g = io.lane >> 4, k = ((g & 1) << 1) | (g >> 1);
+    const int row = io.v + NIO * (i + k);
+    if ((io.lane & 15) == 0 && i + k < NR && row < 16 * MT) rs_lds[row] = row < Bp ? 1.0f / sqrtf(v * inv_d + eps) : 0.f;
   }
 }
 
@@ -858,29 +900,54 @@ struct Epi {
   bool keep_x;  // residual epilogue: x may stay in LDS alone (a later epilogue of the launch writes it to memory)
 };
 
-// The rotation factors of a thread's item of the QKV epilogue (16 floats: cos, sin of eight pairs), requested before
-// the wait for the partial tiles: they do not depend on the product, and read inside the epilogue their latency stood
-// between the reduction and the stores of every layer.  Covers the first item of each thread (there is no second one
-// unless a workgroup has more than 256 / rows column tiles in the pass; later items read theirs in place).
-struct QkvPre {
+// A thread's first item of the epilogue, worked out before the wait for the partial tiles: where it lies (three integer
+// divisions), and what it needs besides them -- the rotation factors of the QKV epilogue (16 floats: cos, sin of eight pairs;
+// read inside the epilogue their latency stood between the reduction and the stores of every layer), x and the gains of
+// the residual ones.  There is no second item unless a workgroup has more than 256 / rows column tiles in the pass; those
+// items are worked out in place.
+struct EpiItem {
+  int b, tt, gt;  // row, column tile of the pass and of the matrix
+  int hs, j;      // QKV: head (q, then k, then v), group of eight pairs
+};
+struct EpiPre {
+  EpiItem at;
   f32x4 c[4];
   bool have;
 };
-template <int NIO>
-__device__ __forceinline__ void qkv_prefetch(const StackArgs &a, const Io &io, int tile_first, int ntc, QkvPre &pre) {
-  const int it = io.tid, dh = a.dh, half = dh >> 1, spj = dh >> 4;
+__device__ __forceinline__ EpiItem epi_item(const StackArgs &a, int mode, int it, int tile_first, int ntc) {
+  EpiItem p;
+  const int bt = mode == MODE_RESID ? it >> 1 : it;
+  p.b = ntc == 1 ? bt : bt / ntc;
+  p.tt = bt - p.b * ntc;
+  p.gt = (int)blockIdx.x + (int)gridDim.x * (tile_first + p.tt);
+  p.hs = p.gt >> (a.dh == 128 ? 3 : 2);  // (head_dim is 64 or 128: four or eight column tiles a head)
+  p.j = p.gt & (a.dh == 128 ? 7 : 3);
+  return p;
+}
+template <int MT, int NIO>
+__device__ __forceinline__ void epi_prefetch(const StackArgs &a, const Io &io, int mode, int x_lds, int tile_first, int ntc, EpiPre &pre) {
+  const int it = io.tid, half = a.dh >> 1;
   pre.have = false;
 #pragma unroll
   for (int i = 0; i < 4; ++i) pre.c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (it >= a.Bp * ntc) return;
-  const int b = it / ntc, tt = it - b * ntc;
-  const int gt = (int)blockIdx.x + (int)gridDim.x * (tile_first + tt);
-  const int hs = gt / spj, j = gt - hs * spj;
-  if (hs >= a.Hq + a.Hkv) return;
-  const f32x4 *cp = reinterpret_cast<const f32x4 *>(a.cs + ((size_t)b * half + 8 * j) * 2);
+  pre.at = epi_item(a, mode, it, tile_first, ntc);
+  if (mode == MODE_QKV) {
+    if (it >= a.Bp * ntc || pre.at.hs >= a.Hq + a.Hkv) return;
+    const f32x4 *cp = reinterpret_cast<const f32x4 *>(a.cs + ((size_t)pre.at.b * half + 8 * pre.at.j) * 2);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) pre.c[i] = cp[i];
-  pre.have = true;
+    for (int i = 0; i < 4; ++i) pre.c[i] = cp[i];
+    pre.have = true;
+  } else if (mode == MODE_RESID && x_lds) {
+    if (it >= a.Bp * ntc * 2) return;
+    const int oct = it & 1, lt = tile_first + pre.at.tt;
+    LDS_AS const f32x4 *xs = (LDS_AS const f32x4 *)(uintptr_t)(io.misc + M_X + ((lt * 16 * MT + pre.at.b) * 16 + 8 * oct) * 4);
+    LDS_AS const f32x4 *gs = (LDS_AS const f32x4 *)(uintptr_t)(io.misc + M_GAIN + (lt * 16 + 8 * oct) * 4);
+    pre.c[0] = xs[0];
+    pre.c[1] = xs[1];
+    pre.c[2] = gs[0];
+    pre.c[3] = gs[1];
+    pre.have = true;
+  }
 }
 
 // Eight consecutive floats of the pass's tile: the MFMA waves' partial tiles, at the
@@ -904,7 +971,7 @@ __device__ __forceinline__ void tile8(unsigned lds0, unsigned byte_off, float (&
 // tile first, with a barrier behind it, took 0.5 - 1 us more per phase).  Same arithmetic as la_stack.h's gemm_epilogue.
 template <int MT, int NIO>
 __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, const Epi &q, int L, int x_lds, int tile_first, int ntc,
-                                              int LDT, const QkvPre &pre) {
+                                              int LDT, const EpiPre &pre) {
   constexpr int NT_IO = NIO * 64;
   const int Bp = a.Bp, d = a.d, ncg = a.ncg, Hq = a.Hq, Hkv = a.Hkv, dh = a.dh;
   const int tid = io.tid;
@@ -914,10 +981,9 @@ __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, 
   const int G = gridDim.x, cu = blockIdx.x;
   if (q.mode == MODE_QKV) {
     for (int it = tid; it < Bp * ntc; it += NT_IO) {
-      const int b = it / ntc, tt = it - b * ntc;
-      const int gt = cu + G * (tile_first + tt);
-      const int half = dh >> 1, spj = dh >> 4, grp = Hq / Hkv;
-      const int hs = gt / spj, j = gt - hs * spj;
+      const EpiItem at = it == tid ? pre.at : epi_item(a, MODE_QKV, it, tile_first, ntc);
+      const int b = at.b, tt = at.tt, hs = at.hs, j = at.j;
+      const int half = dh >> 1, grp = Hq / Hkv;
       const float rsf = rs_lds[b];
       float tr[16];
       {
@@ -978,16 +1044,20 @@ __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, 
     }
   } else if (q.mode == MODE_RESID) {
     for (int it = tid; it < Bp * ntc * 2; it += NT_IO) {
-      const int oct = it & 1, bt = it >> 1;
-      const int b = bt / ntc, tt = bt - b * ntc;
-      const int gt = cu + G * (tile_first + tt);
+      const int oct = it & 1;
+      const EpiItem at = it == tid ? pre.at : epi_item(a, MODE_RESID, it, tile_first, ntc);
+      const int b = at.b, tt = at.tt, gt = at.gt;
       const int col = 16 * gt + 8 * oct;
       f32x4 *xp = reinterpret_cast<f32x4 *>(a.x + (size_t)b * d + col);
       float tr[8];
       tile8<NW, REG>(io.lds0, (unsigned)(b * LDT + 16 * tt + 8 * oct) * 4u, tr);
       LDS_AS f32x4 *xs = (LDS_AS f32x4 *)(uintptr_t)(io.misc + M_X + (((tile_first + tt) * 16 * MT + b) * 16 + 8 * oct) * 4);
+      const bool early = it == tid && pre.have;  // (x and the gains are in registers)
       f32x4 x0, x1;
-      if (x_lds) {
+      if (early) {
+        x0 = pre.c[0];
+        x1 = pre.c[1];
+      } else if (x_lds) {
         x0 = xs[0];
         x1 = xs[1];
       } else {
@@ -1016,7 +1086,13 @@ __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, 
       if (q.gain) {
         if (oct == 0) st32f(rsrc_of(q.rsq_out), (unsigned)(b * ncg + gt) * 4, sq);
         float gp[8];
-        if (x_lds) {
+        if (early) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            gp[i] = pre.c[2][i];
+            gp[4 + i] = pre.c[3][i];
+          }
+        } else if (x_lds) {
           LDS_AS const f32x4 *gs = (LDS_AS const f32x4 *)(uintptr_t)(io.misc + M_GAIN + ((tile_first + tt) * 16 + 8 * oct) * 4);
           const f32x4 g0 = gs[0], g1 = gs[1];
 #pragma unroll
@@ -1036,8 +1112,8 @@ __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, 
   } else if (q.mode == MODE_GATEUP) {
     __amdgpu_buffer_rsrc_t rp = rsrc_of(q.act_a);
     for (int it = tid; it < Bp * ntc; it += NT_IO) {
-      const int b = it / ntc, tt = it - b * ntc;
-      const int gt = cu + G * (tile_first + tt);
+      const EpiItem at = it == tid ? pre.at : epi_item(a, MODE_GATEUP, it, tile_first, ntc);
+      const int b = at.b, tt = at.tt, gt = at.gt;
       const float rsf = rs_lds[b];
       float gp[8], up[8];
       tile8<NW, REG>(io.lds0, (unsigned)(b * LDT + 16 * tt) * 4u, gp);
@@ -1095,11 +1171,11 @@ __device__ __forceinline__ bool io_pass(const StackArgs &a, Io &io, const Pass &
   if (!load_operand<MT, NW>(io, A, p.KT, a_seq, LA_DBG_BITS(a.dbg))) return false;
   if (io.tr && io.v == 0 && io.lane == 0 && p.pidx == 0) io.tr[3] = wall_clock64() - t_a;  // (reported as "waited for weights": the operand's way in)
   if (rsq_in) row_factors_finish<MT, NIO>(io, a.Bp, a.inv_d, a.eps, rs);
-  QkvPre pre;
-  pre.have = false;
-  if (q.mode == MODE_QKV) qkv_prefetch<NIO>(a, io, p.tile0, p.NT, pre);
+  EpiPre pre;
+  if (q.mode != MODE_RESID) epi_prefetch<MT, NIO>(a, io, q.mode, x_lds, p.tile0, p.NT, pre);
   between();  // (bookkeeping of the caller that needs no result of this pass: it runs while the MFMA waves finish)
   if (!io_barrier<NIO>(io)) return false;  // (the row factors, gains and x tiles the IO waves staged for each other)
+  if (q.mode == MODE_RESID) epi_prefetch<MT, NIO>(a, io, q.mode, x_lds, p.tile0, p.NT, pre);
   for (int w = 0; w < NW; ++w)
     if (!io_wait_ge(io, K_PDONE + w, pseq + 1u)) return false;
   if (p.pidx == 0) io_mark(io, 1);
@@ -1517,12 +1593,35 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
   if (x_lds) r_x_stage<MT, NIO>(a, io, nt_x);
 
   for (int layer = a.lb; layer < a.le; ++layer) {
-    uint16_t *Kc = a.K + (size_t)layer * a.layer_elems, *Vc = a.V + (size_t)layer * a.layer_elems;
-    uint16_t *xa0 = a.xa + (size_t)(2 * layer) * a.xa_stride, *xa1 = xa0 + a.xa_stride;
-    float *rsq0 = a.rsq + (size_t)(2 * layer) * a.rsq_stride, *rsq1 = rsq0 + a.rsq_stride;
-    uint16_t *attn_l = a.attn_a + (size_t)layer * a.attn_stride, *act_l = a.act_a + (size_t)layer * a.act_stride;
+    uint16_t *Kc = nullptr, *Vc = nullptr, *xa0 = nullptr, *xa1 = nullptr, *attn_l = nullptr, *act_l = nullptr;
+    float *rsq0 = nullptr, *rsq1 = nullptr;
     for (int gemm = 0; gemm < 4; ++gemm) {
-      if (!io_grid_sync<NIO>(a, io, ++epoch)) return;
+      if (!io_grid_arrive<NIO>(a, io, ++epoch)) return;
+      const uint16_t *A = nullptr;
+      const float *rsq_in = nullptr;
+      Epi q{};
+      switch (gemm) {
+        case 0:
+          Kc = a.K + (size_t)layer * a.layer_elems; Vc = a.V + (size_t)layer * a.layer_elems;
+          xa0 = a.xa + (size_t)(2 * layer) * a.xa_stride; xa1 = xa0 + a.xa_stride;
+          rsq0 = a.rsq + (size_t)(2 * layer) * a.rsq_stride; rsq1 = rsq0 + a.rsq_stride;
+          attn_l = a.attn_a + (size_t)layer * a.attn_stride; act_l = a.act_a + (size_t)layer * a.act_stride;
+          A = xa0; rsq_in = rsq0; q.mode = MODE_QKV; q.Kc = Kc; q.Vc = Vc;
+          break;
+        case 1:
+          A = attn_l; q.mode = MODE_RESID; q.gain = a.gains[layer].g_mlp; q.xa_out = xa1; q.rsq_out = rsq1; q.keep_x = true;
+          break;
+        case 2:
+          A = xa1; rsq_in = rsq1; q.mode = MODE_GATEUP; q.act_a = act_l;
+          break;
+        default:
+          A = act_l; q.mode = MODE_RESID;
+          q.gain = layer + 1 < a.le ? a.gains[layer + 1].g_attn : nullptr;
+          q.xa_out = xa0 + 2 * a.xa_stride; q.rsq_out = rsq0 + 2 * a.rsq_stride; q.keep_x = layer + 1 < a.le;
+          break;
+      }
+      if (q.mode == MODE_RESID && x_lds) r_gain_stage(q.gain, io, nt_x);  // (this workgroup's epilogues are through with the last gains)
+      if (!io_grid_wait<NIO>(a, io, epoch)) return;
       set_phase(1 + 5 * (layer - a.lb) + (gemm <= 1 ? gemm : gemm + 1));
       if (gemm == 1) {
         if (att_u0 < n_su) {
@@ -1538,26 +1637,6 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
         if (!io_grid_sync<NIO>(a, io, ++epoch)) return;
         set_phase(1 + 5 * (layer - a.lb) + 2);
       }
-      const uint16_t *A = nullptr;
-      const float *rsq_in = nullptr;
-      Epi q{};
-      switch (gemm) {
-        case 0:
-          A = xa0; rsq_in = rsq0; q.mode = MODE_QKV; q.Kc = Kc; q.Vc = Vc;
-          break;
-        case 1:
-          A = attn_l; q.mode = MODE_RESID; q.gain = a.gains[layer].g_mlp; q.xa_out = xa1; q.rsq_out = rsq1; q.keep_x = true;
-          break;
-        case 2:
-          A = xa1; rsq_in = rsq1; q.mode = MODE_GATEUP; q.act_a = act_l;
-          break;
-        default:
-          A = act_l; q.mode = MODE_RESID;
-          q.gain = layer + 1 < a.le ? a.gains[layer + 1].g_attn : nullptr;
-          q.xa_out = xa0 + 2 * a.xa_stride; q.rsq_out = rsq0 + 2 * a.rsq_stride; q.keep_x = layer + 1 < a.le;
-          break;
-      }
-      if (q.mode == MODE_RESID && x_lds) r_gain_stage(q.gain, io, nt_x);
       bool first = true;
       while (!pw.done && pw.cur.layer == layer && pw.cur.gemm == gemm) {
         if (!first) {
