@@ -157,7 +157,7 @@ struct MfmaModel {
   uint16_t *xa_u = nullptr;                                                    // unembedding input
   float *rsq = nullptr, *rsq_u = nullptr;
   Top *un_part = nullptr;
-  int un_parts_per_cu = 0;
+  int un_parts_per_cu = 0, un_parts_bound = 0;
   float *att_part = nullptr;    // attention with the keys split over workgroups: one partial record per workgroup
   unsigned *att_cnt = nullptr;  // ... and per unit the number of records delivered
   unsigned *sync = nullptr;
@@ -392,7 +392,9 @@ int mfma_set_head(la_model *m, const void *unembed, hipStream_t s) {
   if (rc) return rc;
   // partial arg-max records per CU: one per reduction chunk of every pass, at any row count
   int passes = ceil_div(f->p_un.nt_max, f->p_un.ntp);
-  f->un_parts_per_cu = passes * f->p_un.ntp;  // an upper bound (chunks hold at least one tile)
+  f->un_parts_bound = passes * f->p_un.ntp;  // (chunks hold at least one tile)
+  // the register-streaming kernel leaves one record per pass: with room for one per tile the final scan read mostly empty ones
+  f->un_parts_per_cu = f->use_r ? passes : f->un_parts_bound;
   if (!f->un_part) f->un_part = (Top *)dalloc((size_t)f->n_wgs * f->un_parts_per_cu * 64 * sizeof(Top));
   LA_REQUIRE(f->un_part != nullptr, LA_ENOMEM, "device allocation failed");
   return LA_OK;
@@ -718,9 +720,9 @@ int mfma_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_
   MfmaModel *f = m->mf;
   LA_REQUIRE(f->ustream != nullptr, LA_EINVAL, "model was created without an unembedding matrix");
   LA_REQUIRE(m->d.d_model <= NA_MAX_D, LA_ERANGE, "d_model=%d exceeds the %d the static scratch array holds", m->d.d_model, NA_MAX_D);
-  LA_REQUIRE((long long)f->n_wgs * f->un_parts_per_cu <= NA_MAX_PARTS, LA_ERANGE,
+  LA_REQUIRE((long long)f->n_wgs * f->un_parts_bound <= NA_MAX_PARTS, LA_ERANGE,
              "vocab=%d needs %lld partial arg-max records, the static scratch array holds %d", m->d.vocab,
-             (long long)f->n_wgs * f->un_parts_per_cu, NA_MAX_PARTS);
+             (long long)f->n_wgs * f->un_parts_bound, NA_MAX_PARTS);
   unsigned char *base = (m->device >= 0 && m->device < NA_MAX_DEVICES) ? na_ptr[m->device] : nullptr;
   LA_REQUIRE(base != nullptr, LA_EHIP, "the static scratch array has no address on device %d", m->device);
   zero_u32_kernel<<<ceil_div((int)(NA_ZERO_BYTES / 4), 256), 256, 0, s>>>((unsigned *)base, (int)(NA_ZERO_BYTES / 4));
