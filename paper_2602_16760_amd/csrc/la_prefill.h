@@ -337,28 +337,6 @@ __global__ __launch_bounds__(256) void pf_norm_kernel(float *x, const float *par
     ss[(size_t)(16 * rt + threadIdx.x) * PF_CHUNKS + chunk] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-// The value of the lane 32 (16) further, and the maximum over the lanes 16 and 32 apart, without the LDS.
-__device__ __forceinline__ float pf_max_q4(float v) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  u2 a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-}
-
-// Two probabilities in the cache's 16-bit type (round to nearest even; no value is out of range).
-template <bool F16>
-__device__ __forceinline__ uint32_t pf_pack_p(float lo, float hi) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  if constexpr (F16) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
-  } else {
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), b2));
-  }
-}
-
 // Causal attention over cache rows 0 .. L0 + row (Section 4.4's plain causal mask).  A workgroup takes four consecutive
 // (row tile, q head) pairs of one kv head (the heads of a row tile are neighbours), a wave one of them; blocks of 64 keys of
 // K and V go through LDS once for all four.  The products and the running softmax are the block kernel's.  Output: operand
@@ -428,7 +406,6 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -1e30f, l_run = 0.f;
-  constexpr float LOG2E = 1.4426950408889634f;
   for (int kb = 0; kb < nkb; ++kb) {
     wait_vmcnt<0>();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -459,7 +436,7 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
       for (int n = 0; n < 2 * NB; ++n)
 #pragma unroll
         for (int i = 0; i < 4; ++i) mx = fmaxf(mx, sc[n][i]);
-      mx = pf_max_q4(mx);
+      mx = max_q4(mx);
       if (__any(mx > m_run)) {  // (otherwise the factor is one in every lane)
         const float m_new = fmaxf(m_run, mx);
         const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * LOG2E);
@@ -478,7 +455,7 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
           pr[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[2 * n + (i >> 2)][i & 3], LOG2E, -mb));
           l_run += pr[i];  // (this lane's keys; added over the lanes at the end)
         }
-        pb[n] = __builtin_bit_cast(v8, u32x4{pf_pack_p<F16>(pr[0], pr[1]), pf_pack_p<F16>(pr[2], pr[3]), pf_pack_p<F16>(pr[4], pr[5]), pf_pack_p<F16>(pr[6], pr[7])});
+        pb[n] = __builtin_bit_cast(v8, u32x4{pack_p<F16>(pr[0], pr[1]), pack_p<F16>(pr[2], pr[3]), pack_p<F16>(pr[4], pr[5]), pack_p<F16>(pr[6], pr[7])});
       }
 #pragma unroll
       for (int n = 0; n < NB; ++n)
@@ -490,8 +467,7 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
     }
   }
   wait_vmcnt<0>();  // (the request past the last block lands before the LDS is given back)
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = sum_q4(l_run);
   if (t0 <= last_tile && row < M) {
     const float inv = 1.0f / l_run;
 #pragma unroll

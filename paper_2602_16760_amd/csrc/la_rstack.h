@@ -306,9 +306,13 @@ __device__ __forceinline__ void build_schedule(const StackArgs &a, int ntmax, in
     const bool last = c.i0 + DK >= c.nk;
     if (n < TAB_MAX) {
       LDS_AS unsigned *e = (LDS_AS unsigned *)(uintptr_t)(tab + TAB_HDR + n * 20);
-      e[0] = c.mask();
-      e[1] = c.frag() - seg0;
-      e[2] = c.a_seq0 + (unsigned)c.i0;
+      // A body with fewer k-tiles than it has room for (a pass's last) holds them in its LAST slots, and its offsets are
+      // those of the k-tiles that would come before: the empty slots are then gone through (and the next body's weights
+      // requested) while the wave waits for the operand, and the partial tile follows its last product at once.
+      const unsigned free_rows = (unsigned)(DK - rows);
+      e[0] = c.mask() << (free_rows * (unsigned)c.pw.cur.NTS);
+      e[1] = c.frag() - seg0 - free_rows * (unsigned)c.pw.cur.nt_all;
+      e[2] = c.a_seq0 + (unsigned)c.i0 - free_rows;
       e[3] = (unsigned)c.pw.cur.nt_all | ((unsigned)c.lg_slots() << 16) | ((unsigned)rows << 24);
       e[4] = (last ? 1u : 0u) | ((unsigned)c.pseq << 16);
     }
@@ -493,8 +497,8 @@ __device__ __forceinline__ void mfma_wave_main(const StackArgs &a, unsigned lds0
     const int lg = (int)((w3 >> 16) & 0xffu);
 #pragma unroll
     for (int j = 0; j < RING_D; ++j) {
-      const bool real = (m >> j) & 1u;
-      ring_load(ring[j], rsrc, (real && !no_weights) ? lane16 : OOB, uni((f0 + (unsigned)(j >> lg) * st + (unsigned)(j & ((1 << lg) - 1))) * 1024u));
+      const bool real = ((m >> j) & 1u) && !no_weights;  // (an empty slot's stream offset may lie in front of the stream)
+      ring_load(ring[j], rsrc, real ? lane16 : OOB, uni(real ? (f0 + (unsigned)(j >> lg) * st + (unsigned)(j & ((1 << lg) - 1))) * 1024u : 0u));
     }
   }
   f32x4 acc[MT][NTMAX];
@@ -682,11 +686,12 @@ __device__ __forceinline__ bool load_operand_1(Io &io, const uint16_t *A, int KT
   while (issued < n_batches) {
     const int i0 = issued * GB;
     const int nv = nk - i0 < GB ? nk - i0 : GB;
-    // ring space: a slot is free once its wave has read the k-tile that was there RS before
-    bool room = (int)(a_seq + (unsigned)nv - done) <= RS;
+    // ring space: a slot is free once its wave has read the k-tile that was there RS before (a whole batch's slots, also where
+    // k-tiles are missing: those are requested out of range and land as zeros)
+    bool room = (int)(a_seq + (unsigned)GB - done) <= RS;
     if (!room) {
       done = ctl_read(ctl_done);
-      room = (int)(a_seq + (unsigned)nv - done) <= RS;
+      room = (int)(a_seq + (unsigned)GB - done) <= RS;
     }
     if (!room || issued - retired == FL) {  // (the first batches go out together: waiting for the first one alone cost 0.3 % at 32 rows and 1.7 % at one row)
       if (issued > retired) {
@@ -1214,7 +1219,8 @@ __device__ __forceinline__ void r_rope_table(const StackArgs &a, const Io &io) {
   constexpr int NT_IO = NIO * 64;
   __amdgpu_buffer_rsrc_t rc = rsrc_of(a.cs);
   int half = a.dh >> 1, total = a.Bp * half;
-  for (int e = blockIdx.x * NT_IO + io.tid; e < total; e += gridDim.x * NT_IO) {
+  // (from the grid's end: the first workgroups have the first operand to make)
+  for (int e = (gridDim.x - 1 - blockIdx.x) * NT_IO + io.tid; e < total; e += gridDim.x * NT_IO) {
     int b = e / half, i = e - b * half;
     double inv = exp2(-(double)i / (double)half * log2(a.theta));
     double s, c;
@@ -1312,79 +1318,76 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
 #pragma unroll
       for (int i = 0; i < 8; ++i) sv[i] = i < 4 ? sa[i] : sb[i - 4];
     };
-    auto softmax = [&](auto masked, const float *sv, int kb, float &corr) {
-      constexpr bool MASKED = decltype(masked)::value;
-      bool ok[8];
-      float mx = -1e30f;
+    // One block's scores to probabilities and the running maximum and sum.  The maximum is compared over the four lanes of a
+    // query row with permlane swaps, the sum stays per lane (the lanes' sums are added when the output is written), and the
+    // output is rescaled only when a maximum moved: with four ds_bpermute and 32 products per block this was a third of a
+    // block's time.
+    auto softmax = [&](auto masked, float *sv, int kb) {
+      if (decltype(masked)::value) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (MASKED) {
+        for (int i = 0; i < 8; ++i) {
           const int key = kb * 32 + (i >> 2) * 16 + 4 * q4 + (i & 3);
-          ok[i] = key < L || (key < total && ((vb >> (key - L)) & 1ull));
-          if (ok[i]) mx = fmaxf(mx, sv[i]);
-        } else {
-          ok[i] = true;
-          mx = fmaxf(mx, sv[i]);
+          if (!(key < L || (key < total && ((vb >> (key - L)) & 1ull)))) sv[i] = -INFINITY;
         }
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run, mx);
-      corr = __expf(m_run - m_new);
-      float p[8], ps = 0.f;
+      const float mx = max_q4(fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7]))));
+      if (__any(mx > m_run)) {  // (otherwise the factor is one in every lane)
+        const float m_new = fmaxf(m_run, mx);
+        const float corr = __builtin_amdgcn_exp2f((m_run - m_new) * LOG2E);
+        m_run = m_new;
+        l_run *= corr;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+      }
+      const float mb = m_run * LOG2E;
+      float p[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        p[i] = ok[i] ? __expf(sv[i] - m_new) : 0.f;
-        ps += p[i];
+        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[i], LOG2E, -mb));
+        l_run += p[i];
       }
-      ps += __shfl_xor(ps, 16, 64);
-      ps += __shfl_xor(ps, 32, 64);
-      l_run = l_run * corr + ps;
-      m_run = m_new;
-      const u32x4 pw = {pack_kv(F16, p[0], p[1]), pack_kv(F16, p[2], p[3]), pack_kv(F16, p[4], p[5]), pack_kv(F16, p[6], p[7])};
+      const u32x4 pw = {pack_p<F16>(p[0], p[1]), pack_p<F16>(p[2], p[3]), pack_p<F16>(p[4], p[5]), pack_p<F16>(p[6], p[7])};
       return __builtin_bit_cast(v8, pw);
     };
-    auto pv = [&](v8 pb, float corr) {
+    auto pv = [&](v8 pb) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        o[dt] *= corr;
-        o[dt] = mma(__builtin_bit_cast(v8, vt[dt]), pb, o[dt]);
-      }
+      for (int dt = 0; dt < DT; ++dt) o[dt] = mma(__builtin_bit_cast(v8, vt[dt]), pb, o[dt]);
     };
     const std::integral_constant<int, 0> plain{};
     const std::integral_constant<int, DEV> coherent{};
     const int kb_split = L >> 5;  // key blocks 0 .. kb_split - 1 end at or before row L ("early")
     const int e_lo = kb_split * ks / S, e_hi = kb_split * (ks + 1) / S;  // this slice's early blocks
     // The blocks that hold rows of this step ("late": at most three, written by other workgroups in
-    // the phase before, so device-scope loads and the mask) are dealt to the waves round-robin and
-    // taken first, one at a time; the early blocks (ordinary loads, every key visible) follow in
-    // the wave's pipeline: the next block's K is requested as soon as the scores are out of the
-    // matrix unit, the next V after P V.
-    for (int kb = kb_split + v; kb < nkb && ks == S - 1; kb += NIO) {
-      float sv[8], corr;
-      load_k(coherent, kb, true);
-      load_v(coherent, kb, true);
+    // the phase before, so device-scope loads and the mask) go to one wave each and are taken first;
+    // the early blocks (ordinary loads, every key visible) follow in the wave's pipeline, the first one's
+    // too: the next block's K is requested as soon as the scores are out of the matrix unit, the next V
+    // after P V.
+    static_assert((LA_MAX_ROWS + 62) / 32 <= NIO, "a wave has one late block at most");
+    const int kl = kb_split + v;
+    int kb = e_lo + v, ne = kb + NIO;
+    float sv[8];
+    if (kl < nkb && ks == S - 1) {
+      load_k(coherent, kl, true);
+      load_v(coherent, kl, true);
       scores(sv);
-      const v8 pb = softmax(std::true_type{}, sv, kb, corr);
-      pv(pb, corr);
+      load_k(plain, kb, kb < e_hi);
+      pv(softmax(std::true_type{}, sv, kl));
+      load_v(plain, kb, kb < e_hi);
+    } else {
+      load_k(plain, kb, kb < e_hi);
+      load_v(plain, kb, kb < e_hi);
     }
     io_mark(io, 9);
-    if (e_lo + v < e_hi) {
-      int kb = e_lo + v, ne = kb + NIO;
-      float sv[8], corr;
-      load_k(plain, kb, true);
-      load_v(plain, kb, true);
+    if (kb < e_hi)
       for (;;) {
         scores(sv);
         load_k(plain, ne, ne < e_hi);
-        const v8 pb = softmax(std::false_type{}, sv, kb, corr);
-        pv(pb, corr);
+        pv(softmax(std::false_type{}, sv, kb));
         load_v(plain, ne, ne < e_hi);
         if (ne >= e_hi) break;
         kb = ne;
         ne += NIO;
       }
-    }
     io_mark(io, 1);
     // merge: waves 1 .. NIO-1 leave (o, m, l) in LDS, wave 0 adds them in wave order
     const unsigned qs = att_seq;
@@ -1445,8 +1448,9 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
           }
         }
       }
+      const float l_row = sum_q4(l_run);
       if (writer && b < a.Bp) {
-        const float inv = 1.0f / l_run;
+        const float inv = 1.0f / l_row;
         const int j = rt / MT;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
@@ -1602,10 +1606,14 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
       Epi q{};
       switch (gemm) {
         case 0:
-          Kc = a.K + (size_t)layer * a.layer_elems; Vc = a.V + (size_t)layer * a.layer_elems;
-          xa0 = a.xa + (size_t)(2 * layer) * a.xa_stride; xa1 = xa0 + a.xa_stride;
-          rsq0 = a.rsq + (size_t)(2 * layer) * a.rsq_stride; rsq1 = rsq0 + a.rsq_stride;
-          attn_l = a.attn_a + (size_t)layer * a.attn_stride; act_l = a.act_a + (size_t)layer * a.act_stride;
+          {
+            int l = layer;
+            asm volatile("" : "+s"(l));  // (the layer's pointers are formed here, not in front of the arrival)
+            Kc = a.K + (size_t)l * a.layer_elems; Vc = a.V + (size_t)l * a.layer_elems;
+            xa0 = a.xa + (size_t)(2 * l) * a.xa_stride; xa1 = xa0 + a.xa_stride;
+            rsq0 = a.rsq + (size_t)(2 * l) * a.rsq_stride; rsq1 = rsq0 + a.rsq_stride;
+            attn_l = a.attn_a + (size_t)l * a.attn_stride; act_l = a.act_a + (size_t)l * a.act_stride;
+          }
           A = xa0; rsq_in = rsq0; q.mode = MODE_QKV; q.Kc = Kc; q.Vc = Vc;
           break;
         case 1:

@@ -362,6 +362,32 @@ __device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
   const _Float16 a = (_Float16)fminf(fmaxf(lo, -lim), lim), b = (_Float16)fminf(fmaxf(hi, -lim), lim);
   return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
 }
+// Two probabilities in the cache's 16-bit type (round to nearest even; no value is out of range).
+template <bool F16>
+__device__ __forceinline__ uint32_t pack_p(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  if constexpr (F16) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
+  } else {
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), b2));
+  }
+}
+constexpr float LOG2E = 1.4426950408889634f;
+// Maximum and sum over the four lanes 16 apart, in each of them, without LDS.
+__device__ __forceinline__ float max_q4(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_q4(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 // byte offset of the 16-byte piece (row b, columns col..col+7, col a multiple of 8) of an
 // operand-fragment buffer with MT row tiles
 __device__ __forceinline__ unsigned frag_piece(int col, int b, int MT) {
