@@ -642,11 +642,13 @@ __device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigne
 // requested out of range, so every batch counts the same).  Up to RS / GB batches in flight,
 // retired one at a time, which publishes their k-tiles.  (Batches, because one turn of this
 // loop costs about half a microsecond of scalar code whatever it moves.)
-// The MT fragments of one operand k-tile (contiguous in memory and in the ring) with one LDS address and one offset.
+// The MT fragments of one operand k-tile (contiguous in memory and in the ring) with one LDS address and one offset; the last
+// row tile's lanes that hold no row of the block are out of range (zeros land, nothing is fetched): a one-row block's operand
+// would otherwise be fifteen parts padding of sixteen.
 template <int MT, int I = 0>
-__device__ __forceinline__ void operand_ktile(__amdgpu_buffer_rsrc_t ra, unsigned dst, unsigned voff, unsigned soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LDS_AS void *)(uintptr_t)dst, 16, voff, soff, I * 1024, 0);
-  if constexpr (I + 1 < MT) operand_ktile<MT, I + 1>(ra, dst, voff, soff);
+__device__ __forceinline__ void operand_ktile(__amdgpu_buffer_rsrc_t ra, unsigned dst, unsigned voff, unsigned voff_last, unsigned soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LDS_AS void *)(uintptr_t)dst, 16, I + 1 < MT ? voff : voff_last, soff, I * 1024, 0);
+  if constexpr (I + 1 < MT) operand_ktile<MT, I + 1>(ra, dst, voff, voff_last, soff);
 }
 
 // The usual case, one MFMA wave per IO wave, with the loop's cost per k-tile cut down: a whole batch that does not wrap
@@ -655,13 +657,14 @@ __device__ __forceinline__ void operand_ktile(__amdgpu_buffer_rsrc_t ra, unsigne
 // nineteen, and the down projection waited for its operand), and the ring space is looked up only when the space
 // known from the last look does not cover the batch.
 template <int MT, int NW>
-__device__ __forceinline__ bool load_operand_1(Io &io, const uint16_t *A, int KT, unsigned &a_seq, int dbg) {
+__device__ __forceinline__ bool load_operand_1(Io &io, const uint16_t *A, int KT, int Bp, unsigned &a_seq, int dbg) {
   constexpr int RS = Lay<MT, NW>::RS, GB = RS >= 16 ? 8 : 4, LPB = GB * MT;
   constexpr int FL0 = RS / GB < 63 / LPB + 1 ? RS / GB : 63 / LPB + 1;  // batches in flight: (FL - 1) LPB loads must fit the counter
   constexpr int FL = FL0 < 4 ? FL0 : 4;
   static_assert(RS % GB == 0 && FL >= 1 && (FL - 1) * LPB <= 63 && (RS & (RS - 1)) == 0, "ring and load counter");
   __amdgpu_buffer_rsrc_t ra = rsrc_of(A);
   const unsigned voff = (dbg & 4) ? OOB : (unsigned)io.lane * 16u;
+  const unsigned voff_last = 16 * (MT - 1) + (io.lane & 15) < Bp ? voff : OOB;
   const int w = io.v;
   const int nk = nk_of(KT, w, NW), n_batches = (nk + GB - 1) / GB;
   const unsigned region = io.lds0 + (unsigned)w * Lay<MT, NW>::REG;
@@ -712,12 +715,12 @@ __device__ __forceinline__ bool load_operand_1(Io &io, const uint16_t *A, int KT
     if (nv == GB && slot0 + GB <= (unsigned)RS) {
       const unsigned dst = region + slot0 * (unsigned)(MT * 1024);
 #pragma unroll
-      for (int g = 0; g < GB; ++g) operand_ktile<MT>(ra, dst + (unsigned)(g * MT * 1024), voff, so + (unsigned)(g * NW * MT * 1024));
+      for (int g = 0; g < GB; ++g) operand_ktile<MT>(ra, dst + (unsigned)(g * MT * 1024), voff, voff_last, so + (unsigned)(g * NW * MT * 1024));
     } else {
 #pragma unroll
       for (int g = 0; g < GB; ++g) {  // (a missing k-tile is requested out of range, so every batch counts the same)
         const unsigned dst = region + ((slot0 + (unsigned)g) & (unsigned)(RS - 1)) * (unsigned)(MT * 1024);
-        operand_ktile<MT>(ra, dst, g < nv ? voff : OOB, g < nv ? so + (unsigned)(g * NW * MT * 1024) : 0u);
+        operand_ktile<MT>(ra, dst, g < nv ? voff : OOB, g < nv ? voff_last : OOB, g < nv ? so + (unsigned)(g * NW * MT * 1024) : 0u);
       }
     }
     a_seq += (unsigned)nv;
@@ -728,8 +731,8 @@ __device__ __forceinline__ bool load_operand_1(Io &io, const uint16_t *A, int KT
 }
 
 template <int MT, int NW>
-__device__ __forceinline__ bool load_operand(Io &io, const uint16_t *A, int KT, unsigned (&a_seq)[NW / (8 - NW)], int dbg) {
-  if constexpr (NW == 8 - NW) return load_operand_1<MT, NW>(io, A, KT, a_seq[0], dbg);
+__device__ __forceinline__ bool load_operand(Io &io, const uint16_t *A, int KT, int Bp, unsigned (&a_seq)[NW / (8 - NW)], int dbg) {
+  if constexpr (NW == 8 - NW) return load_operand_1<MT, NW>(io, A, KT, Bp, a_seq[0], dbg);
   constexpr int NIO = 8 - NW, SV = NW / NIO, RS = Lay<MT, NW>::RS, GB = 4, LPB = GB * SV * MT;
   constexpr int FL0 = RS / GB < 63 / LPB + 1 ? RS / GB : 63 / LPB + 1;  // batches in flight: (FL - 1) LPB loads must fit the counter
   constexpr int FL = FL0 < 8 ? FL0 : 8;
@@ -1173,7 +1176,7 @@ __device__ __forceinline__ bool io_pass(const StackArgs &a, Io &io, const Pass &
   if (p.pidx == 0) io_mark(io, 10);
   RowStat<MT, NIO> rs;
   if (rsq_in) row_factors_load<MT, NIO>(io, rsq_in, a.Bp, a.ncg, rs);
-  if (!load_operand<MT, NW>(io, A, p.KT, a_seq, LA_DBG_BITS(a.dbg))) return false;
+  if (!load_operand<MT, NW>(io, A, p.KT, a.Bp, a_seq, LA_DBG_BITS(a.dbg))) return false;
   if (io.tr && io.v == 0 && io.lane == 0 && p.pidx == 0) io.tr[3] = wall_clock64() - t_a;  // (reported as "waited for weights": the operand's way in)
   if (rsq_in) row_factors_finish<MT, NIO>(io, a.Bp, a.inv_d, a.eps, rs);
   EpiPre pre;
