@@ -53,21 +53,21 @@ struct PfGemm {
 };
 
 // The epilogue of a wave's tile.  The products are formed with the weight fragment as the MFMA's first operand, so
-// a lane holds FOUR CONSECUTIVE COLUMNS of one row: acc[m][j][i] is row 16 (r0 + m) + c16, column 4 q4 + i of column
+// a lane holds FOUR CONSECUTIVE COLUMNS of one row (NM row tiles x NTW column tiles): acc[m][j][i] is row 16 (r0 + m) + c16, column 4 q4 + i of column
 // tile t0 + j.  Every store is then an 8- or 16-byte vector (the cache's V layout aside), and the partner of a RoPE
 // pair or of a gate channel (8 columns further) sits 32 lanes further.
-template <int MODE, int NTW>
-__device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[4][NTW], int r0, int t0, int lane, int slice, LDS_AS const float *rf) {
+template <int MODE, int NM, int NTW>
+__device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[NM][NTW], int r0, int t0, int lane, int slice, LDS_AS const float *rf) {
   const int q4 = lane >> 4, c16 = lane & 15;
-  float rsm[4];  // row factors of the norm
+  float rsm[NM];  // row factors of the norm
 #pragma unroll
-  for (int m = 0; m < 4; ++m) rsm[m] = MODE == PF_PART ? 0.f : rf[16 * m + c16];
+  for (int m = 0; m < NM; ++m) rsm[m] = MODE == PF_PART ? 0.f : rf[16 * m + c16];
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     const int t = t0 + j;
     if (t >= p.ntiles) continue;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < NM; ++m) {
       const int row = 16 * (r0 + m) + c16;
       const f32x4 v = acc[m][j];
       if (MODE == PF_PART) {
@@ -131,6 +131,16 @@ __device__ __forceinline__ void pf_epilogue(const PfGemm &p, const f32x4 (&acc)[
 template <int N>
 __device__ __forceinline__ void pf_wait_lds_reads() {  // at most N LDS operations of this wave outstanding
   asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// Row factor of the norm from the partial sums of squares.
+__device__ __forceinline__ float pf_row_factor(const PfGemm &p, int row) {
+  if (row >= p.M) return 0.f;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  const f32x4 *sp = reinterpret_cast<const f32x4 *>(p.ss + (size_t)row * PF_CHUNKS);
+#pragma unroll
+  for (int i = 0; i < PF_CHUNKS / 4; ++i) a += sp[i];
+  return 1.0f / sqrtf(((a[0] + a[1]) + (a[2] + a[3])) * p.inv_d + p.eps);
 }
 
 // One product.  A workgroup computes a tile of 64 WM rows x 16 WN NTW columns, a wave 64 rows x 16 NTW columns of it; the
@@ -242,16 +252,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   for (int s = 0; s < NS; ++s) request();
   // row factors of the norm into LDS, while the first stages are on their way
   LDS_AS float *rf = (LDS_AS float *)(uintptr_t)(lds0 + NS * F * 1024u);
-  if (MODE != PF_PART && (int)threadIdx.x < 16 * RTB) {
-    const int row = 16 * rb * RTB + (int)threadIdx.x;
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (row < p.M) {
-      const f32x4 *sp = reinterpret_cast<const f32x4 *>(p.ss + (size_t)row * PF_CHUNKS);
-#pragma unroll
-      for (int i = 0; i < PF_CHUNKS / 4; ++i) a += sp[i];
-    }
-    rf[threadIdx.x] = row < p.M ? 1.0f / sqrtf(((a[0] + a[1]) + (a[2] + a[3])) * p.inv_d + p.eps) : 0.f;
-  }
+  if (MODE != PF_PART && (int)threadIdx.x < 16 * RTB) rf[threadIdx.x] = pf_row_factor(p, 16 * rb * RTB + (int)threadIdx.x);
   wait_vmcnt<(NS - 1) * LPW>();
   pf_wait_lds_reads<0>();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -281,13 +282,109 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   if (r < n_kt) mul(fa[0], fb[0]);
   wait_vmcnt<0>();  // (the requests past the last k-tile land before the LDS is given back)
   const int r0 = rb * RTB + 4 * wm;
-  if (r0 < p.RT) pf_epilogue<MODE, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
+  if (r0 < p.RT) pf_epilogue<MODE, 4, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
 }
 
 template <int MODE, int WM, int WN, int NTW, int NS>
 __global__ __launch_bounds__(64 * WM * WN, 2) void pf_tile_kernel(PfGemm p) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t pf_lds[];
   pf_tile_body<MODE, WM, WN, NTW, NS>(p, (LDS_AS uint8_t *)pf_lds);
+}
+
+// The QKV product for 65 to 128 rows, which has 96 of the smallest tiles for 256 CUs and an epilogue that cannot take slices of
+// the contraction: a workgroup takes two column tiles and all rows, and its four waves share the contraction (wave w the
+// k-tiles w, w + 4, ..., which is how the weights lie); each streams its fragments into registers, NS k-tiles ahead, with
+// no barrier until the four sums are added.  MT: row tiles that hold rows (padding is neither loaded nor multiplied).  Bound by
+// the activations' way in, which every workgroup repeats: 77 rows of the 7B shape 37.5 -> 23.8 us, 120 rows 38.7 -> 28.0; the
+// wider matrices are faster in tiles (gate/up at 77 rows 57.8 us, this way 75.7).
+template <int MT, int NS>
+__device__ __forceinline__ void pf_qkv_few_body(const PfGemm &p, LDS_AS uint8_t *lds) {
+  constexpr int CT = 2;
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int t0 = p.t_first + (int)blockIdx.x * CT;
+  const unsigned lds0 = (unsigned)(uintptr_t)lds;
+  LDS_AS float *rf = (LDS_AS float *)(uintptr_t)(lds0 + 4u * MT * CT * 1024u);
+  if ((int)threadIdx.x < 16 * MT) rf[threadIdx.x] = pf_row_factor(p, (int)threadIdx.x);
+  // this wave's k-tiles: wave + 4 i, i < nk; fragment (before + i) of a tile's stream
+  const int nk = p.KT > wave ? (p.KT - wave + 3) / 4 : 0;
+  int before = 0;
+  for (int w = 0; w < wave; ++w) before += p.KT > w ? (p.KT - w + 3) / 4 : 0;
+  const uint8_t *wb[CT];
+  unsigned wstep[CT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j) {
+    const int t = t0 + j < p.ntiles ? t0 + j : p.ntiles - 1;  // (a group past the last tile repeats it; its result is dropped)
+    const int c = uni(t % p.G), lt = uni(t / p.G);
+    unsigned off = p.frag0;
+    for (int q = 0; q < p.n_prev; ++q) off += (unsigned)((p.prev_ntiles[q] > c ? (p.prev_ntiles[q] - c + p.G - 1) / p.G : 0) * p.prev_KT[q]);
+    const unsigned nt = uni((unsigned)((p.ntiles - c + p.G - 1) / p.G));
+    wstep[j] = nt * 1024u;
+    wb[j] = p.wstream + (size_t)c * p.cu_bytes + ((size_t)off + (unsigned)lt + (size_t)before * nt) * 1024u + (unsigned)lane * 16u;
+  }
+  const uint8_t *ab = (const uint8_t *)p.A + (size_t)lane * 16u;
+  const size_t a_kt = (size_t)p.RT * 1024u;
+  auto load = [&](int i, u32x4 (&a)[MT], u32x4 (&b)[CT]) {
+    const uint8_t *ap = ab + (size_t)(wave + 4 * i) * a_kt;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) b[j] = *(const u32x4 *)(wb[j] + (size_t)i * wstep[j]);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) a[m] = *(const u32x4 *)(ap + (unsigned)m * 1024u);
+  };
+  f32x4 acc[MT][CT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mul = [&](const u32x4 (&a)[MT], const u32x4 (&b)[CT]) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[j]), __builtin_bit_cast(f16x8, a[m]), acc[m][j], 0, 0, 0);
+  };
+  // A window of NS k-tiles.  The loop has no branch around a load (requests past the last k-tile repeat it and are never
+  // used), so that the compiler counts the loads on their way instead of waiting for all of them.
+  if (nk > 0) {
+    u32x4 sa[NS][MT], sb[NS][CT];
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) load(s < nk ? s : nk - 1, sa[s], sb[s]);
+    int i = 0;
+    for (; i + NS <= nk; i += NS) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int nx = i + s + NS - 1;
+        load(nx < nk ? nx : nk - 1, sa[(s + NS - 1) % NS], sb[(s + NS - 1) % NS]);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(sa[s], sb[s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+      if (i + s < nk) mul(sa[s], sb[s]);
+  }
+  LDS_AS f32x4 *part = (LDS_AS f32x4 *)(uintptr_t)lds0 + lane;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) part[((wave * MT + m) * CT + j) * 64] = acc[m][j];
+  __syncthreads();
+  for (int m = wave; m < MT; m += 4) {  // a wave finishes every fourth row tile
+    f32x4 sum[1][CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      sum[0][j] = part[(m * CT + j) * 64];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) sum[0][j] += part[((w * MT + m) * CT + j) * 64];
+    }
+    pf_epilogue<PF_QKV, 1, CT>(p, sum, m, t0, lane, 0, rf + 16 * m);
+  }
+}
+
+template <int MT, int NS>
+__global__ __launch_bounds__(256, 2) void pf_qkv_few_kernel(PfGemm p) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t pf_lds[];
+  pf_qkv_few_body<MT, NS>(p, (LDS_AS uint8_t *)pf_lds);
 }
 
 // The residual stream takes in the products of the projection before (x += the slices' products, added in slice order),
@@ -578,9 +675,30 @@ static void pf_choose(const PfGemm &p, int max_split, int cus, int &tile, int &S
     }
 }
 
+template <int MT, int NS>
+static int pf_launch_qkv_few(const PfGemm &p, hipStream_t s, bool prepare) {
+  constexpr int bytes = 4 * MT * 2 * 1024 + MT * 64;
+  if (prepare) {
+    LA_HIP(hipFuncSetAttribute((const void *)pf_qkv_few_kernel<MT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    return LA_OK;
+  }
+  pf_qkv_few_kernel<MT, NS><<<ceil_div(p.ntiles - p.t_first, 2), 256, bytes, s>>>(p);
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+static int pf_launch_qkv_few(const PfGemm &p, int row_tiles, hipStream_t s, bool prepare) {
+  switch (row_tiles) {
+  case 5: return pf_launch_qkv_few<5, 4>(p, s, prepare);
+  case 6: return pf_launch_qkv_few<6, 4>(p, s, prepare);
+  case 7: return pf_launch_qkv_few<7, 3>(p, s, prepare);
+  default: return pf_launch_qkv_few<8, 3>(p, s, prepare);
+  }
+}
+
 template <int MODE>
 static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int *S = nullptr) {
   ProfScope ps(name, s);
+  if (MODE == PF_QKV && p.M > 64 && p.M <= 128 && p.NW == 4) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
   int tile;
   pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, cus, tile, p.S);
   if (S) *S = p.S;
@@ -630,6 +748,10 @@ static int pf_alloc(la_model *m, PfBuffers &b) {
     int rc = pf_launch_tile<PF_QKV>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_PART>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_GATEUP>(i, PfGemm{}, nullptr, true);
+    if (rc) return rc;
+  }
+  for (int i = 5; i <= 8; ++i) {
+    int rc = pf_launch_qkv_few(PfGemm{}, i, nullptr, true);
     if (rc) return rc;
   }
   uint8_t *p = (uint8_t *)dalloc(total);

@@ -67,10 +67,10 @@ def _reference(sh, embed, tok, L0, old, dtype):
 
 
 @pytest.mark.parametrize("name,dtype,cases", [
-    ("mistral7b", "bf16", [(65, 0), (128, 1), (130, 37), (257, 0), (300, 31), (700, 5), (1023, 0), (1100, 32), (2200, 3)]),
+    ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (257, 0), (300, 31), (700, 5), (1023, 0), (1100, 32), (2200, 3)]),
     ("mistral7b", "f16", [(193, 33), (1025, 0)]),
     ("nemo12b", "bf16", [(400, 64), (1024, 0)]),
-    ("small64_bf16", "bf16", [(65, 7), (191, 0), (2049, 100)]),
+    ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (2049, 100)]),
 ])
 def test_prompt_pass_sizes(name, dtype, cases):
     import torch
