@@ -10,7 +10,7 @@ namespace la {
 struct PoolView {
   uint32_t *stamp;
   int32_t *toks;
-  uint32_t *counter;
+  uint32_t *counter, *ticket;
   int vocab, N, G;
 };
 
@@ -208,28 +208,35 @@ __global__ __launch_bounds__(64) void state_init_kernel(PoolView p, la_step_stat
   }
 }
 
-// One wave: verification with a candidate per lane, harvest with a pool slot per lane, the next block with a row per lane;
-// what the step reads comes into LDS at once.  (One thread doing all of it took 23 us, most of it waiting for one word
-// after the other.)
-__global__ __launch_bounds__(64) void accept_kernel(PoolView p, la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total,
-                                                    int W, int N, int G, int32_t *kv_L, const int32_t *err) {
+// LDS words written by one lane of the (single remaining) wave are read by others: a wave's LDS operations are in order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The accept phase in one launch: a workgroup per layer and verification row.  Every workgroup verifies for itself (a candidate
+// per lane), those whose row is accepted move it in their layer (cache relocation: the rows of candidate best_k go from block
+// rows v(k, j) to cache rows L0 + j, j = 1 .. e - 1), and the one that is through last -- all others have read the state by
+// then; nobody waits -- does the rest with one wave: harvest with a pool slot per lane, the next block with a row per lane.
+// What the step reads comes into LDS at once.  (One thread doing all of it took 23 us, most of it waiting for one word after
+// the other; the relocation as a launch of its own cost 16 accepts 40 us.)
+template <typename T>
+__global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total, int W, int N, int G,
+                                                     int32_t *kv_L, const int32_t *err, T *K, T *V, size_t layer_elems, int Hkv, int dh, int v_blocked,
+                                                     int max_len) {
   __shared__ int32_t id[LA_MAX_ROWS], win[LA_MAX_ROWS], cand[LA_MAX_ROWS], newest[LA_MAX_ROWS];
-  const int lane = threadIdx.x, n1 = N - 1, rows = 1 + (W + G) * n1;
-  if (lane < rows) id[lane] = ids[lane];
-  win[lane] = lane < W * n1 ? st->win[lane] : 0;
-  cand[lane] = st->cand[lane];
+  __shared__ int is_last;
+  const int lane = threadIdx.x & 63, n1 = N - 1, rows = 1 + (W + G) * n1;
+  if (threadIdx.x < 64) {
+    if (lane < rows) id[lane] = ids[lane];
+    win[lane] = lane < W * n1 ? st->win[lane] : 0;
+    cand[lane] = st->cand[lane];
+  }
   const int emitted_before = st->n_emitted, n_cand = st->n_cand, L0 = st->L, Bp = st->Bp;
   const int error = *err;  // what the launches before this one on the model raised (0: nothing)
   const int steps = st->steps, matched = st->matched_steps;
   __syncthreads();
   const int remaining = max_total - emitted_before;
-  if (remaining <= 0) {  // budget spent: the step is a no-op
-    if (lane == 0) {
-      st->error = error;
-      st->last_emitted = 0;
-    }
-    return;
-  }
   // candidate `lane` matches m tokens; the longest match wins, the lowest candidate of equal ones
   int m = 0;
   if (lane < n_cand && cand[lane * n1] == id[0]) {
@@ -244,19 +251,44 @@ __global__ __launch_bounds__(64) void accept_kernel(PoolView p, la_step_state *s
   }
   const int best_m = best >> 6, best_k = best_m > 0 ? 63 - (best & 63) : 0;
   const int e = best_m + 1 < remaining ? best_m + 1 : remaining;
+  const int row = (int)blockIdx.y + 1, src = L0 + v_row_index(W, N, best_k, row), dst = L0 + row;
+  if (row < e && src < max_len && dst < max_len && L0 >= 0) {
+    T *Kl = K + (size_t)blockIdx.x * layer_elems;
+    T *Vl = V + (size_t)blockIdx.x * layer_elems;
+    const int n = Hkv * dh;
+    for (int i = threadIdx.x; i < n; i += 256) {
+      Kl[(size_t)dst * n + i] = Kl[(size_t)src * n + i];
+      const int h = i / dh, c = i - h * dh;
+      Vl[v_index(v_blocked, dst, h, c, Hkv, dh)] = Vl[v_index(v_blocked, src, h, c, Hkv, dh)];
+    }
+  }
+  __syncthreads();  // (every wave has what it needs of the state)
+  if (threadIdx.x == 0) {
+    is_last = atomicAdd(p.ticket, 1u) + 1u == gridDim.x * gridDim.y;
+    if (is_last) *p.ticket = 0u;
+  }
+  __syncthreads();
+  if (!is_last || threadIdx.x >= 64) return;
+  if (remaining <= 0) {  // budget spent: the step is a no-op
+    if (lane == 0) {
+      st->error = error;
+      st->last_emitted = 0;
+    }
+    return;
+  }
   if (lane < e) emitted[emitted_before + lane] = lane == 0 ? id[0] : id[v_row_index(W, N, best_k, lane)];
   const int last = e == 1 ? id[0] : id[v_row_index(W, N, best_k, e - 1)];
   // harvest: each window column yields one n-gram ending in the model's newest guess; then the columns move up
   int n_next = 0;
   if (N >= 2) {
     if (lane < W) newest[lane] = id[la_row_index(W, N - 2, lane)];
-    __syncthreads();
+    wave_sync();
     pool_harvest(p, win, newest, W, lane);
     const int up = lane + W < W * n1 ? win[lane + W] : lane < W * n1 ? newest[lane - W * (n1 - 1)] : 0;
-    __syncthreads();
+    wave_sync();
     if (lane < W * n1) win[lane] = st->win[lane] = up;
     n_next = pool_lookup(p, last, cand, st->cand, lane);
-    __syncthreads();
+    wave_sync();
   }
   build_block(st, W, N, n_next, L0 + e, Bp, last, win, cand, lane);
   if (lane == 0) {
@@ -341,27 +373,6 @@ __global__ __launch_bounds__(64) void jacobi_accept_kernel(la_step_state *st, co
   st->c0 = last;
 }
 
-// Cache relocation: the accepted verification rows of candidate last_k move from block rows
-// v(k, j) to cache rows L0 + j, j = 1..e-1, in every layer (L0 = cache length before the step).
-template <typename T>
-__global__ void kv_commit_kernel(const la_step_state *st, T *K, T *V, size_t layer_elems, int Hkv, int dh,
-                                 int v_blocked, int W, int N, int max_len) {
-  int e = st->last_emitted;
-  int j = blockIdx.y + 1;
-  if (j >= e) return;
-  int L0 = st->L - e;
-  int src = L0 + v_row_index(W, N, st->last_k, j), dst = L0 + j;
-  if (src >= max_len || dst >= max_len || L0 < 0) return;
-  T *Kl = K + (size_t)blockIdx.x * layer_elems;
-  T *Vl = V + (size_t)blockIdx.x * layer_elems;
-  int n = Hkv * dh;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    Kl[(size_t)dst * n + i] = Kl[(size_t)src * n + i];
-    int h = i / dh, c = i % dh;
-    Vl[v_index(v_blocked, dst, h, c, Hkv, dh)] = Vl[v_index(v_blocked, src, h, c, Hkv, dh)];
-  }
-}
-
 }  // namespace la
 
 using namespace la;
@@ -397,7 +408,7 @@ extern "C" int la_pool_alloc(int vocab, int N, int G, la_pool **out) {
   size_t n1 = N > 1 ? N - 1 : 1;
   if (hipMalloc(&p->stamp, slots * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&p->toks, slots * n1 * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&p->counter, sizeof(uint32_t)) != hipSuccess) {
+      hipMalloc(&p->counter, 2 * sizeof(uint32_t)) != hipSuccess || hipMemset(p->counter, 0, 2 * sizeof(uint32_t)) != hipSuccess) {  // (counter, ticket)
     la_free_pool(p);
     set_error("pool allocation failed");
     return LA_ENOMEM;
@@ -414,7 +425,7 @@ extern "C" void la_free_pool(la_pool *p) {
   delete p;
 }
 
-static PoolView view(la_pool *p) { return PoolView{p->stamp, p->toks, p->counter, p->vocab, p->N, p->G}; }
+static PoolView view(la_pool *p) { return PoolView{p->stamp, p->toks, p->counter, p->counter + 1, p->vocab, p->N, p->G}; }
 
 extern "C" int la_state_init(la_pool *p, la_kv *kv, const la_lookahead_desc *d, const int32_t *prompt, int P, int Bp,
                              int seed_pool, la_step_state *state, void *stream) {
@@ -456,18 +467,14 @@ extern "C" int la_ngram_accept(la_pool *p, la_kv *kv, const la_lookahead_desc *d
   hipStream_t s = (hipStream_t)stream;
   {
     ProfScope ps("ngram_accept", s);
-    accept_kernel<<<1, 64, 0, s>>>(view(p), state, ids, emitted, max_total, d->W, d->N, d->G, kv->L_dev, kv->err_dev);
-  }
-  if (d->N >= 2) {
-    ProfScope ps("kv_commit", s);
     const la_model_desc &md = kv->m->d;
-    dim3 grid(kv->n_layers, d->N - 1);
+    const dim3 grid(d->N >= 2 ? kv->n_layers : 1, d->N >= 2 ? d->N - 1 : 1);
     if (md.dtype == LA_F32)
-      kv_commit_kernel<float><<<grid, 256, 0, s>>>(state, (float *)kv->K, (float *)kv->V, kv->layer_elems(),
-                                                    md.n_kv_heads, md.head_dim, kv->v_blocked, d->W, d->N, kv->max_len);
+      accept_kernel<float><<<grid, 256, 0, s>>>(view(p), state, ids, emitted, max_total, d->W, d->N, d->G, kv->L_dev, kv->err_dev, (float *)kv->K,
+                                                (float *)kv->V, kv->layer_elems(), md.n_kv_heads, md.head_dim, kv->v_blocked, kv->max_len);
     else
-      kv_commit_kernel<uint16_t><<<grid, 256, 0, s>>>(state, (uint16_t *)kv->K, (uint16_t *)kv->V, kv->layer_elems(),
-                                                       md.n_kv_heads, md.head_dim, kv->v_blocked, d->W, d->N, kv->max_len);
+      accept_kernel<uint16_t><<<grid, 256, 0, s>>>(view(p), state, ids, emitted, max_total, d->W, d->N, d->G, kv->L_dev, kv->err_dev, (uint16_t *)kv->K,
+                                                   (uint16_t *)kv->V, kv->layer_elems(), md.n_kv_heads, md.head_dim, kv->v_blocked, kv->max_len);
   }
   LA_HIP(hipGetLastError());
   kv->L_bound += d->N;
