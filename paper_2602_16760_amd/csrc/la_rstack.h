@@ -577,6 +577,29 @@ __device__ __forceinline__ bool io_wait_ge(Io &io, int word, unsigned want) {
   }
 }
 
+// ... on NW consecutive counters that are written one by one (four at a time in one read).
+template <int NW>
+__device__ __forceinline__ bool io_wait_all_ge(Io &io, int word, unsigned want) {
+  static_assert(NW % 4 == 0, "whole 16-byte reads");
+  unsigned spins = 0;
+  for (;;) {
+    bool all = true;
+#pragma unroll
+    for (int w = 0; w < NW; w += 4) {
+      const u32x4 x = ctl_read4(io.ctl + 4 * (word + w));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) all = all && (int)(uni(x[k]) - want) >= 0;
+    }
+    if (all) return true;
+    __builtin_amdgcn_s_sleep(1);
+    if ((++spins & 255u) == 0 && (ctl_read(io.ctl + 4 * K_DEAD) != 0 || spins > SPIN_LDS)) {
+      ctl_write(io.ctl + 4 * K_DEAD, 1u);
+      io.ok = 0;
+      return false;
+    }
+  }
+}
+
 template <int NIO>
 __device__ __forceinline__ bool io_barrier(Io &io) {
   io.bar_seq += NIO;
@@ -1184,8 +1207,7 @@ __device__ __forceinline__ bool io_pass(const StackArgs &a, Io &io, const Pass &
   between();  // (bookkeeping of the caller that needs no result of this pass: it runs while the MFMA waves finish)
   if (!io_barrier<NIO>(io)) return false;  // (the row factors, gains and x tiles the IO waves staged for each other)
   if (q.mode == MODE_RESID) epi_prefetch<MT, NIO>(a, io, q.mode, x_lds, p.tile0, p.NT, pre);
-  for (int w = 0; w < NW; ++w)
-    if (!io_wait_ge(io, K_PDONE + w, pseq + 1u)) return false;
+  if (!io_wait_all_ge<NW>(io, K_PDONE, pseq + 1u)) return false;
   if (p.pidx == 0) io_mark(io, 1);
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   const int LDT = 16 * p.NTS + 4;

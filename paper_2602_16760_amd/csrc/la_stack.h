@@ -254,6 +254,11 @@ __device__ __forceinline__ unsigned ctl_read(unsigned addr) {
   asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
   return uni(v);
 }
+__device__ __forceinline__ u32x4 ctl_read4(unsigned addr) {  // four consecutive words (addr a multiple of 16)
+  u32x4 v;
+  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
+  return v;
+}
 __device__ __forceinline__ unsigned ctl_read_lanes(unsigned addr) {  // a different word per lane
   unsigned v;
   asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
