@@ -407,7 +407,7 @@ def run_split_sweep(args):
 
 
 def prefill_report(shape, n_tok, seconds):
-    """The prompt pass (la_prefill: one matrix product per weight matrix and 1024-token chunk, causal attention over
+    """The prompt pass (la_prefill: one matrix product per weight matrix and 2048-token chunk, causal attention over
     the cache) against the matrix-core roofline: 2 flop per weight and token in the GEMMs plus the attention products."""
     d, F, qd, kvd = shape.d_model, shape.d_ffn, shape.q_dim, shape.kv_dim
     weights = shape.n_layers * (d * (qd + 2 * kvd) + qd * d + 3 * d * F)

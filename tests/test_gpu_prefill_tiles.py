@@ -106,3 +106,33 @@ def test_prompt_pass_sizes(name, dtype, cases):
     finally:
         torch.cuda.synchronize()
         B.la_free_model(model)
+
+
+def test_prompt_pass_agrees_with_the_block_kernel():
+    """One call of 300 tokens (the large-M pass) against pieces of 64, the largest that go through the block kernel:
+    each is within TOL of the same float64 rows, so they are within twice that of each other."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    sh = replace(synth.SHAPES["mistral7b"], n_layers=2, vocab=512)
+    embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, torch.bfloat16)
+    model = B.la_init_model(sh, embed)
+    kvs = [B.la_kv_alloc(model, 300) for _ in range(2)]
+    try:
+        for l in range(sh.n_layers):
+            B.la_model_set_layer(model, l, _layer(sh, l, torch.bfloat16))
+            torch.cuda.synchronize()
+        tok = torch.arange(300, device="cuda", dtype=torch.int32) * 7 % sh.vocab
+        B.la_prefill(model, kvs[0], tok, 0)
+        for s in range(0, 300, 64):
+            B.la_prefill(model, kvs[1], tok[s:s + 64].contiguous(), s)
+        for l in range(sh.n_layers):
+            rows = [[torch.empty((300, sh.n_kv_heads, sh.head_dim), dtype=torch.bfloat16, device="cuda") for _ in "kv"] for _ in kvs]
+            for kv, r in zip(kvs, rows):
+                B.la_kv_read(kv, l, 0, 300, *r)
+            for a, b in zip(*rows):
+                assert ((a.double() - b.double()).abs().max() / b.double().abs().max()).item() <= 2 * TOL["bf16"]
+    finally:
+        torch.cuda.synchronize()
+        for kv in kvs:
+            B.la_free_kv(kv)
+        B.la_free_model(model)
