@@ -462,7 +462,8 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
   const int kvh = uni((int)blockIdx.x % Hkv), w0 = uni((n_task - 1 - (int)blockIdx.x / Hkv) * 4);  // (the longest rows first)
   const unsigned lds0 = (unsigned)(uintptr_t)lds;
   const int last_row = L0 + M - 1, last_tile = n_tile - 1;
-  auto blocks_of = [&](int rt) { return ((L0 + 16 * rt + 15 < last_row ? L0 + 16 * rt + 15 : last_row) / PF_KEYS) + 1; };  // blocks that hold a visible key
+  auto last_key = [&](int rt) { return L0 + 16 * rt + 15 < last_row ? L0 + 16 * rt + 15 : last_row; };  // last one that a row of the tile sees
+  auto blocks_of = [&](int rt) { return last_key(rt) / PF_KEYS + 1; };                                  // blocks that hold a visible key
   const int nkb = uni(blocks_of((w0 + 3 < last_tile ? w0 + 3 : last_tile) / g));
   // K half: row-major [key][DH], the 16-byte pieces of a row permuted by the key so that sixteen keys' equal pieces lie in
   // different banks; V half: the cache's own blocks.  The last block may reach past the cache's last 32-key block: those
@@ -498,7 +499,7 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) q[kt] = *(const v8 *)(Q + ((((size_t)h * RT + rt) * KT + kt) * 64 + lane) * 8);
   request();
-  const int nkb_w = uni(blocks_of(rt)), full = uni((L0 + 16 * rt + 1) / PF_KEYS);  // blocks 0 .. full - 1 are visible to every row of the tile
+  const int last_t = uni(last_key(rt)), nkb_w = uni(blocks_of(rt)), full = uni((L0 + 16 * rt + 1) / PF_KEYS);  // blocks 0 .. full - 1 are visible to every row of the tile
   f32x4 o[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -555,12 +556,14 @@ __device__ __forceinline__ void pf_attn_body(LDS_AS uint8_t *lds, const uint16_t
         pb[n] = __builtin_bit_cast(v8, u32x4{pack_p<F16>(pr[0], pr[1]), pack_p<F16>(pr[2], pr[3]), pack_p<F16>(pr[4], pr[5]), pack_p<F16>(pr[6], pr[7])});
       }
 #pragma unroll
-      for (int n = 0; n < NB; ++n)
+      for (int n = 0; n < NB; ++n) {
+        if (n > 0 && kb * PF_KEYS + 32 * n > last_t) break;  // (no row sees these keys, and what they hold need not be finite)
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
           const v8 vf = __builtin_bit_cast(v8, *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(HALF + (n * DT + dt) * 1024) + (unsigned)lane * 16u));
           o[dt] = mma(vf, pb[n], o[dt]);
         }
+      }
     }
   }
   wait_vmcnt<0>();  // (the request past the last block lands before the LDS is given back)

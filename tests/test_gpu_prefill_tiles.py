@@ -136,3 +136,40 @@ def test_prompt_pass_agrees_with_the_block_kernel():
         for kv in kvs:
             B.la_free_kv(kv)
         B.la_free_model(model)
+
+
+def test_a_token_that_is_not_finite_stays_out_of_the_key_blocks_before_it():
+    """Rows whose 32-key block ends before the token: bit for bit what they are without it (a masked key's probability is
+    zero, and zero times a value that is not finite would not be)."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    sh = replace(synth.SHAPES["mistral7b"], n_layers=2, vocab=512)
+    embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, torch.bfloat16)
+    embed[511] = float("nan")
+    model = B.la_init_model(sh, embed)
+    try:
+        for l in range(sh.n_layers):
+            B.la_model_set_layer(model, l, _layer(sh, l, torch.bfloat16))
+            torch.cuda.synchronize()
+        for n, at in ((100, 32), (200, 100), (300, 255)):
+            got = []
+            for bad in (False, True):
+                tok = torch.arange(n, device="cuda", dtype=torch.int32) * 7 % 511
+                if bad:
+                    tok[at] = 511
+                kv = B.la_kv_alloc(model, n)
+                try:
+                    B.la_prefill(model, kv, tok, 0)
+                    rows = [[torch.empty((at // 32 * 32, sh.n_kv_heads, sh.head_dim), dtype=torch.bfloat16, device="cuda") for _ in "kv"]
+                            for _ in range(sh.n_layers)]
+                    for l in range(sh.n_layers):
+                        B.la_kv_read(kv, l, 0, at // 32 * 32, *rows[l])
+                    got.append(rows)
+                finally:
+                    torch.cuda.synchronize()
+                    B.la_free_kv(kv)
+            for a, b in zip(got[0], got[1]):
+                assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]), f"{n} tokens, token {at}"
+    finally:
+        torch.cuda.synchronize()
+        B.la_free_model(model)
