@@ -109,7 +109,8 @@ typedef struct {
  *   win      lookahead window, win[r*W + c], r < N-1, c < W
  *   cand     candidates being verified in this block, cand[k*(N-1) + j], k < n_cand
  *   counters: steps, steps with at least one candidate token accepted, tokens emitted so
- *            far, and for the last step: tokens emitted, winning candidate, match length. */
+ *            far, and for the last step: tokens emitted, winning candidate, match length
+ *   reserved the library's own; 0 whenever no call that takes the state is running. */
 typedef struct {
   int32_t L, c0, n_cand, Bp;
   int32_t steps, matched_steps, n_emitted, last_emitted, last_k, last_m;

@@ -10,7 +10,7 @@ namespace la {
 struct PoolView {
   uint32_t *stamp;
   int32_t *toks;
-  uint32_t *counter, *ticket;
+  uint32_t *counter;
   int vocab, N, G;
 };
 
@@ -218,6 +218,8 @@ __device__ __forceinline__ void wave_sync() {
 // per lane), those whose row is accepted move it in their layer (cache relocation: the rows of candidate best_k go from block
 // rows v(k, j) to cache rows L0 + j, j = 1 .. e - 1), and the one that is through last -- all others have read the state by
 // then; nobody waits -- does the rest with one wave: harvest with a pool slot per lane, the next block with a row per lane.
+// The workgroups are counted in st->reserved (zero between launches): a word of the state and not of the pool, which several
+// generations may share, and cleared by the init kernels on the stream that the accepts follow on.
 // What the step reads comes into LDS at once.  (One thread doing all of it took 23 us, most of it waiting for one word after
 // the other; the relocation as a launch of its own cost 16 accepts 40 us.)
 template <typename T>
@@ -264,8 +266,8 @@ __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *
   }
   __syncthreads();  // (every wave has what it needs of the state)
   if (threadIdx.x == 0) {
-    is_last = atomicAdd(p.ticket, 1u) + 1u == gridDim.x * gridDim.y;
-    if (is_last) *p.ticket = 0u;
+    is_last = atomicAdd(&st->reserved, 1) + 1 == (int)(gridDim.x * gridDim.y);
+    if (is_last) st->reserved = 0;
   }
   __syncthreads();
   if (!is_last || threadIdx.x >= 64) return;
@@ -408,7 +410,7 @@ extern "C" int la_pool_alloc(int vocab, int N, int G, la_pool **out) {
   size_t n1 = N > 1 ? N - 1 : 1;
   if (hipMalloc(&p->stamp, slots * sizeof(uint32_t)) != hipSuccess ||
       hipMalloc(&p->toks, slots * n1 * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&p->counter, 2 * sizeof(uint32_t)) != hipSuccess || hipMemset(p->counter, 0, 2 * sizeof(uint32_t)) != hipSuccess) {  // (counter, ticket)
+      hipMalloc(&p->counter, sizeof(uint32_t)) != hipSuccess) {
     la_free_pool(p);
     set_error("pool allocation failed");
     return LA_ENOMEM;
@@ -425,7 +427,7 @@ extern "C" void la_free_pool(la_pool *p) {
   delete p;
 }
 
-static PoolView view(la_pool *p) { return PoolView{p->stamp, p->toks, p->counter, p->counter + 1, p->vocab, p->N, p->G}; }
+static PoolView view(la_pool *p) { return PoolView{p->stamp, p->toks, p->counter, p->vocab, p->N, p->G}; }
 
 extern "C" int la_state_init(la_pool *p, la_kv *kv, const la_lookahead_desc *d, const int32_t *prompt, int P, int Bp,
                              int seed_pool, la_step_state *state, void *stream) {

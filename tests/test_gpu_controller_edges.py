@@ -57,3 +57,40 @@ def test_controller_edges(W, N, G, Bp, V, P):
         torch.cuda.synchronize()
         B.la_free_pool(pool)
         eng.close()
+
+
+def test_generations_on_two_streams_share_a_pool_without_slots():
+    """G = 0: nothing is kept in the pool, so generations on different streams may share one.  It is made while the default
+    stream is busy: what the accept kernels count with has to be ready on their own streams all the same."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    W, N, G, Bp, V, steps = 10, 7, 0, 64, 5, 24
+    engs = [gpu_engine(synth.SHAPES["small64_bf16"], 200, head=False) for _ in range(2)]
+    rng = np.random.default_rng(3)
+    prompts = [rng.integers(0, V, size=50).astype(np.int32) for _ in engs]
+    ids = [rng.integers(0, V, size=(steps, Bp)).astype(np.int32) for _ in engs]
+    dev = [(B.to_device(p), B.to_device(i)) for p, i in zip(prompts, ids)]
+    states, emitted = [B.new_state() for _ in engs], [torch.zeros(steps, dtype=torch.int32, device="cuda") for _ in engs]
+    streams = [torch.cuda.Stream() for _ in engs]
+    torch.cuda.synchronize()
+    torch.cuda._sleep(50_000_000)
+    pool = B.la_pool_alloc(engs[0].shape.vocab, N, G)
+    try:
+        for k, s in enumerate(streams):
+            B.la_state_init(pool, engs[k].kv, W, N, G, dev[k][0], Bp, True, states[k], stream=s)
+        for i in range(steps):
+            for k, s in enumerate(streams):
+                B.la_ngram_accept(pool, engs[k].kv, W, N, G, dev[k][1][i], states[k], emitted[k], steps, stream=s)
+        torch.cuda.synchronize()
+        for k in range(2):
+            ost = ola.LookaheadState(prompts[k], W, N, G, Bp)
+            for i in range(steps):
+                ost.step(ids[k][i], steps - len(ost.emitted))
+            assert_state_equal(B.read_state(states[k]), ost, W, N, G, Bp)
+            assert B.read_state(states[k]).reserved == 0
+            assert list(emitted[k].cpu().numpy()) == ost.emitted
+    finally:
+        torch.cuda.synchronize()
+        B.la_free_pool(pool)
+        for e in engs:
+            e.close()
