@@ -208,8 +208,13 @@ int la_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_t 
  * with a causal attention kernel over the cache; shorter prompts, and models on the plain
  * kernels, go through the block kernel in causal chunks of LA_MAX_ROWS rows.  Everything is
  * enqueued on `stream`; the hidden states are not returned (generation restarts from the last
- * prompt token as c0).  The first large prompt on a model allocates its buffers (about
- * 2048 x (d_model x 14 + d_ffn x 2 + Hq x dh x 4) bytes).  LA_ERANGE: L0 + n > max_len.
+ * prompt token as c0).  The model's first prompt of more than LA_MAX_ROWS tokens allocates
+ * buffers for 128 rows, about 128 x (d_model x 38 + d_ffn x 2 + Hq x dh x 4) bytes; the first of
+ * 128 tokens or more those of a whole chunk, about 2048 x (d_model x 14 + d_ffn x 2 + Hq x dh x 4)
+ * bytes, or on a card that has less memory left of half, a quarter, ... of it with as much
+ * shorter chunks; without memory for 128 rows the prompt goes through the block kernel.  The
+ * buffers stay with the model; a captured first prompt allocates them like any other.
+ * LA_ERANGE: L0 + n > max_len.
  * (Chunked prefill is the paper's named future work, Section 8.) */
 int la_prefill(la_model *m, la_kv *kv, const int32_t *tok, int n, int L0, void *stream);
 

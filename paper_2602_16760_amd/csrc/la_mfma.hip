@@ -135,8 +135,9 @@ struct GemmPlan {
   int N = 0, K = 0, KT = 0, ntiles = 0, ntp = 1, nt_max = 0;
 };
 
-struct PfBuffers {  // the large-M prompt pass (la_prefill.h), allocated at its first use
-  uint8_t *base = nullptr;  // the one allocation; the rest are its parts
+struct PfBuffers {  // a set of buffers of the large-M prompt pass (la_prefill.h), allocated at its first use
+  uint8_t *base = nullptr;      // the one allocation; the rest are its parts
+  int rows = 0, part_rows = 0;  // rows of a chunk; rows of the slices' products together
   float *x = nullptr, *part = nullptr, *ss = nullptr, *cs = nullptr;
   uint16_t *A = nullptr, *Q = nullptr, *attn = nullptr, *act = nullptr;
 };
@@ -166,7 +167,7 @@ struct MfmaModel {
   unsigned epoch = 0;
   unsigned long long *trace = nullptr;  // LA_TRACE=1: per-phase timestamps, printed after each launch
   int trace_phases = 0;
-  PfBuffers pf;
+  PfBuffers pf, pf_few;
 };
 
 static int env_int(const char *name, int dflt) {
@@ -207,7 +208,7 @@ void mfma_destroy(la_model *m) {
   void *ps[] = {f->wstream, f->ustream, f->xa, f->attn_a, f->act_a, f->qf, f->xa_u, f->rsq_u, f->rsq, f->un_part,
                 f->sync, f->dev_gains, f->zero_len, f->trace, f->att_part, f->att_cnt,
                 f->sched[0][0], f->sched[0][1], f->sched[1][0], f->sched[1][1], f->sched[2][0], f->sched[2][1],
-                f->pf.base};
+                f->pf.base, f->pf_few.base};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   delete f;

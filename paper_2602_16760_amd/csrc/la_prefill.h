@@ -13,19 +13,10 @@
 // Both operands of the products are MFMA fragments of 1 KB: the activations are stored as [k-tile][row tile][lane][8
 // halves] by their producers, and a weight fragment is the 1 KB block of the per-CU streams the block kernel reads.
 #pragma once
+#include "la_prefill_plan.h"
 
 namespace la {
 
-// Rows of one prompt chunk (buffers are sized for it).  At 2048 rows a 4096-column matrix fills the chip with one slice
-// of the contraction: 2048 tokens, four layers, 2.77 ms against 3.02 in chunks of 1024; 1100 tokens 1.89 against 2.05.  4096
-// rows gain nothing more (3000 tokens at 1000: 5.4 ms against 4.5, two rounds of which the second is nearly empty).
-constexpr int PF_ROWS = 2048;
-// Shorter prompts are one block of the block kernel (64 rows of the 7B shape, eight layers: 1.14 ms); two blocks read the
-// weights twice (77 tokens 1.92 ms, the products' 128-row tiles 1.24).
-constexpr int PF_MIN = LA_MAX_ROWS + 1;
-constexpr int PF_CHUNKS = 32;   // partial sums of squares per row (column chunks of pf_norm_kernel)
-constexpr int PF_PART_ROWS = 4096;  // rows of all slices' products together
-constexpr int PF_MAX_SPLIT = 8; // most slices of a contraction
 constexpr int PF_KEYS = 64;     // keys of a block of the attention
 
 enum PfMode { PF_QKV = 0, PF_PART = 1, PF_GATEUP = 2 };
@@ -652,20 +643,18 @@ static int pf_launch_tile(int tile, const PfGemm &p, hipStream_t s, bool prepare
   }
 }
 
-static_assert(PF_PART_ROWS >= PF_ROWS, "one slice of a whole chunk");
-
 // Tile and number of slices of the contraction by estimated time: whole rounds of the chip's CUs times the k-tiles of a
 // slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  The estimate picks the
 // fastest or within 5 % of it of the tiles that were measured at 77, 129, 200, 300, 400, 512, 700 and 1023 rows.  Only
 // the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
 // for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
-static void pf_choose(const PfGemm &p, int max_split, int cus, int &tile, int &S) {
+static void pf_choose(const PfGemm &p, int max_split, int part_rows, int cus, int &tile, int &S) {
   float best = 0.f;
   tile = -1;
   for (int i = 0; i < PF_N_TILES; ++i)
     for (int k = 1; k <= max_split; ++k) {
       const PfTile &t = PF_TILES[i];
-      if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > PF_PART_ROWS)) break;
+      if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > part_rows)) break;
       const int n = ceil_div(p.RT, t.rows) * ceil_div(p.ntiles - p.t_first, t.cols) * k, round = t.per_cu * cus, rest = n % round;
       float us = (float)(n / round) * t.t_full + (rest == 0 ? 0.f : rest <= cus ? t.t_single : t.t_full);
       us *= (float)ceil_div(p.KT, k);
@@ -699,11 +688,11 @@ static int pf_launch_qkv_few(const PfGemm &p, int row_tiles, hipStream_t s, bool
 }
 
 template <int MODE>
-static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int *S = nullptr) {
+static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int part_rows = 0, int *S = nullptr) {
   ProfScope ps(name, s);
   if (MODE == PF_QKV && p.M > 64 && p.M <= 128 && p.NW == 4) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
   int tile;
-  pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, cus, tile, p.S);
+  pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
   if (S) *S = p.S;
   return pf_launch_tile<MODE>(tile, p, s, false);
 }
@@ -734,50 +723,58 @@ static int pf_launch_attn(const PfBuffers &b, const PfGemm &p, int M, int RT, in
   return LA_OK;
 }
 
-// One allocation for all buffers (eight took 0.4 ms of the first prompt).  They need no clearing: what the products read of
-// rows past the prompt's end only reaches rows past its end.
-static int pf_alloc(la_model *m, PfBuffers &b) {
+// One allocation for all buffers of a set (eight took 0.4 ms of the first prompt).  They need no clearing: what the products
+// read of rows past the prompt's end only reaches rows past its end.  The thread's capture mode is relaxed meanwhile, so that
+// a first prompt may be captured into a graph (its buffers are the model's, not the graph's) and does not end a capture of
+// another thread.  No memory: b stays empty, and that is no error.
+static int pf_alloc(la_model *m, int most, int least, PfBuffers &b) {
   const la_model_desc &d = m->d;
-  const size_t R = PF_ROWS, dm = d.d_model, qd = m->qdim();
-  size_t total = 0;
-  auto place = [&](size_t bytes) {
-    const size_t at = total;
-    total += (bytes + 1023) / 1024 * 1024;
-    return at;
-  };
-  const size_t x = place(R * dm * 4), part = place(PF_PART_ROWS * dm * 4), ss = place(R * PF_CHUNKS * 4), cs = place(R * d.head_dim * 4),
-               A = place(R * dm * 2), Q = place(R * qd * 2), attn = place(R * qd * 2), act = place(R * (size_t)d.d_ffn * 2);
-  for (int i = 0; i < PF_N_TILES; ++i) {
-    int rc = pf_launch_tile<PF_QKV>(i, PfGemm{}, nullptr, true);
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  int rc = LA_OK;
+  for (int i = 0; !rc && i < PF_N_TILES; ++i) {
+    rc = pf_launch_tile<PF_QKV>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_PART>(i, PfGemm{}, nullptr, true);
     if (!rc) rc = pf_launch_tile<PF_GATEUP>(i, PfGemm{}, nullptr, true);
-    if (rc) return rc;
   }
-  for (int i = 5; i <= 8; ++i) {
-    int rc = pf_launch_qkv_few(PfGemm{}, i, nullptr, true);
-    if (rc) return rc;
+  for (int i = 5; !rc && i <= 8; ++i) rc = pf_launch_qkv_few(PfGemm{}, i, nullptr, true);
+  uint8_t *p = nullptr;
+  if (!rc) {
+    const PfLayout l = pf_fit(PfDims{(size_t)d.d_model, (size_t)m->qdim(), (size_t)d.head_dim, (size_t)d.d_ffn}, most, least,
+                              [&](size_t bytes) { return (p = (uint8_t *)dalloc(bytes)) != nullptr; });
+    if (p)
+      b = PfBuffers{p, l.rows, l.part_rows, (float *)(p + l.x), (float *)(p + l.part), (float *)(p + l.ss), (float *)(p + l.cs),
+                    (uint16_t *)(p + l.A), (uint16_t *)(p + l.Q), (uint16_t *)(p + l.attn), (uint16_t *)(p + l.act)};
   }
-  uint8_t *p = (uint8_t *)dalloc(total);
-  LA_REQUIRE(p != nullptr, LA_ENOMEM, "device allocation of the prefill buffers (%zu bytes) failed", total);
-  b = PfBuffers{p, (float *)(p + x), (float *)(p + part), (float *)(p + ss), (float *)(p + cs),
-                (uint16_t *)(p + A), (uint16_t *)(p + Q), (uint16_t *)(p + attn), (uint16_t *)(p + act)};
-  return LA_OK;
+  if (!rc && !p) (void)hipGetLastError();  // (the next launch's check would report the failed allocation)
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return rc;
 }
 
-int mfma_prefill_rows(const la_model *m) { return m->mf && m->mf->use_r && m->embed ? PF_ROWS : 0; }
-int mfma_prefill_min() { return PF_MIN; }
+static PfBuffers &pf_buffers(MfmaModel *f) { return f->pf.base ? f->pf : f->pf_few; }
 
-// One prompt chunk of M <= PF_ROWS tokens at positions L0 .. L0 + M - 1 through every layer (the caller sets the cache
+// *rows: of a chunk of a prompt of n tokens, its buffers allocated; 0: the prompt goes through the block kernel (it is short,
+// the model has no large-M path, or the card has no memory left for the buffers).
+int mfma_prefill_rows(la_model *m, int n, int *rows) {
+  MfmaModel *f = m->mf;
+  *rows = 0;
+  if (!f || !f->use_r || !m->embed || n < PF_MIN) return LA_OK;
+  for (int l = 0; l < m->d.n_layers; ++l) LA_REQUIRE(m->layers[l].set, LA_EINVAL, "layer %d has no weights", l);
+  int rc = LA_OK;
+  if (!f->pf.base && n >= PF_LONG) rc = pf_alloc(m, PF_ROWS, f->pf_few.base ? 2 * PF_LONG : PF_LONG, f->pf);
+  if (!rc && !f->pf.base && !f->pf_few.base) rc = pf_alloc(m, PF_LONG, PF_LONG, f->pf_few);
+  *rows = rc ? 0 : pf_buffers(f).rows;
+  return rc;
+}
+
+// One prompt chunk of M tokens (as many as mfma_prefill_rows says at most) at positions L0 .. L0 + M - 1 through every layer (the caller sets the cache
 // length afterwards).
 int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0, hipStream_t s) {
   MfmaModel *f = m->mf;
   const la_model_desc &d = m->d;
   LA_REQUIRE(f->use_r, LA_EINVAL, "the large-M prompt pass reads the register-streaming kernel's weight layout");
-  if (!f->pf.base) {
-    int rc = pf_alloc(m, f->pf);
-    if (rc) return rc;
-  }
-  PfBuffers &b = f->pf;
+  PfBuffers &b = pf_buffers(f);
+  LA_REQUIRE(M <= b.rows, LA_EINVAL, "%d rows in buffers of %d", M, b.rows);
   const int RT = (M + 63) / 64 * 4, RTr = (M + 15) / 16, half = d.head_dim / 2, f16 = d.dtype == LA_F16;
   {
     ProfScope ps("pf_embed", s);
@@ -832,10 +829,10 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
     if (d.head_dim == 128) rc = f16 ? pf_launch_attn<128, true>(b, p, M, RT, RTr, s) : pf_launch_attn<128, false>(b, p, M, RT, RTr, s);
     else rc = f16 ? pf_launch_attn<64, true>(b, p, M, RT, RTr, s) : pf_launch_attn<64, false>(b, p, M, RT, RTr, s);
     if (rc) return rc;
-    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(1, b.attn), s, "pf_gemm_o", f->n_wgs, &S_o))) return rc;
+    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(1, b.attn), s, "pf_gemm_o", f->n_wgs, b.part_rows, &S_o))) return rc;
     if ((rc = pf_launch_norm(S_o, b.x, b.part, m->layers[l].g_mlp, M, d.d_model, RT, b.ss, b.A, s))) return rc;
     if ((rc = pf_launch_gemm<PF_GATEUP>(gemm_args(2, b.A), s, "pf_gemm_gateup", f->n_wgs))) return rc;
-    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(3, b.act), s, "pf_gemm_down", f->n_wgs, &S_down))) return rc;
+    if ((rc = pf_launch_gemm<PF_PART>(gemm_args(3, b.act), s, "pf_gemm_down", f->n_wgs, b.part_rows, &S_down))) return rc;
   }
   LA_HIP(hipGetLastError());
   return LA_OK;

@@ -1,0 +1,68 @@
+// The large-M prompt pass's decisions that need no GPU: sizes of its buffers.  Plain C++, so that a program without HIP can
+// include it.
+#pragma once
+#include <stddef.h>
+
+#include "la.h"
+
+namespace la {
+
+// Rows of one prompt chunk (buffers are sized for it).  At 2048 rows a 4096-column matrix fills the chip with one slice
+// of the contraction: 2048 tokens, four layers, 2.77 ms against 3.02 in chunks of 1024; 1100 tokens 1.89 against 2.05.  4096
+// rows gain nothing more (3000 tokens at 1000: 5.4 ms against 4.5, two rounds of which the second is nearly empty).
+constexpr int PF_ROWS = 2048;
+// Shorter prompts are one block of the block kernel (64 rows of the 7B shape, eight layers: 1.14 ms); two blocks read the
+// weights twice (77 tokens 1.92 ms, the products' 128-row tiles 1.24).
+constexpr int PF_MIN = LA_MAX_ROWS + 1;
+constexpr int PF_CHUNKS = 32;       // partial sums of squares per row (column chunks of pf_norm_kernel)
+constexpr int PF_PART_ROWS = 4096;  // rows of all slices' products together, at most
+constexpr int PF_MAX_SPLIT = 8;     // most slices of a contraction
+
+// Two sets of buffers: prompts shorter than PF_LONG run in one of PF_LONG rows (26 MB at the 7B shape), so that a program
+// of short prompts does not hold a whole chunk's (212 MB); the first longer prompt gets a set of PF_ROWS rows, or of as many
+// as the card has memory left for, halving down to PF_LONG.
+constexpr int PF_LONG = 128;
+
+struct PfDims {
+  size_t d_model, qdim, head_dim, d_ffn;
+};
+struct PfLayout {
+  int rows = 0, part_rows = 0;  // rows of a chunk; rows of the slices' products together
+  size_t x = 0, part = 0, ss = 0, cs = 0, A = 0, Q = 0, attn = 0, act = 0, total = 0;  // byte offsets in the one allocation, its size
+};
+
+inline PfLayout pf_layout(const PfDims &d, int rows) {
+  PfLayout l;
+  l.rows = rows;
+  l.part_rows = PF_MAX_SPLIT * rows < PF_PART_ROWS ? PF_MAX_SPLIT * rows : PF_PART_ROWS;
+  const size_t R = (size_t)rows;
+  auto place = [&](size_t bytes) {
+    const size_t at = l.total;
+    l.total += (bytes + 1023) / 1024 * 1024;
+    return at;
+  };
+  l.x = place(R * d.d_model * 4);
+  l.part = place((size_t)l.part_rows * d.d_model * 4);
+  l.ss = place(R * PF_CHUNKS * 4);
+  l.cs = place(R * d.head_dim * 4);
+  l.A = place(R * d.d_model * 2);
+  l.Q = place(R * d.qdim * 2);
+  l.attn = place(R * d.qdim * 2);
+  l.act = place(R * d.d_ffn * 2);
+  return l;
+}
+
+// The largest set of `most` rows, halved down to `least`, that alloc(bytes) succeeds for; rows = 0: none.
+template <typename Alloc>
+inline PfLayout pf_fit(const PfDims &d, int most, int least, Alloc alloc) {
+  for (int rows = most; rows >= least; rows /= 2) {
+    const PfLayout l = pf_layout(d, rows);
+    if (alloc(l.total)) return l;
+  }
+  return PfLayout{};
+}
+
+static_assert(PF_PART_ROWS >= PF_ROWS, "one slice of a whole chunk");
+static_assert(PF_ROWS % PF_LONG == 0 && PF_MIN <= PF_LONG, "chunks halve down to the smaller set");
+
+}  // namespace la

@@ -1,0 +1,63 @@
+"""The prompt pass's host decisions (la_prefill_plan.h, plain C++): a small program prints them, checked here without a GPU."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_16760_amd", "csrc")
+SHAPES = {"7b": (4096, 4096, 128, 14336), "12b": (5120, 4096, 128, 14336), "small64": (384, 384, 64, 1056)}  # d, Hq dh, dh, F
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include "la_prefill_plan.h"
+using namespace la;
+static void show(const PfLayout &l) {
+  printf("%d %d %zu %zu %zu %zu %zu %zu %zu %zu %zu\n", l.rows, l.part_rows, l.x, l.part, l.ss, l.cs, l.A, l.Q, l.attn, l.act, l.total);
+}
+int main(int, char **v) {
+  const auto num = [&](int i) { return (size_t)atoll(v[i]); };
+  if (!strcmp(v[1], "layout")) show(pf_layout(PfDims{num(2), num(3), num(4), num(5)}, (int)num(6)));
+  if (!strcmp(v[1], "fit"))
+    show(pf_fit(PfDims{num(2), num(3), num(4), num(5)}, PF_ROWS, PF_LONG, [&](size_t bytes) { return bytes <= num(6); }));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(PROGRAM)
+    exe = str(d / "plan")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-I", os.path.join(ROOT, "include"), str(d / "plan.cpp"), "-o", exe], check=True)
+    return lambda *a: [[int(x) for x in line.split()] for line in
+                       subprocess.run([exe, *map(str, a)], check=True, capture_output=True, text=True).stdout.splitlines()]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("rows", [128, 256, 512, 1024, 2048])
+def test_buffers_hold_every_chunk_and_do_not_overlap(plan, shape, rows):
+    d, qd, dh, F = SHAPES[shape]
+    r, part_rows, *at, total = plan("layout", d, qd, dh, F, rows)[0]
+    assert r == rows and part_rows >= rows
+    sizes = [4 * rows * d, 4 * part_rows * d, 4 * rows * 32, 4 * rows * dh, 2 * rows * d, 2 * rows * qd, 2 * rows * qd, 2 * rows * F]
+    for a, size, end in zip(at, sizes, at[1:] + [total]):
+        assert a % 1024 == 0 and a + size <= end
+
+
+def test_a_short_prompt_takes_a_short_prompts_buffers(plan):
+    total = plan("layout", *SHAPES["7b"], 128)[0][-1]
+    assert total <= 128 * (4096 * 38 + 14336 * 2 + 4096 * 4 + 4 * 32 + 4 * 128) + 8 * 1024
+    assert total < 27e6 < 200e6 < plan("layout", *SHAPES["7b"], 2048)[0][-1]
+
+
+def test_buffers_shrink_to_the_memory_that_is_left(plan):
+    sizes = {rows: plan("layout", *SHAPES["7b"], rows)[0][-1] for rows in (128, 256, 512, 1024, 2048)}
+    for rows, size in sizes.items():
+        assert plan("fit", *SHAPES["7b"], size)[0][0] == rows
+        assert plan("fit", *SHAPES["7b"], size - 1)[0][0] == (rows // 2 if rows > 128 else 0)
+    # what a chunk of 1024 tokens once took (residual stream, operands, no slices' products) is enough for a prompt
+    once = 1024 * (4096 * 8 + 14336 * 2 + 4096 * 4)
+    assert plan("fit", *SHAPES["7b"], once)[0][0] >= 256
