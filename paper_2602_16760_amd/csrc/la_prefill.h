@@ -282,12 +282,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void pf_tile_kernel(PfGemm p) {
   pf_tile_body<MODE, WM, WN, NTW, NS>(p, (LDS_AS uint8_t *)pf_lds);
 }
 
-// The QKV product for 65 to 128 rows, which has 96 of the smallest tiles for 256 CUs and an epilogue that cannot take slices of
-// the contraction: a workgroup takes two column tiles and all rows, and its four waves share the contraction (wave w the
+// The QKV product for 65 to 128 rows where it has few columns (pf_qkv_few; 96 of the smallest tiles for 256 CUs at the 7B shape)
+// and an epilogue that cannot take slices of the contraction: a workgroup takes two column tiles and all rows, and its four waves share the contraction (wave w the
 // k-tiles w, w + 4, ..., which is how the weights lie); each streams its fragments into registers, NS k-tiles ahead, with
 // no barrier until the four sums are added.  MT: row tiles that hold rows (padding is neither loaded nor multiplied).  Bound by
 // the activations' way in, which every workgroup repeats: 77 rows of the 7B shape 37.5 -> 23.8 us, 120 rows 38.7 -> 28.0; the
-// wider matrices are faster in tiles (gate/up at 77 rows 57.8 us, this way 75.7).
+// gate/up product is faster in tiles (77 rows 57.8 us, this way 75.7).
 template <int MT, int NS>
 __device__ __forceinline__ void pf_qkv_few_body(const PfGemm &p, LDS_AS uint8_t *lds) {
   constexpr int CT = 2;
@@ -690,7 +690,8 @@ static int pf_launch_qkv_few(const PfGemm &p, int row_tiles, hipStream_t s, bool
 template <int MODE>
 static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int part_rows = 0, int *S = nullptr) {
   ProfScope ps(name, s);
-  if (MODE == PF_QKV && p.M > 64 && p.M <= 128 && p.NW == 4) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
+  static_assert(R_NW == 4, "pf_qkv_few_kernel's waves take the k-tiles as they lie for four MFMA waves");
+  if (MODE == PF_QKV && pf_qkv_few(p.M, p.ntiles - p.t_first, cus)) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
   int tile;
   pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
   if (S) *S = p.S;

@@ -1,4 +1,4 @@
-// The large-M prompt pass's decisions that need no GPU: sizes of its buffers.  Plain C++, so that a program without HIP can
+// The large-M prompt pass's decisions that need no GPU: sizes of its buffers, which kernel a product takes.  Plain C++, so that a program without HIP can
 // include it.
 #pragma once
 #include <stddef.h>
@@ -61,6 +61,13 @@ inline PfLayout pf_fit(const PfDims &d, int most, int least, Alloc alloc) {
   }
   return PfLayout{};
 }
+
+// The QKV product of M rows and n_tiles column tiles by the kernel without tiles (pf_qkv_few_kernel: two column tiles and all rows a
+// workgroup): up to 128 rows, while its workgroups are one round of the chip.  us, without / with tiles, at 65 and 128 rows:
+// 4096 x 6144 (192 workgroups) 27 / 39, 30 / 39; 4096 x 8192 (256) 29 / 38, 32 / 40; beyond one round every workgroup's own
+// pass over the activations costs more than the tiles: 4096 x 12288 (384) 46 / 42, 52 / 43; 8192 x 10240 (320) 78 / 67, 93 / 67.
+// The last layer's 2048 columns of K and V: 16 / 37, 21 / 38.
+inline bool pf_qkv_few(int M, int n_tiles, int cus) { return M > LA_MAX_ROWS && M <= 128 && (n_tiles + 1) / 2 <= cus; }
 
 static_assert(PF_PART_ROWS >= PF_ROWS, "one slice of a whole chunk");
 static_assert(PF_ROWS % PF_LONG == 0 && PF_MIN <= PF_LONG, "chunks halve down to the smaller set");

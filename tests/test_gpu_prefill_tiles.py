@@ -70,12 +70,14 @@ def _reference(sh, embed, tok, L0, old, dtype):
     ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (257, 0), (300, 31), (700, 5), (1023, 0), (1100, 32), (2200, 3)]),
     ("mistral7b", "f16", [(193, 33), (1025, 0)]),
     ("nemo12b", "bf16", [(400, 64), (1024, 0)]),
+    ("mistral7b/32 kv heads", "bf16", [(65, 0), (128, 9)]),  # (12288 columns of QKV: more than one round of the few-row product)
     ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (2049, 100)]),
 ])
 def test_prompt_pass_sizes(name, dtype, cases):
     import torch
     from paper_2602_16760_amd import binding as B
-    sh = replace(synth.SHAPES[name], n_layers=2, dtype=dtype, vocab=512)
+    name, _, wide = name.partition("/")
+    sh = replace(synth.SHAPES[name], n_layers=2, dtype=dtype, vocab=512, **({"n_kv_heads": 32} if wide else {}))
     td = torch.bfloat16 if dtype == "bf16" else torch.float16
     embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, td)
     model = B.la_init_model(sh, embed)

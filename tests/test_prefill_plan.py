@@ -22,6 +22,7 @@ int main(int, char **v) {
   if (!strcmp(v[1], "layout")) show(pf_layout(PfDims{num(2), num(3), num(4), num(5)}, (int)num(6)));
   if (!strcmp(v[1], "fit"))
     show(pf_fit(PfDims{num(2), num(3), num(4), num(5)}, PF_ROWS, PF_LONG, [&](size_t bytes) { return bytes <= num(6); }));
+  if (!strcmp(v[1], "few")) printf("%d\n", pf_qkv_few((int)num(2), (int)num(3), (int)num(4)) ? 1 : 0);
 }
 """
 
@@ -61,3 +62,12 @@ def test_buffers_shrink_to_the_memory_that_is_left(plan):
     # what a chunk of 1024 tokens once took (residual stream, operands, no slices' products) is enough for a prompt
     once = 1024 * (4096 * 8 + 14336 * 2 + 4096 * 4)
     assert plan("fit", *SHAPES["7b"], once)[0][0] >= 256
+
+
+@pytest.mark.parametrize("rows,tiles,few", [
+    (64, 384, 0), (65, 384, 1), (128, 384, 1), (129, 384, 0),             # 6144 columns
+    (65, 512, 1), (128, 512, 1), (65, 513, 0), (65, 640, 0), (77, 768, 0),  # one round of 256 workgroups, and beyond it
+    (100, 128, 1), (100, 1, 1),                                             # K and V of the last layer
+])
+def test_few_row_products_go_without_tiles_while_they_are_one_round(plan, rows, tiles, few):
+    assert plan("few", rows, tiles, 256) == [[few]]
