@@ -90,47 +90,77 @@ __device__ __forceinline__ int pool_lookup(const PoolView &p, int key, int32_t *
   return __popcll(__ballot(sv != 0u));
 }
 
+// LDS words written by one lane of the (single remaining) wave are read by others: a wave's LDS operations are in order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Inserts (win[c] -> tuple of column c) for c = 0 .. W - 1 in that order: a tuple that is present gets a new stamp, else a
-// free slot is taken, else the one with the smallest stamp.  A wave takes as many columns at once as it has lanes for their
-// slots, if their keys differ (lane: slot s of column c); columns that share a key go one at a time.
-__device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *win, const int32_t *newest, int W, int lane) {
+// free slot is taken, else the one with the smallest stamp.  Keys do not meet, so a wave takes as many of them at once as it has
+// lanes for their slots (lane: slot s of a key), and each key's columns in order, its slots in registers and LDS meanwhile: a
+// column that shares its key with others costs no trip to memory.  (One by one through memory, 31 columns of one key with 32
+// slots made an accept 101 us, one thread had taken 52; now 19.  15 columns, 15
+// slots, five keys: 10 us, one thread 43.)
+struct HarvestLds {
+  int32_t lead[LA_MAX_ROWS], next[LA_MAX_ROWS];  // first column of the k-th key; the next column with the same key
+  int32_t tok[256];                              // tuples of the slots at hand (224 words at most: W = 7, N = 5, G = 8)
+};
+__device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *win, const int32_t *newest, int W, HarvestLds &h, int lane) {
   const int G = p.G, n1 = p.N - 1;
   const uint32_t now = *p.counter;
   if (lane == 0) *p.counter = now + (uint32_t)W;
   if (G == 0) return;
-  const int per = 64 / G;
-  for (int c0 = 0; c0 < W;) {
-    int n = W - c0 < per ? W - c0 : per;
-    // the first column of the batch whose key an earlier one of the batch has: the batch ends in front of it
-    bool again = false;
-    if (lane > 0 && lane < n)
-      for (int i = 0; i < lane; ++i) again = again || win[c0 + i] == win[c0 + lane];
-    const uint64_t rep = __ballot(again);
-    if (rep) n = __ffsll((long long)rep) - 1;
-    const int col = lane / G, s = lane - col * G, c = c0 + col;
-    const int key = col < n ? win[c] : -1;
-    const bool in = col < n && key >= 0 && key < p.vocab;
-    const size_t slot = in ? (size_t)key * G + s : 0;
-    const uint32_t sv = in ? p.stamp[slot] : 0u;
-    bool same = in && sv != 0u;
-    if (in)
-      for (int j = 0; j < n1; ++j) same = (p.toks[slot * n1 + j] == (j + 1 < n1 ? win[(j + 1) * W + c] : newest[c])) && same;
-    const uint64_t mine = ((G < 64 ? 1ull << G : 0ull) - 1ull) << (col * G < 64 ? col * G : 0);
-    const uint64_t hit = __ballot(same) & mine, empty = __ballot(in && sv == 0u) & mine;
-    bool oldest = true;
-    for (int i = 0; i < G; ++i) {
-      const uint32_t o = (uint32_t)__shfl((int)sv, col * G + i < 64 ? col * G + i : 63, 64);
-      oldest = oldest && (i == s || o > sv);
-    }
-    const bool take = in && (hit ? same : empty ? lane == __ffsll((long long)empty) - 1 : oldest);
-    if (take) {
-      p.stamp[slot] = now + (uint32_t)c + 1u;
-      if (!hit)
-        for (int j = 0; j < n1; ++j) p.toks[slot * n1 + j] = j + 1 < n1 ? win[(j + 1) * W + c] : newest[c];
-    }
-    __threadfence();  // (the next batch, and the lookup, read what this one stored)
-    c0 += n;
+  const int my_key = lane < W ? win[lane] : -1;
+  bool first = my_key >= 0 && my_key < p.vocab;
+  int next = W;
+  for (int c = W - 1; c >= 0; --c) {
+    const bool same = __builtin_amdgcn_readlane(my_key, c) == my_key;
+    if (same && c < lane) first = false;
+    if (same && c > lane) next = c;
   }
+  h.next[lane] = next;
+  const uint64_t firsts = __ballot(first);
+  if (first) h.lead[__popcll(firsts & ((1ull << lane) - 1ull))] = lane;
+  wave_sync();
+  const int n_keys = __popcll(firsts), per = 64 / G, g = lane / G, s = lane - g * G;
+  const uint64_t mine = ((1ull << G) - 1ull) << (g * G < 64 ? g * G : 0);  // (G < 64)
+  for (int k0 = 0; k0 < n_keys; k0 += per) {
+    const bool in = g < per && k0 + g < n_keys;
+    int c = in ? h.lead[k0 + g] : W;
+    const size_t slot = in ? (size_t)win[c] * G + s : 0;
+    const uint32_t stamp0 = in ? p.stamp[slot] : 0u;
+    uint32_t sv = stamp0;
+    int32_t *tok = h.tok + (in ? lane * n1 : 0);
+    if (in)
+      for (int j = 0; j < n1; ++j) tok[j] = p.toks[slot * n1 + j];
+    bool replaced = false;
+    while (__any(c < W)) {
+      const bool on = c < W;
+      bool same = on && sv != 0u;
+      if (on)
+        for (int j = 0; j < n1; ++j) same = (tok[j] == (j + 1 < n1 ? win[(j + 1) * W + c] : newest[c])) && same;
+      const uint64_t hit = __ballot(same) & mine, empty = __ballot(on && sv == 0u) & mine;
+      bool oldest = true;
+      if (__any(on && !hit && !empty))
+        for (int i = 0; i < G; ++i) {
+          const uint32_t o = (uint32_t)__shfl((int)sv, g * G + i < 64 ? g * G + i : 63, 64);
+          oldest = oldest && (i == s || o > sv);
+        }
+      if (on && (hit ? same : empty ? lane == __ffsll((long long)empty) - 1 : oldest)) {
+        sv = now + (uint32_t)c + 1u;
+        if (!hit) {
+          for (int j = 0; j < n1; ++j) tok[j] = j + 1 < n1 ? win[(j + 1) * W + c] : newest[c];
+          replaced = true;
+        }
+      }
+      if (on) c = h.next[c];
+    }
+    if (sv != stamp0) p.stamp[slot] = sv;
+    if (replaced)
+      for (int j = 0; j < n1; ++j) p.toks[slot * n1 + j] = tok[j];
+  }
+  __threadfence();  // (the lookup reads what this stored)
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
@@ -208,12 +238,6 @@ __global__ __launch_bounds__(64) void state_init_kernel(PoolView p, la_step_stat
   }
 }
 
-// LDS words written by one lane of the (single remaining) wave are read by others: a wave's LDS operations are in order.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The accept phase in one launch: a workgroup per layer and verification row.  Every workgroup verifies for itself (a candidate
 // per lane), those whose row is accepted move it in their layer (cache relocation: the rows of candidate best_k go from block
 // rows v(k, j) to cache rows L0 + j, j = 1 .. e - 1), and the one that is through last -- all others have read the state by
@@ -227,6 +251,7 @@ __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *
                                                      int32_t *kv_L, const int32_t *err, T *K, T *V, size_t layer_elems, int Hkv, int dh, int v_blocked,
                                                      int max_len) {
   __shared__ int32_t id[LA_MAX_ROWS], win[LA_MAX_ROWS], cand[LA_MAX_ROWS], newest[LA_MAX_ROWS];
+  __shared__ HarvestLds harvest;
   __shared__ int is_last;
   const int lane = threadIdx.x & 63, n1 = N - 1, rows = 1 + (W + G) * n1;
   if (threadIdx.x < 64) {
@@ -285,7 +310,7 @@ __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *
   if (N >= 2) {
     if (lane < W) newest[lane] = id[la_row_index(W, N - 2, lane)];
     wave_sync();
-    pool_harvest(p, win, newest, W, lane);
+    pool_harvest(p, win, newest, W, harvest, lane);
     const int up = lane + W < W * n1 ? win[lane + W] : lane < W * n1 ? newest[lane - W * (n1 - 1)] : 0;
     wave_sync();
     if (lane < W * n1) win[lane] = st->win[lane] = up;

@@ -15,8 +15,11 @@ pytestmark = pytest.mark.gpu
     (5, 4, 5, 32, 3, 600),      # three keys: columns share keys in every step, all keys full
     (7, 4, 7, 43, 1, 300),      # one token throughout: one tuple, seen 297 times
     (7, 4, 7, 64, 40, 1500),    # keys spread over several stretches of 256 positions
-    (31, 2, 32, 64, 12, 257),   # 32 slots per key: two columns at a time
-    (1, 2, 62, 64, 90, 2000),   # 62 slots: one column at a time
+    (31, 2, 32, 64, 12, 257),   # 32 slots per key: two keys at a time
+    (1, 2, 62, 64, 90, 2000),   # 62 slots: one key at a time
+    (31, 2, 32, 64, 2, 100),    # all columns on one or two keys of many slots
+    (15, 2, 15, 31, 40, 900),   # full keys, some shared: the oldest slot is looked for
+    (8, 5, 7, 61, 3, 200),      # most words of tuples at hand
     (10, 7, 0, 64, 5, 50),      # no pool
     (0, 3, 4, 16, 6, 70),       # no window
     (9, 8, 0, 64, 5, 4),        # prompt shorter than an n-gram
