@@ -606,18 +606,6 @@ __global__ __launch_bounds__(256) void pf_embed_kernel(const uint16_t *E, const 
 }
 
 // ---- host side ----------------------------------------------------------------------------------------
-// The tiles pf_choose picks from, and what a k-tile of them costs: of the two smallest, two workgroups fit a CU.
-struct PfTile {
-  int rows, cols;         // in 16 x 16 tiles
-  int per_cu;
-  float t_full, t_single;  // us per k-tile of a round that fills the chip, and of one with a workgroup per CU at most
-};
-// (from the products of the 7B shape at 77 .. 1023 rows, launch overhead included)
-constexpr PfTile PF_TILES[] = {
-    {16, 14, 1, 0.85f, 0.85f}, {16, 10, 1, 0.66f, 0.66f}, {16, 8, 1, 0.57f, 0.57f}, {8, 12, 1, 0.50f, 0.50f}, {8, 8, 2, 0.70f, 0.45f}, {8, 4, 2, 0.52f, 0.30f},
-};
-constexpr int PF_N_TILES = 6;
-
 template <int MODE, int WM, int WN, int NTW, int NS>
 static int pf_launch_tile(const PfGemm &p, hipStream_t s, bool prepare) {
   constexpr int bytes = NS * (4 * WM + WN * NTW) * 1024 + WM * 256;
@@ -641,30 +629,6 @@ static int pf_launch_tile(int tile, const PfGemm &p, hipStream_t s, bool prepare
   case 4: return pf_launch_tile<MODE, 2, 2, 4, 4>(p, s, prepare);
   default: return pf_launch_tile<MODE, 2, 2, 2, 6>(p, s, prepare);
   }
-}
-
-// Tile and number of slices of the contraction by estimated time: whole rounds of the chip's CUs times the k-tiles of a
-// slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  The estimate picks the
-// fastest or within 5 % of it of the tiles that were measured at 77, 129, 200, 300, 400, 512, 700 and 1023 rows.  Only
-// the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
-// for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
-static void pf_choose(const PfGemm &p, int max_split, int part_rows, int cus, int &tile, int &S) {
-  float best = 0.f;
-  tile = -1;
-  for (int i = 0; i < PF_N_TILES; ++i)
-    for (int k = 1; k <= max_split; ++k) {
-      const PfTile &t = PF_TILES[i];
-      if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > part_rows)) break;
-      const int n = ceil_div(p.RT, t.rows) * ceil_div(p.ntiles - p.t_first, t.cols) * k, round = t.per_cu * cus, rest = n % round;
-      float us = (float)(n / round) * t.t_full + (rest == 0 ? 0.f : rest <= cus ? t.t_single : t.t_full);
-      us *= (float)ceil_div(p.KT, k);
-      if (max_split > 1) us += (float)k * (float)p.M * (float)p.d * 8.f / 4.5e6f;
-      if (tile < 0 || us < best) {
-        best = us;
-        tile = i;
-        S = k;
-      }
-    }
 }
 
 template <int MT, int NS>
@@ -693,7 +657,7 @@ static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, in
   static_assert(R_NW == 4, "pf_qkv_few_kernel's waves take the k-tiles as they lie for four MFMA waves");
   if (MODE == PF_QKV && pf_qkv_few(p.M, p.ntiles - p.t_first, cus)) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
   int tile;
-  pf_choose(p, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
+  pf_choose(PfProduct{p.RT, p.M, p.KT, p.ntiles - p.t_first, p.d}, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
   if (S) *S = p.S;
   return pf_launch_tile<MODE>(tile, p, s, false);
 }

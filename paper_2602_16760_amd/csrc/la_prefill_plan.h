@@ -62,6 +62,50 @@ inline PfLayout pf_fit(const PfDims &d, int most, int least, Alloc alloc) {
   return PfLayout{};
 }
 
+// The tiles pf_choose picks from (pf_launch_tile has their kernels), and what a k-tile of them costs: of the two smallest, two
+// workgroups fit a CU.
+struct PfTile {
+  int rows, cols;         // in 16 x 16 tiles
+  int per_cu;
+  float t_full, t_single;  // us per k-tile of a round that fills the chip, and of one with a workgroup per CU at most
+};
+// (from the products of the 7B shape at 77 .. 1023 rows, launch overhead included)
+constexpr PfTile PF_TILES[] = {
+    {16, 14, 1, 0.85f, 0.85f}, {16, 10, 1, 0.66f, 0.66f}, {16, 8, 1, 0.57f, 0.57f}, {8, 12, 1, 0.50f, 0.50f}, {8, 8, 2, 0.70f, 0.45f}, {8, 4, 2, 0.52f, 0.30f},
+};
+constexpr int PF_N_TILES = 6;
+
+struct PfProduct {
+  int RT, M, KT, n_tiles, d;  // row tiles of the buffers, rows, k-tiles, column tiles wanted, row length of the products
+};
+// Tile and number of slices of the contraction by estimated time: whole rounds of the chip's CUs times the k-tiles of a
+// slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  Against every tile and
+// split at 90 .. 2048 rows of the 7B and 12B shapes and a 2048-wide one, 95 of 129 products are within 5 % of the fastest.  The
+// chip is taken for one pool of CUs, but the column groups are dealt to eight XCDs: where an XCD's share is more than its 32
+// CUs hold, there is a round that the estimate does not see (7B, 700 rows, three slices: down 166 us against 109, O 62 against
+// 38; 7B, 1300 rows: down 303 against 191; 12B, 300 rows: down 121 against 75).  Only
+// the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
+// for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
+inline void pf_choose(const PfProduct &p, int max_split, int part_rows, int cus, int &tile, int &S) {
+  auto up = [](int a, int b) { return (a + b - 1) / b; };
+  float best = 0.f;
+  tile = -1;
+  for (int i = 0; i < PF_N_TILES; ++i)
+    for (int k = 1; k <= max_split; ++k) {
+      const PfTile &t = PF_TILES[i];
+      if (k > 1 && (p.KT / k < 4 || (long long)k * p.M > part_rows)) break;
+      const int n = up(p.RT, t.rows) * up(p.n_tiles, t.cols) * k, round = t.per_cu * cus, rest = n % round;
+      float us = (float)(n / round) * t.t_full + (rest == 0 ? 0.f : rest <= cus ? t.t_single : t.t_full);
+      us *= (float)up(p.KT, k);
+      if (max_split > 1) us += (float)k * (float)p.M * (float)p.d * 8.f / 4.5e6f;
+      if (tile < 0 || us < best) {
+        best = us;
+        tile = i;
+        S = k;
+      }
+    }
+}
+
 // The QKV product of M rows and n_tiles column tiles by the kernel without tiles (pf_qkv_few_kernel: two column tiles and all rows a
 // workgroup): up to 128 rows, while its workgroups are one round of the chip.  us, without / with tiles, at 65 and 128 rows:
 // 4096 x 6144 (192 workgroups) 27 / 39, 30 / 39; 4096 x 8192 (256) 29 / 38, 32 / 40; beyond one round every workgroup's own

@@ -27,6 +27,19 @@ def prefill_both(shape, eng, okv, L, seed=0):
     B.la_kv_set_len(eng.kv, L)
 
 
+def launch_names(call):
+    """The kernels that a call launches, by their names in the library's own launch record."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    B.la_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        B.la_profile_enable(False)
+    return set(B.la_profile_read())
+
+
 def row_rel_err(got, want):
     """Per row: max |got - want| / max |want| (the parity metric for hidden states)."""
     got = np.asarray(got, dtype=np.float64)

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_util import gpu_engine, oracle_model, row_rel_err
+from gpu_util import gpu_engine, launch_names, oracle_model, row_rel_err
 from oracle import transformer as otf
 
 pytestmark = pytest.mark.gpu
@@ -34,10 +34,17 @@ def test_large_prompt_pass_matches_oracle_and_the_chunked_pass(name, n_tok):
     small = gpu_engine(shape, n_tok + 64, seed=6)
     try:
         td = B.to_device(np.asarray(toks, dtype=np.int32))
-        B.la_prefill(big.model, big.kv, td, 0)                       # 128 tokens or more: the large-M pass
+        # more than 64 tokens: the large-M pass; pieces of 50 (starts that are no multiples of 32): the block kernel
+        ran = launch_names(lambda: B.la_prefill(big.model, big.kv, td, 0))
+        assert "pf_gemm_qkv" in ran and "layer_stack" not in ran
         assert B.la_kv_get_len(big.kv) == n_tok
-        for s in range(0, n_tok, 100):                               # pieces below 128 tokens: the block kernel
-            B.la_prefill(small.model, small.kv, td[s:s + 100].contiguous(), s)
+
+        def pieces():
+            for s in range(0, n_tok, 50):
+                B.la_prefill(small.model, small.kv, td[s:s + 50].contiguous(), s)
+
+        ran = launch_names(pieces)
+        assert "layer_stack" in ran and not any(name.startswith("pf_") for name in ran)
         assert B.la_kv_get_len(small.kv) == n_tok
         torch.cuda.synchronize()
         tol = TOL[shape.dtype]

@@ -7,8 +7,19 @@ from dataclasses import replace
 import pytest
 
 import synth
+from gpu_util import launch_names
 
 pytestmark = pytest.mark.gpu
+# (shape, dtype, [(tokens, start)]).  Every kernel that the pass picks from for these shapes between 65 and 2200 tokens runs at
+# one of these sizes: test_prefill_plan.py asserts it, without a GPU.
+SIZES = [
+    ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (180, 3), (257, 0), (300, 31), (600, 0), (700, 5), (1023, 0),
+                           (1100, 32), (1300, 0), (1600, 0), (2200, 3)]),
+    ("mistral7b", "f16", [(193, 33), (1025, 0)]),
+    ("nemo12b", "bf16", [(105, 0), (400, 64), (1024, 0)]),
+    ("mistral7b/32 kv heads", "bf16", [(65, 0), (128, 9)]),  # (12288 columns of QKV: more than one round of the few-row product)
+    ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (2049, 100)]),
+]
 # max |got - want| over max |want| of a layer's cache rows: the bars of the prompt-pass parity tests (one storage
 # rounding of the rows on top of the hidden-state error of one layer)
 TOL = {"bf16": 2e-2, "f16": 2e-3}
@@ -66,18 +77,16 @@ def _reference(sh, embed, tok, L0, old, dtype):
     return out
 
 
-@pytest.mark.parametrize("name,dtype,cases", [
-    ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (257, 0), (300, 31), (700, 5), (1023, 0), (1100, 32), (2200, 3)]),
-    ("mistral7b", "f16", [(193, 33), (1025, 0)]),
-    ("nemo12b", "bf16", [(400, 64), (1024, 0)]),
-    ("mistral7b/32 kv heads", "bf16", [(65, 0), (128, 9)]),  # (12288 columns of QKV: more than one round of the few-row product)
-    ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (2049, 100)]),
-])
+def shape_of(name, dtype):
+    name, _, wide = name.partition("/")
+    return replace(synth.SHAPES[name], n_layers=2, dtype=dtype, vocab=512, **({"n_kv_heads": 32} if wide else {}))
+
+
+@pytest.mark.parametrize("name,dtype,cases", SIZES)
 def test_prompt_pass_sizes(name, dtype, cases):
     import torch
     from paper_2602_16760_amd import binding as B
-    name, _, wide = name.partition("/")
-    sh = replace(synth.SHAPES[name], n_layers=2, dtype=dtype, vocab=512, **({"n_kv_heads": 32} if wide else {}))
+    sh = shape_of(name, dtype)
     td = torch.bfloat16 if dtype == "bf16" else torch.float16
     embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, td)
     model = B.la_init_model(sh, embed)
@@ -110,29 +119,40 @@ def test_prompt_pass_sizes(name, dtype, cases):
         B.la_free_model(model)
 
 
-def test_prompt_pass_agrees_with_the_block_kernel():
-    """One call of 300 tokens (the large-M pass) against pieces of 64, the largest that go through the block kernel:
-    each is within TOL of the same float64 rows, so they are within twice that of each other."""
+@pytest.mark.parametrize("name,dtype,piece", [("mistral7b", "bf16", 64), ("mistral7b", "bf16", 61), ("mistral7b", "f16", 50), ("small64_bf16", "bf16", 45)])
+def test_prompt_pass_agrees_with_the_block_kernel(name, dtype, piece):
+    """One call of 300 tokens (the large-M pass) against pieces that go through the block kernel, at starts inside and on the
+    edges of key blocks.  The two add in another order: a stored element moves by one step of its type where the sums fall
+    on either side of a rounding, at most 2^-7 (bf16) or 2^-10 (f16) of the largest one, and the second layer's inputs by what
+    such steps do to the first one's output; as much again is allowed for that."""
     import torch
     from paper_2602_16760_amd import binding as B
-    sh = replace(synth.SHAPES["mistral7b"], n_layers=2, vocab=512)
-    embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, torch.bfloat16)
+    sh = shape_of(name, dtype)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    bar = 2.0 ** (-6 if dtype == "bf16" else -9)
+    embed = _normal("embed", (sh.vocab, sh.d_model), 1.0, td)
     model = B.la_init_model(sh, embed)
     kvs = [B.la_kv_alloc(model, 300) for _ in range(2)]
     try:
         for l in range(sh.n_layers):
-            B.la_model_set_layer(model, l, _layer(sh, l, torch.bfloat16))
+            B.la_model_set_layer(model, l, _layer(sh, l, td))
             torch.cuda.synchronize()
         tok = torch.arange(300, device="cuda", dtype=torch.int32) * 7 % sh.vocab
-        B.la_prefill(model, kvs[0], tok, 0)
-        for s in range(0, 300, 64):
-            B.la_prefill(model, kvs[1], tok[s:s + 64].contiguous(), s)
+
+        def pieces():
+            for s in range(0, 300, piece):
+                B.la_prefill(model, kvs[1], tok[s:s + piece].contiguous(), s)
+
+        assert "layer_stack" not in launch_names(lambda: B.la_prefill(model, kvs[0], tok, 0))
+        assert not any(n.startswith("pf_") for n in launch_names(pieces))
         for l in range(sh.n_layers):
-            rows = [[torch.empty((300, sh.n_kv_heads, sh.head_dim), dtype=torch.bfloat16, device="cuda") for _ in "kv"] for _ in kvs]
+            rows = [[torch.empty((300, sh.n_kv_heads, sh.head_dim), dtype=td, device="cuda") for _ in "kv"] for _ in kvs]
             for kv, r in zip(kvs, rows):
                 B.la_kv_read(kv, l, 0, 300, *r)
-            for a, b in zip(*rows):
-                assert ((a.double() - b.double()).abs().max() / b.double().abs().max()).item() <= 2 * TOL["bf16"]
+            for c, a, b in zip("KV", *rows):
+                e = ((a.double() - b.double()).abs().max() / b.double().abs().max()).item()
+                print(f"{name} {dtype} pieces of {piece}, layer {l} {c}: {e:.2e}", flush=True)
+                assert e <= bar
     finally:
         torch.cuda.synchronize()
         for kv in kvs:

@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_prefill_tiles import SIZES, shape_of
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_16760_amd", "csrc")
 SHAPES = {"7b": (4096, 4096, 128, 14336), "12b": (5120, 4096, 128, 14336), "small64": (384, 384, 64, 1056)}  # d, Hq dh, dh, F
@@ -12,6 +14,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include "la_prefill_plan.h"
 using namespace la;
 static void show(const PfLayout &l) {
@@ -22,6 +25,27 @@ int main(int, char **v) {
   if (!strcmp(v[1], "layout")) show(pf_layout(PfDims{num(2), num(3), num(4), num(5)}, (int)num(6)));
   if (!strcmp(v[1], "fit"))
     show(pf_fit(PfDims{num(2), num(3), num(4), num(5)}, PF_ROWS, PF_LONG, [&](size_t bytes) { return bytes <= num(6); }));
+  if (!strcmp(v[1], "routes")) {  // the products of every layer, then of the last one (its K and V columns): prompt lengths v[6] .. v[7]
+    const int d = (int)num(2), qd = (int)num(3), kvd = (int)num(4), F = (int)num(5);
+    for (int n = (int)num(6); n <= (int)num(7); ++n) {
+      const int rows = n < PF_LONG ? PF_LONG : PF_ROWS, part_rows = pf_layout(PfDims{(size_t)d, (size_t)qd, 128, (size_t)F}, rows).part_rows;
+      for (int done = 0; done < n; done += rows) {
+        const int M = n - done < rows ? n - done : rows, RT = (M + 63) / 64 * 4;
+        int tile = 0, S = 0;
+        for (int cols : {qd + 2 * kvd, 2 * kvd}) {
+          pf_choose(PfProduct{RT, M, d / 32, cols / 16, d}, 1, part_rows, 256, tile, S);
+          if (pf_qkv_few(M, cols / 16, 256)) printf("0 %d %d %d\n", n, 100 + (M + 15) / 16, 1);
+          else printf("0 %d %d %d\n", n, tile, S);
+        }
+        pf_choose(PfProduct{RT, M, d / 32, 2 * F / 16, d}, 1, part_rows, 256, tile, S);
+        printf("2 %d %d %d\n", n, tile, S);
+        for (int K : {qd, F}) {
+          pf_choose(PfProduct{RT, M, K / 32, d / 16, d}, PF_MAX_SPLIT, part_rows, 256, tile, S);
+          printf("1 %d %d %d\n", n, tile, S);
+        }
+      }
+    }
+  }
   if (!strcmp(v[1], "few")) printf("%d\n", pf_qkv_few((int)num(2), (int)num(3), (int)num(4)) ? 1 : 0);
 }
 """
@@ -71,3 +95,22 @@ def test_buffers_shrink_to_the_memory_that_is_left(plan):
 ])
 def test_few_row_products_go_without_tiles_while_they_are_one_round(plan, rows, tiles, few):
     assert plan("few", rows, tiles, 256) == [[few]]
+
+
+def test_the_gpu_sizes_reach_every_kernel_the_pass_picks_from(plan):
+    """(product, tile or row tiles of the few-row kernel) and the numbers of slices, over all prompts of 65 to 2200 tokens of the
+    shapes that the GPU test runs, against those at its sizes."""
+    kernels, slices, have_kernels, have_slices = {}, {}, set(), set()
+    for name, dtype, cases in SIZES:
+        sh = shape_of(name, dtype)
+        tested = {n for n, _ in cases}
+        dims = (sh.d_model, sh.q_dim, sh.kv_dim, sh.d_ffn)
+        for mode, n, tile, S in plan("routes", *dims, 65, 2200):
+            kernels.setdefault((mode, tile), (name, n))
+            slices.setdefault(S, (name, n))
+            if n in tested:
+                have_kernels.add((mode, tile))
+                have_slices.add(S)
+    assert {k: at for k, at in kernels.items() if k not in have_kernels} == {}
+    assert {s: at for s, at in slices.items() if s not in have_slices} == {}
+    assert len(kernels) >= 3 * 6 + 4  # all six tiles of the three kinds of product, four heights of the few-row kernel
