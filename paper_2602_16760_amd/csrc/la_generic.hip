@@ -1,6 +1,7 @@
 // Any-shape kernels in fp32 arithmetic: the LA_F32 model's compute path, and the path of
-// LA_BF16 models whose shape the MFMA kernels do not cover.  Plain, one op per kernel:
-// these shapes are small (the tiny decoder of the test configuration), so clarity wins.
+// LA_BF16 models whose shape the MFMA kernels do not cover.  These shapes are small (the tiny
+// decoder of the test configuration), so what counts is launches: the norms and SwiGLU are part
+// of the products, six launches a layer.
 #include "la_device.h"
 #include "la_internal.h"
 
@@ -349,14 +350,19 @@ static int gemm_kind(int MT, dim3 grid, hipStream_t s, const float *A, int lda, 
   switch (MT) {
   case 1: gemm_generic_kernel<T, 1, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
   case 2: gemm_generic_kernel<T, 2, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
-  case 3: gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
-  default: gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  default:
+    if constexpr (KIND != GEMM_WIDE) {  // (two row tiles at most)
+      if (MT == 3) gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec);
+      else gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec);
+    }
   }
   LA_HIP(hipGetLastError());
   return LA_OK;
 }
 
-// N: columns of C (GLU: half the columns of W).  64 columns per workgroup once that alone gives every CU some.
+// N: columns of C (GLU: half the columns of W).  64 columns per workgroup once that alone gives each of 256 CUs some, up to two
+// row tiles (16 columns / 64, us): 4096 x 32768 179 / 144 at one row, 253 / 158 at 32; 1024 x 16384 25 / 21 and 29 / 26;
+// 1024 x 8192 14 / 21 and 18 / 26.
 template <typename T>
 static int gemm(const char *name, const float *A, int lda, const float *gain, float eps, const void *W, int ldw, float *C, int ldc, int M, int K,
                 int N, int accumulate, bool glu, hipStream_t s) {

@@ -391,10 +391,11 @@ int mfma_set_head(la_model *m, const void *unembed, hipStream_t s) {
   dst.r_nw = f->use_r ? R_NW : 0;
   int rc = pack(u, dst, s);
   if (rc) return rc;
-  // partial arg-max records per CU: one per reduction chunk of every pass, at any row count
+  // partial arg-max records per CU, at any row count: the LDS-ring kernel leaves one per reduction chunk of every pass, at most
+  // one per column tile; the register-streaming kernel one per pass (with room for one per tile the final scan read mostly
+  // empty ones)
   int passes = ceil_div(f->p_un.nt_max, f->p_un.ntp);
-  f->un_parts_bound = passes * f->p_un.ntp;  // (chunks hold at least one tile)
-  // the register-streaming kernel leaves one record per pass: with room for one per tile the final scan read mostly empty ones
+  f->un_parts_bound = passes * f->p_un.ntp;
   f->un_parts_per_cu = f->use_r ? passes : f->un_parts_bound;
   if (!f->un_part) f->un_part = (Top *)dalloc((size_t)f->n_wgs * f->un_parts_per_cu * 64 * sizeof(Top));
   LA_REQUIRE(f->un_part != nullptr, LA_ENOMEM, "device allocation failed");
@@ -692,7 +693,7 @@ namespace la {
 constexpr size_t NA_SYNC_BYTES = (size_t)SYNC_STRIDE * 66 * 4;
 constexpr size_t NA_ZERO_BYTES = NA_SYNC_BYTES + 256;  // barrier words, then the length / error pair
 constexpr int NA_MAX_D = 8192;                         // d_model
-constexpr int NA_MAX_PARTS = 4096;                     // workgroups x partial records per workgroup
+constexpr int NA_MAX_PARTS = 4096;                     // workgroups x column tiles (a partial record each) per workgroup
 constexpr size_t NA_OFF_XA = NA_ZERO_BYTES;
 constexpr size_t NA_OFF_RSQ = NA_OFF_XA + (size_t)LA_MAX_ROWS * NA_MAX_D * 2;
 constexpr size_t NA_OFF_TOP = NA_OFF_RSQ + (size_t)LA_MAX_ROWS * (NA_MAX_D / 16) * 4;
@@ -721,8 +722,9 @@ int mfma_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_
   MfmaModel *f = m->mf;
   LA_REQUIRE(f->ustream != nullptr, LA_EINVAL, "model was created without an unembedding matrix");
   LA_REQUIRE(m->d.d_model <= NA_MAX_D, LA_ERANGE, "d_model=%d exceeds the %d the static scratch array holds", m->d.d_model, NA_MAX_D);
+  // (the documented limit, which counts a record per column tile whatever kernel runs)
   LA_REQUIRE((long long)f->n_wgs * f->un_parts_bound <= NA_MAX_PARTS, LA_ERANGE,
-             "vocab=%d needs %lld partial arg-max records, the static scratch array holds %d", m->d.vocab,
+             "vocab=%d is beyond this entry point's limit: %lld partial arg-max records at one per column tile, %d at most", m->d.vocab,
              (long long)f->n_wgs * f->un_parts_bound, NA_MAX_PARTS);
   unsigned char *base = (m->device >= 0 && m->device < NA_MAX_DEVICES) ? na_ptr[m->device] : nullptr;
   LA_REQUIRE(base != nullptr, LA_EHIP, "the static scratch array has no address on device %d", m->device);

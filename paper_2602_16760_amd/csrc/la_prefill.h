@@ -143,8 +143,9 @@ __device__ __forceinline__ float pf_row_factor(const PfGemm &p, int row) {
 // into whole rounds of 256 CUs; smaller tiles are for the narrower matrices and fewer rows (pf_choose).  One workgroup
 // barrier per k-tile: past it every wave's part of the next stage is in, and nobody reads the stage any more that the
 // next requests overwrite (its fragments are in registers, one k-tile ahead of the products).
-// Measured (1023 rows, 7B shape, before: 64 x 64 per wave, activations from L2 into registers): gate/up 257 -> 205 us
-// (1170 TFLOP/s, what a large library product reaches on this card), QKV 92 -> 65, O 51 -> 42, down 147 -> 117.
+// Measured (1023 rows, 7B shape, a pass of eight layers, before: 64 x 64 per wave, activations from L2 into registers):
+// gate/up 258 -> 219 us (1100 TFLOP/s; a large library product reaches 1219 on this card), QKV 91 -> 65, O 50 -> 43, down
+// 144 -> 120.  Over 32 layers, at the clock that such a pass is left with, gate/up is 227 in the mean (206 at best) and QKV 70.
 template <int MODE, int WM, int WN, int NTW, int NS>
 __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf_lds) {
   constexpr int NWV = WM * WN;                 // waves

@@ -12,7 +12,9 @@ namespace la {
 // rows gain nothing more (3000 tokens at 1000: 5.4 ms against 4.5, two rounds of which the second is nearly empty).
 constexpr int PF_ROWS = 2048;
 // Shorter prompts are one block of the block kernel (64 rows of the 7B shape, eight layers: 1.14 ms); two blocks read the
-// weights twice (77 tokens 1.92 ms, the products' 128-row tiles 1.24).
+// weights twice (77 tokens 1.92 ms, the products' 128-row tiles 1.24).  The line is drawn for the prompt: what 2048 tokens leave
+// over is a chunk of its own however short it is (2049 tokens of eight layers 7.9 ms, as 2048 + 1 in two calls 7.4; 2048 + 64
+// 8.0 and 7.8; chunks of 1024 with smaller tiles had taken 13.6).
 constexpr int PF_MIN = LA_MAX_ROWS + 1;
 constexpr int PF_CHUNKS = 32;       // partial sums of squares per row (column chunks of pf_norm_kernel)
 constexpr int PF_PART_ROWS = 4096;  // rows of all slices' products together, at most
