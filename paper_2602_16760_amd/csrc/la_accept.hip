@@ -73,18 +73,45 @@ __device__ __forceinline__ void build_block(la_step_state *st, int W, int N, int
   st->tok[i] = tok;
 }
 
-// Candidates of `key` (its G slots: stamp and tuple of slot s in lane s), most recently inserted first, into cand[k*(N-1)+j]
-// (LDS and, where it is kept, the state); returns the count.  Stamps are distinct, so a slot's place is the number of
-// later ones.
-__device__ __forceinline__ int pool_lookup(const PoolView &p, int key, int32_t *cand, int32_t *state_cand, int lane) {
-  if (p.G == 0 || key < 0 || key >= p.vocab) return 0;
+// A slot on its way from the pool: its stamp and its tuple's first words (all requested before any is waited for: with one after
+// the other each cost a trip to memory), the rest of a longer tuple when it is put into LDS.
+struct SlotIn {
+  const int32_t *src;  // NULL: no slot in this lane
+  uint32_t stamp;
+  int32_t t[4];
+};
+__device__ __forceinline__ SlotIn slot_request(const PoolView &p, bool in, size_t slot) {
   const int n1 = p.N - 1;
-  const uint32_t sv = lane < p.G ? p.stamp[(size_t)key * p.G + lane] : 0u;
+  SlotIn r{};
+  if (!in) return r;
+  r.src = p.toks + slot * n1;
+  r.stamp = p.stamp[slot];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) r.t[u] = r.src[u < n1 ? u : n1 - 1];
+  return r;
+}
+__device__ __forceinline__ void slot_put(const SlotIn &r, int32_t *dst, int n1) {
+  if (r.src == nullptr) return;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (u < n1) dst[u] = r.t[u];
+  for (int j = 4; j < n1; ++j) dst[j] = r.src[j];
+}
+// The slots of `key`, slot s in lane s.
+__device__ __forceinline__ SlotIn key_request(const PoolView &p, int key, int lane) {
+  const bool in = lane < p.G && key >= 0 && key < p.vocab;
+  return slot_request(p, in, in ? (size_t)key * p.G + lane : 0);
+}
+
+// Candidates from a key's slots (stamp of slot s in lane s, its tuple in tok[s (N-1)]), most recently inserted first, into cand[k*(N-1)+j] (LDS and, where it is kept, the
+// state); returns the count.  Stamps are distinct, so a slot's place is the number of later ones.
+__device__ __forceinline__ int pool_order(const PoolView &p, uint32_t sv, const int32_t *tok, int32_t *cand, int32_t *state_cand, int lane) {
+  const int n1 = p.N - 1;
   int place = 0;
-  for (int s = 0; s < p.G; ++s) place += (uint32_t)__shfl((int)sv, s, 64) > sv ? 1 : 0;
+  for (int s = 0; s < p.G; ++s) place += (uint32_t)__builtin_amdgcn_readlane((int)sv, s) > sv ? 1 : 0;
   if (sv != 0u)
     for (int j = 0; j < n1; ++j) {
-      const int32_t t = p.toks[((size_t)key * p.G + lane) * n1 + j];
+      const int32_t t = tok[lane * n1 + j];
       cand[place * n1 + j] = t;
       state_cand[place * n1 + j] = t;
     }
@@ -103,15 +130,30 @@ __device__ __forceinline__ void wave_sync() {
 // column that shares its key with others costs no trip to memory.  (One by one through memory, 31 columns of one key with 32
 // slots made an accept 101 us, one thread had taken 52; now 19.  15 columns, 15
 // slots, five keys: 10 us, one thread 43.)
+// In two steps: the first keys' slots come in while the accept's other work is on its way (harvest_load, which writes nothing but
+// LDS), the rest follows when every workgroup has read what it needs.
 struct HarvestLds {
   int32_t lead[LA_MAX_ROWS], next[LA_MAX_ROWS];  // first column of the k-th key; the next column with the same key
   int32_t tok[256];                              // tuples of the slots at hand (224 words at most: W = 7, N = 5, G = 8)
 };
-__device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *win, const int32_t *newest, int W, HarvestLds &h, int lane) {
-  const int G = p.G, n1 = p.N - 1;
-  const uint32_t now = *p.counter;
-  if (lane == 0) *p.counter = now + (uint32_t)W;
-  if (G == 0) return;
+struct HarvestAt {
+  int n_keys, c;  // keys; this lane's first column (W: none)
+  size_t slot;
+  SlotIn in;
+};
+__device__ __forceinline__ void harvest_slots(const PoolView &p, const int32_t *win, int W, HarvestLds &h, int lane, int k0, HarvestAt &at) {
+  const int G = p.G, per = 64 / G, g = lane / G, s = lane - g * G;
+  const bool in = g < per && k0 + g < at.n_keys;
+  at.c = in ? h.lead[k0 + g] : W;
+  at.slot = in ? (size_t)win[at.c] * G + s : 0;
+  at.in = slot_request(p, in, at.slot);
+}
+__device__ __forceinline__ void harvest_load(const PoolView &p, const int32_t *win, int W, HarvestLds &h, int lane, HarvestAt &at) {
+  at.n_keys = 0;
+  at.c = W;
+  at.slot = 0;
+  at.in = SlotIn{};
+  if (p.G == 0) return;
   const int my_key = lane < W ? win[lane] : -1;
   bool first = my_key >= 0 && my_key < p.vocab;
   int next = W;
@@ -123,18 +165,26 @@ __device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *w
   h.next[lane] = next;
   const uint64_t firsts = __ballot(first);
   if (first) h.lead[__popcll(firsts & ((1ull << lane) - 1ull))] = lane;
+  at.n_keys = __popcll(firsts);
   wave_sync();
-  const int n_keys = __popcll(firsts), per = 64 / G, g = lane / G, s = lane - g * G;
+  harvest_slots(p, win, W, h, lane, 0, at);
+}
+__device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *win, const int32_t *newest, int W, HarvestLds &h, int lane, HarvestAt &at,
+                                             uint32_t now) {
+  const int G = p.G, n1 = p.N - 1;
+  if (lane == 0) *p.counter = now + (uint32_t)W;
+  if (G == 0) return;
+  const int per = 64 / G, g = lane / G, s = lane - g * G;
   const uint64_t mine = ((1ull << G) - 1ull) << (g * G < 64 ? g * G : 0);  // (G < 64)
-  for (int k0 = 0; k0 < n_keys; k0 += per) {
-    const bool in = g < per && k0 + g < n_keys;
-    int c = in ? h.lead[k0 + g] : W;
-    const size_t slot = in ? (size_t)win[c] * G + s : 0;
-    const uint32_t stamp0 = in ? p.stamp[slot] : 0u;
-    uint32_t sv = stamp0;
-    int32_t *tok = h.tok + (in ? lane * n1 : 0);
-    if (in)
-      for (int j = 0; j < n1; ++j) tok[j] = p.toks[slot * n1 + j];
+  for (int k0 = 0; k0 < at.n_keys; k0 += per) {
+    int32_t *tok = h.tok + (at.c < W ? lane * n1 : 0);
+    if (k0 > 0) {
+      harvest_slots(p, win, W, h, lane, k0, at);
+      tok = h.tok + (at.c < W ? lane * n1 : 0);
+      slot_put(at.in, tok, n1);
+    }
+    int c = at.c;
+    uint32_t sv = at.in.stamp;
     bool replaced = false;
     while (__any(c < W)) {
       const bool on = c < W;
@@ -157,11 +207,10 @@ __device__ __forceinline__ void pool_harvest(const PoolView &p, const int32_t *w
       }
       if (on) c = h.next[c];
     }
-    if (sv != stamp0) p.stamp[slot] = sv;
+    if (sv != at.in.stamp) p.stamp[at.slot] = sv;
     if (replaced)
-      for (int j = 0; j < n1; ++j) p.toks[slot * n1 + j] = tok[j];
+      for (int j = 0; j < n1; ++j) p.toks[at.slot * n1 + j] = tok[j];
   }
-  __threadfence();  // (the lookup reads what this stored)
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
@@ -220,13 +269,18 @@ __global__ __launch_bounds__(256) void pool_seed_kernel(PoolView p, const int32_
 
 __global__ __launch_bounds__(64) void state_init_kernel(PoolView p, la_step_state *st, const int32_t *prompt, int P, int W, int N, int G,
                                                         int Bp, uint32_t inserted, int32_t *kv_L) {
-  __shared__ int32_t win[LA_MAX_ROWS], cand[LA_MAX_ROWS];
+  __shared__ int32_t win[LA_MAX_ROWS], cand[LA_MAX_ROWS], slots[LA_MAX_ROWS];
   const int lane = threadIdx.x, c0 = prompt[P - 1];
   if (lane < W * (N - 1)) {
     const int r = lane / W, c = lane - r * W;
     win[lane] = st->win[lane] = prompt[(r + c) % P];
   }
-  const int n_cand = N >= 2 ? pool_lookup(p, c0, cand, st->cand, lane) : 0;
+  int n_cand = 0;
+  if (N >= 2) {
+    const SlotIn in = key_request(p, c0, lane);
+    slot_put(in, slots + (in.src ? lane * (N - 1) : 0), N - 1);
+    n_cand = pool_order(p, in.stamp, slots, cand, st->cand, lane);
+  }
   __syncthreads();
   build_block(st, W, N, n_cand, P - 1, Bp, c0, win, cand, lane);
   if (lane == 0) {
@@ -247,13 +301,16 @@ __global__ __launch_bounds__(64) void state_init_kernel(PoolView p, la_step_stat
 // then; nobody waits -- does the rest with one wave: harvest with a pool slot per lane, the next block with a row per lane.
 // The workgroups are counted in st->reserved (zero between launches): a word of the state and not of the pool, which several
 // generations may share, and cleared by the init kernels on the stream that the accepts follow on.
-// What the step reads comes into LDS at once.  (One thread doing all of it took 23 us, most of it waiting for one word after
-// the other; the relocation as a launch of its own cost 16 accepts 40 us.)
+// Bound by the trips to memory that depend on each other: the state; with it known, the pool's slots (of the window's keys and of
+// the last accepted token) beside the moving rows and the count; the next block out.  (One thread doing all of it took 23 us, most
+// of it waiting for one word after the other; the relocation as a launch of its own cost 16 accepts 40 us; slots asked for after
+// the count, a tuple's words and a moved row's elements one after the other: 7.4 us an accept at W = 7, N = 4, G = 7 where
+// nothing is accepted, now 6.3; 40 tokens in all, so that rows move in 2 layers 9.4 -> 8.2, in 32 layers 10.3 -> 8.8.)
 template <typename T>
 __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *st, const int32_t *ids, int32_t *emitted, int max_total, int W, int N, int G,
                                                      int32_t *kv_L, const int32_t *err, T *K, T *V, size_t layer_elems, int Hkv, int dh, int v_blocked,
                                                      int max_len) {
-  __shared__ int32_t id[LA_MAX_ROWS], win[LA_MAX_ROWS], cand[LA_MAX_ROWS], newest[LA_MAX_ROWS];
+  __shared__ int32_t id[LA_MAX_ROWS], win[LA_MAX_ROWS], cand[LA_MAX_ROWS], newest[LA_MAX_ROWS], slots[LA_MAX_ROWS];
   __shared__ HarvestLds harvest;
   __shared__ int is_last;
   const int lane = threadIdx.x & 63, n1 = N - 1, rows = 1 + (W + G) * n1;
@@ -281,15 +338,43 @@ __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *
   }
   const int best_m = best >> 6, best_k = best_m > 0 ? 63 - (best & 63) : 0;
   const int e = best_m + 1 < remaining ? best_m + 1 : remaining;
+  const int last = e <= 1 ? id[0] : id[v_row_index(W, N, best_k, e - 1)];
+  // the pool's slots that the serial part will need, while the rows move and the workgroups are counted (nothing of the pool is
+  // written before the last one is through here)
+  HarvestAt at;
+  uint32_t sv = 0u, now = 0u;
+  if (N >= 2 && threadIdx.x < 64) {
+    now = *p.counter;
+    const SlotIn in = key_request(p, last, lane);
+    harvest_load(p, win, W, harvest, lane, at);
+    sv = in.stamp;
+    slot_put(in, slots + (in.src ? lane * n1 : 0), n1);
+    slot_put(at.in, harvest.tok + (at.in.src ? lane * n1 : 0), n1);
+  }
   const int row = (int)blockIdx.y + 1, src = L0 + v_row_index(W, N, best_k, row), dst = L0 + row;
   if (row < e && src < max_len && dst < max_len && L0 >= 0) {
     T *Kl = K + (size_t)blockIdx.x * layer_elems;
     T *Vl = V + (size_t)blockIdx.x * layer_elems;
     const int n = Hkv * dh;
-    for (int i = threadIdx.x; i < n; i += 256) {
-      Kl[(size_t)dst * n + i] = Kl[(size_t)src * n + i];
-      const int h = i / dh, c = i - h * dh;
-      Vl[v_index(v_blocked, dst, h, c, Hkv, dh)] = Vl[v_index(v_blocked, src, h, c, Hkv, dh)];
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * 256) {  // (all loads of a turn before its first store)
+      T k[4], v[4];
+      auto at_v = [&](int row, int i) {
+        const int h = i / dh;
+        return v_index(v_blocked, row, h, i - h * dh, Hkv, dh);
+      };
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 256 * u < n ? i0 + 256 * u : i0;
+        k[u] = Kl[(size_t)src * n + i];
+        v[u] = Vl[at_v(src, i)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 256 * u;
+        if (i >= n) continue;
+        Kl[(size_t)dst * n + i] = k[u];
+        Vl[at_v(dst, i)] = v[u];
+      }
     }
   }
   __syncthreads();  // (every wave has what it needs of the state)
@@ -307,17 +392,22 @@ __global__ __launch_bounds__(256) void accept_kernel(PoolView p, la_step_state *
     return;
   }
   if (lane < e) emitted[emitted_before + lane] = lane == 0 ? id[0] : id[v_row_index(W, N, best_k, lane)];
-  const int last = e == 1 ? id[0] : id[v_row_index(W, N, best_k, e - 1)];
   // harvest: each window column yields one n-gram ending in the model's newest guess; then the columns move up
   int n_next = 0;
   if (N >= 2) {
     if (lane < W) newest[lane] = id[la_row_index(W, N - 2, lane)];
     wave_sync();
-    pool_harvest(p, win, newest, W, harvest, lane);
+    pool_harvest(p, win, newest, W, harvest, lane, at, now);
+    if (__any(lane < W && win[lane] == last)) {  // a column has just been inserted under the key that is looked up
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      const SlotIn in = key_request(p, last, lane);
+      sv = in.stamp;
+      slot_put(in, slots + (in.src ? lane * n1 : 0), n1);
+    }
     const int up = lane + W < W * n1 ? win[lane + W] : lane < W * n1 ? newest[lane - W * (n1 - 1)] : 0;
     wave_sync();
     if (lane < W * n1) win[lane] = st->win[lane] = up;
-    n_next = pool_lookup(p, last, cand, st->cand, lane);
+    n_next = pool_order(p, sv, slots, cand, st->cand, lane);
     wave_sync();
   }
   build_block(st, W, N, n_next, L0 + e, Bp, last, win, cand, lane);
