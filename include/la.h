@@ -276,8 +276,8 @@ int la_lookahead_layout(const la_lookahead_desc *la, int t, int n_cand, int Bp, 
  * 1 <= n <= LA_MAX_ROWS. */
 int la_causal_layout(int t, int n, int32_t *pos_host, uint64_t *vis_host);
 
-/* Sets how many times a workgroup polls a grid barrier's release word (about a microsecond
- * per poll) before it gives up and the launch reports LA_EHIP; 0 restores the default
+/* Sets how long a workgroup polls for a grid barrier's release (in units of about a
+ * microsecond) before it gives up and the launch reports LA_EHIP; 0 restores the default
  * (2^21, about two seconds).  Takes effect from the next launch on the model. */
 int la_set_barrier_timeout(la_model *m, unsigned polls);
 

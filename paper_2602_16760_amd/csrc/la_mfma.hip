@@ -236,7 +236,7 @@ int mfma_create(la_model *m) {
   hipDeviceProp_t prop;
   LA_HIP(hipGetDeviceProperties(&prop, m->device));
   int cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-  f->n_wgs = std::max(1, std::min(env_int("LA_WGS", cus), cus));  // one resident workgroup per CU: the barrier needs co-residency
+  f->n_wgs = std::max(1, std::min({env_int("LA_WGS", cus), cus, rs::GB_MAX_WGS}));  // one resident workgroup per CU: the barrier needs co-residency
   f->use_r = env_int("LA_LDS_RING", 0) == 0;
   LA_REQUIRE(f->use_r || d.dtype != LA_F16, LA_EINVAL, "LA_F16 models run on the register-streaming kernel only (unset LA_LDS_RING)");
   LA_REQUIRE((size_t)prop.sharedMemPerBlockOptin >= (size_t)LDS_BYTES || (size_t)prop.maxSharedMemoryPerMultiProcessor >= (size_t)LDS_BYTES,

@@ -80,7 +80,7 @@ constexpr int lds_bytes() { return NW * Lay<MT, NW>::REG + M_BYTES + NW * (16 + 
 constexpr int K_DEAD = 0;      // a wait timed out: every wave leaves the kernel
 constexpr int K_IOBAR = 1;     // arrivals at the IO-wave barrier
 constexpr int K_GPASS = 2;     // last grid-barrier epoch seen released
-constexpr int K_SPARE = 3;
+constexpr int K_FAR = 3;       // a workgroup runs on another XCD than its group of the grid barrier is named after
 constexpr int K_ALAND = 8;     // [8..15] per MFMA wave: operand k-tiles landed in its ring (monotonic over the launch)
 constexpr int K_ADONE = 16;    // [16..23] per MFMA wave: operand k-tiles it has read
 constexpr int K_PDONE = 24;    // [24..31] per MFMA wave: passes whose partial tile is in LDS
@@ -475,7 +475,7 @@ __device__ __forceinline__ void mfma_wave_main(const StackArgs &a, unsigned lds0
   const unsigned lane16 = (unsigned)lane * 16u;
   const bool no_weights = (LA_DBG_BITS(a.dbg) & 1) != 0;  // (timing experiment: no weight traffic)
   // buffer resource over this CU's stream
-  const uint64_t base = (uint64_t)(a.wstream + (size_t)blockIdx.x * a.cu_bytes);
+  const uint64_t base = (uint64_t)(a.wstream + (size_t)(int)blockIdx.x * a.cu_bytes);
   u32x4 rsrc;
   rsrc[0] = uni((unsigned)base);
   rsrc[1] = uni((unsigned)(base >> 32));
@@ -556,6 +556,7 @@ struct Io {
   int v, lane, tid; // IO wave index, lane, thread index among the IO threads
   unsigned bar_seq;
   int ok;
+  bool near;        // every workgroup is on the XCD that its group of the grid barrier is named after (known after the first barrier)
   unsigned long long *tr;  // timeline slots of the running phase (workgroup 0, IO wave 0, lane 0) or null
   int ph;                  // phase number (timeline)
 };
@@ -607,53 +608,99 @@ __device__ __forceinline__ bool io_barrier(Io &io) {
   return io_wait_ge(io, K_IOBAR, io.bar_seq);
 }
 
-// Grid barrier, run by the IO waves (same counters and protocol as la_stack.h's grid_sync), in two halves: what a wave works
-// out between them (the next phase's pointers, which need memory reads of their own) costs nothing while the others arrive.
+// Grid barrier, run by the IO waves, in two halves: what a wave works out between them (the next phase's pointers, which need
+// memory reads of their own) costs nothing while the others arrive.
+// Bound by the trips between the XCDs: a store that another XCD sees takes 300 - 400 ns, an atomic as long (and those on one
+// word queue up), a store or a load in the XCD's own L2 under 200.  So there are no atomics: workgroup i belongs to group i % 8
+// (its XCD, as workgroups are dealt out), every IO wave stores the epoch into a word of its own of its group, one wave of the
+// group's first workgroup polls them all and stores the epoch into a word of each of the eight groups' lines, and every workgroup
+// polls its own group's line: one trip between XCDs.  Alone 1.84 -> 1.40 us (256 workgroups; counters per 16 workgroups, a top
+// counter and one release word before); in the kernel small_bf16 (15 phases, 31 rows) 129.8 -> 122.7 us, the 7B shape's 30 layers,
+// L = 512, one row 2894 -> 2867, 32 rows 3250 -> 3200, 24 layers, L = 2048, 43 rows 3132 -> 3079.  A sleep between polls, or one
+// word per workgroup behind a barrier of its IO waves, is slower.  Everything here has to stay wave-uniform (uni): a result
+// that the compiler takes for divergent turns the phases after it into per-lane loops (+ 0.5 us a phase).
+// The first barrier of a launch makes no assumption about where workgroups run: its words are stored for the whole device, and
+// carry a bit where a workgroup is not on the XCD its group is named after.  If any carries it, all words of the launch are stored
+// so; else those that only the group's own XCD reads stay in its L2.
+constexpr int GB_GROUPS = 8, GB_LINE = 64, GB_GROUP_WORDS = 128, GB_MAX_WGS = GB_GROUPS * GB_GROUP_WORDS / 4;
+constexpr unsigned GB_FAR = 1u << 30, GB_EPOCH = GB_FAR - 1u;
+static_assert(GB_GROUPS * (GB_GROUP_WORDS + GB_LINE) <= SYNC_STRIDE * 66, "words of the barrier");
+__device__ __forceinline__ unsigned xcc_id() {
+  unsigned v;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(v));
+  return v;
+}
+
+// Polls words p[0 .. n - 1] (lane i: word i, and word i + 64 of PER = 2) until all have reached the epoch; *far: one carries GB_FAR.
+template <int PER>
+__device__ __forceinline__ bool io_poll_words(const StackArgs &a, const Io &io, const unsigned *p, int n, unsigned epoch, bool *far) {
+  unsigned spins = 0;
+  for (;;) {
+    unsigned v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = io.lane + 64 * k < n ? __hip_atomic_load(p + io.lane + 64 * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : epoch;
+    bool in = true, bit = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      in = in && (v[k] & GB_EPOCH) >= epoch;
+      bit = bit || (v[k] & GB_FAR) != 0;
+    }
+    if (uni((int)__all(in)) != 0) {
+      *far = uni((int)__any(bit)) != 0;
+      return true;
+    }
+    if ((++spins >> 2) > a.spin_global) return false;  // (four polls a microsecond)
+  }
+}
 template <int NIO>
 __device__ __forceinline__ bool io_grid_arrive(const StackArgs &a, Io &io, unsigned epoch) {
+  static_assert(NIO == 4, "words of a workgroup");
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   io_mark(io, 2);
   if (LA_TRACE_PTR(a) && io.v == 0 && io.lane == 0 && (blockIdx.x == 0 || blockIdx.x > 2)) {  // (timeline: when each workgroup ends a phase)
     const int k = io.ph - a.trace_sel;
-    if (k >= 0 && k < 8) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * blockIdx.x + 8 + k] = wall_clock64();
+    if (k >= 0 && k < 8) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * (int)blockIdx.x + 8 + k] = wall_clock64();
   }
-  wait_vmcnt<0>();  // this wave's stores are acknowledged
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");  // this wave's stores are acknowledged
   io_mark(io, 6);
-  if (!io_barrier<NIO>(io)) return false;
+  if (io.lane == 0) {
+    unsigned *w = a.sync + GB_GROUP_WORDS * (blockIdx.x % GB_GROUPS) + NIO * (blockIdx.x / GB_GROUPS) + io.v;
+    if (io.near) __hip_atomic_store(w, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_store(w, epoch | (xcc_id() != blockIdx.x % GB_GROUPS ? GB_FAR : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   io_mark(io, 7);
-  if (io.v == 0 && io.lane == 0) {
-    unsigned n = gridDim.x;
-    unsigned g = blockIdx.x / SYNC_GROUP;
-    unsigned gsize = (g + 1) * SYNC_GROUP <= n ? SYNC_GROUP : n - g * SYNC_GROUP;
-    unsigned *gc = a.sync + SYNC_STRIDE * g, *top = a.sync + SYNC_STRIDE * 64, *rel = a.sync + SYNC_STRIDE * 65;
-    unsigned old = __hip_atomic_fetch_add(gc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1 == epoch * gsize) {
-      unsigned t = __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (t + 1 == epoch * a.n_groups) __hip_atomic_store(rel, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int G = (int)gridDim.x, wg = (int)blockIdx.x;
+  if (wg < GB_GROUPS && io.v == NIO - 1) {  // collects its group
+    bool far;
+    const bool ok = io_poll_words<2>(a, io, a.sync + GB_GROUP_WORDS * wg, NIO * ((G - wg + GB_GROUPS - 1) / GB_GROUPS), epoch, &far);
+    if (ok && io.lane < GB_GROUPS)
+      __hip_atomic_store(a.sync + GB_GROUPS * GB_GROUP_WORDS + GB_LINE * io.lane + wg, epoch | (far ? GB_FAR : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!ok && io.lane == 0) {
+      raise_error(a, 4);
+      ctl_write(io.ctl + 4 * K_DEAD, 1u);
     }
   }
-  return true;
+  return ctl_read(io.ctl + 4 * K_DEAD) == 0;
 }
 template <int NIO>
 __device__ __forceinline__ bool io_grid_wait(const StackArgs &a, Io &io, unsigned epoch) {
-  if (io.v == 0 && io.lane == 0) {
-    unsigned *rel = a.sync + SYNC_STRIDE * 65;
-    unsigned spins = 0;
-    bool ok = true;
-    while ((int)(__hip_atomic_load(rel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - epoch) < 0) {
-      __builtin_amdgcn_s_sleep(1);
-      if (++spins > a.spin_global) {
-        raise_error(a, 4);
-        ok = false;
-        break;
-      }
+  const int G = (int)gridDim.x, wg = (int)blockIdx.x;
+  bool ok = true, far;
+  if (io.v == 0) {
+    ok = io_poll_words<1>(a, io, a.sync + GB_GROUPS * GB_GROUP_WORDS + GB_LINE * (wg % GB_GROUPS), G < GB_GROUPS ? G : GB_GROUPS, epoch, &far);
+    if (ok && io.lane == 0) {
+      ctl_write(io.ctl + 4 * K_FAR, far ? 1u : 0u);
+      ctl_write(io.ctl + 4 * K_GPASS, epoch);
     }
-    if (ok) ctl_write(io.ctl + 4 * K_GPASS, epoch);
-    else ctl_write(io.ctl + 4 * K_DEAD, 1u);
   }
-  const bool ok = io_wait_ge(io, K_GPASS, epoch);
+  if (!ok && io.lane == 0) {
+    raise_error(a, 4);
+    ctl_write(io.ctl + 4 * K_DEAD, 1u);
+  }
+  ok = io_wait_ge(io, K_GPASS, epoch) && ok;
+  if (epoch == a.epoch0 + 1u) io.near = uni((int)(ctl_read(io.ctl + 4 * K_FAR) == 0)) != 0;
   io_mark(io, 8);
-  return ok;
+  return uni((int)ok) != 0;
 }
 template <int NIO>
 __device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigned epoch) {
@@ -1009,7 +1056,7 @@ __device__ __forceinline__ void pass_epilogue(const StackArgs &a, const Io &io, 
   const float *cs = a.cs;
   constexpr int NW = 8 - NIO, REG = Lay<MT, 8 - NIO>::REG;
   LDS_AS const float *rs_lds = (LDS_AS const float *)(uintptr_t)(io.misc + M_RS);
-  const int G = gridDim.x, cu = blockIdx.x;
+  const int G = (int)gridDim.x, cu = (int)blockIdx.x;
   if (q.mode == MODE_QKV) {
     for (int it = tid; it < Bp * ntc; it += NT_IO) {
       const EpiItem at = it == tid ? pre.at : epi_item(a, MODE_QKV, it, tile_first, ntc);
@@ -1223,7 +1270,7 @@ __device__ __forceinline__ void r_prep(const StackArgs &a, const Io &io, const f
   constexpr int NT_IO = NIO * 64;
   __amdgpu_buffer_rsrc_t rq = rsrc_of(rsq_out), rx = rsrc_of(xa_out);
   const int octs = a.d >> 3, total = a.Bp * octs;
-  for (int it = blockIdx.x * NT_IO + io.tid; it < total; it += gridDim.x * NT_IO) {
+  for (int it = (int)blockIdx.x * NT_IO + io.tid; it < total; it += (int)gridDim.x * NT_IO) {
     const int r = it / octs, oct = it - r * octs, c0 = oct * 8;
     const f32x4 *xp = reinterpret_cast<const f32x4 *>(a.x + (size_t)r * a.d + c0);
     f32x4 x0 = xp[0], x1 = xp[1];
@@ -1245,7 +1292,7 @@ __device__ __forceinline__ void r_rope_table(const StackArgs &a, const Io &io) {
   __amdgpu_buffer_rsrc_t rc = rsrc_of(a.cs);
   int half = a.dh >> 1, total = a.Bp * half;
   // (from the grid's end: the first workgroups have the first operand to make)
-  for (int e = (gridDim.x - 1 - blockIdx.x) * NT_IO + io.tid; e < total; e += gridDim.x * NT_IO) {
+  for (int e = ((int)gridDim.x - 1 - (int)blockIdx.x) * NT_IO + io.tid; e < total; e += (int)gridDim.x * NT_IO) {
     int b = e / half, i = e - b * half;
     double inv = exp2(-(double)i / (double)half * log2(a.theta));
     double s, c;
@@ -1300,7 +1347,7 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
   // sum has one order whoever forms it.
   const int n_units = a.Hkv * n_rt;
   constexpr unsigned PART = DT * 1024u + 512u;  // bytes of a record: DT output tiles (16 B per lane each), then (m, l) per lane
-  for (int su = su0; su < n_units * S; su += gridDim.x) {
+  for (int su = su0; su < n_units * S; su += (int)gridDim.x) {
     const int u = su % n_units, ks = su / n_units;
     // unit u = kvh + Hkv * rt sits on workgroup att_first + u: with 8 kv heads (and the first unit on a multiple of 8)
     // all units of a kv head run on one XCD and share its K, V lines in that XCD's L2 (requesting those lines ahead, during
@@ -1498,8 +1545,8 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
 template <int NIO>
 __device__ __forceinline__ void r_unembed_final(const StackArgs &a, const Io &io) {
   __amdgpu_buffer_rsrc_t ru = rsrc_of(a.un_part);
-  const int n_part = gridDim.x * a.un_parts_per_cu;
-  for (int b = blockIdx.x * NIO + io.v; b < a.Bp; b += gridDim.x * NIO) {
+  const int n_part = (int)gridDim.x * a.un_parts_per_cu;
+  for (int b = (int)blockIdx.x * NIO + io.v; b < a.Bp; b += (int)gridDim.x * NIO) {
     Top best{-INFINITY, 0x7fffffff, -INFINITY};
     for (int s0 = io.lane; s0 < n_part; s0 += 64 * 8) {
       Top c[8];
@@ -1545,7 +1592,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
   io.misc = lds0 + NW * Lay<MT, NW>::REG;
   io.ctl = io.misc + M_CTL;
   io.v = v; io.lane = lane; io.tid = v * 64 + lane;
-  io.bar_seq = 0; io.ok = 1;
+  io.bar_seq = 0; io.ok = 1; io.near = false;
   io.tr = nullptr;
   io.ph = 0;
   int ph = 0;  // phase number as in la_stack.h: first operand, then five per layer
@@ -1573,7 +1620,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
       const int nt = pw.tiles_of(4), ntp = a.un.ntp < Geo<MT>::NTMAX ? a.un.ntp : Geo<MT>::NTMAX;
       const int used = (nt + ntp - 1) / ntp;
       for (int it = io.tid; it < (a.un_parts_per_cu - used) * 64; it += NIO * 64) {
-        unsigned o = (unsigned)(((size_t)(blockIdx.x * a.un_parts_per_cu + used + (it >> 6)) * 64 + (it & 63)) * sizeof(Top));
+        unsigned o = (unsigned)(((size_t)((int)blockIdx.x * a.un_parts_per_cu + used + (it >> 6)) * 64 + (it & 63)) * sizeof(Top));
         st32f(rp, o, -INFINITY);
         __builtin_amdgcn_raw_buffer_store_b32(0x7fffffffu, rp, o + 4, 0, DEV);
         st32f(rp, o + 8, -INFINITY);
@@ -1589,7 +1636,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
       first = false;
       Epi q{};
       q.mode = MODE_UNEMBED;
-      q.un_part = a.un_part + (size_t)blockIdx.x * a.un_parts_per_cu * 64;
+      q.un_part = a.un_part + (size_t)(int)blockIdx.x * a.un_parts_per_cu * 64;
       q.part = pw.cur.pidx;
       const Pass cur = pw.cur;
       if (!io_pass<MT, NW>(a, io, cur, pseq, a.xa, nullptr, q, L, 0, a_seq, [&]() { pw.next(); })) return;
@@ -1706,7 +1753,7 @@ __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
   {
     constexpr int N16 = NW * TAB_BYTES / 16;
     static_assert(NW * TAB_BYTES % 16 == 0, "whole 16-byte pieces");
-    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.sched) + (size_t)blockIdx.x * N16;
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.sched) + (size_t)(int)blockIdx.x * N16;
     LDS_AS u32x4 *dst = (LDS_AS u32x4 *)(lds + NW * Lay<MT, NW>::REG + M_BYTES);
     for (int i = threadIdx.x; i < N16; i += WG_THREADS) dst[i] = src[i];
   }
@@ -1717,7 +1764,7 @@ __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
   if (wave < NW) {
     mfma_wave_main<MT, NW>(a, lds0, wave, lane);
     if (LA_TRACE_PTR(a) && lane == 0 && (blockIdx.x == 0 || blockIdx.x == 200)) LA_TRACE_PTR(a)[16 + (blockIdx.x ? 8 : 0) + wave] = wall_clock64();
-    if (LA_TRACE_PTR(a) && lane == 0 && blockIdx.x > 2) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * blockIdx.x + wave] = wall_clock64();
+    if (LA_TRACE_PTR(a) && lane == 0 && blockIdx.x > 2) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * (int)blockIdx.x + wave] = wall_clock64();
   } else {
     __builtin_amdgcn_s_setprio(3);  // (the IO waves' short bursts go first: measured neutral at 32 rows, 1.6 % on the one-row step; the other way round costs 0.8 %)
     io_wave_main<MT, NW>(a, lds0, wave - NW, lane, L);
@@ -1725,7 +1772,7 @@ __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
     if (lane == 0 && ctl_read(lds0 + NW * Lay<MT, NW>::REG + M_CTL + 4 * K_DEAD) != 0)
       raise_error(a, 4);
     if (LA_TRACE_PTR(a) && lane == 0 && (blockIdx.x == 0 || blockIdx.x == 200)) LA_TRACE_PTR(a)[16 + (blockIdx.x ? 8 : 0) + wave] = wall_clock64();  // (timeline: when each wave ends)
-    if (LA_TRACE_PTR(a) && lane == 0 && blockIdx.x > 2) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * blockIdx.x + wave] = wall_clock64();
+    if (LA_TRACE_PTR(a) && lane == 0 && blockIdx.x > 2) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * (int)blockIdx.x + wave] = wall_clock64();
     if (LA_TRACE_PTR(a) && wave == 7 && blockIdx.x == 0) {  // (timeline of MFMA wave 0: LDS -> the workgroup's trace words; the MFMA waves finish before the last epilogue)
       const unsigned v = ctl_read_lanes(lds0 + NW * Lay<MT, NW>::REG + M_BYTES + NW * TAB_BYTES + 4u * (unsigned)lane);
       LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG + lane] = v;  // (the words of workgroups 1 and 2, which leave theirs alone)
