@@ -1,9 +1,10 @@
 // Any-shape kernels in fp32 arithmetic: the LA_F32 model's compute path, and the path of
 // LA_BF16 models whose shape the MFMA kernels do not cover.  These shapes are small (the tiny
 // decoder of the test configuration), so what counts is launches: the norms and SwiGLU are part
-// of the products, six launches a layer.
+// of the products, six launches a layer; five (la_plain.h) where layers and heads allow it.
 #include "la_device.h"
 #include "la_internal.h"
+#include "la_plain.h"
 
 namespace la {
 
@@ -374,9 +375,58 @@ static int gemm(const char *name, const float *A, int lda, const float *gain, fl
   return gemm_kind<T, GEMM_16>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
 }
 
+// la_plain.h's attention takes heads that are whole groups of 16 channels and a layer's cache within 32-bit offsets; beside the
+// general products it runs where its workgroups are a few rounds of the chip (a row, a head and 64 channels each; two 2048-wide
+// layers with 16 heads of 128, L = 47, 17 rows 287 against 290 us, L = 3000 577 / 633, but 64 rows 420 / 405; 4096 wide, 32 heads,
+// L = 3000, 17 rows 1156 / 1074).
+static bool plain_heads(const la_model *m, const la_kv *kv) { return m->d.head_dim % 16 == 0 && kv->layer_elems() * m->esize < (size_t)1 << 31; }
+static bool plain_attention_pays(const la_model *m, const la_kv *kv, int Bp) {
+  return plain_heads(m, kv) && Bp * m->d.n_q_heads * ceil_div(m->d.head_dim, 64) <= 1024;
+}
+// Its products take layers that also fit 32-bit offsets and are small: more loads on their way and fewer launches gain there, a pass
+// over the activations per eight columns of gate costs where there are many.  A forward of two fp32 layers at 1 / 17 / 37 / 64 rows,
+// L = 47, and at 17 rows, L = 3000, us, before -> now: 256 wide (2.8 MB a layer) 50 / 63 / 73 / 80, 222 -> 40 / 50 / 62 / 72, 111;
+// 512 wide (11 MB) 68 / 85 / 102 / 115, 244 -> 54 / 70 / 88 / 108, 134; 768 wide (24 MB) 83 / 105 / 126 / 145, 264 -> 74 / 93 / 116 / 145, 155.
+// 1024 wide (43 MB) they would take 95 / 128 / 165 / 208 against the general ones' 96 / 124 / 152 / 176.
+constexpr size_t PL_LAYER_BYTES = (size_t)32 << 20;
+static bool plain_layers(const la_model *m, const la_kv *kv) {
+  const la_model_desc &d = m->d;
+  const size_t qd = m->qdim(), dm = d.d_model, F = d.d_ffn, pad = 16 * PL_WAVES * 6;
+  for (size_t n : {(dm + pad) * m->nqkv(), (qd + pad) * dm, (dm + pad) * 2 * F, (F + pad) * dm, (LA_MAX_ROWS + 1) * (dm + qd + F) + pad})
+    if (n * 4 >= (size_t)1 << 31) return false;
+  return plain_heads(m, kv) && (dm * (m->nqkv() + qd) + 3 * dm * F) * m->esize <= PL_LAYER_BYTES;
+}
+
+template <typename T>
+static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis, la_kv *kv, hipStream_t s) {
+  const la_model_desc &d = m->d;
+  const int nqkv = m->nqkv(), qd = m->qdim(), F = d.d_ffn, dm = d.d_model;
+  int rc = launch_rope_table(m, pos, Bp, s);
+  if (rc) return rc;
+  for (int l = lb; l < le; ++l) {
+    const GenericLayer &w = m->layers[l];
+    LA_REQUIRE(w.set, LA_EINVAL, "layer %d has no weights", l);
+    T *Kc = (T *)kv->K + (size_t)l * kv->layer_elems(), *Vc = (T *)kv->V + (size_t)l * kv->layer_elems();
+    auto product = [&](const float *A, int K, const float *gain, const void *W, int ldw, int N, float *out, int ldo) {
+      PlProduct p{};
+      p.A = A; p.lda = K; p.M = Bp; p.K = K; p.gain = gain; p.eps = d.rms_eps; p.W = W; p.ldw = ldw; p.N = N; p.out = out; p.ldo = ldo;
+      p.cs = m->rope_cs; p.Kc = Kc; p.Vc = Vc; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.dh = d.head_dim; p.max_len = kv->max_len;
+      p.L_dev = kv->L_dev; p.err = kv->err_dev; p.err_map = m->err_map;
+      return p;
+    };
+    if ((rc = plain_product<T, PL_QKV>("plain_qkv", product(hidden, dm, w.g_attn, w.wqkv, nqkv, nqkv, m->qkv, qd), nqkv / 16, s))) return rc;
+    if ((rc = plain_attention<T>(m->qkv, qd, d, Kc, Vc, kv, Bp, vis, m->attn, s))) return rc;
+    if ((rc = plain_product<T, PL_RESID>("plain_o", product(m->attn, qd, nullptr, w.wo, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
+    if ((rc = plain_product<T, PL_GLU>("plain_gateup", product(hidden, dm, w.g_mlp, w.wgu, 2 * F, F, m->act, F), ceil_div(F, 8), s))) return rc;
+    if ((rc = plain_product<T, PL_RESID>("plain_down", product(m->act, F, nullptr, w.wdown, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
+  }
+  return LA_OK;
+}
+
 template <typename T>
 static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis,
                      la_kv *kv, hipStream_t s) {
+  if (plain_layers(m, kv)) return plain_forward_t<T>(m, lb, le, hidden, Bp, pos, vis, kv, s);
   const la_model_desc &d = m->d;
   int nqkv = m->nqkv(), qd = m->qdim(), F = d.d_ffn, dm = d.d_model;
   int rc = launch_rope_table(m, pos, Bp, s);
@@ -392,7 +442,9 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
       rope_kvwrite_kernel<T><<<Bp, 256, 0, s>>>(m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, m->rope_cs, Kc, Vc,
                                                  kv->L_dev, kv->max_len, Bp, kv->err_dev, m->err_map);
     }
-    {
+    if (plain_attention_pays(m, kv, Bp)) {
+      if ((rc = plain_attention<T>(m->qkv, nqkv, d, Kc, Vc, kv, Bp, vis, m->attn, s))) return rc;
+    } else {
       ProfScope p("attention", s);
       attention_generic_kernel<T><<<dim3(Bp, d.n_q_heads), 256, 0, s>>>(
           m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev, kv->max_len, Bp, vis, m->attn);

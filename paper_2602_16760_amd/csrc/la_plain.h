@@ -1,0 +1,318 @@
+// The plain kernels of small layers (fp32 arithmetic; included by la_generic.hip): five launches a layer, each of which requests
+// everything it reads before it waits for any of it.  Such a launch is a chain of memory latencies around next to no arithmetic:
+// its loads in turns, and rotation and cache rows as a launch of their own, were half of a step of the tiny shape.
+#pragma once
+#include "la_device.h"
+#include "la_internal.h"
+
+namespace la {
+
+constexpr int PL_WAVES = 8, PL_THREADS = 64 * PL_WAVES;
+typedef float pl_f4 __attribute__((ext_vector_type(4)));
+typedef unsigned pl_u4 __attribute__((ext_vector_type(4)));
+constexpr unsigned PL_OOB = 0x80000000u;
+
+// Buffer loads: what lies past a matrix's end comes back as zero, and offsets are 32 bits.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pl_rsrc(const void *p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ float pl_load(__amdgpu_buffer_rsrc_t r, unsigned i) {  // element i
+  if constexpr (sizeof(T) == 4) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, i * 4u, 0, 0));
+  } else {
+    const T v = __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, i * 2u, 0, 0));
+    return load_as_float<T>(&v);
+  }
+}
+// Sixteen consecutive elements from element i (a multiple of 16).
+template <typename T>
+__device__ __forceinline__ void pl_load16(float *out, __amdgpu_buffer_rsrc_t r, unsigned i) {
+  constexpr int PER = 16 / sizeof(T);
+#pragma unroll
+  for (int n = 0; n < 16 / PER; ++n) {
+    const pl_u4 v = __builtin_bit_cast(pl_u4, __builtin_amdgcn_raw_buffer_load_b128(r, (i + (unsigned)(n * PER)) * (unsigned)sizeof(T), 0, 0));
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      if constexpr (sizeof(T) == 4) {
+        out[n * PER + e] = __uint_as_float(v[e]);
+      } else {
+        const T h = __builtin_bit_cast(T, (uint16_t)(v[e >> 1] >> (16 * (e & 1))));
+        out[n * PER + e] = load_as_float<T>(&h);
+      }
+    }
+  }
+}
+
+enum PlKind { PL_QKV = 0, PL_RESID = 1, PL_GLU = 2 };
+
+struct PlProduct {
+  const float *A;     // [M][lda]
+  int lda, M, K;
+  const float *gain;  // of the norm: A is x * gain, and the sums are multiplied by its row factor (NULL: A as it is)
+  float eps;
+  const void *W;      // [K][ldw]
+  int ldw, N;         // N: columns of the result (GLU: of gate, and as many of up behind them)
+  float *out;         // RESID: added to; GLU: the SwiGLU; QKV: q
+  int ldo;
+  // QKV: rotation table [row][pair][2], this layer's cache, where the block's rows go
+  const float *cs;
+  void *Kc, *Vc;
+  int Hq, Hkv, dh, max_len;
+  const int32_t *L_dev;
+  int32_t *err, *err_map;
+};
+
+// One product.  A workgroup takes 16 columns and all rows; its eight waves share the contraction, 16 deep at a time (the same order as
+// gemm_generic_kernel's), NP slices of it on their way at once, and their sums are added in gemm_generic_kernel's order, an element per thread.
+//   QKV: eight channels of the lower half of a head and their rotation partners; rotates, and writes K and V to the cache.
+//   GLU: eight channels of gate and the same of up.
+// Bound: a launch, the weights' way from memory (each is read by one wave) and the sums' through LDS.  Step of the tiny shape (256
+// wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below.
+template <typename T, int MT, int KIND, int NP>
+__global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) {
+  __shared__ __attribute__((aligned(16))) float part[PL_WAVES * MT * 256];  // [wave][row tile][lane][4]
+  __shared__ float sqs[PL_WAVES * 64];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
+  const int t = blockIdx.x, K = p.K, M = p.M, per = p.dh >> 4, head = KIND == PL_QKV ? t / per : 0, jj = t - head * per, half = p.dh >> 1;
+  // source column (columns past the end read the last one, their results are dropped)
+  int col;
+  if (KIND == PL_QKV) col = head * p.dh + (c16 < 8 ? 8 * jj + c16 : half + 8 * jj + c16 - 8);
+  else if (KIND == PL_GLU) col = (8 * t + (c16 & 7) < p.N ? 8 * t + (c16 & 7) : p.N - 1) + (c16 < 8 ? 0 : p.N);
+  else col = 16 * t + c16 < p.N ? 16 * t + c16 : p.N - 1;
+  const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
+  const bool vec = (((uintptr_t)p.A | (size_t)p.lda * 4) % 16 == 0) && K % 4 == 0;
+  int L = 0;
+  if (KIND == PL_QKV) L = *p.L_dev;
+  pl_f4 acc[MT];
+  float sq[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    acc[mt] = pl_f4{0.f, 0.f, 0.f, 0.f};
+    sq[mt] = 0.f;
+  }
+  for (int k0 = 16 * wave; k0 < K; k0 += 16 * PL_WAVES * NP) {
+    pl_f4 b[NP], g[NP], x[NP][MT];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const int k = k0 + 16 * PL_WAVES * n + 4 * q4;
+      if (k0 + 16 * PL_WAVES * n >= K) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[n][j] = pl_load<T>(rw, (unsigned)((k + j) * p.ldw + col));
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const unsigned o = (unsigned)((16 * mt + c16) * p.lda + k) * 4u;  // (rows past the end: zeros)
+        if (vec) {
+          x[n][mt] = __builtin_bit_cast(pl_f4, __builtin_amdgcn_raw_buffer_load_b128(ra, k < K ? o : PL_OOB, 0, 0));
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[n][mt][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, k + j < K ? o + 4u * j : PL_OOB, 0, 0));
+        }
+      }
+      if (p.gain) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[n][j] = pl_load<float>(rg, (unsigned)(k + j));
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      if (k0 + 16 * PL_WAVES * n >= K) continue;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v = x[n][mt][j];
+          if (p.gain) sq[mt] = fmaf(v, v, sq[mt]);
+          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(p.gain ? v * g[n][j] : v, b[n][j], acc[mt], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    reinterpret_cast<pl_f4 *>(part)[(wave * MT + mt) * 64 + lane] = acc[mt];
+    if (p.gain) {
+      sq[mt] += __shfl_xor(sq[mt], 16, 64);
+      sq[mt] += __shfl_xor(sq[mt], 32, 64);
+      if (q4 == 0) sqs[wave * 64 + 16 * mt + c16] = sq[mt];
+    }
+  }
+  __syncthreads();
+  if (KIND == PL_QKV && (L < 0 || L + M > p.max_len)) {
+    if (t == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
+      *p.err = 1;
+      __hip_atomic_store(p.err_map, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    return;
+  }
+  for (int it = threadIdx.x; it < 256 * MT; it += PL_THREADS) {
+    const int mt = it >> 8, r16 = (it >> 4) & 15, row = 16 * mt + r16, c = it & 15;
+    const float *pp = part + (size_t)(mt * 64 + 16 * (r16 >> 2) + c) * 4 + (r16 & 3);
+    constexpr int HALF = PL_WAVES / 2, WS = MT * 256;
+    float v = pp[HALF * WS] + pp[0];
+#pragma unroll
+    for (int w = 1; w < HALF; ++w) v += pp[(w + HALF) * WS] + pp[w * WS];
+    if (p.gain) {
+      float q = sqs[row];
+#pragma unroll
+      for (int w = 1; w < PL_WAVES; ++w) q += sqs[w * 64 + row];
+      v *= 1.0f / sqrtf(q / (float)K + p.eps);
+    }
+    const float other = KIND == PL_RESID ? 0.f : __shfl_xor(v, 8, 64);
+    if (row >= M) continue;
+    if (KIND == PL_QKV) {
+      const int ch = c < 8 ? 8 * jj + c : half + 8 * jj + c - 8;
+      float y = v;
+      if (head < p.Hq + p.Hkv) {
+        const float *cs = p.cs + ((size_t)row * half + 8 * jj + (c & 7)) * 2;
+        y = c < 8 ? v * cs[0] - other * cs[1] : v * cs[0] + other * cs[1];
+      }
+      if (head < p.Hq) p.out[(size_t)row * p.ldo + head * p.dh + ch] = y;
+      else if (head < p.Hq + p.Hkv) store_from_float<T>((T *)p.Kc + ((size_t)(L + row) * p.Hkv + head - p.Hq) * p.dh + ch, y);
+      else store_from_float<T>((T *)p.Vc + ((size_t)(L + row) * p.Hkv + head - p.Hq - p.Hkv) * p.dh + ch, y);
+    } else if (KIND == PL_GLU) {
+      if (c < 8 && 8 * t + c < p.N) p.out[(size_t)row * p.ldo + 8 * t + c] = v / (1.0f + expf(-v)) * other;
+    } else if (16 * t + c < p.N) {
+      p.out[(size_t)row * p.ldo + 16 * t + c] += v;
+    }
+  }
+}
+
+__device__ __forceinline__ float pl_wave_max(float v) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) v = fmaxf(v, __shfl_xor(v, w, 64));
+  return v;
+}
+__device__ __forceinline__ float pl_wave_sum(float v) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) v += __shfl_xor(v, w, 64);
+  return v;
+}
+
+// Attention: one workgroup per (row b, query head, 64 channels of the output; larger heads form their scores once per 64 channels).
+// A wave takes every eighth piece of 64 keys, a key per lane for the scores and a channel per lane for the output, with the running
+// maximum and sum; the waves are added in wave order.  A piece's V is requested before its scores are formed, the next piece's K
+// behind them.  A workgroup has eight waves, or as many as there can be pieces if those are fewer (the sums are the same).
+// Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
+// 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
+// 28 -> 12, L = 4000 108 -> 41.
+template <typename T>
+__global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float *q, int ldq, int Hq, int Hkv, int dh, const T *Kc, const T *Vc, const int32_t *L_dev,
+                                                                     int max_len, int Bp, const uint64_t *vis, float *out) {
+  __shared__ __attribute__((aligned(16))) float qs[256], ps[PL_WAVES][64], os[PL_WAVES][64 + 2];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int b = blockIdx.x, hq = blockIdx.y, u0 = 64 * blockIdx.z, L = *L_dev;
+  if (L < 0 || L + Bp > max_len) return;
+  const int kvh = hq / (Hq / Hkv), nkv = Hkv * dh, total = L + Bp, n_chunks = (total + 63) >> 6;
+  const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)total * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)total * nkv * sizeof(T));  // (rows past the end: zeros)
+  const uint64_t vb = vis[b];
+  const float scale = 1.0f / sqrtf((float)dh);
+  float kv[64], vv[64], m = -INFINITY, l = 0.f;
+  pl_f4 o = {0.f, 0.f, 0.f, 0.f};  // (every fourth key each)
+  auto load_k = [&](int ck, int c0) {  // channels c0 .. c0 + 63 of this lane's key
+    const unsigned at = (unsigned)((64 * ck + lane) * nkv + kvh * dh + c0);
+#pragma unroll
+    for (int c = 0; c < 64; c += 16)
+      if (c0 + c < dh) pl_load16<T>(kv + c, rk, at + (unsigned)c);  // (head_dim is a multiple of 16)
+  };
+  if (wave < n_chunks) load_k(wave, 0);
+  for (int i = threadIdx.x; i < dh; i += blockDim.x) qs[i] = q[(size_t)b * ldq + hq * dh + i];
+  __syncthreads();
+  for (int ck = wave; ck < n_chunks; ck += PL_WAVES) {
+    const int key = 64 * ck + lane;
+    unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));  // this lane's channel of the 64 keys
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+      vv[j] = pl_load<T>(rv, at);
+      at += (unsigned)nkv;
+      asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
+    }
+    float s0 = 0.f, s1 = 0.f;
+    for (int c0 = 0; c0 < dh; c0 += 64) {
+      if (c0 > 0) load_k(ck, c0);
+#pragma unroll
+      for (int c = 0; c < 64; c += 16)
+        if (c0 + c < dh) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 0; e < 16; e += 4) {
+            const pl_f4 qv = *reinterpret_cast<const pl_f4 *>(qs + c0 + c + e);
+            s0 = fmaf(qv[0], kv[c + e], s0);
+            s1 = fmaf(qv[1], kv[c + e + 1], s1);
+            s0 = fmaf(qv[2], kv[c + e + 2], s0);
+            s1 = fmaf(qv[3], kv[c + e + 3], s1);
+          }
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (ck + PL_WAVES < n_chunks) load_k(ck + PL_WAVES, 0);
+    const bool ok = key < total && (key < L || ((vb >> (key - L)) & 1ull));
+    const float v = ok ? (s0 + s1) * scale : -INFINITY;
+    const float m_new = fmaxf(m, pl_wave_max(v));
+    const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
+    const float p = ok ? expf(v - m_new) : 0.f;
+    l = l * corr + pl_wave_sum(p);
+    m = m_new;
+    o *= corr;
+    ps[wave][lane] = p;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // A probability of zero leaves its V row out: what a row does not see need not be finite.
+#pragma unroll
+    for (int j = 0; j < 64; j += 4) {
+      if (j % 16 == 0) __builtin_amdgcn_sched_barrier(0);
+      const pl_f4 pj = *reinterpret_cast<const pl_f4 *>(&ps[wave][j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = fmaf(pj[e], pj[e] != 0.f ? vv[j + e] : 0.f, o[e]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  os[wave][lane] = ((o[0] + o[1]) + o[2]) + o[3];
+  if (lane == 0) {
+    os[wave][64] = m;
+    os[wave][65] = l;
+  }
+  __syncthreads();
+  if (wave != 0 || u0 + lane >= dh) return;
+  const int n_w = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
+  float mm = -INFINITY, ll = 0.f, acc = 0.f;
+  for (int w = 0; w < n_w; ++w) mm = fmaxf(mm, os[w][64]);
+  for (int w = 0; w < n_w; ++w) {
+    const float f = os[w][64] == -INFINITY ? 0.f : expf(os[w][64] - mm);
+    ll = fmaf(os[w][65], f, ll);
+    acc = fmaf(os[w][lane], f, acc);
+  }
+  out[(size_t)b * (Hq * dh) + hq * dh + u0 + lane] = acc / ll;
+}
+
+// ---- host side --------------------------------------------------------------------------------------
+template <typename T>
+static int plain_attention(const float *q, int ldq, const la_model_desc &d, const T *Kc, const T *Vc, const la_kv *kv, int Bp, const uint64_t *vis, float *out,
+                           hipStream_t s) {
+  ProfScope ps("plain_attention", s);
+  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES ? pieces : PL_WAVES;  // (L_bound: no less than the length on the device)
+  plain_attention_kernel<T><<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev,
+                                                                                                   kv->max_len, Bp, vis, out);
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+
+template <typename T, int KIND, int NP>
+static int plain_product_np(const PlProduct &p, int n_tiles, hipStream_t s) {
+  switch (ceil_div(p.M, 16)) {
+  case 1: plain_product_kernel<T, 1, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
+  case 2: plain_product_kernel<T, 2, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
+  case 3: plain_product_kernel<T, 3, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
+  default: plain_product_kernel<T, 4, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
+  }
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+// (contractions of at most 256 need two slices a wave, and fewer registers)
+template <typename T, int KIND>
+static int plain_product(const char *name, const PlProduct &p, int n_tiles, hipStream_t s) {
+  ProfScope ps(name, s);
+  return p.K <= 2 * 16 * PL_WAVES ? plain_product_np<T, KIND, 2>(p, n_tiles, s) : plain_product_np<T, KIND, 6>(p, n_tiles, s);
+}
+
+}  // namespace la

@@ -1,0 +1,72 @@
+"""The launches of small plain layers (fp32 arithmetic, five a layer) at their edges: contractions around 256 and 768 (two and six
+slices of a wave, and several turns), widths that are no multiple of 8 or 16, heads of 16 to 256 channels, contexts around 64 and
+512 keys; and what a row does not see need not be finite.  Against the oracle at the bars of the plain kernels' test: 1e-4 per row
+in fp32, for 16-bit storage plus the rounding of the block's own K, V rows to the cache type."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import gpu_engine, oracle_model, prefill_both, row_rel_err
+from oracle import lookahead as ola
+from oracle import transformer as otf
+
+pytestmark = pytest.mark.gpu
+TOL = {"f32": 1e-4, "bf16": 2e-2, "f16": 2e-3}
+
+
+@pytest.mark.parametrize("dims,dtype,rows,L", [
+    # layers, d, q heads, kv heads, head_dim, F, vocab
+    ((2, 256, 4, 2, 64, 768, 100), "f32", 16, 48),
+    ((2, 257, 3, 1, 16, 769, 100), "f32", 17, 47),
+    ((1, 255, 4, 4, 48, 13, 100), "f32", 33, 511),
+    ((1, 772, 2, 1, 96, 1601, 100), "f32", 64, 449),
+    ((2, 60, 8, 2, 128, 100, 100), "f32", 1, 512),
+    ((1, 44, 2, 2, 256, 24, 100), "f32", 49, 1100),
+    ((1, 100, 4, 2, 32, 70, 200), "bf16", 48, 0),
+    ((1, 68, 4, 4, 80, 33, 50), "f16", 5, 600),
+    ((1, 1536, 6, 2, 128, 4096, 50), "f32", 17, 100),   # larger layers: this attention beside the general products
+])
+def test_small_plain_layers(dims, dtype, rows, L):
+    from paper_2602_16760_amd import binding as B
+    nl, d, hq, hkv, dh, F, V = dims
+    shape = synth.ModelShape(f"plain{d}", nl, d, hq, hkv, dh, F, V, 1e-5, 1e4, dtype)
+    om = oracle_model(shape, seed=3)
+    okv = otf.KVCache(shape, L + rows)
+    eng = gpu_engine(shape, L + rows, seed=3)
+    try:
+        if L:
+            prefill_both(shape, eng, okv, L)
+        pos, vis = ola.causal_block(L, rows)
+        x = synth.hidden_block(shape, rows, 1)
+        want = otf.forward_block(om, okv, x, pos, vis)
+        B.la_profile_enable(True)
+        got = eng.forward(x, pos, vis)
+        ran = B.la_profile_read()
+        B.la_profile_enable(False)
+        assert "plain_attention" in ran and ("plain_qkv" in ran) == (d < 1536)
+        assert row_rel_err(got, want).max() <= TOL[dtype]
+        again = eng.forward(x, pos, vis)
+        assert np.array_equal(got, again)
+    finally:
+        eng.close()
+
+
+def test_rows_that_are_not_seen_may_hold_anything():
+    """One row of the block is infinite: the rows that do not see it give what they give without it."""
+    shape = synth.SHAPES["tiny_f32"]
+    eng = gpu_engine(shape, 128, seed=4)
+    try:
+        x = synth.hidden_block(shape, 6, 2)
+        pos, vis = ola.causal_block(0, 6)
+        vis = [int(v) for v in vis]
+        vis[3] &= ~(1 << 2)  # rows 3 and 4 see neither row 2 nor a row that does
+        vis[4] &= ~(1 << 2)
+        want = eng.forward(x, pos, vis)
+        bad = x.copy()
+        bad[2] = np.inf
+        got = eng.forward(bad, pos, vis)
+        keep = [0, 1, 3, 4]
+        assert np.isfinite(want[keep]).all()
+        assert np.array_equal(got[keep], want[keep])
+    finally:
+        eng.close()
