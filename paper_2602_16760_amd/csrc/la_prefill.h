@@ -156,12 +156,12 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int wm = wave % WM, wn = wave / WM;
   const int n_cg = (p.ntiles - p.t_first + CTB - 1) / CTB, RB = (p.RT + RTB - 1) / RTB;
-  const int xcd = (int)blockIdx.x % 8;
-  int turn = (int)blockIdx.x / 8;
-  const int rb = turn % RB;
-  turn /= RB;
-  const int slice = turn % p.S, cg = (turn / p.S) * 8 + xcd;
-  if (cg >= n_cg) return;  // (the whole workgroup)
+  // An XCD takes a run of the tiles, row blocks first (they share the weights in its L2), and all XCDs as many, to one: with whole
+  // column groups dealt to them, some had a round of workgroups more than the chip needs (7B shape, 700 rows: down
+  // 166 -> 91 us, O 61 -> 36; 1300 rows: 298 -> 160, 101 -> 57; 1600 rows: gate/up 452 -> 390; 12B shape, 300 rows: down 121 -> 67).
+  const int tiles = RB * p.S * n_cg, per_xcd = (tiles + 7) / 8, turn = (int)blockIdx.x / 8, tile = ((int)blockIdx.x % 8) * per_xcd + turn;
+  if (tile >= tiles || turn >= per_xcd) return;  // (the whole workgroup)
+  const int rb = tile % RB, slice = tile / RB % p.S, cg = tile / (RB * p.S);
   const int row0 = p.KT * slice / p.S, row1 = p.KT * (slice + 1) / p.S, n_kt = row1 - row0;
   const unsigned lds0 = (unsigned)(uintptr_t)pf_lds;
   // what this wave brings of a k-tile: fragments wave * LPW ..; 0 .. RTB - 1 are the activations' row tiles
@@ -616,7 +616,7 @@ static int pf_launch_tile(const PfGemm &p, hipStream_t s, bool prepare) {
     return LA_OK;
   }
   const int n_cg = ceil_div(p.ntiles - p.t_first, WN * NTW), RB = ceil_div(p.RT, 4 * WM);
-  pf_tile_kernel<MODE, WM, WN, NTW, NS><<<RB * p.S * ((n_cg + 7) / 8 * 8), 64 * WM * WN, bytes, s>>>(p);
+  pf_tile_kernel<MODE, WM, WN, NTW, NS><<<(RB * p.S * n_cg + 7) / 8 * 8, 64 * WM * WN, bytes, s>>>(p);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }

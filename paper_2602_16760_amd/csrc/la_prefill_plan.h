@@ -81,11 +81,8 @@ struct PfProduct {
   int RT, M, KT, n_tiles, d;  // row tiles of the buffers, rows, k-tiles, column tiles wanted, row length of the products
 };
 // Tile and number of slices of the contraction by estimated time: whole rounds of the chip's CUs times the k-tiles of a
-// slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  Against every tile and
-// split at 90 .. 2048 rows of the 7B and 12B shapes and a 2048-wide one, 77 of 99 O, gate/up and down products are within 5 % of
-// the fastest.  The chip is taken for one pool of CUs, but the column groups are dealt to eight XCDs: where an XCD's share is more than its 32
-// CUs hold, there is a round that the estimate does not see (7B, 700 rows, three slices: down 166 us against 109, O 62 against
-// 38; 7B, 1300 rows: down 303 against 191; 12B, 300 rows: down 121 against 75).  Only
+// slice, and the slices' products written and read once (8 bytes an element at about 4.5 TB/s).  (The tiles are dealt to the eight
+// XCDs evenly, so that the chip counts as one pool of CUs.)  Only
 // the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
 // for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
 inline void pf_choose(const PfProduct &p, int max_split, int part_rows, int cus, int &tile, int &S) {
