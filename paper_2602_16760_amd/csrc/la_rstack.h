@@ -79,8 +79,6 @@ constexpr int lds_bytes() { return NW * Lay<MT, NW>::REG + M_BYTES + NW * (16 + 
 // control words (32-bit, at M_CTL)
 constexpr int K_DEAD = 0;      // a wait timed out: every wave leaves the kernel
 constexpr int K_IOBAR = 1;     // arrivals at the IO-wave barrier
-constexpr int K_GPASS = 2;     // last grid-barrier epoch seen released
-constexpr int K_FAR = 3;       // a workgroup runs on another XCD than its group of the grid barrier is named after
 constexpr int K_ALAND = 8;     // [8..15] per MFMA wave: operand k-tiles landed in its ring (monotonic over the launch)
 constexpr int K_ADONE = 16;    // [16..23] per MFMA wave: operand k-tiles it has read
 constexpr int K_PDONE = 24;    // [24..31] per MFMA wave: passes whose partial tile is in LDS
@@ -614,10 +612,11 @@ __device__ __forceinline__ bool io_barrier(Io &io) {
 // word queue up), a store or a load in the XCD's own L2 under 200.  So there are no atomics: workgroup i belongs to group i % 8
 // (its XCD, as workgroups are dealt out), every IO wave stores the epoch into a word of its own of its group, one wave of the
 // group's first workgroup polls them all and stores the epoch into a word of each of the eight groups' lines, and every workgroup
-// polls its own group's line: one trip between XCDs.  Alone 1.84 -> 1.40 us (256 workgroups; counters per 16 workgroups, a top
+// polls its own group's line, each IO wave for itself: one trip between XCDs.  Alone 1.84 -> 1.40 us (256 workgroups; counters per 16 workgroups, a top
 // counter and one release word before); in the kernel small_bf16 (15 phases, 31 rows) 129.8 -> 122.7 us, the 7B shape's 30 layers,
 // L = 512, one row 2894 -> 2867, 32 rows 3250 -> 3200, 24 layers, L = 2048, 43 rows 3132 -> 3079.  A sleep between polls, or one
-// word per workgroup behind a barrier of its IO waves, is slower.  Everything here has to stay wave-uniform (uni): a result
+// word per workgroup behind a barrier of its IO waves, is slower; one wave polling for the four and telling them through LDS costs
+// 1.2 us a step of small_bf16.  Everything here has to stay wave-uniform (uni): a result
 // that the compiler takes for divergent turns the phases after it into per-lane loops (+ 0.5 us a phase).
 // The first barrier of a launch makes no assumption about where workgroups run: its words are stored for the whole device, and
 // carry a bit where a workgroup is not on the XCD its group is named after.  If any carries it, all words of the launch are stored
@@ -685,20 +684,14 @@ __device__ __forceinline__ bool io_grid_arrive(const StackArgs &a, Io &io, unsig
 template <int NIO>
 __device__ __forceinline__ bool io_grid_wait(const StackArgs &a, Io &io, unsigned epoch) {
   const int G = (int)gridDim.x, wg = (int)blockIdx.x;
-  bool ok = true, far;
-  if (io.v == 0) {
-    ok = io_poll_words<1>(a, io, a.sync + GB_GROUPS * GB_GROUP_WORDS + GB_LINE * (wg % GB_GROUPS), G < GB_GROUPS ? G : GB_GROUPS, epoch, &far);
-    if (ok && io.lane == 0) {
-      ctl_write(io.ctl + 4 * K_FAR, far ? 1u : 0u);
-      ctl_write(io.ctl + 4 * K_GPASS, epoch);
-    }
-  }
-  if (!ok && io.lane == 0) {
+  bool far;
+  const bool ok = io_poll_words<1>(a, io, a.sync + GB_GROUPS * GB_GROUP_WORDS + GB_LINE * (wg % GB_GROUPS), G < GB_GROUPS ? G : GB_GROUPS, epoch, &far);
+  if (ok) {
+    if (epoch == a.epoch0 + 1u) io.near = !far;
+  } else if (io.lane == 0) {
     raise_error(a, 4);
     ctl_write(io.ctl + 4 * K_DEAD, 1u);
   }
-  ok = io_wait_ge(io, K_GPASS, epoch) && ok;
-  if (epoch == a.epoch0 + 1u) io.near = uni((int)(ctl_read(io.ctl + 4 * K_FAR) == 0)) != 0;
   io_mark(io, 8);
   return uni((int)ok) != 0;
 }
