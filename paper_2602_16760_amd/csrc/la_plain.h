@@ -189,9 +189,10 @@ __device__ __forceinline__ float pl_wave_sum(float v) {
 }
 
 // Attention: one workgroup per (row b, query head, 64 channels of the output; larger heads form their scores once per 64 channels).
-// A wave takes every eighth piece of 64 keys, a key per lane for the scores and a channel per lane for the output, with the running
+// A wave takes every eighth piece of 64 keys (every n_waves-th), a key per lane for the scores and a channel per lane for the output, with the running
 // maximum and sum; the waves are added in wave order.  A piece's V is requested before its scores are formed, the next piece's K
-// behind them.  A workgroup has eight waves, or as many as there can be pieces if those are fewer (the sums are the same).
+// behind them.  A workgroup has eight waves, or as many as the host's bound on the length allows pieces if those are fewer (the sums
+// are the same).  Accepts that a replayed graph makes leave that bound behind the length: waves then take more pieces each.
 // Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
 // 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
 // 28 -> 12, L = 4000 108 -> 41.
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
                                                                      int max_len, int Bp, const uint64_t *vis, float *out) {
   __shared__ __attribute__((aligned(16))) float qs[256], ps[PL_WAVES][64], os[PL_WAVES][64 + 2];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int b = blockIdx.x, hq = blockIdx.y, u0 = 64 * blockIdx.z, L = *L_dev;
+  const int n_waves = (int)blockDim.x >> 6, b = blockIdx.x, hq = blockIdx.y, u0 = 64 * blockIdx.z, L = *L_dev;
   if (L < 0 || L + Bp > max_len) return;
   const int kvh = hq / (Hq / Hkv), nkv = Hkv * dh, total = L + Bp, n_chunks = (total + 63) >> 6;
   const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)total * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)total * nkv * sizeof(T));  // (rows past the end: zeros)
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   if (wave < n_chunks) load_k(wave, 0);
   for (int i = threadIdx.x; i < dh; i += blockDim.x) qs[i] = q[(size_t)b * ldq + hq * dh + i];
   __syncthreads();
-  for (int ck = wave; ck < n_chunks; ck += PL_WAVES) {
+  for (int ck = wave; ck < n_chunks; ck += n_waves) {
     const int key = 64 * ck + lane;
     unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));  // this lane's channel of the 64 keys
 #pragma unroll
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (ck + PL_WAVES < n_chunks) load_k(ck + PL_WAVES, 0);
+    if (ck + n_waves < n_chunks) load_k(ck + n_waves, 0);
     const bool ok = key < total && (key < L || ((vb >> (key - L)) & 1ull));
     const float v = ok ? (s0 + s1) * scale : -INFINITY;
     const float m_new = fmaxf(m, pl_wave_max(v));
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   }
   __syncthreads();
   if (wave != 0 || u0 + lane >= dh) return;
-  const int n_w = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
+  const int n_w = n_chunks < n_waves ? n_chunks : n_waves;
   float mm = -INFINITY, ll = 0.f, acc = 0.f;
   for (int w = 0; w < n_w; ++w) mm = fmaxf(mm, os[w][64]);
   for (int w = 0; w < n_w; ++w) {
@@ -290,7 +291,10 @@ template <typename T>
 static int plain_attention(const float *q, int ldq, const la_model_desc &d, const T *Kc, const T *Vc, const la_kv *kv, int Bp, const uint64_t *vis, float *out,
                            hipStream_t s) {
   ProfScope ps("plain_attention", s);
-  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES ? pieces : PL_WAVES;  // (L_bound: no less than the length on the device)
+  // L_bound is no less than the length on the device now; a captured launch serves the lengths of its replays, and has every wave
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  LA_HIP(hipStreamIsCapturing(s, &capture));
+  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && capture == hipStreamCaptureStatusNone ? pieces : PL_WAVES;
   plain_attention_kernel<T><<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev,
                                                                                                    kv->max_len, Bp, vis, out);
   LA_HIP(hipGetLastError());

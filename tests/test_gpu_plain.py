@@ -70,3 +70,51 @@ def test_rows_that_are_not_seen_may_hold_anything():
         assert np.array_equal(got[keep], want[keep])
     finally:
         eng.close()
+
+
+def test_lengths_that_replayed_accepts_reach():
+    """A captured forward and accept, replayed until the cache holds more pieces of 64 keys than it did when it was captured, and
+    behind that an eager forward, whose host knows nothing of the replays: a captured launch sums as one that knows the length (the
+    same bits), the eager one in another order (the plain kernels' bar)."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    shape, L0, rows = synth.SHAPES["tiny_f32"], 40, 16
+    eng = gpu_engine(shape, 400, seed=5)
+    okv = otf.KVCache(shape, 400)
+    stream = torch.cuda.Stream()
+    try:
+        prefill_both(shape, eng, okv, 300)
+        x = torch.from_numpy(np.ascontiguousarray(synth.hidden_block(shape, rows, 3), dtype=np.float32)).cuda()
+        pos, vis = (B.to_device(a) for a in B.la_causal_layout(L0, rows))
+        state, emitted, h = B.new_state(), torch.zeros(300, dtype=torch.int32, device="cuda"), x.clone()
+        B.la_jacobi_init(eng.kv, 1, B.to_device(np.zeros(L0 + 1, dtype=np.int32)), 1, state)
+        ids = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+        def forward():
+            h.copy_(x)
+            B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)
+
+        forward()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            forward()
+            B.la_jacobi_accept(eng.kv, 1, ids, state, emitted, 300)
+        for n in (1, 30, 60, 150):
+            for _ in range(n):
+                graph.replay()
+            got = h.clone()
+            forward()  # (at the length behind the last accept)
+            stale = h.clone()
+            L = int(B.la_kv_get_len(eng.kv))
+            forward()
+            assert row_rel_err(stale.cpu().numpy(), h.cpu().numpy()).max() <= TOL["f32"]
+            B.la_kv_set_len(eng.kv, L - 1)
+            forward()
+            assert torch.equal(got, h), L
+            B.la_kv_set_len(eng.kv, L)
+            torch.cuda.synchronize()
+        assert L == L0 + 241
+    finally:
+        torch.cuda.synchronize()
+        eng.close()
