@@ -175,6 +175,11 @@ int la_embed(la_model *m, const int32_t *tok, int Bp, float *hidden, void *strea
  * residual, RMSNorm, SwiGLU MLP + residual.
  * hidden: device float [Bp, d], in/out.  pos: device int32 [Bp].  vis: device uint64 [Bp];
  * every row must see at least itself.  Does not change L.
+ * May be captured into a graph, like la_unembed_argmax and la_prefill, and replayed between other calls
+ * on the model (in stream order, as they use the model's scratch memory).  On the matrix-core path a
+ * captured launch has a small fill kernel in front of it, and the model has to have run a block since
+ * its last la_model_set_layer (the first one uploads the layers' gain pointers and synchronises).  What replays add
+ * to L is not part of the host-side bound below.
  * LA_EINVAL: Bp not in 1..LA_MAX_ROWS or a NULL pointer; LA_ERANGE: layer range outside the
  * model, or the host-side bound on L plus Bp exceeds max_len. */
 int la_forward_layers(la_model *m, int layer_begin, int layer_end, float *hidden, int Bp,

@@ -235,9 +235,19 @@ int recover_if_needed(la_model *m, hipStream_t s) {
   if (!m->recover) return LA_OK;
   set_i32_kernel<<<1, 1, 0, s>>>(m->err_dev, 0);
   LA_HIP(hipGetLastError());
-  if (m->mf) mfma_reset_sync(m, s);
+  if (m->mf) {
+    const int rc = mfma_reset_sync(m, s);
+    if (rc) return rc;
+  }
   m->recover = false;
   return LA_OK;
+}
+
+bool stream_captures(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // (the next launch's check would report it)
+  return true;
 }
 }  // namespace la
 

@@ -102,6 +102,9 @@ struct la_pool {
 namespace la {
 // Non-blocking: reports (once) an error that a kernel of an earlier launch on this model stored to its host word.
 int pending_error(const la_model *m);
+// Whether what is enqueued on `s` goes into a graph, which may run it any number of times; true where the runtime does not tell (it
+// refuses to for the legacy stream while a blocking stream captures), so what is done for a graph has to be right without one.
+bool stream_captures(hipStream_t s);
 // Clears the error word and the barrier words on `s` after an error was reported, so that the next launch starts clean.
 int recover_if_needed(la_model *m, hipStream_t s);
 #define LA_PENDING(m)                     \
@@ -128,7 +131,7 @@ int mfma_forward(la_model *m, int lb, int le, float *hidden, int Bp, const int32
                  const uint64_t *vis, la_kv *kv, hipStream_t s);
 int mfma_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2,
                         hipStream_t s);
-void mfma_reset_sync(la_model *m, hipStream_t s);
+int mfma_reset_sync(la_model *m, hipStream_t s);
 int mfma_prefill_rows(la_model *m, int n, int *rows);  // of a large-M chunk of an n-token prompt, buffers allocated; 0: block kernel
 int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0, hipStream_t s);
 int mfma_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2,

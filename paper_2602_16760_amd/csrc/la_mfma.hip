@@ -6,6 +6,7 @@
 #include <mutex>
 #include <new>
 
+#include "la_barrier.h"
 #include "la_rstack.h"
 
 namespace la {
@@ -164,7 +165,7 @@ struct MfmaModel {
   unsigned *sync = nullptr;
   unsigned *sched[3][2] = {};  // register-streaming kernel: schedule tables per ring depth (32, 24, 16 slots) and mode (stack, unembedding)
   int32_t *zero_len = nullptr;  // a cache length of 0: the unembedding has no cache to overflow
-  unsigned epoch = 0;
+  BarrierEpochs epochs;
   unsigned long long *trace = nullptr;  // LA_TRACE=1: per-phase timestamps, printed after each launch
   int trace_phases = 0;
   PfBuffers pf, pf_few;
@@ -215,10 +216,14 @@ void mfma_destroy(la_model *m) {
   m->mf = nullptr;
 }
 
-void mfma_reset_sync(la_model *m, hipStream_t s) {
-  MfmaModel *f = m->mf;
+static int clear_sync(MfmaModel *f, hipStream_t s) {
   zero_u32_kernel<<<ceil_div(SYNC_STRIDE * 66, 256), 256, 0, s>>>(f->sync, SYNC_STRIDE * 66);
-  f->epoch = 0;
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+int mfma_reset_sync(la_model *m, hipStream_t s) {
+  m->mf->epochs.cleared(stream_captures(s));
+  return clear_sync(m->mf, s);
 }
 
 static int na_setup(int device);  // address of the static scratch array on this device (defined with its entry point below)
@@ -270,6 +275,7 @@ int mfma_create(la_model *m) {
   f->ucu_bytes = (size_t)(((size_t)f->p_un.nt_max * f->p_un.KT + CHUNK - 1) / CHUNK * CHUNK) * 1024;
   LA_REQUIRE(f->ucu_bytes < ((size_t)1 << 31), LA_EINVAL, "one CU's unembedding stream exceeds 2 GiB");
   f->host_gains.resize(d.n_layers);
+  f->epochs.init((unsigned)std::max(5 * d.n_layers, 2), !f->use_r);  // (five barriers a layer; the unembedding's two)
   size_t R = LA_MAX_ROWS, nl = d.n_layers;
   size_t QR = (size_t)g * MAX_MT * 16;
   int n_sync = SYNC_STRIDE * 66;
@@ -405,17 +411,17 @@ int mfma_set_head(la_model *m, const void *unembed, hipStream_t s) {
 static GemmDev dev_plan(const GemmPlan &p) { return GemmDev{p.KT, p.ntiles, p.ntp}; }
 
 // fresh_sync: a.sync was cleared on `s` just before and does not belong to the model, so the launch starts at barrier
-// epoch 0 and leaves the model's epoch alone; such launches are not traced.
+// epoch 0 and leaves the model's epochs alone; such launches are not traced.
 static int launch_stack(const char *name, MfmaModel *f, StackArgs a, int n_barriers, hipStream_t s, bool fresh_sync = false) {
   if (fresh_sync) {
     a.epoch0 = 0;
   } else {
-    if (f->epoch > (1u << 26)) {  // keep the monotonic counters far from wrapping
-      zero_u32_kernel<<<ceil_div(SYNC_STRIDE * 66, 256), 256, 0, s>>>(f->sync, SYNC_STRIDE * 66);
-      f->epoch = 0;
+    const BarrierEpochs::Launch at = f->epochs.launch((unsigned)n_barriers, stream_captures(s));
+    if (at.clear) {
+      const int rc = clear_sync(f, s);
+      if (rc) return rc;
     }
-    a.epoch0 = f->epoch;
-    f->epoch += (unsigned)n_barriers;
+    a.epoch0 = at.epoch0;
   }
   a.n_groups = (unsigned)ceil_div(f->n_wgs, SYNC_GROUP);
   a.sched = f->sched[a.MT <= 2 ? 0 : a.MT == 3 ? 1 : 2][a.mode];

@@ -1,0 +1,106 @@
+"""Calls of the matrix-core path's block kernel captured into a graph: every replay, with eager calls between them, gives what the
+eager call gives, bit for bit."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import gpu_engine
+from test_gpu_prefill_buffers import _model
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("env", [{}, {"LA_WGS": "37"}, {"LA_LDS_RING": "1"}])
+def test_replayed_layers_and_head(monkeypatch, env):
+    """(LA_LDS_RING: the earlier persistent kernel, whose barrier counts arrivals.)"""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    shape, L, rows = synth.SHAPES["small_bf16"], 45, 31
+    eng = gpu_engine(shape, L + rows, seed=3)
+    stream = torch.cuda.Stream()
+    try:
+        for l in range(shape.n_layers):
+            eng.fill_kv(l, *synth.kv_fill(shape, l, L, 4))
+        B.la_kv_set_len(eng.kv, L)
+        pos, vis = (B.to_device(a) for a in B.la_lookahead_layout(5, 4, 5, L, 5, rows))
+        blocks = [torch.from_numpy(np.ascontiguousarray(synth.hidden_block(shape, rows, s), dtype=np.float32)).cuda() for s in range(3)]
+        x = blocks[0].clone()
+
+        def buffers():
+            return x.clone(), torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros((rows, 2), device="cuda")
+
+        def step(h, ids, top2):
+            h.copy_(x)
+            B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)
+            B.la_unembed_argmax(eng.model, h, ids, top2)
+
+        want, eager, captured = [], buffers(), buffers()
+        for b in blocks:
+            x.copy_(b)
+            step(*eager)
+            want.append([t.clone() for t in eager])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            step(*captured)
+        for turn, between in enumerate((0, 1, 0, 3, 1, 2)):
+            x.copy_(blocks[turn % 3])
+            for t in captured:
+                t.zero_()
+            graph.replay()
+            for got, w in zip(captured, want[turn % 3]):
+                assert torch.equal(got, w), f"replay {turn}"
+            for k in range(between):
+                x.copy_(blocks[k])
+                step(*eager)
+                for got, w in zip(eager, want[k]):
+                    assert torch.equal(got, w), f"eager call {k} behind replay {turn}"
+        torch.cuda.synchronize()
+        assert B.la_kv_get_len(eng.kv) == L  # (no error is pending either)
+    finally:
+        torch.cuda.synchronize()
+        eng.close()
+
+
+def test_replayed_short_prompt():
+    """A prompt that goes through the block kernel."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    n, sh = 50, replace(synth.SHAPES["small_bf16"], vocab=512)
+    models = [_model(sh) for _ in range(2)]
+    kvs = [B.la_kv_alloc(m, 320) for m in models]
+    tok = torch.zeros(n, device="cuda", dtype=torch.int32)
+    stream = torch.cuda.Stream()
+
+    def rows(kv):
+        out = [[torch.empty((n, sh.n_kv_heads, sh.head_dim), dtype=torch.bfloat16, device="cuda") for _ in "kv"] for _ in range(sh.n_layers)]
+        for l, r in enumerate(out):
+            B.la_kv_read(kv, l, 0, n, *r)
+        return [x for r in out for x in r]
+
+    try:
+        B.la_prefill(models[0], kvs[0], tok[:40], 0)  # (a model's first block uploads its gains and waits)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.la_prefill(models[0], kvs[0], tok, 0)
+        for turn in range(5):
+            tok.copy_(torch.arange(n, device="cuda", dtype=torch.int32) * (7 + turn) % sh.vocab)
+            graph.replay()
+            got = rows(kvs[0])
+            assert B.la_kv_get_len(kvs[0]) == n
+            B.la_prefill(models[1], kvs[1], tok, 0)
+            assert all(torch.equal(a, b) for a, b in zip(got, rows(kvs[1]))), f"replay {turn}"
+            for k in range(turn % 3):
+                B.la_prefill(models[0], kvs[0], tok[:31 + k], 0)  # (the model goes on being used between the replays)
+            torch.cuda.synchronize()
+    finally:
+        torch.cuda.synchronize()
+        for kv in kvs:
+            B.la_free_kv(kv)
+        for m in models:
+            B.la_free_model(m)
