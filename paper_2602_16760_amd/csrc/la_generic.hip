@@ -51,6 +51,7 @@ __device__ __forceinline__ float block_max(float v, float *red) {
 // (2 layers of the tiny shape, 17 rows: 256 x 512 28 us, 688 x 256 70 us; now 4 - 6 us a launch).
 //   gain != NULL: A is x * gain and the sums are multiplied by the row factor 1 / sqrt(mean x^2 + eps) of the norm.
 //   GLU: C[M, F] = silu(gate) * up.
+//   L_dev != NULL: C stays as it is where M rows behind the length *L_dev do not fit the cache (the block is skipped as a whole).
 // A lane's four contraction indices of a turn are consecutive: the k-th matrix instruction of the turn takes the k-th of
 // them from every lane, in both operands alike.
 enum GemmKind { GEMM_16 = 0, GEMM_WIDE = 1, GEMM_GLU = 2 };
@@ -59,13 +60,14 @@ constexpr int GEMM_WAVES = 8;
 
 template <typename T, int MT, int KIND>
 __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const float *A, int lda, const float *gain, float eps, const T *W, int ldw,
-                                                                       float *C, int ldc, int M, int K, int N, int accumulate, int vec) {
+                                                                       float *C, int ldc, int M, int K, int N, int accumulate, int vec, const int32_t *L_dev, int max_len) {
   constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1, HALF = GEMM_WAVES / 2;
   extern __shared__ __attribute__((aligned(16))) float gemm_lds[];
   f4 *part = reinterpret_cast<f4 *>(gemm_lds);                     // [wave of the lower half][MT][CT][lane]
   float *sqs = gemm_lds + HALF * MT * CT * 64 * 4;           // [wave][16 MT] sums of squares
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
   const int c0 = blockIdx.x * (KIND == GEMM_WIDE ? 64 : 16);
+  const int L = L_dev ? *L_dev : 0;
   // (columns past the end read the last one; their results are dropped)
   int col[CT];
 #pragma unroll
@@ -144,6 +146,7 @@ __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const flo
 #pragma unroll
     for (int n = 0; n < MT * CT; ++n) mine[n * 64] = acc[n / CT][n % CT] + mine[n * 64];
   __syncthreads();
+  if (L_dev && (L < 0 || L + M > max_len)) return;
   // a wave finishes a row tile's columns: the same lane layout as the products (column c16, rows 4 q4 + i)
   for (int it = wave; it < MT * (KIND == GEMM_GLU ? 1 : CT); it += GEMM_WAVES) {
     const int mt = KIND == GEMM_GLU ? it : it / CT, ct = KIND == GEMM_GLU ? 0 : it % CT;
@@ -345,34 +348,37 @@ int launch_argmax_rows(const float *logits, int Bp, int V, int32_t *ids, float *
 
 template <typename T, int KIND>
 static int gemm_kind(int MT, dim3 grid, hipStream_t s, const float *A, int lda, const float *gain, float eps, const T *W, int ldw, float *C, int ldc, int M,
-                     int K, int N, int accumulate, int vec) {
+                     int K, int N, int accumulate, int vec, const int32_t *L_dev, int max_len) {
   constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1;
   const size_t lds = (size_t)GEMM_WAVES * MT * (CT * 32 * 4 + 16) * sizeof(float);
   switch (MT) {
-  case 1: gemm_generic_kernel<T, 1, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
-  case 2: gemm_generic_kernel<T, 2, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec); break;
+  case 1: gemm_generic_kernel<T, 1, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len); break;
+  case 2: gemm_generic_kernel<T, 2, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len); break;
   default:
     if constexpr (KIND != GEMM_WIDE) {  // (two row tiles at most)
-      if (MT == 3) gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec);
-      else gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec);
+      if (MT == 3) gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
+      else gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
     }
   }
   LA_HIP(hipGetLastError());
   return LA_OK;
 }
 
-// N: columns of C (GLU: half the columns of W).  64 columns per workgroup once that alone gives each of 256 CUs some, up to two
+// N: columns of C (GLU: half the columns of W).  into: C is added to, unless the block does not fit this cache.
+// 64 columns per workgroup once that alone gives each of 256 CUs some, up to two
 // row tiles (16 columns / 64, us): 4096 x 32768 179 / 144 at one row, 253 / 158 at 32; 1024 x 16384 25 / 21 and 29 / 26;
 // 1024 x 8192 14 / 21 and 18 / 26.
 template <typename T>
 static int gemm(const char *name, const float *A, int lda, const float *gain, float eps, const void *W, int ldw, float *C, int ldc, int M, int K,
-                int N, int accumulate, bool glu, hipStream_t s) {
+                int N, const la_kv *into, bool glu, hipStream_t s) {
   ProfScope p(name, s);
+  const int32_t *L_dev = into ? into->L_dev : nullptr;
+  const int accumulate = into != nullptr, max_len = into ? into->max_len : 0;
   const int MT = ceil_div(M, 16), vec = ((uintptr_t)A | (size_t)lda * 4) % 16 == 0;
-  if (glu) return gemm_kind<T, GEMM_GLU>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
+  if (glu) return gemm_kind<T, GEMM_GLU>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
   if (N >= 64 * 256 && MT <= 2)
-    return gemm_kind<T, GEMM_WIDE>(MT, ceil_div(N, 64), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
-  return gemm_kind<T, GEMM_16>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec);
+    return gemm_kind<T, GEMM_WIDE>(MT, ceil_div(N, 64), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
+  return gemm_kind<T, GEMM_16>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
 }
 
 // la_plain.h's attention takes heads that are whole groups of 16 channels and a layer's cache within 32-bit offsets; beside the
@@ -436,7 +442,7 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
     LA_REQUIRE(w.set, LA_EINVAL, "layer %d has no weights", l);
     T *Kc = (T *)kv->K + (size_t)l * kv->layer_elems();
     T *Vc = (T *)kv->V + (size_t)l * kv->layer_elems();
-    if ((rc = gemm<T>("gemm_qkv", hidden, dm, w.g_attn, d.rms_eps, w.wqkv, nqkv, m->qkv, nqkv, Bp, dm, nqkv, 0, false, s))) return rc;
+    if ((rc = gemm<T>("gemm_qkv", hidden, dm, w.g_attn, d.rms_eps, w.wqkv, nqkv, m->qkv, nqkv, Bp, dm, nqkv, nullptr, false, s))) return rc;
     {
       ProfScope p("rope_kvwrite", s);
       rope_kvwrite_kernel<T><<<Bp, 256, 0, s>>>(m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, m->rope_cs, Kc, Vc,
@@ -449,9 +455,9 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
       attention_generic_kernel<T><<<dim3(Bp, d.n_q_heads), 256, 0, s>>>(
           m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev, kv->max_len, Bp, vis, m->attn);
     }
-    if ((rc = gemm<T>("gemm_o", m->attn, qd, nullptr, 0.f, w.wo, dm, hidden, dm, Bp, qd, dm, 1, false, s))) return rc;
-    if ((rc = gemm<T>("gemm_gateup", hidden, dm, w.g_mlp, d.rms_eps, w.wgu, 2 * F, m->act, F, Bp, dm, F, 0, true, s))) return rc;
-    if ((rc = gemm<T>("gemm_down", m->act, F, nullptr, 0.f, w.wdown, dm, hidden, dm, Bp, F, dm, 1, false, s))) return rc;
+    if ((rc = gemm<T>("gemm_o", m->attn, qd, nullptr, 0.f, w.wo, dm, hidden, dm, Bp, qd, dm, kv, false, s))) return rc;
+    if ((rc = gemm<T>("gemm_gateup", hidden, dm, w.g_mlp, d.rms_eps, w.wgu, 2 * F, m->act, F, Bp, dm, F, nullptr, true, s))) return rc;
+    if ((rc = gemm<T>("gemm_down", m->act, F, nullptr, 0.f, w.wdown, dm, hidden, dm, Bp, F, dm, kv, false, s))) return rc;
     LA_HIP(hipGetLastError());
   }
   return LA_OK;
@@ -469,7 +475,7 @@ int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *id
   int rc;
   auto head = [&](auto t) {
     using T = decltype(t);
-    return gemm<T>("gemm_unembed", hidden, d.d_model, m->g_final, d.rms_eps, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, 0, false, s);
+    return gemm<T>("gemm_unembed", hidden, d.d_model, m->g_final, d.rms_eps, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, nullptr, false, s);
   };
   rc = d.dtype == LA_F32 ? head(float{}) : d.dtype == LA_F16 ? head(_Float16{}) : head(uint16_t{});
   if (rc) return rc;

@@ -55,12 +55,14 @@ struct PlProduct {
   int ldw, N;         // N: columns of the result (GLU: of gate, and as many of up behind them)
   float *out;         // RESID: added to; GLU: the SwiGLU; QKV: q
   int ldo;
+  // a block that does not fit the cache behind its length is skipped as a whole: QKV reports it, RESID leaves `out` as it is
+  const int32_t *L_dev;
+  int max_len;
+  int32_t *err, *err_map;
   // QKV: rotation table [row][pair][2], this layer's cache, where the block's rows go
   const float *cs;
   void *Kc, *Vc;
-  int Hq, Hkv, dh, max_len;
-  const int32_t *L_dev;
-  int32_t *err, *err_map;
+  int Hq, Hkv, dh;
 };
 
 // One product.  A workgroup takes 16 columns and all rows; its eight waves share the contraction, 16 deep at a time (the same order as
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
   const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
   const bool vec = (((uintptr_t)p.A | (size_t)p.lda * 4) % 16 == 0) && K % 4 == 0;
   int L = 0;
-  if (KIND == PL_QKV) L = *p.L_dev;
+  if (KIND != PL_GLU) L = *p.L_dev;
   pl_f4 acc[MT];
   float sq[MT];
 #pragma unroll
@@ -137,8 +139,8 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
     }
   }
   __syncthreads();
-  if (KIND == PL_QKV && (L < 0 || L + M > p.max_len)) {
-    if (t == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
+  if (KIND != PL_GLU && (L < 0 || L + M > p.max_len)) {
+    if (KIND == PL_QKV && t == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
       *p.err = 1;
       __hip_atomic_store(p.err_map, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
