@@ -294,9 +294,7 @@ static int plain_attention(const float *q, int ldq, const la_model_desc &d, cons
                            hipStream_t s) {
   ProfScope ps("plain_attention", s);
   // L_bound is no less than the length on the device now; a captured launch serves the lengths of its replays, and has every wave
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  LA_HIP(hipStreamIsCapturing(s, &capture));
-  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && capture == hipStreamCaptureStatusNone ? pieces : PL_WAVES;
+  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && !stream_captures(s) ? pieces : PL_WAVES;
   plain_attention_kernel<T><<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev,
                                                                                                    kv->max_len, Bp, vis, out);
   LA_HIP(hipGetLastError());

@@ -104,3 +104,42 @@ def test_replayed_short_prompt():
             B.la_free_kv(kv)
         for m in models:
             B.la_free_model(m)
+
+
+@pytest.mark.parametrize("name", ["tiny_f32", "small_bf16"])
+def test_the_legacy_stream_beside_a_capture(name):
+    """While a blocking stream captures, the runtime does not tell whether the legacy stream does; a block on it runs as ever."""
+    import ctypes as C
+    import torch
+    from paper_2602_16760_amd import binding as B
+    hip = C.CDLL("libamdhip64.so")
+    shape, rows, L = synth.SHAPES[name], 17, 40
+    eng = gpu_engine(shape, 100, seed=3)
+    blocking, graph = C.c_void_p(), C.c_void_p()
+    try:
+        for l in range(shape.n_layers):
+            eng.fill_kv(l, *synth.kv_fill(shape, l, L, 4))
+        B.la_kv_set_len(eng.kv, L)
+        pos, vis = (B.to_device(a) for a in B.la_causal_layout(L, rows))
+        x = torch.from_numpy(np.ascontiguousarray(synth.hidden_block(shape, rows, 3), dtype=np.float32)).cuda()
+        want, got = x.clone(), [x.clone() for _ in range(3)]
+        B.la_forward_layers(eng.model, 0, shape.n_layers, want, pos, vis, eng.kv)
+        torch.cuda.synchronize()
+        assert torch.cuda.current_stream().cuda_stream == 0
+        assert hip.hipStreamCreate(C.byref(blocking)) == 0
+        assert hip.hipStreamBeginCapture(blocking, 2) == 0  # (relaxed: the thread's other calls stay allowed)
+        try:
+            for h in got[:2]:
+                B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)
+        finally:
+            assert hip.hipStreamEndCapture(blocking, C.byref(graph)) == 0
+        B.la_forward_layers(eng.model, 0, shape.n_layers, got[2], pos, vis, eng.kv)
+        torch.cuda.synchronize()
+        assert all(torch.equal(h, want) for h in got)
+    finally:
+        if graph:
+            hip.hipGraphDestroy(graph)
+        if blocking:
+            hip.hipStreamDestroy(blocking)
+        torch.cuda.synchronize()
+        eng.close()
