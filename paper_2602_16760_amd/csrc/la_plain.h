@@ -191,10 +191,11 @@ __device__ __forceinline__ float pl_wave_sum(float v) {
 }
 
 // Attention: one workgroup per (row b, query head, 64 channels of the output; larger heads form their scores once per 64 channels).
-// A wave takes every eighth piece of 64 keys (every n_waves-th), a key per lane for the scores and a channel per lane for the output, with the running
-// maximum and sum; the waves are added in wave order.  A piece's V is requested before its scores are formed, the next piece's K
-// behind them.  A workgroup has eight waves, or as many as the host's bound on the length allows pieces if those are fewer (the sums
-// are the same).  Accepts that a replayed graph makes leave that bound behind the length: waves then take more pieces each.
+// The keys go in pieces of 64 to eight shares, piece k to share k % 8, and a wave takes a share: a key per lane for the scores and a
+// channel per lane for the output, with the running maximum and sum; the shares are added in order.  A piece's V is requested before its
+// scores are formed, the share's next K behind them.  A workgroup has eight waves, or as many as the host's bound on the length
+// allows pieces if those are fewer.  That is a matter of time only: accepts that a replayed graph makes leave the bound behind the length, and waves
+// then take more than one share each, so that the sums depend on the length alone.
 // Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
 // 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
 // 28 -> 12, L = 4000 108 -> 41.
@@ -209,78 +210,82 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)total * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)total * nkv * sizeof(T));  // (rows past the end: zeros)
   const uint64_t vb = vis[b];
   const float scale = 1.0f / sqrtf((float)dh);
-  float kv[64], vv[64], m = -INFINITY, l = 0.f;
-  pl_f4 o = {0.f, 0.f, 0.f, 0.f};  // (every fourth key each)
+  float kv[64], vv[64];
   auto load_k = [&](int ck, int c0) {  // channels c0 .. c0 + 63 of this lane's key
     const unsigned at = (unsigned)((64 * ck + lane) * nkv + kvh * dh + c0);
 #pragma unroll
     for (int c = 0; c < 64; c += 16)
       if (c0 + c < dh) pl_load16<T>(kv + c, rk, at + (unsigned)c);  // (head_dim is a multiple of 16)
   };
-  if (wave < n_chunks) load_k(wave, 0);
+  const int n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
+  if (wave < n_shares) load_k(wave, 0);
   for (int i = threadIdx.x; i < dh; i += blockDim.x) qs[i] = q[(size_t)b * ldq + hq * dh + i];
   __syncthreads();
-  for (int ck = wave; ck < n_chunks; ck += n_waves) {
-    const int key = 64 * ck + lane;
-    unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));  // this lane's channel of the 64 keys
+  for (int share = wave; share < n_shares; share += n_waves) {
+    float m = -INFINITY, l = 0.f;
+    pl_f4 o = {0.f, 0.f, 0.f, 0.f};  // (every fourth key each)
+    if (share != wave) load_k(share, 0);
+    for (int ck = share; ck < n_chunks; ck += PL_WAVES) {
+      const int key = 64 * ck + lane;
+      unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));  // this lane's channel of the 64 keys
 #pragma unroll
-    for (int j = 0; j < 64; ++j) {
-      vv[j] = pl_load<T>(rv, at);
-      at += (unsigned)nkv;
-      asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
-    }
-    float s0 = 0.f, s1 = 0.f;
-    for (int c0 = 0; c0 < dh; c0 += 64) {
-      if (c0 > 0) load_k(ck, c0);
+      for (int j = 0; j < 64; ++j) {
+        vv[j] = pl_load<T>(rv, at);
+        at += (unsigned)nkv;
+        asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
+      }
+      float s0 = 0.f, s1 = 0.f;
+      for (int c0 = 0; c0 < dh; c0 += 64) {
+        if (c0 > 0) load_k(ck, c0);
 #pragma unroll
-      for (int c = 0; c < 64; c += 16)
-        if (c0 + c < dh) {
-          __builtin_amdgcn_sched_barrier(0);
+        for (int c = 0; c < 64; c += 16)
+          if (c0 + c < dh) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int e = 0; e < 16; e += 4) {
-            const pl_f4 qv = *reinterpret_cast<const pl_f4 *>(qs + c0 + c + e);
-            s0 = fmaf(qv[0], kv[c + e], s0);
-            s1 = fmaf(qv[1], kv[c + e + 1], s1);
-            s0 = fmaf(qv[2], kv[c + e + 2], s0);
-            s1 = fmaf(qv[3], kv[c + e + 3], s1);
+            for (int e = 0; e < 16; e += 4) {
+              const pl_f4 qv = *reinterpret_cast<const pl_f4 *>(qs + c0 + c + e);
+              s0 = fmaf(qv[0], kv[c + e], s0);
+              s1 = fmaf(qv[1], kv[c + e + 1], s1);
+              s0 = fmaf(qv[2], kv[c + e + 2], s0);
+              s1 = fmaf(qv[3], kv[c + e + 3], s1);
+            }
           }
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (ck + n_waves < n_chunks) load_k(ck + n_waves, 0);
-    const bool ok = key < total && (key < L || ((vb >> (key - L)) & 1ull));
-    const float v = ok ? (s0 + s1) * scale : -INFINITY;
-    const float m_new = fmaxf(m, pl_wave_max(v));
-    const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
-    const float p = ok ? expf(v - m_new) : 0.f;
-    l = l * corr + pl_wave_sum(p);
-    m = m_new;
-    o *= corr;
-    ps[wave][lane] = p;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // A probability of zero leaves its V row out: what a row does not see need not be finite.
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (ck + PL_WAVES < n_chunks) load_k(ck + PL_WAVES, 0);
+      const bool ok = key < total && (key < L || ((vb >> (key - L)) & 1ull));
+      const float v = ok ? (s0 + s1) * scale : -INFINITY;
+      const float m_new = fmaxf(m, pl_wave_max(v));
+      const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
+      const float p = ok ? expf(v - m_new) : 0.f;
+      l = l * corr + pl_wave_sum(p);
+      m = m_new;
+      o *= corr;
+      ps[wave][lane] = p;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // A probability of zero leaves its V row out: what a row does not see need not be finite.
 #pragma unroll
-    for (int j = 0; j < 64; j += 4) {
-      if (j % 16 == 0) __builtin_amdgcn_sched_barrier(0);
-      const pl_f4 pj = *reinterpret_cast<const pl_f4 *>(&ps[wave][j]);
+      for (int j = 0; j < 64; j += 4) {
+        if (j % 16 == 0) __builtin_amdgcn_sched_barrier(0);
+        const pl_f4 pj = *reinterpret_cast<const pl_f4 *>(&ps[wave][j]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = fmaf(pj[e], pj[e] != 0.f ? vv[j + e] : 0.f, o[e]);
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(pj[e], pj[e] != 0.f ? vv[j + e] : 0.f, o[e]);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-  os[wave][lane] = ((o[0] + o[1]) + o[2]) + o[3];
-  if (lane == 0) {
-    os[wave][64] = m;
-    os[wave][65] = l;
+    os[share][lane] = ((o[0] + o[1]) + o[2]) + o[3];
+    if (lane == 0) {
+      os[share][64] = m;
+      os[share][65] = l;
+    }
   }
   __syncthreads();
   if (wave != 0 || u0 + lane >= dh) return;
-  const int n_w = n_chunks < n_waves ? n_chunks : n_waves;
   float mm = -INFINITY, ll = 0.f, acc = 0.f;
-  for (int w = 0; w < n_w; ++w) mm = fmaxf(mm, os[w][64]);
-  for (int w = 0; w < n_w; ++w) {
+  for (int w = 0; w < n_shares; ++w) mm = fmaxf(mm, os[w][64]);
+  for (int w = 0; w < n_shares; ++w) {
     const float f = os[w][64] == -INFINITY ? 0.f : expf(os[w][64] - mm);
     ll = fmaf(os[w][65], f, ll);
     acc = fmaf(os[w][lane], f, acc);
@@ -293,7 +298,7 @@ template <typename T>
 static int plain_attention(const float *q, int ldq, const la_model_desc &d, const T *Kc, const T *Vc, const la_kv *kv, int Bp, const uint64_t *vis, float *out,
                            hipStream_t s) {
   ProfScope ps("plain_attention", s);
-  // L_bound is no less than the length on the device now; a captured launch serves the lengths of its replays, and has every wave
+  // (a captured launch serves the lengths of its replays, and has every wave)
   const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && !stream_captures(s) ? pieces : PL_WAVES;
   plain_attention_kernel<T><<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev,
                                                                                                    kv->max_len, Bp, vis, out);

@@ -118,3 +118,50 @@ def test_lengths_that_replayed_accepts_reach():
     finally:
         torch.cuda.synchronize()
         eng.close()
+
+
+@pytest.mark.parametrize("dims,dtype", [
+    ((2, 256, 4, 2, 64, 688, 100), "f32"),
+    ((1, 1536, 6, 2, 128, 4096, 50), "bf16"),  # (this attention beside the general products)
+])
+def test_sums_depend_on_the_length_alone(dims, dtype):
+    """What the host knows of the length decides how many waves a workgroup of the attention has, not what a row becomes: the same
+    bits behind replayed accepts, which the host knows nothing of, and once it has asked for the length."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    nl, d, hq, hkv, dh, F, V = dims
+    shape, L0, rows = synth.ModelShape(f"bound{d}", nl, d, hq, hkv, dh, F, V, 1e-5, 1e4, dtype), 40, 16
+    eng = gpu_engine(shape, 700, seed=5)
+    try:
+        for l in range(nl):
+            eng.fill_kv(l, *synth.kv_fill(shape, l, 640, 4))
+        x = torch.from_numpy(np.ascontiguousarray(synth.hidden_block(shape, rows, 3), dtype=np.float32)).cuda()
+        pos, vis = (B.to_device(a) for a in B.la_causal_layout(L0, rows))
+        state, emitted = B.new_state(), torch.zeros(700, dtype=torch.int32, device="cuda")
+        B.la_jacobi_init(eng.kv, 1, B.to_device(np.zeros(L0 + 1, dtype=np.int32)), 1, state)
+        ids = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+        def forward():
+            h = x.clone()
+            B.la_profile_enable(True)
+            B.la_forward_layers(eng.model, 0, nl, h, pos, vis, eng.kv)
+            torch.cuda.synchronize()
+            B.la_profile_enable(False)
+            assert "plain_attention" in B.la_profile_read()
+            return h
+
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            B.la_jacobi_accept(eng.kv, 1, ids, state, emitted, 700)
+        for n in (60, 100, 250, 180):  # 2, 4, 8 pieces of 64 keys and a part, 10 and a part
+            for _ in range(n):
+                graph.replay()
+            torch.cuda.synchronize()
+            behind = forward()
+            L = int(B.la_kv_get_len(eng.kv))
+            assert torch.equal(behind, forward()), L
+        assert L == L0 + 590
+    finally:
+        torch.cuda.synchronize()
+        eng.close()
