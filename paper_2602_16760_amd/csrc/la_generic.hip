@@ -389,18 +389,27 @@ static bool plain_heads(const la_model *m, const la_kv *kv) { return m->d.head_d
 static bool plain_attention_pays(const la_model *m, const la_kv *kv, int Bp) {
   return plain_heads(m, kv) && Bp * m->d.n_q_heads * ceil_div(m->d.head_dim, 64) <= 1024;
 }
-// Its products take layers that also fit 32-bit offsets and are small: more loads on their way and fewer launches gain there, a pass
-// over the activations per eight columns of gate costs where there are many.  A forward of two fp32 layers at 1 / 17 / 37 / 64 rows,
-// L = 47, and at 17 rows, L = 3000, us, before -> now: 256 wide (2.8 MB a layer) 50 / 63 / 73 / 80, 222 -> 40 / 50 / 62 / 72, 111;
-// 512 wide (11 MB) 68 / 85 / 102 / 115, 244 -> 54 / 70 / 88 / 108, 134; 768 wide (24 MB) 83 / 105 / 126 / 145, 264 -> 74 / 93 / 116 / 145, 155.
-// 1024 wide (43 MB) they would take 95 / 128 / 165 / 208 against the general ones' 96 / 124 / 152 / 176.
-constexpr size_t PL_LAYER_BYTES = (size_t)32 << 20;
+// Its products take layers that also fit 32-bit offsets, of up to 16 M weights, whose products are one round of the chip each: a workgroup
+// of eight waves with six slices of its operands on their way has a CU to itself, with two slices (contractions of at most 256)
+// there is room for two.  A second round reads all activations again and waits as long as the first.  Both sides of the lines, a forward of two
+// layers at 1 / 17 / 48 / 64 rows, L = 47, us, these products (the general ones):
+//   512 wide, 2048 of gate: bf16 68 / - / 109 / 127 (72 / - / 111 / 124), fp32 60 / - / 104 / 123 (71 / - / 111 / 125)
+//   512 wide, 2064 of gate: bf16 70 / - / 119 / 138 (73 / - / 110 / 122), fp32 62 / - / 114 / 135 (72 / - / 111 / 123)
+//   256 wide, 4096 of gate: bf16 80 / 102 / 127 / 149 (83 / 106 / 128 / 143), fp32 66 / 92 / 122 / 145 (81 / 103 / 126 / 142)
+//   256 wide, 8192 of gate: bf16 119 / 152 / 201 / 243 (125 / 157 / 192 / 220), fp32 94 / 135 / 184 / 225 (121 / 150 / 188 / 215)
+//   1024 wide, 2752 of gate: bf16 104 / 132 / - / 208 (99 / 125 / - / 175), fp32 92 / 124 / - / 205 (100 / 126 / - / 176)
+//   1536 wide, 2048 of gate (16.5 M): bf16 110 / - / 177 / 212 (110 / - / 182 / 210), fp32 109 / - / 167 / 200 (109 / - / 180 / 207)
+//   2048 wide, 2048 of gate (25 M): bf16 130 / - / 201 / 250 (129 / - / 213 / 250), fp32 137 / - / 206 / 249 (127 / - / 211 / 249)
+// The rule does not ask for the rows: the two kinds of products round differently, and a row must not depend on the block it is in.
+constexpr size_t PL_LAYER_WEIGHTS = (size_t)1 << 24;
+static bool plain_round(int K, int workgroups) { return workgroups <= (K <= 2 * 16 * PL_WAVES ? 2 : 1) * 256; }
 static bool plain_layers(const la_model *m, const la_kv *kv) {
   const la_model_desc &d = m->d;
   const size_t qd = m->qdim(), dm = d.d_model, F = d.d_ffn, pad = 16 * PL_WAVES * 6;
   for (size_t n : {(dm + pad) * m->nqkv(), (qd + pad) * dm, (dm + pad) * 2 * F, (F + pad) * dm, (LA_MAX_ROWS + 1) * (dm + qd + F) + pad})
     if (n * 4 >= (size_t)1 << 31) return false;
-  return plain_heads(m, kv) && (dm * (m->nqkv() + qd) + 3 * dm * F) * m->esize <= PL_LAYER_BYTES;
+  return plain_heads(m, kv) && dm * (m->nqkv() + qd) + 3 * dm * F <= PL_LAYER_WEIGHTS && plain_round(dm, m->nqkv() / 16) && plain_round(dm, ceil_div(F, 8)) &&
+         plain_round(qd, ceil_div(dm, 16)) && plain_round(F, ceil_div(dm, 16));
 }
 
 template <typename T>

@@ -165,3 +165,36 @@ def test_sums_depend_on_the_length_alone(dims, dtype):
     finally:
         torch.cuda.synchronize()
         eng.close()
+
+
+@pytest.mark.parametrize("dims,dtype,small", [
+    # layers, d, q heads, kv heads, head_dim, F, vocab
+    ((1, 512, 8, 4, 48, 2048, 50), "bf16", True),     # 256 workgroups for gate and up
+    ((1, 264, 4, 2, 48, 2056, 50), "f16", False),     # 257
+    ((1, 768, 12, 6, 80, 2064, 50), "bf16", False),   # 258
+    ((1, 256, 4, 2, 48, 4096, 50), "bf16", True),     # 512, of the kernel with two slices
+    ((1, 256, 4, 2, 48, 4100, 50), "f32", False),     # 513
+    ((1, 272, 172, 43, 16, 64, 50), "f32", False),    # 258 for QKV
+    ((1, 1536, 8, 8, 64, 2048, 50), "f32", True),     # 12.6 M weights
+    ((1, 1792, 20, 10, 64, 2048, 50), "f32", False),  # 17.9 M
+])
+def test_layers_of_one_round_take_the_small_products(dims, dtype, small):
+    """Both sides of the rule's lines, for either size of element; against the oracle at the bars above."""
+    from paper_2602_16760_amd import binding as B
+    nl, d, hq, hkv, dh, F, V = dims
+    shape, L, rows = synth.ModelShape(f"round{d}", nl, d, hq, hkv, dh, F, V, 1e-5, 1e4, dtype), 47, 17
+    om, okv = oracle_model(shape, seed=3), otf.KVCache(shape, L + rows)
+    eng = gpu_engine(shape, L + rows, seed=3)
+    try:
+        prefill_both(shape, eng, okv, L)
+        pos, vis = ola.causal_block(L, rows)
+        x = synth.hidden_block(shape, rows, 1)
+        want = otf.forward_block(om, okv, x, pos, vis)
+        B.la_profile_enable(True)
+        got = eng.forward(x, pos, vis)
+        ran = B.la_profile_read()
+        B.la_profile_enable(False)
+        assert ("plain_qkv" in ran) == small and ("gemm_qkv" in ran) != small
+        assert row_rel_err(got, want).max() <= TOL[dtype]
+    finally:
+        eng.close()
