@@ -2,6 +2,8 @@
 // LA_BF16 models whose shape the MFMA kernels do not cover.  These shapes are small (the tiny
 // decoder of the test configuration), so what counts is launches: the norms and SwiGLU are part
 // of the products, six launches a layer; five (la_plain.h) where layers and heads allow it.
+#include <type_traits>
+
 #include "la_device.h"
 #include "la_internal.h"
 #include "la_plain.h"
@@ -51,23 +53,24 @@ __device__ __forceinline__ float block_max(float v, float *red) {
 // (2 layers of the tiny shape, 17 rows: 256 x 512 28 us, 688 x 256 70 us; now 4 - 6 us a launch).
 //   gain != NULL: A is x * gain and the sums are multiplied by the row factor 1 / sqrt(mean x^2 + eps) of the norm.
 //   GLU: C[M, F] = silu(gate) * up.
-//   L_dev != NULL: C stays as it is where M rows behind the length *L_dev do not fit the cache (the block is skipped as a whole).
+//   ADD: C is added to; it stays as it is where M rows behind the length *L_dev do not fit the cache (the block is skipped as a whole).
+//   The length is requested behind the contraction, while the waves' sums come together (in front of it it held up the first operands: a
+//   forward of two fp32 layers 1280 wide, 17 rows, 150 us against 146, 146 without the look at it).
 // A lane's four contraction indices of a turn are consecutive: the k-th matrix instruction of the turn takes the k-th of
 // them from every lane, in both operands alike.
 enum GemmKind { GEMM_16 = 0, GEMM_WIDE = 1, GEMM_GLU = 2 };
 typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int GEMM_WAVES = 8;
 
-template <typename T, int MT, int KIND>
+template <typename T, int MT, int KIND, bool ADD>
 __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const float *A, int lda, const float *gain, float eps, const T *W, int ldw,
-                                                                       float *C, int ldc, int M, int K, int N, int accumulate, int vec, const int32_t *L_dev, int max_len) {
+                                                                       float *C, int ldc, int M, int K, int N, int vec, const int32_t *L_dev, int max_len) {
   constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1, HALF = GEMM_WAVES / 2;
   extern __shared__ __attribute__((aligned(16))) float gemm_lds[];
   f4 *part = reinterpret_cast<f4 *>(gemm_lds);                     // [wave of the lower half][MT][CT][lane]
   float *sqs = gemm_lds + HALF * MT * CT * 64 * 4;           // [wave][16 MT] sums of squares
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
   const int c0 = blockIdx.x * (KIND == GEMM_WIDE ? 64 : 16);
-  const int L = L_dev ? *L_dev : 0;
   // (columns past the end read the last one; their results are dropped)
   int col[CT];
 #pragma unroll
@@ -129,6 +132,8 @@ __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const flo
         for (int ct = 0; ct < CT; ++ct) acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[ct][j], acc[mt][ct], 0, 0, 0);
       }
   }
+  int L = 0;
+  if constexpr (ADD) L = (int)__builtin_amdgcn_raw_buffer_load_b32(pl_rsrc(L_dev, 4), 0, 0, 0);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
     if (gain) {
@@ -146,7 +151,7 @@ __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const flo
 #pragma unroll
     for (int n = 0; n < MT * CT; ++n) mine[n * 64] = acc[n / CT][n % CT] + mine[n * 64];
   __syncthreads();
-  if (L_dev && (L < 0 || L + M > max_len)) return;
+  if (ADD && (L < 0 || L + M > max_len)) return;
   // a wave finishes a row tile's columns: the same lane layout as the products (column c16, rows 4 q4 + i)
   for (int it = wave; it < MT * (KIND == GEMM_GLU ? 1 : CT); it += GEMM_WAVES) {
     const int mt = KIND == GEMM_GLU ? it : it / CT, ct = KIND == GEMM_GLU ? 0 : it % CT;
@@ -171,7 +176,7 @@ __global__ __launch_bounds__(64 * GEMM_WAVES) void gemm_generic_kernel(const flo
       float v = s[i] * r;
       if (KIND == GEMM_GLU) v = v / (1.0f + expf(-v)) * (u[i] * r);
       float *cp = C + (size_t)row * ldc + c;
-      *cp = accumulate ? *cp + v : v;
+      *cp = ADD ? *cp + v : v;
     }
   }
 }
@@ -346,18 +351,18 @@ int launch_argmax_rows(const float *logits, int Bp, int V, int32_t *ids, float *
   return LA_OK;
 }
 
-template <typename T, int KIND>
+template <typename T, int KIND, bool ADD>
 static int gemm_kind(int MT, dim3 grid, hipStream_t s, const float *A, int lda, const float *gain, float eps, const T *W, int ldw, float *C, int ldc, int M,
-                     int K, int N, int accumulate, int vec, const int32_t *L_dev, int max_len) {
+                     int K, int N, int vec, const int32_t *L_dev, int max_len) {
   constexpr int CT = KIND == GEMM_WIDE ? 4 : KIND == GEMM_GLU ? 2 : 1;
   const size_t lds = (size_t)GEMM_WAVES * MT * (CT * 32 * 4 + 16) * sizeof(float);
   switch (MT) {
-  case 1: gemm_generic_kernel<T, 1, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len); break;
-  case 2: gemm_generic_kernel<T, 2, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len); break;
+  case 1: gemm_generic_kernel<T, 1, KIND, ADD><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, vec, L_dev, max_len); break;
+  case 2: gemm_generic_kernel<T, 2, KIND, ADD><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, vec, L_dev, max_len); break;
   default:
     if constexpr (KIND != GEMM_WIDE) {  // (two row tiles at most)
-      if (MT == 3) gemm_generic_kernel<T, 3, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
-      else gemm_generic_kernel<T, 4, KIND><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
+      if (MT == 3) gemm_generic_kernel<T, 3, KIND, ADD><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, vec, L_dev, max_len);
+      else gemm_generic_kernel<T, 4, KIND, ADD><<<grid, 64 * GEMM_WAVES, lds, s>>>(A, lda, gain, eps, W, ldw, C, ldc, M, K, N, vec, L_dev, max_len);
     }
   }
   LA_HIP(hipGetLastError());
@@ -372,13 +377,17 @@ template <typename T>
 static int gemm(const char *name, const float *A, int lda, const float *gain, float eps, const void *W, int ldw, float *C, int ldc, int M, int K,
                 int N, const la_kv *into, bool glu, hipStream_t s) {
   ProfScope p(name, s);
-  const int32_t *L_dev = into ? into->L_dev : nullptr;
-  const int accumulate = into != nullptr, max_len = into ? into->max_len : 0;
   const int MT = ceil_div(M, 16), vec = ((uintptr_t)A | (size_t)lda * 4) % 16 == 0;
-  if (glu) return gemm_kind<T, GEMM_GLU>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
+  auto run = [&](auto kind, auto add, int wgs) {
+    return gemm_kind<T, decltype(kind)::value, decltype(add)::value>(MT, wgs, s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, vec,
+                                                                     into ? into->L_dev : nullptr, into ? into->max_len : 0);
+  };
+  using std::bool_constant;
+  using std::integral_constant;
+  if (glu) return run(integral_constant<int, GEMM_GLU>{}, bool_constant<false>{}, ceil_div(N, 16));
   if (N >= 64 * 256 && MT <= 2)
-    return gemm_kind<T, GEMM_WIDE>(MT, ceil_div(N, 64), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
-  return gemm_kind<T, GEMM_16>(MT, ceil_div(N, 16), s, A, lda, gain, eps, (const T *)W, ldw, C, ldc, M, K, N, accumulate, vec, L_dev, max_len);
+    return into ? run(integral_constant<int, GEMM_WIDE>{}, bool_constant<true>{}, ceil_div(N, 64)) : run(integral_constant<int, GEMM_WIDE>{}, bool_constant<false>{}, ceil_div(N, 64));
+  return into ? run(integral_constant<int, GEMM_16>{}, bool_constant<true>{}, ceil_div(N, 16)) : run(integral_constant<int, GEMM_16>{}, bool_constant<false>{}, ceil_div(N, 16));
 }
 
 // la_plain.h's attention takes heads that are whole groups of 16 channels and a layer's cache within 32-bit offsets; beside the
