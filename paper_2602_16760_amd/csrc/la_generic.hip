@@ -391,12 +391,14 @@ static int gemm(const char *name, const float *A, int lda, const float *gain, fl
 }
 
 // la_plain.h's attention takes heads that are whole groups of 16 channels and a layer's cache within 32-bit offsets; beside the
-// general products it runs where its workgroups are a few rounds of the chip (a row, a head and 64 channels each; two 2048-wide
-// layers with 16 heads of 128, L = 47, 17 rows 287 against 290 us, L = 3000 577 / 633, but 64 rows 420 / 405; 4096 wide, 32 heads,
-// L = 3000, 17 rows 1156 / 1074).
+// general products it runs where its workgroups (a row, a head and 64 channels each) are a few rounds of the chip for the fullest
+// block: two bf16 layers 1024 wide, 16 heads of 64, L = 47, 17 / 64 rows 125 / 174 us against 126 / 180, L = 3000, 64 rows 371 / 408. Twice the
+// workgroups (2048 wide, 16 heads of 128): L = 47, 17 / 64 rows 287 / 420 against 290 / 405, L = 3000, 17 rows 577 / 633; four times (4096
+// wide, 32 heads), L = 3000, 17 rows 1156 / 1074.  Not by the rows of a block: a row must not depend on the block it is in, and the two
+// kernels sum in different orders.
 static bool plain_heads(const la_model *m, const la_kv *kv) { return m->d.head_dim % 16 == 0 && kv->layer_elems() * m->esize < (size_t)1 << 31; }
-static bool plain_attention_pays(const la_model *m, const la_kv *kv, int Bp) {
-  return plain_heads(m, kv) && Bp * m->d.n_q_heads * ceil_div(m->d.head_dim, 64) <= 1024;
+static bool plain_attention_pays(const la_model *m, const la_kv *kv) {
+  return plain_heads(m, kv) && m->d.n_q_heads * ceil_div(m->d.head_dim, 64) <= 16;
 }
 // Its products take layers that also fit 32-bit offsets, of up to 16 M weights, whose products are one round of the chip each: a workgroup
 // of eight waves with six slices of its operands on their way has a CU to itself, with two slices (contractions of at most 256)
@@ -466,7 +468,7 @@ static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const i
       rope_kvwrite_kernel<T><<<Bp, 256, 0, s>>>(m->qkv, d.n_q_heads, d.n_kv_heads, d.head_dim, m->rope_cs, Kc, Vc,
                                                  kv->L_dev, kv->max_len, Bp, kv->err_dev, m->err_map);
     }
-    if (plain_attention_pays(m, kv, Bp)) {
+    if (plain_attention_pays(m, kv)) {
       if ((rc = plain_attention<T>(m->qkv, nqkv, d, Kc, Vc, kv, Bp, vis, m->attn, s))) return rc;
     } else {
       ProfScope p("attention", s);

@@ -198,3 +198,32 @@ def test_layers_of_one_round_take_the_small_products(dims, dtype, small):
         assert row_rel_err(got, want).max() <= TOL[dtype]
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("dims,dtype,attention", [
+    ((1, 256, 4, 2, 64, 688, 50), "f32", "plain_attention"),
+    ((1, 512, 16, 4, 48, 2064, 50), "bf16", "plain_attention"),  # general products
+    ((1, 512, 16, 4, 128, 6000, 50), "f32", "attention"),        # 32 workgroups a row
+    ((1, 512, 17, 17, 64, 6000, 50), "f32", "attention"),
+])
+def test_a_row_does_not_depend_on_the_block_it_is_in(dims, dtype, attention):
+    """The first rows of a causal block, in blocks of every height: the same bits, from the same kernels."""
+    from paper_2602_16760_amd import binding as B
+    nl, d, hq, hkv, dh, F, V = dims
+    shape, L, most = synth.ModelShape(f"rows{d}", nl, d, hq, hkv, dh, F, V, 1e-5, 1e4, dtype), 300, 64
+    eng = gpu_engine(shape, L + most, seed=3)
+    try:
+        eng.fill_kv(0, *synth.kv_fill(shape, 0, L, 4))
+        B.la_kv_set_len(eng.kv, L)
+        pos, vis = ola.causal_block(L, most)
+        x, last = synth.hidden_block(shape, most, 1), None
+        for rows in (most, 49, 33, 32, 17, 16, 1):
+            B.la_profile_enable(True)
+            got = eng.forward(x[:rows], pos[:rows], vis[:rows])
+            ran = B.la_profile_read()
+            B.la_profile_enable(False)
+            assert last is None or np.array_equal(got, last[:rows]), rows
+            assert attention in ran
+            last = got
+    finally:
+        eng.close()
