@@ -283,7 +283,7 @@ int la_causal_layout(int t, int n, int32_t *pos_host, uint64_t *vis_host);
 
 /* Sets how long a workgroup polls for a grid barrier's release (in units of about a
  * microsecond) before it gives up and the launch reports LA_EHIP; 0 restores the default
- * (2^21, about two seconds).  Takes effect from the next launch on the model. */
+ * (2^21, about two seconds); 2^30 - 2 (18 minutes) is the most.  Takes effect from the next launch on the model. */
 int la_set_barrier_timeout(la_model *m, unsigned polls);
 
 /* ---- latency model of the split deployment (host arithmetic) --------------------------- */

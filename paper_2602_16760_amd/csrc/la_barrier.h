@@ -1,7 +1,18 @@
-// Host side of the persistent kernels' grid barrier (plain C++): which epochs a launch counts from.
+// The persistent kernels' grid barrier, what of it is plain C++: which epochs a launch counts from, and when a wait gives up.
 #pragma once
 
+#ifdef __HIPCC__
+#define LA_HD __host__ __device__
+#else
+#define LA_HD
+#endif
+
 namespace la {
+
+// A wait is patient for a number of units of about a microsecond, four polls each.
+constexpr unsigned PATIENCE = 1u << 21, PATIENCE_MOST = (1u << 30) - 2;  // (the most that 32 bits of polls can pass)
+inline unsigned barrier_patience(unsigned units) { return units == 0 ? PATIENCE : units < PATIENCE_MOST ? units : PATIENCE_MOST; }
+LA_HD inline bool patience_over(unsigned polls, unsigned units) { return (polls >> 2) > units; }
 
 // A launch of n barriers passes epochs e + 1 .. e + n and leaves them in the barrier words.  A wait ends on any word that has reached its
 // epoch, so what a launch finds there must be below its first.  A captured launch is replayed with the epoch that it was captured

@@ -73,7 +73,7 @@ struct la_model {
   int32_t *err_dev = nullptr;
   int32_t *err_host = nullptr, *err_map = nullptr;
   bool recover = false;          // an error was reported: the next launch clears err_dev and the barrier words first
-  unsigned barrier_spins = 0;    // polls of the grid barrier's release word before a workgroup gives up (0: the default)
+  unsigned barrier_spins = 0;    // units of about a microsecond that a wait at the grid barrier is patient for (0: the default)
   int nqkv() const { return (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim; }
   int qdim() const { return d.n_q_heads * d.head_dim; }
   int kvdim() const { return d.n_kv_heads * d.head_dim; }

@@ -6,7 +6,6 @@
 #include <mutex>
 #include <new>
 
-#include "la_barrier.h"
 #include "la_rstack.h"
 
 namespace la {
@@ -628,7 +627,7 @@ static StackArgs base_stack_args(la_model *m, int Bp) {
   a.att_cnt = f->att_cnt;
   a.err = m->err_dev;
   a.err_map = m->err_map;
-  a.spin_global = m->barrier_spins ? m->barrier_spins : SPIN_GLOBAL;
+  a.spin_global = barrier_patience(m->barrier_spins);
 #ifdef LA_EXPERIMENTS
   a.dbg = env_int("LA_DBG", 0);
 #endif

@@ -648,7 +648,7 @@ __device__ __forceinline__ bool io_poll_words(const StackArgs &a, const Io &io, 
       *far = uni((int)__any(bit)) != 0;
       return true;
     }
-    if ((++spins >> 2) > a.spin_global) return false;  // (four polls a microsecond)
+    if (patience_over(++spins, a.spin_global)) return false;
   }
 }
 template <int NIO>

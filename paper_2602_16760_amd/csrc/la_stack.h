@@ -42,6 +42,7 @@
 #pragma once
 #include <type_traits>
 
+#include "la_barrier.h"
 #include "la_device.h"
 #include "la_internal.h"
 
@@ -74,7 +75,6 @@ constexpr int NT_HINT = 2;                 // cache policy nt: streamed once
 constexpr int SYNC_GROUP = 16;             // workgroups per arrival counter of the grid barrier
 constexpr int SYNC_STRIDE = 64;            // 32-bit words between barrier variables (256 B)
 constexpr unsigned SPIN_LDS = 1u << 24;    // polls of an LDS word (~0.1 us each) before giving up
-constexpr unsigned SPIN_GLOBAL = 1u << 21; // polls of a global word (~1 us each) before giving up
 
 // LDS map (bytes)
 constexpr int LDS_RING = 0;
@@ -168,7 +168,7 @@ struct StackArgs {
   int max_len;
   int32_t *err;      // device error word: 1 the block does not fit the cache, 4 a grid barrier gave up
   int32_t *err_map;  // mapped host word that receives the same code (plain store), read by the host without synchronising
-  unsigned spin_global;  // polls of the barrier's release word before a workgroup gives up
+  unsigned spin_global;  // patience of a wait at the grid barrier, in units of about a microsecond
   // attention with the keys split over workgroups (register-streaming kernel): partial (o, m, l) records per
   // split unit, and per unit a counter of the records delivered
   float *att_part;

@@ -54,6 +54,23 @@ int main(int, char **v) {
 }
 """
 
+PATIENCE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "la_barrier.h"
+using namespace la;
+int main(int, char **v) {
+  const unsigned units = barrier_patience((unsigned)strtoul(v[1], nullptr, 10));
+  // the first poll that ends the wait, by bisection over what a 32-bit count of polls can say; 0: none
+  unsigned long long lo = 0, hi = 1ull << 32;
+  while (lo + 1 < hi) {
+    const unsigned long long mid = (lo + hi) / 2;
+    (patience_over((unsigned)mid, units) ? hi : lo) = mid;
+  }
+  printf("%u %llu\n", units, hi < 1ull << 32 ? hi : 0);
+}
+"""
+
 
 def _program(tmp_path_factory, name, text):
     d = tmp_path_factory.mktemp(name)
@@ -76,3 +93,15 @@ def test_no_launch_finds_words_that_have_reached_its_epochs(epochs, counters, la
     assert wrong == 0 and highest < 1 << 30
     if layers == 40 and not counters:
         assert restarts >= 1
+
+
+@pytest.fixture(scope="module")
+def patience(tmp_path_factory):
+    return _program(tmp_path_factory, "patience", PATIENCE)
+
+
+@pytest.mark.parametrize("asked,units", [(0, 1 << 21), (1, 1), (1000, 1000), ((1 << 30) - 2, (1 << 30) - 2), ((1 << 30) - 1, (1 << 30) - 2),
+                                         (1 << 30, (1 << 30) - 2), ((1 << 32) - 1, (1 << 30) - 2)])
+def test_every_wait_ends(patience, asked, units):
+    """Whatever la_set_barrier_timeout was given: a wait's 32-bit count of polls reaches its end, four polls a unit."""
+    assert patience(asked) == [units, 4 * (units + 1)]
