@@ -13,6 +13,12 @@ namespace la {
 constexpr unsigned PATIENCE = 1u << 21, PATIENCE_MOST = (1u << 30) - 2;  // (the most that 32 bits of polls can pass)
 inline unsigned barrier_patience(unsigned units) { return units == 0 ? PATIENCE : units < PATIENCE_MOST ? units : PATIENCE_MOST; }
 LA_HD inline bool patience_over(unsigned polls, unsigned units) { return (polls >> 2) > units; }
+// Whether a wait ends without result after one more poll: its patience is over, or its workgroup is marked dead by another wave (dead(),
+// which costs a trip to LDS: looked at every 256 polls, 64 us).
+template <typename Dead>
+LA_HD inline bool wait_over(unsigned &polls, unsigned units, Dead dead) {
+  return patience_over(++polls, units) || ((polls & 255u) == 0 && dead());
+}
 
 // A launch of n barriers passes epochs e + 1 .. e + n and leaves them in the barrier words.  A wait ends on any word that has reached its
 // epoch, so what a launch finds there must be below its first.  A captured launch is replayed with the epoch that it was captured

@@ -648,7 +648,7 @@ __device__ __forceinline__ bool io_poll_words(const StackArgs &a, const Io &io, 
       *far = uni((int)__any(bit)) != 0;
       return true;
     }
-    if (patience_over(++spins, a.spin_global)) return false;
+    if (wait_over(spins, a.spin_global, [&]() { return ctl_read(io.ctl + 4 * K_DEAD) != 0; })) return false;
   }
 }
 template <int NIO>

@@ -71,6 +71,18 @@ int main(int, char **v) {
 }
 """
 
+DEAD = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "la_barrier.h"
+int main(int, char **v) {
+  const unsigned units = (unsigned)atoi(v[1]), dies = (unsigned)atoi(v[2]);  // another wave marks the workgroup before this poll
+  unsigned polls = 0, looks = 0;
+  while (!la::wait_over(polls, units, [&]() { ++looks; return polls >= dies; })) {}
+  printf("%u %u\n", polls, looks);
+}
+"""
+
 
 def _program(tmp_path_factory, name, text):
     d = tmp_path_factory.mktemp(name)
@@ -105,3 +117,10 @@ def patience(tmp_path_factory):
 def test_every_wait_ends(patience, asked, units):
     """Whatever la_set_barrier_timeout was given: a wait's 32-bit count of polls reaches its end, four polls a unit."""
     assert patience(asked) == [units, 4 * (units + 1)]
+
+
+@pytest.mark.parametrize("units,dies,polls", [(1 << 21, 1, 256), (1 << 21, 256, 256), (1 << 21, 257, 512), (1 << 21, 5_000_000, 5_000_192), (1, 1, 8),
+                                              (1000, 1 << 30, 4004)])
+def test_a_wait_ends_with_its_workgroup(tmp_path_factory, units, dies, polls):
+    """At the next look at the mark, long before its own patience; a look is every 256 polls."""
+    assert _program(tmp_path_factory, "dead", DEAD)(units, dies) == [polls, polls // 256]
