@@ -14,10 +14,11 @@ constexpr unsigned PATIENCE = 1u << 21, PATIENCE_MOST = (1u << 30) - 2;  // (the
 inline unsigned barrier_patience(unsigned units) { return units == 0 ? PATIENCE : units < PATIENCE_MOST ? units : PATIENCE_MOST; }
 LA_HD inline bool patience_over(unsigned polls, unsigned units) { return (polls >> 2) > units; }
 // Whether a wait ends without result after one more poll: its patience is over, or its workgroup is marked dead by another wave (dead(),
-// which costs a trip to LDS: looked at every 256 polls, 64 us).
+// which costs a trip to LDS: looked at every 256 polls, 64 us).  Neither is expected: laid out in the way of the polls the two took
+// small_bf16's 15 barriers 0.6 us more.
 template <typename Dead>
 LA_HD inline bool wait_over(unsigned &polls, unsigned units, Dead dead) {
-  return patience_over(++polls, units) || ((polls & 255u) == 0 && dead());
+  return __builtin_expect(patience_over(++polls, units), 0) || (__builtin_expect((polls & 255u) == 0, 0) && dead());
 }
 
 // A launch of n barriers passes epochs e + 1 .. e + n and leaves them in the barrier words.  A wait ends on any word that has reached its
