@@ -11,14 +11,22 @@
 namespace la {
 
 namespace rs {
-extern template int launch_rstack_kernel<1, 4>(const StackArgs &, int, hipStream_t);
-extern template int launch_rstack_kernel<2, 4>(const StackArgs &, int, hipStream_t);
-extern template int launch_rstack_kernel<3, 4>(const StackArgs &, int, hipStream_t);
-extern template int launch_rstack_kernel<4, 4>(const StackArgs &, int, hipStream_t);
-extern template int prepare_rstack_kernel<1, 4>(int, int);
-extern template int prepare_rstack_kernel<2, 4>(int, int);
-extern template int prepare_rstack_kernel<3, 4>(int, int);
-extern template int prepare_rstack_kernel<4, 4>(int, int);
+extern template int launch_rstack_kernel<1, 4, false>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<2, 4, false>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<3, 4, false>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<4, 4, false>(const StackArgs &, int, hipStream_t);
+extern template int prepare_rstack_kernel<1, 4, false>(int, int);
+extern template int prepare_rstack_kernel<2, 4, false>(int, int);
+extern template int prepare_rstack_kernel<3, 4, false>(int, int);
+extern template int prepare_rstack_kernel<4, 4, false>(int, int);
+extern template int launch_rstack_kernel<1, 4, true>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<2, 4, true>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<3, 4, true>(const StackArgs &, int, hipStream_t);
+extern template int launch_rstack_kernel<4, 4, true>(const StackArgs &, int, hipStream_t);
+extern template int prepare_rstack_kernel<1, 4, true>(int, int);
+extern template int prepare_rstack_kernel<2, 4, true>(int, int);
+extern template int prepare_rstack_kernel<3, 4, true>(int, int);
+extern template int prepare_rstack_kernel<4, 4, true>(int, int);
 }  // namespace rs
 constexpr int R_NW = 4;  // MFMA waves of the register-streaming kernel
 
@@ -165,6 +173,7 @@ struct MfmaModel {
   unsigned *sched[3][2] = {};  // register-streaming kernel: schedule tables per ring depth (32, 24, 16 slots) and mode (stack, unembedding)
   int32_t *zero_len = nullptr;  // a cache length of 0: the unembedding has no cache to overflow
   BarrierEpochs epochs;
+  int far_from = 0;  // n_wgs: no workgroup
   unsigned long long *trace = nullptr;  // LA_TRACE=1: per-phase timestamps, printed after each launch
   int trace_phases = 0;
   PfBuffers pf, pf_few;
@@ -242,14 +251,21 @@ int mfma_create(la_model *m) {
   int cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   f->n_wgs = std::max(1, std::min({env_int("LA_WGS", cus), cus, rs::GB_MAX_WGS}));  // one resident workgroup per CU: the barrier needs co-residency
   f->use_r = env_int("LA_LDS_RING", 0) == 0;
+  f->far_from = env_int("LA_FAR_FROM", f->n_wgs);
   LA_REQUIRE(f->use_r || d.dtype != LA_F16, LA_EINVAL, "LA_F16 models run on the register-streaming kernel only (unset LA_LDS_RING)");
   LA_REQUIRE((size_t)prop.sharedMemPerBlockOptin >= (size_t)LDS_BYTES || (size_t)prop.maxSharedMemoryPerMultiProcessor >= (size_t)LDS_BYTES,
              LA_EINVAL, "the device offers less LDS per workgroup than the %d bytes the kernel needs", LDS_BYTES);
   {  // co-residency of the grid: the barrier would otherwise wait for workgroups that cannot start
-    int rc = f->use_r ? rs::prepare_rstack_kernel<1, R_NW>(f->n_wgs, cus) : prepare_stack_kernel<1>(f->n_wgs, cus);
-    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<2, R_NW>(f->n_wgs, cus) : prepare_stack_kernel<2>(f->n_wgs, cus);
-    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<3, R_NW>(f->n_wgs, cus) : prepare_stack_kernel<3>(f->n_wgs, cus);
-    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<4, R_NW>(f->n_wgs, cus) : prepare_stack_kernel<4>(f->n_wgs, cus);
+    int rc = f->use_r ? rs::prepare_rstack_kernel<1, R_NW, false>(f->n_wgs, cus) : prepare_stack_kernel<1>(f->n_wgs, cus);
+    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<2, R_NW, false>(f->n_wgs, cus) : prepare_stack_kernel<2>(f->n_wgs, cus);
+    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<3, R_NW, false>(f->n_wgs, cus) : prepare_stack_kernel<3>(f->n_wgs, cus);
+    if (!rc) rc = f->use_r ? rs::prepare_rstack_kernel<4, R_NW, false>(f->n_wgs, cus) : prepare_stack_kernel<4>(f->n_wgs, cus);
+    if (!rc && f->use_r && f->far_from < f->n_wgs) {
+      rc = rs::prepare_rstack_kernel<1, R_NW, true>(f->n_wgs, cus);
+      if (!rc) rc = rs::prepare_rstack_kernel<2, R_NW, true>(f->n_wgs, cus);
+      if (!rc) rc = rs::prepare_rstack_kernel<3, R_NW, true>(f->n_wgs, cus);
+      if (!rc) rc = rs::prepare_rstack_kernel<4, R_NW, true>(f->n_wgs, cus);
+    }
     if (rc) return rc;
   }
   int qd = m->qdim(), nqkv = m->nqkv(), g = d.n_q_heads / d.n_kv_heads;
@@ -431,12 +447,19 @@ static int launch_stack(const char *name, MfmaModel *f, StackArgs a, int n_barri
   int rc;
   {
     ProfScope ps(name, s);
-    if (f->use_r) {
+    if (f->use_r && f->far_from < f->n_wgs) {
       switch (a.MT) {
-      case 1: rc = rs::launch_rstack_kernel<1, R_NW>(a, f->n_wgs, s); break;
-      case 2: rc = rs::launch_rstack_kernel<2, R_NW>(a, f->n_wgs, s); break;
-      case 3: rc = rs::launch_rstack_kernel<3, R_NW>(a, f->n_wgs, s); break;
-      default: rc = rs::launch_rstack_kernel<4, R_NW>(a, f->n_wgs, s); break;
+      case 1: rc = rs::launch_rstack_kernel<1, R_NW, true>(a, f->n_wgs, s); break;
+      case 2: rc = rs::launch_rstack_kernel<2, R_NW, true>(a, f->n_wgs, s); break;
+      case 3: rc = rs::launch_rstack_kernel<3, R_NW, true>(a, f->n_wgs, s); break;
+      default: rc = rs::launch_rstack_kernel<4, R_NW, true>(a, f->n_wgs, s); break;
+      }
+    } else if (f->use_r) {
+      switch (a.MT) {
+      case 1: rc = rs::launch_rstack_kernel<1, R_NW, false>(a, f->n_wgs, s); break;
+      case 2: rc = rs::launch_rstack_kernel<2, R_NW, false>(a, f->n_wgs, s); break;
+      case 3: rc = rs::launch_rstack_kernel<3, R_NW, false>(a, f->n_wgs, s); break;
+      default: rc = rs::launch_rstack_kernel<4, R_NW, false>(a, f->n_wgs, s); break;
       }
     } else {
       switch (a.MT) {
@@ -627,6 +650,7 @@ static StackArgs base_stack_args(la_model *m, int Bp) {
   a.att_cnt = f->att_cnt;
   a.err = m->err_dev;
   a.err_map = m->err_map;
+  a.far_from = f->far_from;
   a.spin_global = barrier_patience(m->barrier_spins);
 #ifdef LA_EXPERIMENTS
   a.dbg = env_int("LA_DBG", 0);

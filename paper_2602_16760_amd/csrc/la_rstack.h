@@ -620,7 +620,8 @@ __device__ __forceinline__ bool io_barrier(Io &io) {
 // that the compiler takes for divergent turns the phases after it into per-lane loops (+ 0.5 us a phase).
 // The first barrier of a launch makes no assumption about where workgroups run: its words are stored for the whole device, and
 // carry a bit where a workgroup is not on the XCD its group is named after.  If any carries it, all words of the launch are stored
-// so; else those that only the group's own XCD reads stay in its L2.
+// so; else those that only the group's own XCD reads stay in its L2.  (FAR: an instance for tests, LA_FAR_FROM=i at a model's creation, in which
+// workgroups i and up say so; one more value that lives through the kernel would cost 1 to 2 % of every launch.)
 constexpr int GB_GROUPS = 8, GB_LINE = 64, GB_GROUP_WORDS = 128, GB_MAX_WGS = GB_GROUPS * GB_GROUP_WORDS / 4;
 constexpr unsigned GB_FAR = 1u << 30, GB_EPOCH = GB_FAR - 1u;
 static_assert(GB_GROUPS * (GB_GROUP_WORDS + GB_LINE) <= SYNC_STRIDE * 66, "words of the barrier");
@@ -651,7 +652,7 @@ __device__ __forceinline__ bool io_poll_words(const StackArgs &a, const Io &io, 
     if (wait_over(spins, a.spin_global, [&]() { return ctl_read(io.ctl + 4 * K_DEAD) != 0; })) return false;
   }
 }
-template <int NIO>
+template <int NIO, bool FAR>
 __device__ __forceinline__ bool io_grid_arrive(const StackArgs &a, Io &io, unsigned epoch) {
   static_assert(NIO == 4, "words of a workgroup");
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -665,7 +666,7 @@ __device__ __forceinline__ bool io_grid_arrive(const StackArgs &a, Io &io, unsig
   if (io.lane == 0) {
     unsigned *w = a.sync + GB_GROUP_WORDS * (blockIdx.x % GB_GROUPS) + NIO * (blockIdx.x / GB_GROUPS) + io.v;
     if (io.near) __hip_atomic_store(w, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    else __hip_atomic_store(w, epoch | (xcc_id() != blockIdx.x % GB_GROUPS ? GB_FAR : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else __hip_atomic_store(w, epoch | (xcc_id() != blockIdx.x % GB_GROUPS || (FAR && (int)blockIdx.x >= a.far_from) ? GB_FAR : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   io_mark(io, 7);
   const int G = (int)gridDim.x, wg = (int)blockIdx.x;
@@ -695,9 +696,9 @@ __device__ __forceinline__ bool io_grid_wait(const StackArgs &a, Io &io, unsigne
   io_mark(io, 8);
   return uni((int)ok) != 0;
 }
-template <int NIO>
+template <int NIO, bool FAR>
 __device__ __forceinline__ bool io_grid_sync(const StackArgs &a, Io &io, unsigned epoch) {
-  return io_grid_arrive<NIO>(a, io, epoch) && io_grid_wait<NIO>(a, io, epoch);
+  return io_grid_arrive<NIO, FAR>(a, io, epoch) && io_grid_wait<NIO>(a, io, epoch);
 }
 
 // The operand of one pass into the rings of the MFMA waves this IO wave serves (w = v, v + NIO,
@@ -1576,7 +1577,7 @@ __device__ __forceinline__ void r_unembed_final(const StackArgs &a, const Io &io
   }
 }
 
-template <int MT, int NW>
+template <int MT, int NW, bool FAR>
 __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, int v, int lane, int L) {
   constexpr int NIO = 8 - NW, SV = NW / NIO;
   static_assert(NW % NIO == 0, "every IO wave serves the same number of MFMA waves");
@@ -1619,7 +1620,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
         st32f(rp, o + 8, -INFINITY);
       }
     }
-    if (!io_grid_sync<NIO>(a, io, ++epoch)) return;
+    if (!io_grid_sync<NIO, FAR>(a, io, ++epoch)) return;
     set_phase(1);
     bool first = true;
     while (!pw.done) {
@@ -1635,7 +1636,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
       if (!io_pass<MT, NW>(a, io, cur, pseq, a.xa, nullptr, q, L, 0, a_seq, [&]() { pw.next(); })) return;
       ++pseq;
     }
-    if (!io_grid_sync<NIO>(a, io, ++epoch)) return;
+    if (!io_grid_sync<NIO, FAR>(a, io, ++epoch)) return;
     set_phase(2);
     r_unembed_final<NIO>(a, io);
     io_mark(io, 2);
@@ -1665,7 +1666,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
     uint16_t *Kc = nullptr, *Vc = nullptr, *xa0 = nullptr, *xa1 = nullptr, *attn_l = nullptr, *act_l = nullptr;
     float *rsq0 = nullptr, *rsq1 = nullptr;
     for (int gemm = 0; gemm < 4; ++gemm) {
-      if (!io_grid_arrive<NIO>(a, io, ++epoch)) return;
+      if (!io_grid_arrive<NIO, FAR>(a, io, ++epoch)) return;
       const uint16_t *A = nullptr;
       const float *rsq_in = nullptr;
       Epi q{};
@@ -1707,7 +1708,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
                              : r_attention<64, MT, NIO, false>(a, io, Kc, Vc, attn_l, L, att_u0, S, att_seq);
           if (!ok) return;
         }
-        if (!io_grid_sync<NIO>(a, io, ++epoch)) return;
+        if (!io_grid_sync<NIO, FAR>(a, io, ++epoch)) return;
         set_phase(1 + 5 * (layer - a.lb) + 2);
       }
       bool first = true;
@@ -1728,7 +1729,7 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
 }
 
 // ---- the persistent kernel ------------------------------------------------------------------------
-template <int MT, int NW>
+template <int MT, int NW, bool FAR>
 __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds_generic[];
   const lds_t lds = (lds_t)lds_generic;
@@ -1760,7 +1761,7 @@ __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
     if (LA_TRACE_PTR(a) && lane == 0 && blockIdx.x > 2) LA_TRACE_PTR(a)[(size_t)TRACE_SLOTS * a.trace_phases + TRACE_WG * (int)blockIdx.x + wave] = wall_clock64();
   } else {
     __builtin_amdgcn_s_setprio(3);  // (the IO waves' short bursts go first: measured neutral at 32 rows, 1.6 % on the one-row step; the other way round costs 0.8 %)
-    io_wave_main<MT, NW>(a, lds0, wave - NW, lane, L);
+    io_wave_main<MT, NW, FAR>(a, lds0, wave - NW, lane, L);
     // a wait that gave up anywhere in the workgroup: tell the host
     if (lane == 0 && ctl_read(lds0 + NW * Lay<MT, NW>::REG + M_CTL + 4 * K_DEAD) != 0)
       raise_error(a, 4);
@@ -1797,28 +1798,28 @@ int write_schedule_tables(const StackArgs &a, int ring, unsigned *out, int n_wgs
 
 // Run once per model: raises the kernel's LDS limit and checks that n_wgs workgroups can be resident at once on `cus`
 // compute units (the grid barrier waits for all of them; what other work shares the GPU is the caller's concern).
-template <int MT, int NW>
+template <int MT, int NW, bool FAR>
 int prepare_rstack_kernel(int n_wgs, int cus) {
   constexpr int bytes = lds_bytes<MT, NW>();
-  LA_HIP(hipFuncSetAttribute((const void *)rstack_kernel<MT, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  LA_HIP(hipFuncSetAttribute((const void *)rstack_kernel<MT, NW, FAR>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
   int per_cu = 0;
-  LA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rstack_kernel<MT, NW>, WG_THREADS, bytes));
+  LA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rstack_kernel<MT, NW, FAR>, WG_THREADS, bytes));
   LA_REQUIRE(per_cu >= 1 && n_wgs <= per_cu * cus, LA_EINVAL,
              "the persistent kernel for %d row tiles cannot keep %d workgroups resident (%d per compute unit on %d units)", MT, n_wgs,
              per_cu, cus);
   return LA_OK;
 }
 
-template <int MT, int NW>
+template <int MT, int NW, bool FAR>
 int launch_rstack_kernel(const StackArgs &a, int n_wgs, hipStream_t s) {
   static bool attr_set = false;
   constexpr int bytes = lds_bytes<MT, NW>();
   static_assert(bytes <= 160 * 1024, "LDS of one CU");
   if (!attr_set) {
-    LA_HIP(hipFuncSetAttribute((const void *)rstack_kernel<MT, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    LA_HIP(hipFuncSetAttribute((const void *)rstack_kernel<MT, NW, FAR>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     attr_set = true;
   }
-  rstack_kernel<MT, NW><<<n_wgs, WG_THREADS, bytes, s>>>(a);
+  rstack_kernel<MT, NW, FAR><<<n_wgs, WG_THREADS, bytes, s>>>(a);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }

@@ -2,7 +2,9 @@
 #include "la_rstack.h"
 namespace la {
 namespace rs {
-template int launch_rstack_kernel<1, 4>(const StackArgs &, int, hipStream_t);
-template int prepare_rstack_kernel<1, 4>(int, int);
+template int launch_rstack_kernel<1, 4, false>(const StackArgs &, int, hipStream_t);
+template int prepare_rstack_kernel<1, 4, false>(int, int);
+template int launch_rstack_kernel<1, 4, true>(const StackArgs &, int, hipStream_t);
+template int prepare_rstack_kernel<1, 4, true>(int, int);
 }
 }  // namespace la

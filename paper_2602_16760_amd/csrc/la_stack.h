@@ -168,6 +168,7 @@ struct StackArgs {
   int max_len;
   int32_t *err;      // device error word: 1 the block does not fit the cache, 4 a grid barrier gave up
   int32_t *err_map;  // mapped host word that receives the same code (plain store), read by the host without synchronising
+  int far_from;          // grid barrier, an instance for tests: workgroups from this one on say that they are not on the XCD they are expected on
   unsigned spin_global;  // patience of a wait at the grid barrier, in units of about a microsecond
   // attention with the keys split over workgroups (register-streaming kernel): partial (o, m, l) records per
   // split unit, and per unit a counter of the records delivered
