@@ -198,7 +198,7 @@ int la_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, fl
  * of 4.1 MiB that every GPU the library runs on holds until the process ends, instead of
  * buffers owned by the model.  The call allocates nothing and frees nothing; it launches one
  * small fill kernel that clears the barrier words, then the unembedding kernel.
- * Only for LA_BF16 models on the matrix-core path; limits: d_model <= 8192 and
+ * Only for LA_BF16 and LA_F16 models on the matrix-core path; limits: d_model <= 8192 and
  * 256 * ceil(vocab / 4096) <= 4096 partial records (vocab <= 65536 on a 256-CU GPU), beyond
  * which it returns LA_ERANGE; LA_EINVAL for other models.  All calls on one GPU share the
  * array, whatever the model: calls that overlap in time on one GPU (two streams, two host

@@ -103,8 +103,9 @@ __device__ __forceinline__ SlotIn key_request(const PoolView &p, int key, int la
   return slot_request(p, in, in ? (size_t)key * p.G + lane : 0);
 }
 
-// Candidates from a key's slots (stamp of slot s in lane s, its tuple in tok[s (N-1)]), most recently inserted first, into cand[k*(N-1)+j] (LDS and, where it is kept, the
-// state); returns the count.  Stamps are distinct, so a slot's place is the number of later ones.
+// Candidates from a key's slots (stamp of slot s in lane s, its tuple in tok[s (N-1)]), most recently inserted first, into
+// cand[k*(N-1)+j] (LDS and, where it is kept, the state); returns the count.  Stamps are distinct, so a slot's place is the number
+// of later ones.
 __device__ __forceinline__ int pool_order(const PoolView &p, uint32_t sv, const int32_t *tok, int32_t *cand, int32_t *state_cand, int lane) {
   const int n1 = p.N - 1;
   int place = 0;

@@ -191,11 +191,11 @@ __device__ __forceinline__ float pl_wave_sum(float v) {
 }
 
 // Attention: one workgroup per (row b, query head, 64 channels of the output; larger heads form their scores once per 64 channels).
-// The keys go in pieces of 64 to eight shares, piece k to share k % 8, and a wave takes a share: a key per lane for the scores and a
-// channel per lane for the output, with the running maximum and sum; the shares are added in order.  A piece's V is requested before its
-// scores are formed, the share's next K behind them.  A workgroup has eight waves, or as many as the host's bound on the length
-// allows pieces if those are fewer.  That is a matter of time only: accepts that a replayed graph makes leave the bound behind the length, and waves
-// then take more than one share each, so that the sums depend on the length alone.
+// The keys go in pieces of 64 to eight shares, piece k to share k % 8, and a wave takes a share: a key per lane for the scores and
+// a channel per lane for the output, with the running maximum and sum; the shares are added in order.  A piece's V is requested
+// before its scores are formed, the share's next K behind them.  A workgroup has eight waves, or as many as the host's bound on the
+// length allows pieces if those are fewer.  That is a matter of time only: accepts that a replayed graph makes leave the bound
+// behind the length, and waves then take more than one share each, so that the sums depend on the length alone.
 // Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
 // 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
 // 28 -> 12, L = 4000 108 -> 41.

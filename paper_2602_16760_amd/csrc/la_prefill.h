@@ -160,7 +160,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   // column groups dealt to them, some had a round of workgroups more than the chip needs (7B shape, 700 rows: down
   // 166 -> 91 us, O 61 -> 36; 1300 rows: 298 -> 160, 101 -> 57; 1600 rows: gate/up 452 -> 390; 12B shape, 300 rows: down 121 -> 67).
   const int tiles = RB * p.S * n_cg, per_xcd = (tiles + 7) / 8, turn = (int)blockIdx.x / 8, tile = ((int)blockIdx.x % 8) * per_xcd + turn;
-  if (tile >= tiles || turn >= per_xcd) return;  // (the whole workgroup)
+  if (tile >= tiles) return;  // (the whole workgroup; the grid is eight times per_xcd)
   const int rb = tile % RB, slice = tile / RB % p.S, cg = tile / (RB * p.S);
   const int row0 = p.KT * slice / p.S, row1 = p.KT * (slice + 1) / p.S, n_kt = row1 - row0;
   const unsigned lds0 = (unsigned)(uintptr_t)pf_lds;

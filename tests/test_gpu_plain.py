@@ -74,8 +74,8 @@ def test_rows_that_are_not_seen_may_hold_anything():
 
 def test_lengths_that_replayed_accepts_reach():
     """A captured forward and accept, replayed until the cache holds more pieces of 64 keys than it did when it was captured, and
-    behind that an eager forward, whose host knows nothing of the replays: a captured launch sums as one that knows the length (the
-    same bits), the eager one in another order (the plain kernels' bar)."""
+    behind that an eager forward, whose host knows nothing of the replays: a captured launch sums as one that knows the length, bit
+    for bit, and so does the eager one (test_sums_depend_on_the_length_alone; held to the plain kernels' bar here)."""
     import torch
     from paper_2602_16760_amd import binding as B
     shape, L0, rows = synth.SHAPES["tiny_f32"], 40, 16
