@@ -612,16 +612,17 @@ __device__ __forceinline__ bool io_barrier(Io &io) {
 // word queue up), a store or a load in the XCD's own L2 under 200.  So there are no atomics: workgroup i belongs to group i % 8
 // (its XCD, as workgroups are dealt out), every IO wave stores the epoch into a word of its own of its group, one wave of the
 // group's first workgroup polls them all and stores the epoch into a word of each of the eight groups' lines, and every workgroup
-// polls its own group's line, each IO wave for itself: one trip between XCDs.  Alone 1.84 -> 1.40 us (256 workgroups; counters per 16 workgroups, a top
-// counter and one release word before); in the kernel small_bf16 (15 phases, 31 rows) 129.8 -> 122.7 us, the 7B shape's 30 layers,
-// L = 512, one row 2894 -> 2867, 32 rows 3250 -> 3200, 24 layers, L = 2048, 43 rows 3132 -> 3079.  A sleep between polls, or one
-// word per workgroup behind a barrier of its IO waves, is slower; one wave polling for the four and telling them through LDS costs
-// 1.2 us a step of small_bf16.  Everything here has to stay wave-uniform (uni): a result
-// that the compiler takes for divergent turns the phases after it into per-lane loops (+ 0.5 us a phase).
+// polls its own group's line, each IO wave for itself: one trip between XCDs.  Alone 1.84 -> 1.40 us (256 workgroups; counters per
+// 16 workgroups, a top counter and one release word before).  A step, both timed in turn: small_bf16 (15 phases, 31 rows) 128.0 ->
+// 123.1 us; the 7B shape's 30 layers, L = 512, one row 2904 -> 2864, 32 rows 3313 -> 3256; 24 layers, L = 2048, 43 rows 3243 -> 3186
+// (where runs of one side differ by 1.3 %).  A sleep between polls, or one word per workgroup behind a barrier of its IO waves, is
+// slower; one wave polling for the four and telling them through LDS costs 1.2 us a step of small_bf16.  Everything here has to
+// stay wave-uniform (uni): a result that the compiler takes for divergent turns the phases after it into per-lane loops (+ 0.5 us
+// a phase).
 // The first barrier of a launch makes no assumption about where workgroups run: its words are stored for the whole device, and
 // carry a bit where a workgroup is not on the XCD its group is named after.  If any carries it, all words of the launch are stored
-// so; else those that only the group's own XCD reads stay in its L2.  (FAR: an instance for tests, LA_FAR_FROM=i at a model's creation, in which
-// workgroups i and up say so; one more value that lives through the kernel would cost 1 to 2 % of every launch.)
+// so; else those that only the group's own XCD reads stay in its L2.  (FAR: an instance for tests, LA_FAR_FROM=i at a model's
+// creation, in which workgroups i and up say so; one more value that lives through the kernel would cost every launch 1 to 2 %.)
 constexpr int GB_GROUPS = 8, GB_LINE = 64, GB_GROUP_WORDS = 128, GB_MAX_WGS = GB_GROUPS * GB_GROUP_WORDS / 4;
 constexpr unsigned GB_FAR = 1u << 30, GB_EPOCH = GB_FAR - 1u;
 static_assert(GB_GROUPS * (GB_GROUP_WORDS + GB_LINE) <= SYNC_STRIDE * 66, "words of the barrier");
