@@ -239,7 +239,7 @@ int recover_if_needed(la_model *m, hipStream_t s) {
     const int rc = mfma_reset_sync(m, s);
     if (rc) return rc;
   }
-  m->recover = false;
+  m->recover = stream_captures(s);  // (a graph may never run, and the next launch outside of it starts clean as well)
   return LA_OK;
 }
 

@@ -88,7 +88,7 @@ struct la_kv {
   void *K = nullptr, *V = nullptr;  // [n_layers][max_len][Hkv][dh] (V: see v_blocked)
   int32_t *L_dev = nullptr;         // committed length, on the device
   int32_t *err_dev = nullptr;       // the model's device error word (not owned)
-  int L_bound = 0;                  // host-side upper bound on L
+  int L_bound = 0;                  // host-side upper bound on L (but for what replays of a captured accept have added)
   size_t layer_elems() const { return (size_t)rows_alloc * m->d.n_kv_heads * m->d.head_dim; }
 };
 

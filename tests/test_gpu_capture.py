@@ -143,3 +143,43 @@ def test_the_legacy_stream_beside_a_capture(name):
             hip.hipStreamDestroy(blocking)
         torch.cuda.synchronize()
         eng.close()
+
+
+def test_recovery_does_not_wait_for_a_graph():
+    """A reported error is cleared by the next launch; where that one is captured, by the next one outside the graph as well, which may
+    never run."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    shape, L0, rows, max_len = synth.SHAPES["tiny_f32"], 40, 17, 64
+    eng = gpu_engine(shape, max_len, seed=3)
+    stream, accept, forward = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    try:
+        prompt = B.to_device(np.zeros(L0 + 1, dtype=np.int32))
+        state, emitted, ids = B.new_state(), torch.zeros(max_len, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        pos, vis = (B.to_device(a) for a in B.la_causal_layout(L0, rows))
+        h = torch.zeros((rows, shape.d_model), device="cuda")
+        B.la_jacobi_init(eng.kv, 1, prompt, 1, state)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(accept, stream=stream):
+            B.la_jacobi_accept(eng.kv, 1, ids, state, emitted, max_len)
+        for _ in range(max_len - L0 - rows + 1):
+            accept.replay()
+        B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)  # skipped: only the device knows the length
+        torch.cuda.synchronize()
+        with pytest.raises(B.LaError):
+            B.la_kv_set_len(eng.kv, L0)
+        B.la_kv_set_len(eng.kv, L0)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(forward, stream=stream):
+            B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)
+        B.la_forward_layers(eng.model, 0, shape.n_layers, h, pos, vis, eng.kv)
+        B.la_jacobi_init(eng.kv, 1, prompt, 1, state)
+        B.la_jacobi_accept(eng.kv, 1, ids, state, emitted, max_len)
+        assert B.read_state(state).error == 0
+        assert B.la_kv_get_len(eng.kv) == L0 + 1
+        forward.replay()
+        torch.cuda.synchronize()
+        assert B.la_kv_get_len(eng.kv) == L0 + 1
+    finally:
+        torch.cuda.synchronize()
+        eng.close()
