@@ -143,9 +143,13 @@ __device__ __forceinline__ float pf_row_factor(const PfGemm &p, int row) {
 // into whole rounds of 256 CUs; smaller tiles are for the narrower matrices and fewer rows (pf_choose).  One workgroup
 // barrier per k-tile: past it every wave's part of the next stage is in, and nobody reads the stage any more that the
 // next requests overwrite (its fragments are in registers, one k-tile ahead of the products).
-// Measured (1023 rows, 7B shape, a pass of eight layers, before: 64 x 64 per wave, activations from L2 into registers):
-// gate/up 258 -> 219 us (1100 TFLOP/s; a large library product reaches 1219 on this card), QKV 91 -> 65, O 50 -> 43, down
-// 144 -> 120.  Over 32 layers, at the clock that such a pass is left with, gate/up is 227 in the mean (206 at best) and QKV 70.
+// A step's requests and fragment reads are dealt out between its products, and the offsets of the requests only ever grow by a constant
+// (but for the ends of the walk's runs): with all requests behind the barrier and their offsets multiplied out, the products waited for some
+// fifty scalar instructions and for the load unit to take 30 KB (a k-tile's other instructions: 79 -> 37 beside 28 products).
+// 1023 rows, 7B shape, us a product, before and after: gate/up 222 -> 202 (1190 TFLOP/s; a large library product reaches 1219 on this
+// card), QKV 66 -> 61, O 44 -> 41, down 123 -> 110; 2048 rows: 428 -> 395, 110 -> 102, 72 -> 66, 223 -> 205.  What is left is paid in clock:
+// with the same operands over and over gate/up takes 131 us, with constant fragments through LDS 176.  Four waves of 128 x 112 or 64 x 128
+// read a third less LDS and are no faster (214, and 106 for down): one wave a SIMD has nothing to do at the barrier.
 template <int MODE, int WM, int WN, int NTW, int NS>
 __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf_lds) {
   constexpr int NWV = WM * WN;                 // waves
@@ -164,74 +168,80 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   const int rb = tile % RB, slice = tile / RB % p.S, cg = tile / (RB * p.S);
   const int row0 = p.KT * slice / p.S, row1 = p.KT * (slice + 1) / p.S, n_kt = row1 - row0;
   const unsigned lds0 = (unsigned)(uintptr_t)pf_lds;
+  const unsigned voff = (unsigned)lane * 16u;
+  // The k-tiles go in the order the weights are stored: row r of a tile's stream is k-tile kt, kt = w, w + NW, ... for w = 0, 1, ...
+  int nx_kt = row0, nx_w = 0;
+  while (nx_kt >= (p.KT - nx_w + p.NW - 1) / p.NW) {
+    nx_kt -= (p.KT - nx_w + p.NW - 1) / p.NW;
+    ++nx_w;
+  }
+  nx_kt = nx_w + p.NW * nx_kt;
   // what this wave brings of a k-tile: fragments wave * LPW ..; 0 .. RTB - 1 are the activations' row tiles
   __amdgpu_buffer_rsrc_t rs[LPW];
-  unsigned of[LPW], mul_a[LPW], mul_b[LPW], dst[LPW];
+  unsigned of[LPW], inc[LPW], dst[LPW];
+  int n_act = 0;
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     int f = wave * LPW + i;
     if (f >= F) f = F - 1;
-    dst[i] = lds0 + (unsigned)f * 1024u;
+    dst[i] = uni(lds0 + (unsigned)f * 1024u);
     if (f < RTB) {
       const int r = rb * RTB + f;
       rs[i] = rsrc_of(p.A);
-      of[i] = uni((unsigned)(r < p.RT ? r : p.RT - 1) * 1024u);
-      mul_a[i] = uni((unsigned)p.RT * 1024u);
-      mul_b[i] = 0u;
+      of[i] = uni((unsigned)((r < p.RT ? r : p.RT - 1) + nx_kt * p.RT) * 1024u);
+      inc[i] = uni((unsigned)(p.NW * p.RT) * 1024u);
+      n_act = i + 1;
     } else {
       const int tj = p.t_first + cg * CTB + f - RTB;
       const int t = tj < p.ntiles ? tj : p.ntiles - 1;  // (a group past the last tile repeats it; its result is dropped)
       const int c = uni(t % p.G), lt = uni(t / p.G);
       unsigned off = p.frag0;
       for (int q = 0; q < p.n_prev; ++q) off += (unsigned)((p.prev_ntiles[q] > c ? (p.prev_ntiles[q] - c + p.G - 1) / p.G : 0) * p.prev_KT[q]);
+      const unsigned nt = (unsigned)((p.ntiles - c + p.G - 1) / p.G);
       rs[i] = rsrc_of(p.wstream + (size_t)c * p.cu_bytes);
-      of[i] = uni((off + (unsigned)lt) * 1024u);
-      mul_a[i] = 0u;
-      mul_b[i] = uni((unsigned)((p.ntiles - c + p.G - 1) / p.G) * 1024u);
+      of[i] = uni((off + (unsigned)lt + (unsigned)row0 * nt) * 1024u);
+      inc[i] = uni(nt * 1024u);
     }
   }
-  const unsigned voff = (unsigned)lane * 16u;
-  // k-tiles in the order the weights are stored: row r of a tile's stream is k-tile kt, kt = w, w + NW, ... for w = 0, 1, ...
-  int nx_row = row0, nx_kt = row0, nx_w = 0;
-  while (nx_kt >= (p.KT - nx_w + p.NW - 1) / p.NW) {
-    nx_kt -= (p.KT - nx_w + p.NW - 1) / p.NW;
-    ++nx_w;
-  }
-  nx_kt = nx_w + p.NW * nx_kt;
+  // requests until the walk leaves the line of its offsets: the end of a run of k-tiles, where the activations' go back, or the last k-tile,
+  // which is requested again from then on and never used
+  int left = uni(row1 - row0 - 1), run = uni((p.KT - 1 - nx_kt) / p.NW);
   unsigned nx_slot = 0;
-  auto request = [&]() {
+  auto advance = [&]() {
+    if (left > 0) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[i], (LDS_AS void *)(uintptr_t)(dst[i] + nx_slot), 16, voff,
-                                               uni(of[i] + (unsigned)nx_kt * mul_a[i] + (unsigned)nx_row * mul_b[i]), 0, 0);
-    const bool more = nx_row + 1 < row1;  // (past the end the last one is requested again and never used)
-    const bool wrap = nx_kt + p.NW >= p.KT;
-    nx_kt = !more ? nx_kt : wrap ? nx_w + 1 : nx_kt + p.NW;
-    nx_w += more && wrap ? 1 : 0;
-    nx_row += more ? 1 : 0;
+      for (int i = 0; i < LPW; ++i) of[i] += inc[i];
+      if (run == 0) {  // from the last k-tile of run w to k-tile w + 1
+        ++nx_w;
+        const int last = nx_w - 1 + (p.KT - nx_w) / p.NW * p.NW;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i)
+          if (i < n_act) of[i] = uni(of[i] - inc[i] - (unsigned)((last - nx_w) * p.RT) * 1024u);
+        run = uni((p.KT - 1 - nx_w) / p.NW + 1);
+      }
+      --run;
+      --left;
+    }
     nx_slot = nx_slot + F * 1024u == NS * F * 1024u ? 0u : nx_slot + F * 1024u;
+  };
+  auto request_one = [&](int i) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[i], (LDS_AS void *)(uintptr_t)(dst[i] + nx_slot), 16, voff, of[i], 0, 0);
   };
   u32x4 fa[2][4], fb[2][NTW];
   unsigned rd_slot = 0;
-  auto read = [&](u32x4 (&a)[4], u32x4 (&b)[NTW]) {
-    const unsigned base = lds0 + rd_slot + voff;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(4 * wm + m) * 1024u);
-#pragma unroll
-    for (int j = 0; j < NTW; ++j) b[j] = *(LDS_AS const u32x4 *)(uintptr_t)(base + (unsigned)(RTB + wn * NTW + j) * 1024u);
-    rd_slot = rd_slot + F * 1024u == NS * F * 1024u ? 0u : rd_slot + F * 1024u;
-  };
+  const unsigned rd_a = lds0 + voff + (unsigned)(4 * wm) * 1024u, rd_b = lds0 + voff + (unsigned)(RTB + wn * NTW) * 1024u;
   f32x4 acc[4][NTW];
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int j = 0; j < NTW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto mul = [&](const u32x4 (&a)[4], const u32x4 (&b)[NTW]) {
-#pragma unroll
-    for (int j = 0; j < NTW; ++j)
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[j]), __builtin_bit_cast(f16x8, a[m]), acc[m][j], 0, 0, 0);
+  auto product = [&](int s, int n) {
+    const int j = n / 4, m = n % 4;
+    acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fb[s][j]), __builtin_bit_cast(f16x8, fa[s][m]), acc[m][j], 0, 0, 0);
+  };
+  auto read_one = [&](int s, int f, unsigned a, unsigned b) {
+    if (f < NTW) fb[s][f < NTW ? f : 0] = *(LDS_AS const u32x4 *)(uintptr_t)(b + (unsigned)f * 1024u);
+    else fa[s][f < NTW ? 0 : f - NTW] = *(LDS_AS const u32x4 *)(uintptr_t)(a + (unsigned)(f - NTW) * 1024u);
   };
   auto turn_over = [&]() {  // everybody's next stage is in, and everybody has read the stage that the next request overwrites
     wait_vmcnt<(NS - 2) * LPW>();
@@ -240,8 +250,35 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
     __builtin_amdgcn_s_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
   };
+  // a step: the products of the k-tile in registers, the fragments of the next one and the requests of one further on between them
+  auto step = [&](int s) {
+    constexpr int P = 4 * NTW, R = 4 + NTW;
+    turn_over();
+    const unsigned a = rd_a + rd_slot, b = rd_b + rd_slot;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) request();
+    for (int n = 0; n < P; ++n) {
+      // read f goes in front of product f P / R, request i in front of product (2 i + 1) P / (2 LPW)
+#pragma unroll
+      for (int f = 0; f < R; ++f)
+        if (f * P / R == n) read_one(s ^ 1, f, a, b);
+#pragma unroll
+      for (int i = 0; i < LPW; ++i)
+        if ((2 * i + 1) * P / (2 * LPW) == n) request_one(i);
+      product(s, n);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n == (2 * LPW - 1) * P / (2 * LPW)) {  // (the last request is out)
+        advance();
+        rd_slot = rd_slot + F * 1024u == NS * F * 1024u ? 0u : rd_slot + F * 1024u;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) request_one(i);
+    advance();
+  }
   // row factors of the norm into LDS, while the first stages are on their way
   LDS_AS float *rf = (LDS_AS float *)(uintptr_t)(lds0 + NS * F * 1024u);
   if (MODE != PF_PART && (int)threadIdx.x < 16 * RTB) rf[threadIdx.x] = pf_row_factor(p, 16 * rb * RTB + (int)threadIdx.x);
@@ -250,28 +287,18 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  read(fa[0], fb[0]);
-  auto step = [&](int s) {
-    turn_over();
-    request();
-    __builtin_amdgcn_sched_barrier(0);
-    read(fa[s ^ 1], fb[s ^ 1]);
-    mul(fa[s], fb[s]);
-    // one fragment read per two products
 #pragma unroll
-    for (int i = 0; i < 4 + NTW; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4 * NTW - 2 * (4 + NTW) > 0 ? 4 * NTW - 2 * (4 + NTW) : 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  };
+  for (int f = 0; f < 4 + NTW; ++f) read_one(0, f, rd_a, rd_b);
+  rd_slot = F * 1024u;
   int r = 0;
   for (; r + 2 <= n_kt; r += 2) {
     step(0);
     step(1);
   }
-  if (r < n_kt) mul(fa[0], fb[0]);
+  if (r < n_kt) {
+#pragma unroll
+    for (int n = 0; n < 4 * NTW; ++n) product(0, n);
+  }
   wait_vmcnt<0>();  // (the requests past the last k-tile land before the LDS is given back)
   const int r0 = rb * RTB + 4 * wm;
   if (r0 < p.RT) pf_epilogue<MODE, 4, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
