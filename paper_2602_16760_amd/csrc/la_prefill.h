@@ -134,10 +134,11 @@ __device__ __forceinline__ float pf_row_factor(const PfGemm &p, int row) {
   return 1.0f / sqrtf(((a[0] + a[1]) + (a[2] + a[3])) * p.inv_d + p.eps);
 }
 
-// One product.  A workgroup computes a tile of 64 WM rows x 16 WN NTW columns, a wave 64 rows x 16 NTW columns of it; the
+// One product.  A workgroup computes a tile of 16 NM WM rows x 16 WN NTW columns, a wave 16 NM rows x 16 NTW columns of it (NM is 4 but in tiles
+// that are cut to the prompt's rows); the
 // fragments of a k-tile (32 deep) come in once per workgroup with direct-to-LDS loads, into a ring of NS stages.
-// Bound: the matrix cores, if the operands get there: a wave reads 4 + NTW fragments of LDS for 4 NTW products (16 cycles
-// each, four waves' reads sharing 128 bytes a cycle), so small tiles are LDS-bound, and a workgroup takes 4 WM + WN NTW KB
+// Bound: the matrix cores, if the operands get there: a wave reads NM + NTW fragments of LDS for NM NTW products (16 cycles
+// each, four waves' reads sharing 128 bytes a cycle), so small tiles are LDS-bound, and a workgroup takes NM WM + WN NTW KB
 // a k-tile through its CU's 64 bytes a cycle.  256 rows x 224 columns (8 waves, one workgroup per CU) needs 79 % of the
 // LDS cycles and 54 % of the load cycles that its products take, and cuts the 28672 columns of the 7B shape's gate/up
 // into whole rounds of 256 CUs; smaller tiles are for the narrower matrices and fewer rows (pf_choose).  One workgroup
@@ -150,16 +151,16 @@ __device__ __forceinline__ float pf_row_factor(const PfGemm &p, int row) {
 // card), QKV 66 -> 61, O 44 -> 41, down 123 -> 110; 2048 rows: 428 -> 395, 110 -> 102, 72 -> 66, 223 -> 205.  What is left is paid in clock:
 // with the same operands over and over gate/up takes 131 us, with constant fragments through LDS 176.  Four waves of 128 x 112 or 64 x 128
 // read a third less LDS and are no faster (214, and 106 for down): one wave a SIMD has nothing to do at the barrier.
-template <int MODE, int WM, int WN, int NTW, int NS>
+template <int MODE, int WM, int WN, int NTW, int NS, int NM>
 __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf_lds) {
-  constexpr int NWV = WM * WN;                 // waves
-  constexpr int RTB = 4 * WM, CTB = WN * NTW;  // row and column tiles of the workgroup
+  constexpr int NWV = WM * WN;                  // waves
+  constexpr int RTB = NM * WM, CTB = WN * NTW;  // row and column tiles of the workgroup
   constexpr int F = RTB + CTB;                 // fragments of a k-tile
   constexpr int LPW = (F + NWV - 1) / NWV;     // ... a wave brings (the last one several times if they do not divide)
   static_assert((NS - 1) * LPW <= 63, "load counter");
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int wm = wave % WM, wn = wave / WM;
-  const int n_cg = (p.ntiles - p.t_first + CTB - 1) / CTB, RB = (p.RT + RTB - 1) / RTB;
+  const int n_cg = (p.ntiles - p.t_first + CTB - 1) / CTB, RB = ((p.M + 15) / 16 + RTB - 1) / RTB;
   // An XCD takes a run of the tiles, row blocks first (they share the weights in its L2), and all XCDs as many, to one: with whole
   // column groups dealt to them, some had a round of workgroups more than the chip needs (7B shape, 700 rows: down
   // 166 -> 91 us, O 61 -> 36; 1300 rows: 298 -> 160, 101 -> 57; 1600 rows: gate/up 452 -> 390; 12B shape, 300 rows: down 121 -> 67).
@@ -227,16 +228,16 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   auto request_one = [&](int i) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[i], (LDS_AS void *)(uintptr_t)(dst[i] + nx_slot), 16, voff, of[i], 0, 0);
   };
-  u32x4 fa[2][4], fb[2][NTW];
+  u32x4 fa[2][NM], fb[2][NTW];
   unsigned rd_slot = 0;
-  const unsigned rd_a = lds0 + voff + (unsigned)(4 * wm) * 1024u, rd_b = lds0 + voff + (unsigned)(RTB + wn * NTW) * 1024u;
-  f32x4 acc[4][NTW];
+  const unsigned rd_a = lds0 + voff + (unsigned)(NM * wm) * 1024u, rd_b = lds0 + voff + (unsigned)(RTB + wn * NTW) * 1024u;
+  f32x4 acc[NM][NTW];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < NM; ++m)
 #pragma unroll
     for (int j = 0; j < NTW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto product = [&](int s, int n) {
-    const int j = n / 4, m = n % 4;
+    const int j = n / NM, m = n % NM;
     acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fb[s][j]), __builtin_bit_cast(f16x8, fa[s][m]), acc[m][j], 0, 0, 0);
   };
   auto read_one = [&](int s, int f, unsigned a, unsigned b) {
@@ -252,7 +253,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   };
   // a step: the products of the k-tile in registers, the fragments of the next one and the requests of one further on between them
   auto step = [&](int s) {
-    constexpr int P = 4 * NTW, R = 4 + NTW;
+    constexpr int P = NM * NTW, R = NM + NTW;
     turn_over();
     const unsigned a = rd_a + rd_slot, b = rd_b + rd_slot;
 #pragma unroll
@@ -288,7 +289,7 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 #pragma unroll
-  for (int f = 0; f < 4 + NTW; ++f) read_one(0, f, rd_a, rd_b);
+  for (int f = 0; f < NM + NTW; ++f) read_one(0, f, rd_a, rd_b);
   rd_slot = F * 1024u;
   int r = 0;
   for (; r + 2 <= n_kt; r += 2) {
@@ -297,17 +298,17 @@ __device__ __forceinline__ void pf_tile_body(const PfGemm &p, LDS_AS uint8_t *pf
   }
   if (r < n_kt) {
 #pragma unroll
-    for (int n = 0; n < 4 * NTW; ++n) product(0, n);
+    for (int n = 0; n < NM * NTW; ++n) product(0, n);
   }
   wait_vmcnt<0>();  // (the requests past the last k-tile land before the LDS is given back)
-  const int r0 = rb * RTB + 4 * wm;
-  if (r0 < p.RT) pf_epilogue<MODE, 4, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 64 * wm);
+  const int r0 = rb * RTB + NM * wm;
+  if (r0 < p.RT) pf_epilogue<MODE, NM, NTW>(p, acc, r0, p.t_first + cg * CTB + wn * NTW, lane, slice, rf + 16 * NM * wm);
 }
 
-template <int MODE, int WM, int WN, int NTW, int NS>
+template <int MODE, int WM, int WN, int NTW, int NS, int NM>
 __global__ __launch_bounds__(64 * WM * WN, 2) void pf_tile_kernel(PfGemm p) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t pf_lds[];
-  pf_tile_body<MODE, WM, WN, NTW, NS>(p, (LDS_AS uint8_t *)pf_lds);
+  pf_tile_body<MODE, WM, WN, NTW, NS, NM>(p, (LDS_AS uint8_t *)pf_lds);
 }
 
 // The QKV product for 65 to 128 rows where it has few columns (pf_qkv_few; 96 of the smallest tiles for 256 CUs at the 7B shape)
@@ -634,16 +635,16 @@ __global__ __launch_bounds__(256) void pf_embed_kernel(const uint16_t *E, const 
 }
 
 // ---- host side ----------------------------------------------------------------------------------------
-template <int MODE, int WM, int WN, int NTW, int NS>
+template <int MODE, int WM, int WN, int NTW, int NS, int NM = 4>
 static int pf_launch_tile(const PfGemm &p, hipStream_t s, bool prepare) {
-  constexpr int bytes = NS * (4 * WM + WN * NTW) * 1024 + WM * 256;
+  constexpr int bytes = NS * (NM * WM + WN * NTW) * 1024 + NM * WM * 64;
   static_assert(bytes <= 160 * 1024, "LDS of one CU");
   if (prepare) {
-    LA_HIP(hipFuncSetAttribute((const void *)pf_tile_kernel<MODE, WM, WN, NTW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    LA_HIP(hipFuncSetAttribute((const void *)pf_tile_kernel<MODE, WM, WN, NTW, NS, NM>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     return LA_OK;
   }
-  const int n_cg = ceil_div(p.ntiles - p.t_first, WN * NTW), RB = ceil_div(p.RT, 4 * WM);
-  pf_tile_kernel<MODE, WM, WN, NTW, NS><<<(RB * p.S * n_cg + 7) / 8 * 8, 64 * WM * WN, bytes, s>>>(p);
+  const int n_cg = ceil_div(p.ntiles - p.t_first, WN * NTW), RB = ceil_div(ceil_div(p.M, 16), NM * WM);
+  pf_tile_kernel<MODE, WM, WN, NTW, NS, NM><<<(RB * p.S * n_cg + 7) / 8 * 8, 64 * WM * WN, bytes, s>>>(p);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }
@@ -656,6 +657,35 @@ static int pf_launch_tile(int tile, const PfGemm &p, hipStream_t s, bool prepare
   case 3: return pf_launch_tile<MODE, 2, 4, 3, 6>(p, s, prepare);
   case 4: return pf_launch_tile<MODE, 2, 2, 4, 4>(p, s, prepare);
   default: return pf_launch_tile<MODE, 2, 2, 2, 6>(p, s, prepare);
+  }
+}
+
+// The tiles that are cut to the prompt's rows (pf_qkv_rows, pf_part_rows, pf_gateup_rows): `rows` row tiles x 6, 8 or 7 columns with a wave per
+// column tile, or 10 and 12 x 14.  The narrow ones take as many stages as let two workgroups into a CU's LDS: more change nothing.
+constexpr int pf_stages(int frags) { return 78 / frags; }
+template <int MODE, int ROWS>
+static int pf_launch_rows(const PfGemm &p, hipStream_t s, bool prepare) {
+  if constexpr (MODE == PF_QKV) return pf_launch_tile<MODE, 1, 6, 1, pf_stages(ROWS + 6), ROWS>(p, s, prepare);
+  else if constexpr (MODE == PF_PART) return pf_launch_tile<MODE, 1, 8, 1, pf_stages(ROWS + 8), ROWS>(p, s, prepare);
+  else if constexpr (ROWS == 10) return pf_launch_tile<MODE, 2, 2, 7, 6, 5>(p, s, prepare);
+  else if constexpr (ROWS == 12) return pf_launch_tile<MODE, 4, 2, 7, 6, 3>(p, s, prepare);
+  else return pf_launch_tile<MODE, 1, 7, 1, pf_stages(ROWS + 7), ROWS>(p, s, prepare);
+}
+template <int MODE>
+static int pf_launch_rows(const PfGemm &p, int rows, hipStream_t s, bool prepare) {
+  if constexpr (MODE == PF_QKV) {
+    if (rows == 3) return pf_launch_rows<MODE, 3>(p, s, prepare);
+    if (rows == 4) return pf_launch_rows<MODE, 4>(p, s, prepare);
+  }
+  if constexpr (MODE == PF_GATEUP) {
+    if (rows == 10) return pf_launch_rows<MODE, 10>(p, s, prepare);
+    if (rows == 12) return pf_launch_rows<MODE, 12>(p, s, prepare);
+  }
+  switch (rows) {
+  case 5: return pf_launch_rows<MODE, 5>(p, s, prepare);
+  case 6: return pf_launch_rows<MODE, 6>(p, s, prepare);
+  case 7: return pf_launch_rows<MODE, 7>(p, s, prepare);
+  default: return pf_launch_rows<MODE, 8>(p, s, prepare);
   }
 }
 
@@ -684,8 +714,17 @@ static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, in
   ProfScope ps(name, s);
   static_assert(R_NW == 4, "pf_qkv_few_kernel's waves take the k-tiles as they lie for four MFMA waves");
   if (MODE == PF_QKV && pf_qkv_few(p.M, p.ntiles - p.t_first, cus)) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
+  const PfProduct prod{p.RT, p.M, p.KT, p.ntiles - p.t_first, p.d};
+  int rows = 0;  // row tiles of a tile that is cut to the prompt's rows
+  if (MODE == PF_QKV) rows = pf_qkv_rows(prod, cus);
+  if (MODE == PF_PART) rows = pf_part_rows(prod, part_rows, cus, p.S);
+  if (MODE == PF_GATEUP) rows = pf_gateup_rows(prod, cus);
+  if (rows) {
+    if (S) *S = p.S;
+    return pf_launch_rows<MODE>(p, rows, s, false);
+  }
   int tile;
-  pf_choose(PfProduct{p.RT, p.M, p.KT, p.ntiles - p.t_first, p.d}, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
+  pf_choose(prod, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
   if (S) *S = p.S;
   return pf_launch_tile<MODE>(tile, p, s, false);
 }
@@ -731,6 +770,10 @@ static int pf_alloc(la_model *m, int most, int least, PfBuffers &b) {
     if (!rc) rc = pf_launch_tile<PF_GATEUP>(i, PfGemm{}, nullptr, true);
   }
   for (int i = 5; !rc && i <= 8; ++i) rc = pf_launch_qkv_few(PfGemm{}, i, nullptr, true);
+  for (int i = 3; !rc && i <= 8; ++i) rc = pf_launch_rows<PF_QKV>(PfGemm{}, i, nullptr, true);
+  for (int i = 5; !rc && i <= 8; ++i) rc = pf_launch_rows<PF_PART>(PfGemm{}, i, nullptr, true);
+  for (int i : {5, 6, 7, 8, 10, 12})
+    if (!rc) rc = pf_launch_rows<PF_GATEUP>(PfGemm{}, i, nullptr, true);
   uint8_t *p = nullptr;
   if (!rc) {
     const PfLayout l = pf_fit(PfDims{(size_t)d.d_model, (size_t)m->qdim(), (size_t)d.head_dim, (size_t)d.d_ffn}, most, least,

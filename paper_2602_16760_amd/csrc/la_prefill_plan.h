@@ -3,6 +3,8 @@
 #pragma once
 #include <stddef.h>
 
+#include <initializer_list>
+
 #include "la.h"
 
 namespace la {
@@ -88,7 +90,7 @@ struct PfProduct {
 // Against every tile and number of slices, 17 lengths of 65 .. 2048 rows, 7B and 12B shapes: within 5 % of the best in 115 of 128
 // products; the others are O (at most 400 rows, up to 23 %: 32 us against 26) and down (at most 256 rows, 6 %), which would take
 // fewer slices of smaller tiles.
-inline void pf_choose(const PfProduct &p, int max_split, int part_rows, int cus, int &tile, int &S) {
+inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus, int &tile, int &S) {
   auto up = [](int a, int b) { return (a + b - 1) / b; };
   float best = 0.f;
   tile = -1;
@@ -106,6 +108,50 @@ inline void pf_choose(const PfProduct &p, int max_split, int part_rows, int cus,
         S = k;
       }
     }
+  return best;
+}
+
+// Tiles that are cut to the prompt's rows, as row tiles of a workgroup (pf_launch_rows has their kernels); 0: pf_choose's.  What they save
+// is a CU's intake: a KB takes a CU 16 ns (lines of its XCD's L2) to 35 ns (weights from memory), whatever the depth of the ring, the
+// policy of the loads or lines requested ahead into L2, and a small product waits for nothing else.
+// Up to 128 rows, of gate/up 7 columns and all rows a workgroup: 28672 columns in one round of 256 CUs, and no padding rows.  us, before (128 x 128
+// tiles on 224 CUs) and now: 77 rows 56.3 -> 46.0, 128 rows 57.6 -> 54.0.  Of O and down 8 columns and all rows, in as many slices as fill
+// the chip: 77 rows 12.6 -> 11.4 and 29.4 -> 28.0, 128 rows 13.7 -> 13.9 and 35.0 -> 32.8.  Where they do not fill half of the chip (small models),
+// pf_choose's smaller tiles do better.
+// Gate/up beyond 256 rows: 10 or 12 row tiles x 14 columns where whole rounds of them cost less than pf_choose's best: us per k-tile 0.64 and 0.69
+// against 0.80 of 16 row tiles.  300 rows 102 -> 89, 600 rows 178 -> 160, 700 rows 208 -> 177.
+// QKV of 129 to 512 rows: a quarter of the rows and 6 columns a workgroup, while that is one round (7B and 12B shapes: 64 column groups).
+// 150 rows 33 -> 29, 200 rows 36.6 -> 32.0, 300 rows 51 -> 38, 400 rows 56 -> 45, 500 rows 59 -> 52.
+constexpr int PF_ROW_COLS_QKV = 6, PF_ROW_COLS_PART = 8, PF_ROW_COLS_GATEUP = 7;
+inline int pf_up(int a, int b) { return (a + b - 1) / b; }
+inline int pf_qkv_rows(const PfProduct &p, int cus) {
+  const int rt = pf_up(p.M, 16), rows = pf_up(rt, 4);
+  return p.M > 128 && p.M <= 512 && pf_up(rt, rows) * pf_up(p.n_tiles, PF_ROW_COLS_QKV) <= cus ? rows : 0;
+}
+inline int pf_part_rows(const PfProduct &p, int part_rows, int cus, int &S) {
+  const int groups = pf_up(p.n_tiles, PF_ROW_COLS_PART);
+  int k = cus / groups < PF_MAX_SPLIT ? cus / groups : PF_MAX_SPLIT;
+  while (k > 1 && (p.KT / k < 4 || (long long)k * p.M > part_rows)) --k;
+  if (p.M <= LA_MAX_ROWS || p.M > 128 || k < 1 || 2 * groups * k <= cus) return 0;
+  S = k;
+  return pf_up(p.M, 16);
+}
+inline int pf_gateup_rows(const PfProduct &p, int cus) {
+  const int rt = pf_up(p.M, 16);
+  if (p.M <= 128) {
+    const int groups = pf_up(p.n_tiles, PF_ROW_COLS_GATEUP);
+    return p.M > LA_MAX_ROWS && groups <= cus && 2 * groups > cus ? rt : 0;
+  }
+  int tile, S, rows = 0;
+  float best = pf_choose(p, 1, 0, cus, tile, S);
+  for (int r : {10, 12}) {
+    const float us = (float)(pf_up(pf_up(rt, r) * pf_up(p.n_tiles, 14), cus) * p.KT) * (r == 10 ? 0.64f : 0.69f);
+    if (us < best) {
+      best = us;
+      rows = r;
+    }
+  }
+  return rows;
 }
 
 // The QKV product of M rows and n_tiles column tiles by the kernel without tiles (pf_qkv_few_kernel: two column tiles and all rows a
