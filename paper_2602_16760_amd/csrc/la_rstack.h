@@ -1483,7 +1483,7 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
       }
       io_mark(io, 4);
       bool writer = true;
-      if (S > 1) {
+      if (__builtin_expect(S > 1, 0)) {
         __amdgpu_buffer_rsrc_t rp = rsrc_of(a.att_part);
         const unsigned mine = (unsigned)su * PART;
 #pragma unroll
@@ -1501,17 +1501,28 @@ __device__ __forceinline__ bool r_attention(const StackArgs &a, Io &io, const ui
           l_run = 0.f;
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-          for (int k = 0; k < S; ++k) {
-            const unsigned rec = (unsigned)(u + n_units * k) * PART;
-            const u32x2 ml2 = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rp, rec + DT * 1024u + (unsigned)lane * 8u, 0, DEV));
-            const float mo = __uint_as_float(ml2[0]), lo = __uint_as_float(ml2[1]);
-            const float m_new = fmaxf(m_run, mo);
-            const float ca = __expf(m_run - m_new), cb = __expf(mo - m_new);
-            l_run = l_run * ca + lo * cb;
+          // (four records at a time: one after the other each cost a trip to memory)
+          for (int k0 = 0; k0 < S; k0 += 4) {
+            u32x2 ml2[4];
+            u32x4 po[4][DT];
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-              o[dt] = o[dt] * ca + __builtin_bit_cast(f32x4, ld128(rp, rec + (unsigned)(dt * 64 + lane) * 16u)) * cb;
-            m_run = m_new;
+            for (int j = 0; j < 4; ++j) {
+              const unsigned rec = k0 + j < S ? (unsigned)(u + n_units * (k0 + j)) * PART : OOB;
+              ml2[j] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rp, rec + DT * 1024u + (unsigned)lane * 8u, 0, DEV));
+#pragma unroll
+              for (int dt = 0; dt < DT; ++dt) po[j][dt] = ld128(rp, rec + (unsigned)(dt * 64 + lane) * 16u);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              if (k0 + j >= S) break;
+              const float mo = __uint_as_float(ml2[j][0]), lo = __uint_as_float(ml2[j][1]);
+              const float m_new = fmaxf(m_run, mo);
+              const float ca = __expf(m_run - m_new), cb = __expf(mo - m_new);
+              l_run = l_run * ca + lo * cb;
+#pragma unroll
+              for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * ca + __builtin_bit_cast(f32x4, po[j][dt]) * cb;
+              m_run = m_new;
+            }
           }
         }
       }
