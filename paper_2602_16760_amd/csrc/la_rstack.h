@@ -1261,11 +1261,11 @@ __device__ __forceinline__ bool io_pass(const StackArgs &a, Io &io, const Pass &
 
 // ---- first operand of a launch, RoPE table, staging (IO threads of all workgroups) ----------------
 template <int NIO>
-__device__ __forceinline__ void r_prep(const StackArgs &a, const Io &io, const float *gain, uint16_t *xa_out, float *rsq_out) {
+__device__ __forceinline__ void r_prep(const StackArgs &a, int tid, const float *gain, uint16_t *xa_out, float *rsq_out) {
   constexpr int NT_IO = NIO * 64;
   __amdgpu_buffer_rsrc_t rq = rsrc_of(rsq_out), rx = rsrc_of(xa_out);
   const int octs = a.d >> 3, total = a.Bp * octs;
-  for (int it = (int)blockIdx.x * NT_IO + io.tid; it < total; it += (int)gridDim.x * NT_IO) {
+  for (int it = (int)blockIdx.x * NT_IO + tid; it < total; it += (int)gridDim.x * NT_IO) {
     const int r = it / octs, oct = it - r * octs, c0 = oct * 8;
     const f32x4 *xp = reinterpret_cast<const f32x4 *>(a.x + (size_t)r * a.d + c0);
     f32x4 x0 = xp[0], x1 = xp[1];
@@ -1619,7 +1619,6 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
   pw.init(a, Geo<MT>::NTMAX);
 
   if (a.mode == 1) {  // unembedding: operand, GEMM passes with arg-max records, final arg-max
-    r_prep<NIO>(a, io, a.g_final, a.xa, a.rsq);
     {
       // every CU writes all of its partial records: the ones it has no pass for stay empty
       __amdgpu_buffer_rsrc_t rp = rsrc_of(a.un_part);
@@ -1670,7 +1669,6 @@ __device__ __forceinline__ void io_wave_main(const StackArgs &a, unsigned lds0, 
   const int att_u0 = (int)blockIdx.x >= att_first ? (int)blockIdx.x - att_first : n_su;
   if (blockIdx.x == 0)  // the delivery counters start every launch at zero (visible after the first grid barrier)
     for (int i = io.tid; i < n_units; i += NIO * 64) __builtin_amdgcn_raw_buffer_store_b32(0u, rsrc_of(a.att_cnt), (unsigned)i * 4u, 0, DEV);
-  r_prep<NIO>(a, io, a.gains[a.lb].g_attn, a.xa + (size_t)(2 * a.lb) * a.xa_stride, a.rsq + (size_t)(2 * a.lb) * a.rsq_stride);
   r_rope_table<NIO>(a, io);
   if (x_lds) r_x_stage<MT, NIO>(a, io, nt_x);
 
@@ -1746,27 +1744,38 @@ __global__ __launch_bounds__(WG_THREADS) void rstack_kernel(StackArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds_generic[];
   const lds_t lds = (lds_t)lds_generic;
   if (LA_TRACE_PTR(a) && blockIdx.x == 0 && threadIdx.x == 0) LA_TRACE_PTR(a)[13] = wall_clock64();  // (timeline: kernel entry)
-  const int L = uni(*a.L_dev);
+  const int L_mem = *a.L_dev;
+  if (threadIdx.x < 64) ((LDS_AS unsigned *)(lds + NW * Lay<MT, NW>::REG + M_CTL))[threadIdx.x] = 0u;
+  const unsigned lds0 = (unsigned)(uintptr_t)lds;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  // The MFMA waves' schedules: the same for every launch of a model with this row-tile count, so they are worked out
+  // once, when the model is created (schedule_tables_kernel), and every launch copies its workgroup's tables into LDS
+  // (built here by one thread per MFMA wave they took 10 - 15 us at the start of every launch).  The IO waves make the first operand meanwhile,
+  // and the length is looked at when both are on their way (a block that does not fit has then written scratch and nothing else).
+  if (wave < NW) {
+    constexpr int N16 = NW * TAB_BYTES / 16, PER = (N16 + 64 * NW - 1) / (64 * NW);
+    static_assert(NW * TAB_BYTES % 16 == 0, "whole 16-byte pieces");
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.sched) + (size_t)(int)blockIdx.x * N16;
+    LDS_AS u32x4 *dst = (LDS_AS u32x4 *)(lds + NW * Lay<MT, NW>::REG + M_BYTES);
+    u32x4 t[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) t[k] = src[(int)threadIdx.x + 64 * NW * k < N16 ? (int)threadIdx.x + 64 * NW * k : N16 - 1];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if ((int)threadIdx.x + 64 * NW * k < N16) dst[(int)threadIdx.x + 64 * NW * k] = t[k];
+  } else if (a.mode == 1) {
+    r_prep<8 - NW>(a, (int)threadIdx.x - 64 * NW, a.g_final, a.xa, a.rsq);
+  } else {
+    r_prep<8 - NW>(a, (int)threadIdx.x - 64 * NW, a.gains[a.lb].g_attn, a.xa + (size_t)(2 * a.lb) * a.xa_stride, a.rsq + (size_t)(2 * a.lb) * a.rsq_stride);
+  }
+  const int L = uni(L_mem);
   if (L < 0 || L + a.Bp > a.max_len) {  // every workgroup takes the same exit: no barrier is left waiting
     if (blockIdx.x == 0 && threadIdx.x == 0) raise_error(a, 1);
     return;
   }
-  if (threadIdx.x < 64) ((LDS_AS unsigned *)(lds + NW * Lay<MT, NW>::REG + M_CTL))[threadIdx.x] = 0u;
-  const unsigned lds0 = (unsigned)(uintptr_t)lds;
-  // The MFMA waves' schedules: the same for every launch of a model with this row-tile count, so they are worked out
-  // once, when the model is created (schedule_tables_kernel), and every launch copies its workgroup's tables into LDS
-  // (built here by one thread per MFMA wave they took 10 - 15 us at the start of every launch).
-  {
-    constexpr int N16 = NW * TAB_BYTES / 16;
-    static_assert(NW * TAB_BYTES % 16 == 0, "whole 16-byte pieces");
-    const u32x4 *src = reinterpret_cast<const u32x4 *>(a.sched) + (size_t)(int)blockIdx.x * N16;
-    LDS_AS u32x4 *dst = (LDS_AS u32x4 *)(lds + NW * Lay<MT, NW>::REG + M_BYTES);
-    for (int i = threadIdx.x; i < N16; i += WG_THREADS) dst[i] = src[i];
-  }
   __syncthreads();  // the only hardware barrier: from here on the waves run decoupled
   if (LA_TRACE_PTR(a) && blockIdx.x == 0 && threadIdx.x == 0) LA_TRACE_PTR(a)[14] = wall_clock64();  // (timeline: schedules written)
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
   if (wave < NW) {
     mfma_wave_main<MT, NW>(a, lds0, wave, lane);
     if (LA_TRACE_PTR(a) && lane == 0 && (blockIdx.x == 0 || blockIdx.x == 200)) LA_TRACE_PTR(a)[16 + (blockIdx.x ? 8 : 0) + wave] = wall_clock64();
