@@ -10,18 +10,10 @@
 
 namespace la {
 
-// cos/sin of pos[b] * theta^(-2i/dh), evaluated in double so that the float result is
-// correctly rounded for every position the cache can hold.
 __global__ void rope_table_kernel(const int32_t *pos, int Bp, int half, double theta, float *cs) {
   int b = blockIdx.x;
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    double inv = exp2(-(double)i / (double)half * log2(theta));
-    double phi = (double)pos[b] * inv;
-    double s, c;
-    sincos(phi, &s, &c);
-    cs[((size_t)b * half + i) * 2 + 0] = (float)c;
-    cs[((size_t)b * half + i) * 2 + 1] = (float)s;
-  }
+  for (int i = threadIdx.x; i < half; i += blockDim.x)
+    rotation(pos[b], i, half, theta, &cs[((size_t)b * half + i) * 2], &cs[((size_t)b * half + i) * 2 + 1]);
 }
 
 __device__ __forceinline__ float block_sum(float v, float *red) {
@@ -316,24 +308,31 @@ __device__ __forceinline__ Top top_merge(Top a, Top b) {
   return r;
 }
 
-__global__ void argmax_rows_kernel(const float *logits, int V, int32_t *ids, float *top2) {
-  __shared__ Top red[256];
+// A workgroup per row.  Bound by a trip to memory: eight values are on their way per thread (one at a time, each was waited for before the
+// next was requested: 17 rows of 1024 4.4 -> 3.2 us).
+__global__ __launch_bounds__(256) void argmax_rows_kernel(const float *logits, int V, int32_t *ids, float *top2) {
+  __shared__ Top red[4];
   const float *r = logits + (size_t)blockIdx.x * V;
   Top t{-INFINITY, 0x7fffffff, -INFINITY};
-  for (int i = threadIdx.x; i < V; i += blockDim.x) {
-    float v = r[i];
-    if (v > t.v1) { t.v2 = t.v1; t.v1 = v; t.i1 = i; }
-    else if (v > t.v2) t.v2 = v;
+  for (int i0 = threadIdx.x; i0 < V; i0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = r[i0 + 256 * u < V ? i0 + 256 * u : i0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (i0 + 256 * u >= V) continue;
+      if (v[u] > t.v1) { t.v2 = t.v1; t.v1 = v[u]; t.i1 = i0 + 256 * u; }
+      else if (v[u] > t.v2) t.v2 = v[u];
+    }
   }
-  red[threadIdx.x] = t;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) t = top_merge(t, Top{__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64)});
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
   __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] = top_merge(red[threadIdx.x], red[threadIdx.x + o]);
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    ids[blockIdx.x] = red[0].i1;
-    if (top2) { top2[blockIdx.x * 2] = red[0].v1; top2[blockIdx.x * 2 + 1] = red[0].v2; }
+    for (int w = 1; w < 4; ++w) t = top_merge(t, red[w]);
+    ids[blockIdx.x] = t.i1;
+    if (top2) { top2[blockIdx.x * 2] = t.v1; top2[blockIdx.x * 2 + 1] = t.v2; }
   }
 }
 
@@ -423,12 +422,19 @@ static bool plain_layers(const la_model *m, const la_kv *kv) {
          plain_round(qd, ceil_div(dm, 16)) && plain_round(F, ceil_div(dm, 16));
 }
 
+// The unembedding takes the same products by the same rule (it sums in the general product's order, bit for bit).  Unembedding and arg-max, fp32,
+// 1 / 17 / 64 rows, us (with the general product, which waits for each turn's loads before it asks for the next): 256 x 1024 5.5 / 6.8 / 9.1 (6.6 / 8.7 /
+// 10.3), 256 x 8192 8.3 / 10.5 / 14.4 (15.7 / 18.2 / 21.6), 1024 x 4096 9.3 / 13.1 / 19.7 (14.4 / 18.0 / 22.5).
+static bool plain_head(const la_model_desc &d) {
+  const size_t dm = d.d_model, V = d.vocab, pad = 16 * PL_WAVES * 6;
+  return (dm + pad) * V * 4 < (size_t)1 << 31 && ((LA_MAX_ROWS + 1) * dm + pad) * 4 < (size_t)1 << 31 && dm * V <= PL_LAYER_WEIGHTS && plain_round(dm, ceil_div(V, 16));
+}
+
 template <typename T>
 static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis, la_kv *kv, hipStream_t s) {
   const la_model_desc &d = m->d;
   const int nqkv = m->nqkv(), qd = m->qdim(), F = d.d_ffn, dm = d.d_model;
-  int rc = launch_rope_table(m, pos, Bp, s);
-  if (rc) return rc;
+  int rc = LA_OK;
   for (int l = lb; l < le; ++l) {
     const GenericLayer &w = m->layers[l];
     LA_REQUIRE(w.set, LA_EINVAL, "layer %d has no weights", l);
@@ -437,10 +443,11 @@ static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, c
       PlProduct p{};
       p.A = A; p.lda = K; p.M = Bp; p.K = K; p.gain = gain; p.eps = d.rms_eps; p.W = W; p.ldw = ldw; p.N = N; p.out = out; p.ldo = ldo;
       p.cs = m->rope_cs; p.Kc = Kc; p.Vc = Vc; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.dh = d.head_dim; p.max_len = kv->max_len;
-      p.L_dev = kv->L_dev; p.err = kv->err_dev; p.err_map = m->err_map;
+      p.L_dev = kv->L_dev; p.err = kv->err_dev; p.err_map = m->err_map; p.pos = pos; p.theta = d.rope_theta;
       return p;
     };
-    if ((rc = plain_product<T, PL_QKV>("plain_qkv", product(hidden, dm, w.g_attn, w.wqkv, nqkv, nqkv, m->qkv, qd), nqkv / 16, s))) return rc;
+    const PlProduct qkv = product(hidden, dm, w.g_attn, w.wqkv, nqkv, nqkv, m->qkv, qd);
+    if ((rc = l == lb ? plain_product<T, PL_QKV_FIRST>("plain_qkv", qkv, nqkv / 16, s) : plain_product<T, PL_QKV>("plain_qkv", qkv, nqkv / 16, s))) return rc;
     if ((rc = plain_attention<T>(m->qkv, qd, d, Kc, Vc, kv, Bp, vis, m->attn, s))) return rc;
     if ((rc = plain_product<T, PL_RESID>("plain_o", product(m->attn, qd, nullptr, w.wo, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
     if ((rc = plain_product<T, PL_GLU>("plain_gateup", product(hidden, dm, w.g_mlp, w.wgu, 2 * F, F, m->act, F), ceil_div(F, 8), s))) return rc;
@@ -495,6 +502,11 @@ int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *id
   int rc;
   auto head = [&](auto t) {
     using T = decltype(t);
+    if (plain_head(d)) {
+      PlProduct p{};
+      p.A = hidden; p.lda = p.K = d.d_model; p.M = Bp; p.gain = m->g_final; p.eps = d.rms_eps; p.W = m->unembed; p.ldw = p.N = p.ldo = d.vocab; p.out = m->logits;
+      return plain_product<T, PL_STORE>("gemm_unembed", p, ceil_div(d.vocab, 16), s);
+    }
     return gemm<T>("gemm_unembed", hidden, d.d_model, m->g_final, d.rms_eps, m->unembed, d.vocab, m->logits, d.vocab, Bp, d.d_model, d.vocab, nullptr, false, s);
   };
   rc = d.dtype == LA_F32 ? head(float{}) : d.dtype == LA_F16 ? head(_Float16{}) : head(uint16_t{});

@@ -44,7 +44,7 @@ __device__ __forceinline__ void pl_load16(float *out, __amdgpu_buffer_rsrc_t r, 
   }
 }
 
-enum PlKind { PL_QKV = 0, PL_RESID = 1, PL_GLU = 2 };
+enum PlKind { PL_QKV = 0, PL_RESID = 1, PL_GLU = 2, PL_STORE = 3, PL_QKV_FIRST = 4 };
 
 struct PlProduct {
   const float *A;     // [M][lda]
@@ -60,21 +60,41 @@ struct PlProduct {
   int max_len;
   int32_t *err, *err_map;
   // QKV: rotation table [row][pair][2], this layer's cache, where the block's rows go
-  const float *cs;
+  float *cs;
   void *Kc, *Vc;
   int Hq, Hkv, dh;
+  // QKV_FIRST: the table is made, from these
+  const int32_t *pos;
+  double theta;
 };
+
+// cos, sin of pos theta^(-2 i / head_dim), evaluated in double so that the float results are correctly rounded for every position the cache can hold.
+__device__ __forceinline__ void rotation(int pos, int i, int half, double theta, float *c, float *s) {
+  const double inv = exp2(-(double)i / (double)half * log2(theta));
+  double ds, dc;
+  sincos((double)pos * inv, &ds, &dc);
+  *c = (float)dc;
+  *s = (float)ds;
+}
 
 // One product.  A workgroup takes 16 columns and all rows; its eight waves share the contraction, 16 deep at a time (the same order as
 // gemm_generic_kernel's), NP slices of it on their way at once, and their sums are added in gemm_generic_kernel's order, an element per thread.
 //   QKV: eight channels of the lower half of a head and their rotation partners; rotates, and writes K and V to the cache.
 //   GLU: eight channels of gate and the same of up.
+//   STORE: the columns as they are (the unembedding).
+//   QKV_FIRST: QKV of the first layer of a call, where more waves make the rotation table meanwhile, each workgroup the pairs of its own tile
+//   (those of head 0 leave them for the layers behind it): a launch in front of the layers cost 2.9 us, the same work in front of the product 1.5.
 // Bound: a launch, the weights' way from memory (each is read by one wave) and the sums' through LDS.  Step of the tiny shape (256
-// wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below.
-template <typename T, int MT, int KIND, int NP>
-__global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) {
+// wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below; -> 56.9 with the table, the unembedding and the arg-max in
+// products of this kind, what an epilogue adds to or rotates by requested with the operands, and K and V of the attention's first piece with q.
+template <typename T, int MT, int KIND0, int NP0>
+__global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0)) void plain_product_kernel(PlProduct p) {
+  constexpr bool FIRST = KIND0 == PL_QKV_FIRST;
+  constexpr int KIND = FIRST ? (int)PL_QKV : KIND0, PER = (MT + 1) / 2;  // elements of the result a thread finishes
+  constexpr int NP = FIRST && MT > 2 && NP0 > 4 ? 4 : NP0;               // (three waves on a SIMD: 168 registers)
   __shared__ __attribute__((aligned(16))) float part[PL_WAVES * MT * 256];  // [wave][row tile][lane][4]
   __shared__ float sqs[PL_WAVES * 64];
+  __shared__ float rot[FIRST ? MT * 16 * 16 : 1];  // [row][pair of the tile][2]
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
   const int t = blockIdx.x, K = p.K, M = p.M, per = p.dh >> 4, head = KIND == PL_QKV ? t / per : 0, jj = t - head * per, half = p.dh >> 1;
   // source column (columns past the end read the last one, their results are dropped)
@@ -82,10 +102,39 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
   if (KIND == PL_QKV) col = head * p.dh + (c16 < 8 ? 8 * jj + c16 : half + 8 * jj + c16 - 8);
   else if (KIND == PL_GLU) col = (8 * t + (c16 & 7) < p.N ? 8 * t + (c16 & 7) : p.N - 1) + (c16 < 8 ? 0 : p.N);
   else col = 16 * t + c16 < p.N ? 16 * t + c16 : p.N - 1;
+  if (FIRST && wave >= PL_WAVES) {
+    for (int e = (int)threadIdx.x - PL_THREADS; e < 8 * M; e += 64 * MT) {
+      const int row = e >> 3, pair = 8 * jj + (e & 7);
+      float c, s;
+      rotation(p.pos[row], pair, half, p.theta, &c, &s);
+      rot[2 * e] = c;
+      rot[2 * e + 1] = s;
+      if (head == 0) {
+        p.cs[((size_t)row * half + pair) * 2] = c;
+        p.cs[((size_t)row * half + pair) * 2 + 1] = s;
+      }
+    }
+    __syncthreads();
+    return;
+  }
   const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
   const bool vec = (((uintptr_t)p.A | (size_t)p.lda * 4) % 16 == 0) && K % 4 == 0;
+  constexpr bool LEN = KIND == PL_QKV || KIND == PL_RESID;
   int L = 0;
-  if (KIND != PL_GLU) L = *p.L_dev;
+  if (LEN) L = *p.L_dev;
+  // what the end adds to or rotates by: behind the sums it was a trip to memory of its own
+  float was[PER][2];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int it = (int)threadIdx.x + PL_THREADS * u, row = 16 * (it >> 8) + ((it >> 4) & 15), c = it & 15;
+    was[u][0] = was[u][1] = 0.f;
+    if (KIND == PL_RESID && row < M && 16 * t + c < p.N) was[u][0] = p.out[(size_t)row * p.ldo + 16 * t + c];
+    if (KIND == PL_QKV && !FIRST && row < M && head < p.Hq + p.Hkv) {
+      const float *cs = p.cs + ((size_t)row * half + 8 * jj + (c & 7)) * 2;
+      was[u][0] = cs[0];
+      was[u][1] = cs[1];
+    }
+  }
   pl_f4 acc[MT];
   float sq[MT];
 #pragma unroll
@@ -139,14 +188,17 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
     }
   }
   __syncthreads();
-  if (KIND != PL_GLU && (L < 0 || L + M > p.max_len)) {
+  if (LEN && (L < 0 || L + M > p.max_len)) {
     if (KIND == PL_QKV && t == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
       *p.err = 1;
       __hip_atomic_store(p.err_map, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     return;
   }
-  for (int it = threadIdx.x; it < 256 * MT; it += PL_THREADS) {
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int it = (int)threadIdx.x + PL_THREADS * u;
+    if (it >= 256 * MT) break;
     const int mt = it >> 8, r16 = (it >> 4) & 15, row = 16 * mt + r16, c = it & 15;
     const float *pp = part + (size_t)(mt * 64 + 16 * (r16 >> 2) + c) * 4 + (r16 & 3);
     constexpr int HALF = PL_WAVES / 2, WS = MT * 256;
@@ -159,14 +211,14 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
       for (int w = 1; w < PL_WAVES; ++w) q += sqs[w * 64 + row];
       v *= 1.0f / sqrtf(q / (float)K + p.eps);
     }
-    const float other = KIND == PL_RESID ? 0.f : __shfl_xor(v, 8, 64);
+    const float other = KIND == PL_RESID || KIND == PL_STORE ? 0.f : __shfl_xor(v, 8, 64);
     if (row >= M) continue;
     if (KIND == PL_QKV) {
       const int ch = c < 8 ? 8 * jj + c : half + 8 * jj + c - 8;
       float y = v;
       if (head < p.Hq + p.Hkv) {
-        const float *cs = p.cs + ((size_t)row * half + 8 * jj + (c & 7)) * 2;
-        y = c < 8 ? v * cs[0] - other * cs[1] : v * cs[0] + other * cs[1];
+        const float cs = FIRST ? rot[(8 * row + (c & 7)) * 2] : was[u][0], sn = FIRST ? rot[(8 * row + (c & 7)) * 2 + 1] : was[u][1];
+        y = c < 8 ? v * cs - other * sn : v * cs + other * sn;
       }
       if (head < p.Hq) p.out[(size_t)row * p.ldo + head * p.dh + ch] = y;
       else if (head < p.Hq + p.Hkv) store_from_float<T>((T *)p.Kc + ((size_t)(L + row) * p.Hkv + head - p.Hq) * p.dh + ch, y);
@@ -174,7 +226,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_product_kernel(PlProduct p) 
     } else if (KIND == PL_GLU) {
       if (c < 8 && 8 * t + c < p.N) p.out[(size_t)row * p.ldo + 8 * t + c] = v / (1.0f + expf(-v)) * other;
     } else if (16 * t + c < p.N) {
-      p.out[(size_t)row * p.ldo + 16 * t + c] += v;
+      p.out[(size_t)row * p.ldo + 16 * t + c] = KIND == PL_STORE ? v : was[u][0] + v;
     }
   }
 }
@@ -198,16 +250,17 @@ __device__ __forceinline__ float pl_wave_sum(float v) {
 // behind the length, and waves then take more than one share each, so that the sums depend on the length alone.
 // Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
 // 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
-// 28 -> 12, L = 4000 108 -> 41.
+// 28 -> 12, L = 4000 108 -> 41.  With K and V of the first piece requested beside q and the length (V waited for both before): L = 47 5.7 -> 5.0.
 template <typename T>
 __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float *q, int ldq, int Hq, int Hkv, int dh, const T *Kc, const T *Vc, const int32_t *L_dev,
                                                                      int max_len, int Bp, const uint64_t *vis, float *out) {
   __shared__ __attribute__((aligned(16))) float qs[256], ps[PL_WAVES][64], os[PL_WAVES][64 + 2];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int n_waves = (int)blockDim.x >> 6, b = blockIdx.x, hq = blockIdx.y, u0 = 64 * blockIdx.z, L = *L_dev;
-  if (L < 0 || L + Bp > max_len) return;
-  const int kvh = hq / (Hq / Hkv), nkv = Hkv * dh, total = L + Bp, n_chunks = (total + 63) >> 6;
-  const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)total * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)total * nkv * sizeof(T));  // (rows past the end: zeros)
+  const int n_waves = (int)blockDim.x >> 6, b = blockIdx.x, hq = blockIdx.y, u0 = 64 * blockIdx.z;
+  const int kvh = hq / (Hq / Hkv), nkv = Hkv * dh;
+  // (rows behind the length are masked whatever they hold, rows behind the cache read as zeros: the first piece needs no length)
+  const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)max_len * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)max_len * nkv * sizeof(T));
+  const int L_mem = *L_dev;
   const uint64_t vb = vis[b];
   const float scale = 1.0f / sqrtf((float)dh);
   float kv[64], vv[64];
@@ -217,9 +270,30 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
     for (int c = 0; c < 64; c += 16)
       if (c0 + c < dh) pl_load16<T>(kv + c, rk, at + (unsigned)c);  // (head_dim is a multiple of 16)
   };
-  const int n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
-  if (wave < n_shares) load_k(wave, 0);
-  for (int i = threadIdx.x; i < dh; i += blockDim.x) qs[i] = q[(size_t)b * ldq + hq * dh + i];
+  auto load_v = [&](int ck) {  // this lane's channel of the 64 keys
+    unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+      vv[j] = pl_load<T>(rv, at);
+      at += (unsigned)nkv;
+      asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
+    }
+  };
+  // q, K and V of the first piece are requested together, q first (loads come back in order)
+  float q_in[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) q_in[u] = (int)(threadIdx.x + u * blockDim.x) < dh ? q[(size_t)b * ldq + hq * dh + threadIdx.x + u * blockDim.x] : 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+  load_k(wave, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_v(wave);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if ((int)(threadIdx.x + u * blockDim.x) < dh) qs[threadIdx.x + u * blockDim.x] = q_in[u];
+  const int L = __builtin_amdgcn_readfirstlane(L_mem);
+  if (L < 0 || L + Bp > max_len) return;
+  const int total = L + Bp, n_chunks = (total + 63) >> 6, n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
   __syncthreads();
   for (int share = wave; share < n_shares; share += n_waves) {
     float m = -INFINITY, l = 0.f;
@@ -227,13 +301,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
     if (share != wave) load_k(share, 0);
     for (int ck = share; ck < n_chunks; ck += PL_WAVES) {
       const int key = 64 * ck + lane;
-      unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));  // this lane's channel of the 64 keys
-#pragma unroll
-      for (int j = 0; j < 64; ++j) {
-        vv[j] = pl_load<T>(rv, at);
-        at += (unsigned)nkv;
-        asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
-      }
+      if (ck != wave) load_v(ck);
       float s0 = 0.f, s1 = 0.f;
       for (int c0 = 0; c0 < dh; c0 += 64) {
         if (c0 > 0) load_k(ck, c0);
@@ -308,11 +376,12 @@ static int plain_attention(const float *q, int ldq, const la_model_desc &d, cons
 
 template <typename T, int KIND, int NP>
 static int plain_product_np(const PlProduct &p, int n_tiles, hipStream_t s) {
-  switch (ceil_div(p.M, 16)) {
-  case 1: plain_product_kernel<T, 1, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
-  case 2: plain_product_kernel<T, 2, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
-  case 3: plain_product_kernel<T, 3, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
-  default: plain_product_kernel<T, 4, KIND, NP><<<n_tiles, PL_THREADS, 0, s>>>(p); break;
+  const int MT = ceil_div(p.M, 16), threads = PL_THREADS + (KIND == PL_QKV_FIRST ? 64 * MT : 0);
+  switch (MT) {
+  case 1: plain_product_kernel<T, 1, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
+  case 2: plain_product_kernel<T, 2, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
+  case 3: plain_product_kernel<T, 3, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
+  default: plain_product_kernel<T, 4, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
   }
   LA_HIP(hipGetLastError());
   return LA_OK;
