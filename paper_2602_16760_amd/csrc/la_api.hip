@@ -243,6 +243,19 @@ int recover_if_needed(la_model *m, hipStream_t s) {
   return LA_OK;
 }
 
+int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, hipStream_t s) {
+  ProfScope ps("embed", s);
+  dim3 grid(rows, (m->d.d_model + EMBED_COLS - 1) / EMBED_COLS);
+  if (m->d.dtype == LA_F32)
+    embed_kernel<float><<<grid, 256, 0, s>>>((const float *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+  else if (m->d.dtype == LA_F16)
+    embed_kernel<_Float16><<<grid, 256, 0, s>>>((const _Float16 *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+  else
+    embed_kernel<uint16_t><<<grid, 256, 0, s>>>((const uint16_t *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+  LA_HIP(hipGetLastError());
+  return LA_OK;
+}
+
 bool stream_captures(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
@@ -266,7 +279,7 @@ extern "C" void la_free_model(la_model *m) {
       if (p) (void)hipFree(p);
   }
   void *ps[] = {m->embed, m->unembed, m->g_final, m->qkv, m->attn, m->act, m->logits, m->rope_cs, m->err_dev,
-                m->pf_hidden, m->pf_pos, m->pf_vis};
+                m->pf_hidden, m->pf_pos, m->pf_vis, m->prompt};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   if (m->err_host) (void)hipHostFree(m->err_host);
@@ -505,17 +518,7 @@ extern "C" int la_embed(la_model *m, const int32_t *tok, int Bp, float *hidden, 
   LA_PENDING(m);
   LA_REQUIRE(Bp >= 1 && Bp <= LA_MAX_ROWS, LA_EINVAL, "Bp=%d outside [1, %d]", Bp, LA_MAX_ROWS);
   LA_REQUIRE(m->embed != nullptr, LA_EINVAL, "model was created without an embedding table");
-  hipStream_t s = (hipStream_t)stream;
-  ProfScope ps("embed", s);
-  dim3 grid(Bp, (m->d.d_model + EMBED_COLS - 1) / EMBED_COLS);
-  if (m->d.dtype == LA_F32)
-    embed_kernel<float><<<grid, 256, 0, s>>>((const float *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
-  else if (m->d.dtype == LA_F16)
-    embed_kernel<_Float16><<<grid, 256, 0, s>>>((const _Float16 *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
-  else
-    embed_kernel<uint16_t><<<grid, 256, 0, s>>>((const uint16_t *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
-  LA_HIP(hipGetLastError());
-  return LA_OK;
+  return launch_embed(m, tok, Bp, hidden, (hipStream_t)stream);
 }
 
 extern "C" int la_forward_layers(la_model *m, int layer_begin, int layer_end, float *hidden, int Bp,
@@ -625,6 +628,16 @@ extern "C" int la_prefill(la_model *m, la_kv *kv, const int32_t *tok, int n, int
     for (int done = 0; !rc && done < n; done += rows) {
       const int M = n - done < rows ? n - done : rows;
       rc = mfma_prefill_chunk(m, kv, tok + done, M, L0 + done, s);
+      if (!rc) rc = la_kv_set_len(kv, L0 + done + M, stream);
+    }
+    return rc;
+  }
+  if (!rc) rc = generic_prefill_rows(m, kv, n, &rows);
+  if (!rc && rows > 0) {
+    if ((rc = recover_if_needed(m, s))) return rc;
+    for (int done = 0; !rc && done < n; done += rows) {
+      const int M = n - done < rows ? n - done : rows;
+      rc = generic_prefill_chunk(m, kv, tok + done, M, s);
       if (!rc) rc = la_kv_set_len(kv, L0 + done + M, stream);
     }
     return rc;

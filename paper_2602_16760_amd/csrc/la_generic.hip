@@ -430,8 +430,12 @@ static bool plain_head(const la_model_desc &d) {
   return (dm + pad) * V * 4 < (size_t)1 << 31 && ((LA_MAX_ROWS + 1) * dm + pad) * 4 < (size_t)1 << 31 && dm * V <= PL_LAYER_WEIGHTS && plain_round(dm, ceil_div(V, 16));
 }
 
+struct PlainScratch {
+  float *q, *attn, *act, *cs;
+};
+// pos, vis NULL: the rows of a prompt, behind the length.
 template <typename T>
-static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis, la_kv *kv, hipStream_t s) {
+static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis, la_kv *kv, const PlainScratch &b, hipStream_t s) {
   const la_model_desc &d = m->d;
   const int nqkv = m->nqkv(), qd = m->qdim(), F = d.d_ffn, dm = d.d_model;
   int rc = LA_OK;
@@ -442,16 +446,17 @@ static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, c
     auto product = [&](const float *A, int K, const float *gain, const void *W, int ldw, int N, float *out, int ldo) {
       PlProduct p{};
       p.A = A; p.lda = K; p.M = Bp; p.K = K; p.gain = gain; p.eps = d.rms_eps; p.W = W; p.ldw = ldw; p.N = N; p.out = out; p.ldo = ldo;
-      p.cs = m->rope_cs; p.Kc = Kc; p.Vc = Vc; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.dh = d.head_dim; p.max_len = kv->max_len;
+      p.cs = b.cs; p.Kc = Kc; p.Vc = Vc; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.dh = d.head_dim; p.max_len = kv->max_len;
       p.L_dev = kv->L_dev; p.err = kv->err_dev; p.err_map = m->err_map; p.pos = pos; p.theta = d.rope_theta;
       return p;
     };
-    const PlProduct qkv = product(hidden, dm, w.g_attn, w.wqkv, nqkv, nqkv, m->qkv, qd);
+    const PlProduct qkv = product(hidden, dm, w.g_attn, w.wqkv, nqkv, nqkv, b.q, qd);
     if ((rc = l == lb ? plain_product<T, PL_QKV_FIRST>("plain_qkv", qkv, nqkv / 16, s) : plain_product<T, PL_QKV>("plain_qkv", qkv, nqkv / 16, s))) return rc;
-    if ((rc = plain_attention<T>(m->qkv, qd, d, Kc, Vc, kv, Bp, vis, m->attn, s))) return rc;
-    if ((rc = plain_product<T, PL_RESID>("plain_o", product(m->attn, qd, nullptr, w.wo, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
-    if ((rc = plain_product<T, PL_GLU>("plain_gateup", product(hidden, dm, w.g_mlp, w.wgu, 2 * F, F, m->act, F), ceil_div(F, 8), s))) return rc;
-    if ((rc = plain_product<T, PL_RESID>("plain_down", product(m->act, F, nullptr, w.wdown, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
+    if (!vis && l + 1 == d.n_layers) break;  // (of a prompt's last layer nobody reads more than the K and V rows)
+    if ((rc = plain_attention<T>(b.q, qd, d, Kc, Vc, kv, Bp, vis, b.attn, s))) return rc;
+    if ((rc = plain_product<T, PL_RESID>("plain_o", product(b.attn, qd, nullptr, w.wo, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
+    if ((rc = plain_product<T, PL_GLU>("plain_gateup", product(hidden, dm, w.g_mlp, w.wgu, 2 * F, F, b.act, F), ceil_div(F, 8), s))) return rc;
+    if ((rc = plain_product<T, PL_RESID>("plain_down", product(b.act, F, nullptr, w.wdown, dm, dm, hidden, dm), ceil_div(dm, 16), s))) return rc;
   }
   return LA_OK;
 }
@@ -459,7 +464,7 @@ static int plain_forward_t(la_model *m, int lb, int le, float *hidden, int Bp, c
 template <typename T>
 static int forward_t(la_model *m, int lb, int le, float *hidden, int Bp, const int32_t *pos, const uint64_t *vis,
                      la_kv *kv, hipStream_t s) {
-  if (plain_layers(m, kv)) return plain_forward_t<T>(m, lb, le, hidden, Bp, pos, vis, kv, s);
+  if (plain_layers(m, kv)) return plain_forward_t<T>(m, lb, le, hidden, Bp, pos, vis, kv, PlainScratch{m->qkv, m->attn, m->act, m->rope_cs}, s);
   const la_model_desc &d = m->d;
   int nqkv = m->nqkv(), qd = m->qdim(), F = d.d_ffn, dm = d.d_model;
   int rc = launch_rope_table(m, pos, Bp, s);
@@ -495,6 +500,50 @@ int generic_forward(la_model *m, int lb, int le, float *hidden, int Bp, const in
   if (m->d.dtype == LA_F32) return forward_t<float>(m, lb, le, hidden, Bp, pos, vis, kv, s);
   if (m->d.dtype == LA_F16) return forward_t<_Float16>(m, lb, le, hidden, Bp, pos, vis, kv, s);
   return forward_t<uint16_t>(m, lb, le, hidden, Bp, pos, vis, kv, s);
+}
+
+// A prompt through the small layers' launches, PL_PROMPT rows at a time: every row is summed as it is in a block, in one launch instead of one for each 64
+// rows, which leave most of the chip idle, and nothing of the last layer but its K and V.  Two fp32 layers 256 wide, us: 65 tokens 129 -> 53, 300 tokens
+// 402 -> 80, 1000 tokens 1414 -> 215, 3000 tokens 5108 -> 1045.
+// Scratch for the rows (6 MB for these layers, some tens at most: plain_layers) comes with the first prompt of more than one block and stays with the model;
+// without memory for it, and for short prompts, the rows go 64 at a time through a block's.  The thread's capture mode is relaxed meanwhile, so that a first prompt may be captured.
+constexpr int PL_PROMPT = 1024;
+int generic_prefill_rows(la_model *m, const la_kv *kv, int n, int *rows) {
+  *rows = 0;
+  if (m->use_mfma || !m->embed || !plain_layers(m, kv)) return LA_OK;
+  for (int l = 0; l < m->d.n_layers; ++l) LA_REQUIRE(m->layers[l].set, LA_EINVAL, "layer %d has no weights", l);
+  if (n > LA_MAX_ROWS && !m->prompt) {
+    const size_t per_row = (size_t)m->d.d_model + 2 * (size_t)m->qdim() + m->d.d_ffn + m->d.head_dim;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    if (hipMalloc((void **)&m->prompt, PL_PROMPT * per_row * 4) != hipSuccess) {
+      m->prompt = nullptr;
+      (void)hipGetLastError();  // (the next launch's check would report it)
+    }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  *rows = n > LA_MAX_ROWS && m->prompt ? PL_PROMPT : LA_MAX_ROWS;
+  return LA_OK;
+}
+
+// M tokens behind the length through every layer (the caller sets the cache length afterwards).
+int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, hipStream_t s) {
+  const la_model_desc &d = m->d;
+  const size_t R = PL_PROMPT;
+  float *x = m->pf_hidden;
+  PlainScratch b{m->qkv, m->attn, m->act, m->rope_cs};
+  if (M > LA_MAX_ROWS) {
+    x = m->prompt;
+    b.q = x + R * d.d_model;
+    b.attn = b.q + R * m->qdim();
+    b.act = b.attn + R * m->qdim();
+    b.cs = b.act + R * d.d_ffn;
+  }
+  const int rc = launch_embed(m, tok, M, x, s);
+  if (rc) return rc;
+  if (d.dtype == LA_F32) return plain_forward_t<float>(m, 0, d.n_layers, x, M, nullptr, nullptr, kv, b, s);
+  if (d.dtype == LA_F16) return plain_forward_t<_Float16>(m, 0, d.n_layers, x, M, nullptr, nullptr, kv, b, s);
+  return plain_forward_t<uint16_t>(m, 0, d.n_layers, x, M, nullptr, nullptr, kv, b, s);
 }
 
 int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2, hipStream_t s) {

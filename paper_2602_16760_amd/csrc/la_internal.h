@@ -65,6 +65,7 @@ struct la_model {
   float *pf_hidden = nullptr;
   int32_t *pf_pos = nullptr;
   uint64_t *pf_vis = nullptr;
+  float *prompt = nullptr;  // generic_prefill_rows: scratch of a prompt's rows
   la::MfmaModel *mf = nullptr;
   // Errors raised by kernels (a block that does not fit the cache: 1; a grid barrier that gave up: 4).  err_dev is the
   // device word the kernels OR into (the caches of this model alias it); err_host is one word of mapped pinned host
@@ -118,6 +119,9 @@ int generic_forward(la_model *m, int lb, int le, float *hidden, int Bp, const in
                     const uint64_t *vis, la_kv *kv, hipStream_t s);
 int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2,
                            hipStream_t s);
+int generic_prefill_rows(la_model *m, const la_kv *kv, int n, int *rows);  // of a chunk of an n-token prompt, scratch allocated; 0: by la_forward_layers
+int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, hipStream_t s);
+int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, hipStream_t s);
 int launch_rope_table(la_model *m, const int32_t *pos, int Bp, hipStream_t s);
 int launch_argmax_rows(const float *logits, int Bp, int V, int32_t *ids, float *top2, hipStream_t s);
 

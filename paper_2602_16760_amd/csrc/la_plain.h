@@ -64,7 +64,7 @@ struct PlProduct {
   void *Kc, *Vc;
   int Hq, Hkv, dh;
   // QKV_FIRST: the table is made, from these
-  const int32_t *pos;
+  const int32_t *pos;  // (NULL: the rows follow the length)
   double theta;
 };
 
@@ -77,7 +77,7 @@ __device__ __forceinline__ void rotation(int pos, int i, int half, double theta,
   *s = (float)ds;
 }
 
-// One product.  A workgroup takes 16 columns and all rows; its eight waves share the contraction, 16 deep at a time (the same order as
+// One product.  A workgroup takes 16 columns and all rows of a block (64 rows of a prompt); its eight waves share the contraction, 16 deep at a time (the same order as
 // gemm_generic_kernel's), NP slices of it on their way at once, and their sums are added in gemm_generic_kernel's order, an element per thread.
 //   QKV: eight channels of the lower half of a head and their rotation partners; rotates, and writes K and V to the cache.
 //   GLU: eight channels of gate and the same of up.
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
   __shared__ float sqs[PL_WAVES * 64];
   __shared__ float rot[FIRST ? MT * 16 * 16 : 1];  // [row][pair of the tile][2]
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, q4 = lane >> 4, c16 = lane & 15;
-  const int t = blockIdx.x, K = p.K, M = p.M, per = p.dh >> 4, head = KIND == PL_QKV ? t / per : 0, jj = t - head * per, half = p.dh >> 1;
+  const int row0 = 64 * blockIdx.y, t = blockIdx.x, K = p.K, M = p.M - row0 < 64 ? p.M - row0 : 64, per = p.dh >> 4, head = KIND == PL_QKV ? t / per : 0, jj = t - head * per, half = p.dh >> 1;
   // source column (columns past the end read the last one, their results are dropped)
   int col;
   if (KIND == PL_QKV) col = head * p.dh + (c16 < 8 ? 8 * jj + c16 : half + 8 * jj + c16 - 8);
@@ -106,18 +106,18 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
     for (int e = (int)threadIdx.x - PL_THREADS; e < 8 * M; e += 64 * MT) {
       const int row = e >> 3, pair = 8 * jj + (e & 7);
       float c, s;
-      rotation(p.pos[row], pair, half, p.theta, &c, &s);
+      rotation(p.pos ? p.pos[row] : *p.L_dev + row0 + row, pair, half, p.theta, &c, &s);
       rot[2 * e] = c;
       rot[2 * e + 1] = s;
       if (head == 0) {
-        p.cs[((size_t)row * half + pair) * 2] = c;
-        p.cs[((size_t)row * half + pair) * 2 + 1] = s;
+        p.cs[((size_t)(row0 + row) * half + pair) * 2] = c;
+        p.cs[((size_t)(row0 + row) * half + pair) * 2 + 1] = s;
       }
     }
     __syncthreads();
     return;
   }
-  const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
+  const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A + (size_t)row0 * p.lda, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
   const bool vec = (((uintptr_t)p.A | (size_t)p.lda * 4) % 16 == 0) && K % 4 == 0;
   constexpr bool LEN = KIND == PL_QKV || KIND == PL_RESID;
   int L = 0;
@@ -128,9 +128,9 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
   for (int u = 0; u < PER; ++u) {
     const int it = (int)threadIdx.x + PL_THREADS * u, row = 16 * (it >> 8) + ((it >> 4) & 15), c = it & 15;
     was[u][0] = was[u][1] = 0.f;
-    if (KIND == PL_RESID && row < M && 16 * t + c < p.N) was[u][0] = p.out[(size_t)row * p.ldo + 16 * t + c];
+    if (KIND == PL_RESID && row < M && 16 * t + c < p.N) was[u][0] = p.out[(size_t)(row0 + row) * p.ldo + 16 * t + c];
     if (KIND == PL_QKV && !FIRST && row < M && head < p.Hq + p.Hkv) {
-      const float *cs = p.cs + ((size_t)row * half + 8 * jj + (c & 7)) * 2;
+      const float *cs = p.cs + ((size_t)(row0 + row) * half + 8 * jj + (c & 7)) * 2;
       was[u][0] = cs[0];
       was[u][1] = cs[1];
     }
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
     }
   }
   __syncthreads();
-  if (LEN && (L < 0 || L + M > p.max_len)) {
-    if (KIND == PL_QKV && t == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
+  if (LEN && (L < 0 || L + p.M > p.max_len)) {
+    if (KIND == PL_QKV && t == 0 && row0 == 0 && threadIdx.x == 0) {  // the device word, and the host's mapped word (read without synchronising)
       *p.err = 1;
       __hip_atomic_store(p.err_map, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -220,13 +220,13 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
         const float cs = FIRST ? rot[(8 * row + (c & 7)) * 2] : was[u][0], sn = FIRST ? rot[(8 * row + (c & 7)) * 2 + 1] : was[u][1];
         y = c < 8 ? v * cs - other * sn : v * cs + other * sn;
       }
-      if (head < p.Hq) p.out[(size_t)row * p.ldo + head * p.dh + ch] = y;
-      else if (head < p.Hq + p.Hkv) store_from_float<T>((T *)p.Kc + ((size_t)(L + row) * p.Hkv + head - p.Hq) * p.dh + ch, y);
-      else store_from_float<T>((T *)p.Vc + ((size_t)(L + row) * p.Hkv + head - p.Hq - p.Hkv) * p.dh + ch, y);
+      if (head < p.Hq) p.out[(size_t)(row0 + row) * p.ldo + head * p.dh + ch] = y;
+      else if (head < p.Hq + p.Hkv) store_from_float<T>((T *)p.Kc + ((size_t)(L + row0 + row) * p.Hkv + head - p.Hq) * p.dh + ch, y);
+      else store_from_float<T>((T *)p.Vc + ((size_t)(L + row0 + row) * p.Hkv + head - p.Hq - p.Hkv) * p.dh + ch, y);
     } else if (KIND == PL_GLU) {
-      if (c < 8 && 8 * t + c < p.N) p.out[(size_t)row * p.ldo + 8 * t + c] = v / (1.0f + expf(-v)) * other;
+      if (c < 8 && 8 * t + c < p.N) p.out[(size_t)(row0 + row) * p.ldo + 8 * t + c] = v / (1.0f + expf(-v)) * other;
     } else if (16 * t + c < p.N) {
-      p.out[(size_t)row * p.ldo + 16 * t + c] = KIND == PL_STORE ? v : was[u][0] + v;
+      p.out[(size_t)(row0 + row) * p.ldo + 16 * t + c] = KIND == PL_STORE ? v : was[u][0] + v;
     }
   }
 }
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   // (rows behind the length are masked whatever they hold, rows behind the cache read as zeros: the first piece needs no length)
   const __amdgpu_buffer_rsrc_t rk = pl_rsrc(Kc, (size_t)max_len * nkv * sizeof(T)), rv = pl_rsrc(Vc, (size_t)max_len * nkv * sizeof(T));
   const int L_mem = *L_dev;
-  const uint64_t vb = vis[b];
+  const uint64_t vb = vis ? vis[b] : 0ull;
   const float scale = 1.0f / sqrtf((float)dh);
   float kv[64], vv[64];
   auto load_k = [&](int ck, int c0) {  // channels c0 .. c0 + 63 of this lane's key
@@ -293,7 +293,8 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
     if ((int)(threadIdx.x + u * blockDim.x) < dh) qs[threadIdx.x + u * blockDim.x] = q_in[u];
   const int L = __builtin_amdgcn_readfirstlane(L_mem);
   if (L < 0 || L + Bp > max_len) return;
-  const int total = L + Bp, n_chunks = (total + 63) >> 6, n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
+  // a prompt (vis = NULL) is causal, and what is behind a row is not looked at: a piece that it sees nothing of adds nothing
+  const int total = vis ? L + Bp : L + b + 1, seen = vis ? L : total, n_chunks = (total + 63) >> 6, n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
   __syncthreads();
   for (int share = wave; share < n_shares; share += n_waves) {
     float m = -INFINITY, l = 0.f;
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
       }
       __builtin_amdgcn_sched_barrier(0);
       if (ck + PL_WAVES < n_chunks) load_k(ck + PL_WAVES, 0);
-      const bool ok = key < total && (key < L || ((vb >> (key - L)) & 1ull));
+      const bool ok = key < total && (key < seen || ((vb >> (key - L)) & 1ull));
       const float v = ok ? (s0 + s1) * scale : -INFINITY;
       const float m_new = fmaxf(m, pl_wave_max(v));
       const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
@@ -376,12 +377,12 @@ static int plain_attention(const float *q, int ldq, const la_model_desc &d, cons
 
 template <typename T, int KIND, int NP>
 static int plain_product_np(const PlProduct &p, int n_tiles, hipStream_t s) {
-  const int MT = ceil_div(p.M, 16), threads = PL_THREADS + (KIND == PL_QKV_FIRST ? 64 * MT : 0);
+  const int MT = p.M < 64 ? ceil_div(p.M, 16) : 4, threads = PL_THREADS + (KIND == PL_QKV_FIRST ? 64 * MT : 0);
   switch (MT) {
   case 1: plain_product_kernel<T, 1, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
   case 2: plain_product_kernel<T, 2, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
   case 3: plain_product_kernel<T, 3, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
-  default: plain_product_kernel<T, 4, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
+  default: plain_product_kernel<T, 4, KIND, NP><<<dim3(n_tiles, ceil_div(p.M, 64)), threads, 0, s>>>(p); break;
   }
   LA_HIP(hipGetLastError());
   return LA_OK;
