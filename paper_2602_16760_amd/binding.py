@@ -8,6 +8,7 @@ this module fails loudly when the library has not been built.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 
 import numpy as np
@@ -122,11 +123,15 @@ def _check(rc):
         raise LaError(rc, lib.la_last_error().decode())
 
 
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream(stream=None):
     """Handle of `stream`, of the current stream without one.  (The stream object that torch.cuda.current_stream() makes for it
-    costs 2.9 us, more than half of a launch; a call of a small kernel waits for the host.)"""
+    costs 2.9 us, more than half of a launch, and torch.cuda.current_device() looks for the runtime's start first; a call of a small
+    kernel waits for the host.)"""
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _raw_stream(_device())
     return stream.cuda_stream
 
 
@@ -235,15 +240,19 @@ def la_free_pool(pool):
     lib.la_free_pool(pool)
 
 
+@functools.lru_cache(maxsize=64, typed=True)
+def _lookahead(W, N, G):
+    """Reference to a descriptor, which the library only reads."""
+    return C.byref(la_lookahead_desc(W, N, G))
+
+
 def la_state_init(pool, kv, W, N, G, prompt, Bp, seed_pool, state, stream=None):
-    d = la_lookahead_desc(W, N, G)
-    _check(lib.la_state_init(pool, kv, C.byref(d), _ptr(prompt), prompt.shape[0], Bp, int(seed_pool), _ptr(state),
+    _check(lib.la_state_init(pool, kv, _lookahead(W, N, G), _ptr(prompt), prompt.shape[0], Bp, int(seed_pool), _ptr(state),
                              _stream(stream)))
 
 
 def la_ngram_accept(pool, kv, W, N, G, ids, state, emitted, max_total, stream=None):
-    d = la_lookahead_desc(W, N, G)
-    _check(lib.la_ngram_accept(pool, kv, C.byref(d), _ptr(ids), _ptr(state), _ptr(emitted), max_total, _stream(stream)))
+    _check(lib.la_ngram_accept(pool, kv, _lookahead(W, N, G), _ptr(ids), _ptr(state), _ptr(emitted), max_total, _stream(stream)))
 
 
 def la_prefill(model, kv, tok, L0=0, stream=None):
