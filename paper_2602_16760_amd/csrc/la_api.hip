@@ -57,7 +57,8 @@ ProfScope::~ProfScope() {
 // before it (8.2 us at 32 rows of 4096; a step of two 7B layers and the head, 64 rows, 336.3 -> 332.4 us).
 constexpr int EMBED_COLS = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T *E, const int32_t *tok, int V, int d, float *hidden) {
+__global__ __launch_bounds__(256) void embed_kernel(const T *E, const int32_t *tok, int V, int d, float *hidden, int32_t *L_dev, int L) {
+  if (L_dev && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *L_dev = L;  // (a prompt's: it takes the place of a launch)
   int t = tok[blockIdx.x];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   int i0 = blockIdx.y * EMBED_COLS + threadIdx.x;
@@ -243,15 +244,15 @@ int recover_if_needed(la_model *m, hipStream_t s) {
   return LA_OK;
 }
 
-int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, hipStream_t s) {
+int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, int32_t *L_dev, int L, hipStream_t s) {
   ProfScope ps("embed", s);
   dim3 grid(rows, (m->d.d_model + EMBED_COLS - 1) / EMBED_COLS);
   if (m->d.dtype == LA_F32)
-    embed_kernel<float><<<grid, 256, 0, s>>>((const float *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+    embed_kernel<float><<<grid, 256, 0, s>>>((const float *)m->embed, tok, m->d.vocab, m->d.d_model, hidden, L_dev, L);
   else if (m->d.dtype == LA_F16)
-    embed_kernel<_Float16><<<grid, 256, 0, s>>>((const _Float16 *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+    embed_kernel<_Float16><<<grid, 256, 0, s>>>((const _Float16 *)m->embed, tok, m->d.vocab, m->d.d_model, hidden, L_dev, L);
   else
-    embed_kernel<uint16_t><<<grid, 256, 0, s>>>((const uint16_t *)m->embed, tok, m->d.vocab, m->d.d_model, hidden);
+    embed_kernel<uint16_t><<<grid, 256, 0, s>>>((const uint16_t *)m->embed, tok, m->d.vocab, m->d.d_model, hidden, L_dev, L);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }
@@ -518,7 +519,7 @@ extern "C" int la_embed(la_model *m, const int32_t *tok, int Bp, float *hidden, 
   LA_PENDING(m);
   LA_REQUIRE(Bp >= 1 && Bp <= LA_MAX_ROWS, LA_EINVAL, "Bp=%d outside [1, %d]", Bp, LA_MAX_ROWS);
   LA_REQUIRE(m->embed != nullptr, LA_EINVAL, "model was created without an embedding table");
-  return launch_embed(m, tok, Bp, hidden, (hipStream_t)stream);
+  return launch_embed(m, tok, Bp, hidden, nullptr, 0, (hipStream_t)stream);
 }
 
 extern "C" int la_forward_layers(la_model *m, int layer_begin, int layer_end, float *hidden, int Bp,
@@ -619,38 +620,44 @@ extern "C" int la_prefill(la_model *m, la_kv *kv, const int32_t *tok, int n, int
   LA_REQUIRE(n >= 0 && L0 >= 0 && (long long)L0 + n <= kv->max_len, LA_ERANGE, "rows [%d, %d) outside the cache (max_len %d)", L0,
              L0 + n, kv->max_len);
   hipStream_t s = (hipStream_t)stream;
-  int rc = la_kv_set_len(kv, L0, stream);
-  int rows = 0;
-  if (!rc && m->use_mfma) rc = mfma_prefill_rows(m, n, &rows);
+  if (n == 0) return la_kv_set_len(kv, L0, stream);
+  LA_PENDING(m);
+  // Each chunk's first launch sets the length that it starts at; a launch at the end sets the prompt's, after an error the one that was reached.
+  kv->L_bound = L0;
+  auto end = [&](int rc) {
+    if (!rc) return la_kv_set_len(kv, L0 + n, stream);
+    set_i32_kernel<<<1, 1, 0, s>>>(kv->L_dev, kv->L_bound);
+    (void)hipGetLastError();
+    return rc;
+  };
+  int rows = 0, rc = LA_OK;
+  if (m->use_mfma) rc = mfma_prefill_rows(m, n, &rows);
   if (!rc && rows > 0) {
     // the large-M pass: one matrix product per weight matrix and prompt chunk
-    if ((rc = recover_if_needed(m, s))) return rc;
+    rc = recover_if_needed(m, s);
     for (int done = 0; !rc && done < n; done += rows) {
-      const int M = n - done < rows ? n - done : rows;
-      rc = mfma_prefill_chunk(m, kv, tok + done, M, L0 + done, s);
-      if (!rc) rc = la_kv_set_len(kv, L0 + done + M, stream);
+      kv->L_bound = L0 + done;
+      rc = mfma_prefill_chunk(m, kv, tok + done, n - done < rows ? n - done : rows, L0 + done, s);
     }
-    return rc;
+    return end(rc);
   }
   if (!rc) rc = generic_prefill_rows(m, kv, n, &rows);
   if (!rc && rows > 0) {
-    if ((rc = recover_if_needed(m, s))) return rc;
+    rc = recover_if_needed(m, s);
     for (int done = 0; !rc && done < n; done += rows) {
-      const int M = n - done < rows ? n - done : rows;
-      rc = generic_prefill_chunk(m, kv, tok + done, M, s);
-      if (!rc) rc = la_kv_set_len(kv, L0 + done + M, stream);
+      kv->L_bound = L0 + done;
+      rc = generic_prefill_chunk(m, kv, tok + done, n - done < rows ? n - done : rows, L0 + done, s);
     }
-    return rc;
+    return end(rc);
   }
   for (int done = 0; !rc && done < n; done += LA_MAX_ROWS) {
     rows = n - done < LA_MAX_ROWS ? n - done : LA_MAX_ROWS;
-    rc = la_embed(m, tok + done, rows, m->pf_hidden, stream);
+    kv->L_bound = L0 + done;
+    rc = launch_embed(m, tok + done, rows, m->pf_hidden, kv->L_dev, L0 + done, s);
     if (rc) break;
     causal_layout_kernel<<<1, 64, 0, s>>>(m->pf_pos, m->pf_vis, L0 + done, rows);
-    LA_HIP(hipGetLastError());
-    rc = la_forward_layers(m, 0, m->d.n_layers, m->pf_hidden, rows, m->pf_pos, m->pf_vis, kv, stream);
-    if (rc) break;
-    rc = la_kv_set_len(kv, L0 + done + rows, stream);
+    if (hipError_t e = hipGetLastError()) rc = hip_fail(e, "causal_layout_kernel");
+    if (!rc) rc = la_forward_layers(m, 0, m->d.n_layers, m->pf_hidden, rows, m->pf_pos, m->pf_vis, kv, stream);
   }
-  return rc;
+  return end(rc);
 }

@@ -526,8 +526,8 @@ int generic_prefill_rows(la_model *m, const la_kv *kv, int n, int *rows) {
   return LA_OK;
 }
 
-// M tokens behind the length through every layer (the caller sets the cache length afterwards).
-int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, hipStream_t s) {
+// M tokens at L0, L0 + 1, ... through every layer (the caller sets the cache length afterwards).
+int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0, hipStream_t s) {
   const la_model_desc &d = m->d;
   const size_t R = PL_PROMPT;
   float *x = m->pf_hidden;
@@ -539,7 +539,7 @@ int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, hip
     b.act = b.attn + R * m->qdim();
     b.cs = b.act + R * d.d_ffn;
   }
-  const int rc = launch_embed(m, tok, M, x, s);
+  const int rc = launch_embed(m, tok, M, x, kv->L_dev, L0, s);
   if (rc) return rc;
   if (d.dtype == LA_F32) return plain_forward_t<float>(m, 0, d.n_layers, x, M, nullptr, nullptr, kv, b, s);
   if (d.dtype == LA_F16) return plain_forward_t<_Float16>(m, 0, d.n_layers, x, M, nullptr, nullptr, kv, b, s);

@@ -120,8 +120,9 @@ int generic_forward(la_model *m, int lb, int le, float *hidden, int Bp, const in
 int generic_unembed_argmax(la_model *m, const float *hidden, int Bp, int32_t *ids, float *top2,
                            hipStream_t s);
 int generic_prefill_rows(la_model *m, const la_kv *kv, int n, int *rows);  // of a chunk of an n-token prompt, scratch allocated; 0: by la_forward_layers
-int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, hipStream_t s);
-int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, hipStream_t s);
+int generic_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0, hipStream_t s);
+// (L_dev: that length is set to L, by the same launch)
+int launch_embed(la_model *m, const int32_t *tok, int rows, float *hidden, int32_t *L_dev, int L, hipStream_t s);
 int launch_rope_table(la_model *m, const int32_t *pos, int Bp, hipStream_t s);
 int launch_argmax_rows(const float *logits, int Bp, int V, int32_t *ids, float *top2, hipStream_t s);
 

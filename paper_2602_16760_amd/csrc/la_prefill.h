@@ -606,11 +606,12 @@ __global__ __launch_bounds__(256, 2) void pf_attn_kernel(const uint16_t *Q, cons
   pf_attn_body<DH, F16>((LDS_AS uint8_t *)pf_kv, Q, Kc, Vc, out, M, RT, RTr, L0, Hq, Hkv);
 }
 
-// x[row] = E[tok[row]] (eight elements per thread at a time), and cos, sin of position L0 + row for every RoPE pair (double
+// The length that the chunk starts at, x[row] = E[tok[row]] (eight elements per thread at a time), and cos, sin of position L0 + row for every RoPE pair (double
 // precision angles, as the block kernel's table); one workgroup per row.
 __global__ __launch_bounds__(256) void pf_embed_kernel(const uint16_t *E, const int32_t *tok, int V, int d, int f16, float *x, float *cs, int half, int L0,
-                                                       double theta) {
+                                                       double theta, int32_t *L_dev) {
   const int row = blockIdx.x;
+  if (row == 0 && threadIdx.x == 0) *L_dev = L0;
   int t = tok[row];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   for (int i = threadIdx.x * 8; i < d; i += 256 * 8) {
@@ -814,7 +815,7 @@ int mfma_prefill_chunk(la_model *m, la_kv *kv, const int32_t *tok, int M, int L0
   const int RT = (M + 63) / 64 * 4, RTr = (M + 15) / 16, half = d.head_dim / 2, f16 = d.dtype == LA_F16;
   {
     ProfScope ps("pf_embed", s);
-    pf_embed_kernel<<<M, 256, 0, s>>>((const uint16_t *)m->embed, tok, d.vocab, d.d_model, f16, b.x, b.cs, half, L0, (double)d.rope_theta);
+    pf_embed_kernel<<<M, 256, 0, s>>>((const uint16_t *)m->embed, tok, d.vocab, d.d_model, f16, b.x, b.cs, half, L0, (double)d.rope_theta, kv->L_dev);
   }
   LA_HIP(hipGetLastError());
   const GemmPlan *plans[4] = {&f->p_qkv, &f->p_o, &f->p_gu, &f->p_down};

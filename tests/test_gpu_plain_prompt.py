@@ -100,3 +100,29 @@ def test_a_first_prompt_can_be_captured():
         torch.cuda.synchronize()
         eng.close()
         ref.close()
+
+
+@pytest.mark.parametrize("name,n", [("tiny", 5), ("tiny", 100), ("small_bf16", 5), ("small_bf16", 100)])
+def test_a_prompt_that_cannot_run_leaves_its_start_as_the_length(name, n):
+    import torch
+    from paper_2602_16760_amd import binding as B
+    sh = SHAPES.get(name) or synth.SHAPES[name]
+    eng = gpu_engine(sh, 300, seed=2)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}[sh.dtype]
+    model = B.la_init_model(sh, torch.zeros(sh.vocab, sh.d_model, dtype=dt, device="cuda"))  # (no layer has weights)
+    kv = B.la_kv_alloc(model, 300)
+    try:
+        tok = torch.zeros(n, dtype=torch.int32, device="cuda")
+        B.la_kv_set_len(kv, 200)
+        with pytest.raises(B.LaError, match="no weights"):
+            B.la_prefill(model, kv, tok, 7)
+        assert B.la_kv_get_len(kv) == 7
+        B.la_prefill(eng.model, eng.kv, tok[:0], 9)
+        assert B.la_kv_get_len(eng.kv) == 9
+        B.la_prefill(eng.model, eng.kv, tok, 9)
+        assert B.la_kv_get_len(eng.kv) == 9 + n
+    finally:
+        torch.cuda.synchronize()
+        B.la_free_kv(kv)
+        B.la_free_model(model)
+        eng.close()
