@@ -210,8 +210,10 @@ int la_unembed_argmax_noalloc(la_model *m, const float *hidden, int Bp, int32_t 
  * (device int32) at positions L0.. through every layer, writes cache rows L0..L0+n-1 and
  * sets L = L0 + n.  Prompts of more than LA_MAX_ROWS tokens on the matrix-core path run as one matrix
  * product per weight matrix and chunk of 2048 tokens (the weights are read once per chunk),
- * with a causal attention kernel over the cache; shorter prompts, and models on the plain
- * kernels, go through the block kernel in causal chunks of LA_MAX_ROWS rows.  Everything is
+ * with a causal attention kernel over the cache; shorter prompts go through the block kernel.  Small models
+ * on the plain kernels run a layer's launches over up to 1024 tokens at a time (scratch of about 4096 x (d_model + 2 Hq x dh + d_ffn + dh)
+ * bytes, allocated by the first prompt of more than LA_MAX_ROWS tokens; without memory for it, LA_MAX_ROWS at a time); larger ones
+ * on the plain kernels in causal blocks of LA_MAX_ROWS rows.  Everything is
  * enqueued on `stream`; the hidden states are not returned (generation restarts from the last
  * prompt token as c0).  The model's first prompt of more than LA_MAX_ROWS tokens allocates
  * buffers for 128 rows, about 128 x (d_model x 38 + d_ffn x 2 + Hq x dh x 4) bytes; the first of

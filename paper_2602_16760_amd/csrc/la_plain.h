@@ -44,6 +44,13 @@ __device__ __forceinline__ void pl_load16(float *out, __amdgpu_buffer_rsrc_t r, 
   }
 }
 
+// A rotated channel (lower: of the lower half of its head); products and sum are rounded one by one wherever this is inlined.
+__device__ __forceinline__ float rotated(bool lower, float mine, float other, float c, float s) {
+#pragma clang fp contract(off)
+  const float a = mine * c, b = other * s;
+  return lower ? a - b : a + b;
+}
+
 enum PlKind { PL_QKV = 0, PL_RESID = 1, PL_GLU = 2, PL_STORE = 3, PL_QKV_FIRST = 4 };
 
 struct PlProduct {
@@ -218,7 +225,7 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
       float y = v;
       if (head < p.Hq + p.Hkv) {
         const float cs = FIRST ? rot[(8 * row + (c & 7)) * 2] : was[u][0], sn = FIRST ? rot[(8 * row + (c & 7)) * 2 + 1] : was[u][1];
-        y = c < 8 ? v * cs - other * sn : v * cs + other * sn;
+        y = rotated(c < 8, v, other, cs, sn);
       }
       if (head < p.Hq) p.out[(size_t)(row0 + row) * p.ldo + head * p.dh + ch] = y;
       else if (head < p.Hq + p.Hkv) store_from_float<T>((T *)p.Kc + ((size_t)(L + row0 + row) * p.Hkv + head - p.Hq) * p.dh + ch, y);
