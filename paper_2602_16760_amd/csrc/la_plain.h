@@ -94,11 +94,15 @@ __device__ __forceinline__ void rotation(int pos, int i, int half, double theta,
 // Bound: a launch, the weights' way from memory (each is read by one wave) and the sums' through LDS.  Step of the tiny shape (256
 // wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below; -> 56.9 with the table, the unembedding and the arg-max in
 // products of this kind, what an epilogue adds to or rotates by requested with the operands, and K and V of the attention's first piece with q.
+// A wide contraction into the residual stream (down: 16 workgroups of the tiny shape, 36 loads a wave) is shared by sixteen waves, whose upper half's
+// sums are added to the lower half's first: tiny shape, 17 rows, 57.9 -> 56.1 us a step, 64 rows 81.1 -> 80.2, error against 64 bits 2.5e-7 -> 2.4e-7.
+constexpr int pl_waves(int kind, int np) { return kind == PL_RESID && np > 2 ? 2 * PL_WAVES : PL_WAVES; }
 template <typename T, int MT, int KIND0, int NP0>
-__global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0)) void plain_product_kernel(PlProduct p) {
+__global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0)) void plain_product_kernel(PlProduct p) {
   constexpr bool FIRST = KIND0 == PL_QKV_FIRST;
   constexpr int KIND = FIRST ? (int)PL_QKV : KIND0, PER = (MT + 1) / 2;  // elements of the result a thread finishes
-  constexpr int NP = FIRST && MT > 2 && NP0 > 4 ? 4 : NP0;               // (three waves on a SIMD: 168 registers)
+  constexpr int WV = pl_waves(KIND0, NP0);
+  constexpr int NP = WV > PL_WAVES ? NP0 / 2 : FIRST && MT > 2 && NP0 > 4 ? 4 : NP0;  // (QKV_FIRST: three waves on a SIMD, 168 registers)
   __shared__ __attribute__((aligned(16))) float part[PL_WAVES * MT * 256];  // [wave][row tile][lane][4]
   __shared__ float sqs[PL_WAVES * 64];
   __shared__ float rot[FIRST ? MT * 16 * 16 : 1];  // [row][pair of the tile][2]
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
   for (int u = 0; u < PER; ++u) {
     const int it = (int)threadIdx.x + PL_THREADS * u, row = 16 * (it >> 8) + ((it >> 4) & 15), c = it & 15;
     was[u][0] = was[u][1] = 0.f;
-    if (KIND == PL_RESID && row < M && 16 * t + c < p.N) was[u][0] = p.out[(size_t)(row0 + row) * p.ldo + 16 * t + c];
+    if (KIND == PL_RESID && threadIdx.x < PL_THREADS && row < M && 16 * t + c < p.N) was[u][0] = p.out[(size_t)(row0 + row) * p.ldo + 16 * t + c];
     if (KIND == PL_QKV && !FIRST && row < M && head < p.Hq + p.Hkv) {
       const float *cs = p.cs + ((size_t)(row0 + row) * half + 8 * jj + (c & 7)) * 2;
       was[u][0] = cs[0];
@@ -149,12 +153,12 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
     acc[mt] = pl_f4{0.f, 0.f, 0.f, 0.f};
     sq[mt] = 0.f;
   }
-  for (int k0 = 16 * wave; k0 < K; k0 += 16 * PL_WAVES * NP) {
+  for (int k0 = 16 * wave; k0 < K; k0 += 16 * WV * NP) {
     pl_f4 b[NP], g[NP], x[NP][MT];
 #pragma unroll
     for (int n = 0; n < NP; ++n) {
-      const int k = k0 + 16 * PL_WAVES * n + 4 * q4;
-      if (k0 + 16 * PL_WAVES * n >= K) continue;
+      const int k = k0 + 16 * WV * n + 4 * q4;
+      if (k0 + 16 * WV * n >= K) continue;
 #pragma unroll
       for (int j = 0; j < 4; ++j) b[n][j] = pl_load<T>(rw, (unsigned)((k + j) * p.ldw + col));
 #pragma unroll
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
     }
 #pragma unroll
     for (int n = 0; n < NP; ++n) {
-      if (k0 + 16 * PL_WAVES * n >= K) continue;
+      if (k0 + 16 * WV * n >= K) continue;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -184,6 +188,19 @@ __global__ __launch_bounds__(PL_THREADS + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0))
           acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(p.gain ? v * g[n][j] : v, b[n][j], acc[mt], 0, 0, 0);
         }
     }
+  }
+  if constexpr (WV > PL_WAVES) {  // the upper half's sums go to the lower half first
+    pl_f4 *pp = reinterpret_cast<pl_f4 *>(part) + (size_t)(wave % PL_WAVES) * MT * 64 + lane;
+    if (wave >= PL_WAVES)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) pp[mt * 64] = acc[mt];
+    __syncthreads();
+    if (wave >= PL_WAVES) {
+      __syncthreads();
+      return;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] += pp[mt * 64];
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -384,7 +401,7 @@ static int plain_attention(const float *q, int ldq, const la_model_desc &d, cons
 
 template <typename T, int KIND, int NP>
 static int plain_product_np(const PlProduct &p, int n_tiles, hipStream_t s) {
-  const int MT = p.M < 64 ? ceil_div(p.M, 16) : 4, threads = PL_THREADS + (KIND == PL_QKV_FIRST ? 64 * MT : 0);
+  const int MT = p.M < 64 ? ceil_div(p.M, 16) : 4, threads = 64 * pl_waves(KIND, NP) + (KIND == PL_QKV_FIRST ? 64 * MT : 0);
   switch (MT) {
   case 1: plain_product_kernel<T, 1, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
   case 2: plain_product_kernel<T, 2, KIND, NP><<<n_tiles, threads, 0, s>>>(p); break;
