@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import functools
 import os
+from operator import index
 
 import numpy as np
 import torch
@@ -240,10 +241,15 @@ def la_free_pool(pool):
     lib.la_free_pool(pool)
 
 
-@functools.lru_cache(maxsize=64, typed=True)
-def _lookahead(W, N, G):
-    """Reference to a descriptor, which the library only reads."""
+@functools.lru_cache(maxsize=64)
+def _descriptor(W, N, G):
     return C.byref(la_lookahead_desc(W, N, G))
+
+
+def _lookahead(W, N, G):
+    """Reference to a descriptor, which the library only reads.  It is kept by the numbers that the arguments hold at this call: an
+    argument itself may change in place (a 0-d tensor, whose hash is its identity) or have no hash (a 0-d array)."""
+    return _descriptor(index(W), index(N), index(G))
 
 
 def la_state_init(pool, kv, W, N, G, prompt, Bp, seed_pool, state, stream=None):

@@ -49,6 +49,34 @@ def test_host_block_layout_matches_oracle(W, N, G, Bp, n_cand):
     assert [int(v) for v in vis] == ovis
 
 
+@pytest.mark.parametrize("call", ["la_ngram_accept", "la_state_init"])
+def test_a_lookahead_descriptor_is_what_the_arguments_hold_at_the_call(call, monkeypatch):
+    """Whatever stands for an integer is taken, also what changes in place or cannot be hashed; what does not is refused."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    seen = []
+
+    class Lib:
+        def __getattr__(self, name):
+            return lambda pool, kv, d, *rest: seen.append((d._obj.W, d._obj.N, d._obj.G)) or 0
+
+    monkeypatch.setattr(B, "lib", Lib())
+    monkeypatch.setattr(B, "_ptr", lambda t: 0)
+    monkeypatch.setattr(B, "_stream", lambda s=None: 0)
+    t = torch.zeros(4, dtype=torch.int32)
+    run = lambda W, N, G: B.la_ngram_accept(None, None, W, N, G, t, t, t, 9) if call == "la_ngram_accept" else B.la_state_init(None, None, W, N, G, t, 4, 1, t)
+    for of in (int, np.int32, np.int64, np.array, torch.tensor):
+        W = of(5)
+        run(W, of(4), of(3))
+        assert seen.pop() == (5, 4, 3)
+        if of in (np.array, torch.tensor):
+            W += 2
+            run(W, of(4), of(3))
+            assert seen.pop() == (7, 4, 3)
+    with pytest.raises(TypeError):
+        run(5.0, 4, 3)
+
+
 def test_host_argument_checks():
     from paper_2602_16760_amd import binding as B
     with pytest.raises(B.LaError) as e:
