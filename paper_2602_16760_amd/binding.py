@@ -124,15 +124,12 @@ def _check(rc):
         raise LaError(rc, lib.la_last_error().decode())
 
 
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-
-
 def _stream(stream=None):
     """Handle of `stream`, of the current stream without one.  (The stream object that torch.cuda.current_stream() makes for it
     costs 2.9 us, more than half of a launch, and torch.cuda.current_device() looks for the runtime's start first; a call of a small
-    kernel waits for the host.)"""
+    kernel waits for the host.  Both names are looked up here: a torch built without a GPU has neither, and the host functions need none.)"""
     if stream is None:
-        return _raw_stream(_device())
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream
 
 

@@ -3,6 +3,8 @@ declares, and its host-side logic (argument checks, block layout) is right."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -75,6 +77,15 @@ def test_a_lookahead_descriptor_is_what_the_arguments_hold_at_the_call(call, mon
             assert seen.pop() == (7, 4, 3)
     with pytest.raises(TypeError):
         run(5.0, 4, 3)
+
+
+def test_host_functions_need_no_gpu_build_of_torch():
+    """A torch built without a GPU has none of the functions that name its device and stream; layouts and the latency model run all the same."""
+    code = ("import torch\n"
+            "for n in [n for n in dir(torch._C) if n.startswith('_cuda_')]: delattr(torch._C, n)\n"
+            "from paper_2602_16760_amd import binding as B\n"
+            "assert len(B.la_causal_layout(3, 5)[0]) == 5 and B.la_rtt_fixed_overhead(62.9, 20.0) > 42.0\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=300)
 
 
 def test_host_argument_checks():
