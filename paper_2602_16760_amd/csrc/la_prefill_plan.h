@@ -77,7 +77,7 @@ struct PfTile {
 constexpr PfTile PF_TILES[] = {
     {16, 14, 1, 0.85f, 0.85f}, {16, 10, 1, 0.66f, 0.66f}, {16, 8, 1, 0.57f, 0.57f}, {8, 12, 1, 0.50f, 0.50f}, {8, 8, 2, 0.70f, 0.45f}, {8, 4, 2, 0.52f, 0.30f},
 };
-constexpr int PF_N_TILES = 6;
+constexpr int PF_N_TILES = 6, PF_SMALLEST = 5;
 
 struct PfProduct {
   int RT, M, KT, n_tiles, d;  // row tiles of the buffers, rows, k-tiles, column tiles wanted, row length of the products
@@ -115,7 +115,9 @@ inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus
 // is a CU's intake: a KB takes a CU 16 ns (lines of its XCD's L2) to 35 ns (weights from memory), whatever the depth of the ring, the
 // policy of the loads or lines requested ahead into L2, and a small product waits for nothing else.
 // Up to 128 rows, of gate/up 7 columns and all rows a workgroup: 28672 columns in one round of 256 CUs, and no padding rows.  us, before (128 x 128
-// tiles on 224 CUs) and now: 77 rows 56.3 -> 46.0, 128 rows 57.6 -> 54.0.  Of O and down 8 columns and all rows, in as many slices as fill
+// tiles on 224 CUs) and now: 77 rows 56.3 -> 46.0, 128 rows 57.6 -> 54.0.  Where pf_choose takes its smallest tiles, which then are at most one
+// to a CU, those are faster (4096 wide, smallest or 128 x 128 tiles / 7 columns: 8192 channels of gate 35.3 / 37.8 at 77 rows and 36.3 / 45.9 at 128, 8704 channels
+// 45.8 / 36.9 and 46.9 / 45.3; 2048 wide, 8192 channels 16.2 / 17.2 and 16.7 / 22.9).  Of O and down 8 columns and all rows, in as many slices as fill
 // the chip: 77 rows 12.6 -> 11.4 and 29.4 -> 28.0, 128 rows 13.7 -> 13.9 and 35.0 -> 32.8.  Where they do not fill half of the chip (small models),
 // pf_choose's smaller tiles do better.
 // Gate/up beyond 256 rows: 10 or 12 row tiles x 14 columns where whole rounds of them cost less than pf_choose's best: us per k-tile 0.64 and 0.69
@@ -138,12 +140,9 @@ inline int pf_part_rows(const PfProduct &p, int part_rows, int cus, int &S) {
 }
 inline int pf_gateup_rows(const PfProduct &p, int cus) {
   const int rt = pf_up(p.M, 16);
-  if (p.M <= 128) {
-    const int groups = pf_up(p.n_tiles, PF_ROW_COLS_GATEUP);
-    return p.M > LA_MAX_ROWS && groups <= cus && 2 * groups > cus ? rt : 0;
-  }
   int tile, S, rows = 0;
   float best = pf_choose(p, 1, 0, cus, tile, S);
+  if (p.M <= 128) return p.M > LA_MAX_ROWS && pf_up(p.n_tiles, PF_ROW_COLS_GATEUP) <= cus && tile != PF_SMALLEST ? rt : 0;
   for (int r : {10, 12}) {
     const float us = (float)(pf_up(pf_up(rt, r) * pf_up(p.n_tiles, 14), cus) * p.KT) * (r == 10 ? 0.64f : 0.69f);
     if (us < best) {

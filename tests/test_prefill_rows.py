@@ -53,6 +53,15 @@ def test_rules_stay_within_their_kernels_and_buffers(rows, dims, cus):
             assert (q, o, w, g) == (0, 0, 0, 0)
 
 
+# Widths at which a rule's line lies, with what is faster on each side of it (the figures are beside the rules): d, q columns, k and v columns, ffn
+def test_gate_up_is_cut_where_the_smallest_tiles_are_more_than_the_chip(rows):
+    for F, cut in ((8192, False), (8704, True), (14336, True)):
+        for d in (2048, 3072, 4096, 6144):
+            for M, *_, g, _ in rows(d, d, 1024, F, 256):
+                if 64 < M <= 128:
+                    assert g == (-(-M // 16) if cut else 0), (d, F, M)
+
+
 # 7B and 12B widths: QKV by 3 .. 8 row tiles (first and last length of each), gate/up by 10 and 12, one row into a row tile and a full one
 SIZES = [("mistral7b", "bf16", [(66, 1), (96, 0), (112, 33), (129, 0), (192, 5), (256, 0), (320, 64), (321, 0), (384, 7), (385, 0), (448, 1), (449, 0), (512, 31), (640, 0)]),
          ("mistral7b", "f16", [(80, 0), (310, 3)]),
