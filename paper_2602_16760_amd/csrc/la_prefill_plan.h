@@ -117,9 +117,15 @@ inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus
 // Up to 128 rows, of gate/up 7 columns and all rows a workgroup: 28672 columns in one round of 256 CUs, and no padding rows.  us, before (128 x 128
 // tiles on 224 CUs) and now: 77 rows 56.3 -> 46.0, 128 rows 57.6 -> 54.0.  Where pf_choose takes its smallest tiles, which then are at most one
 // to a CU, those are faster (4096 wide, smallest or 128 x 128 tiles / 7 columns: 8192 channels of gate 35.3 / 37.8 at 77 rows and 36.3 / 45.9 at 128, 8704 channels
-// 45.8 / 36.9 and 46.9 / 45.3; 2048 wide, 8192 channels 16.2 / 17.2 and 16.7 / 22.9).  Of O and down 8 columns and all rows, in as many slices as fill
-// the chip: 77 rows 12.6 -> 11.4 and 29.4 -> 28.0, 128 rows 13.7 -> 13.9 and 35.0 -> 32.8.  Where they do not fill half of the chip (small models),
-// pf_choose's smaller tiles do better.
+// 45.8 / 36.9 and 46.9 / 45.3; 2048 wide, 8192 channels 16.2 / 17.2 and 16.7 / 22.9).
+// Of O and down 8 columns and all rows, in as many slices as fill the chip (if that is more than half of it), but where pf_choose takes its smallest tiles:
+// those are faster there, too.  us with what the slices cost pf_norm, tiles / cut: down of 4096 x 14336 77 rows 31.0 / 29.5, 128 rows 34.8 / 34.1; O of
+// 4096 x 4096 77 rows 13.3 / 12.9, 96 rows 12.6 / 13.8, 128 rows 13.3 / 15.2; O of 5120 x 4096 97 rows 21.1 / 18.5, 112 rows 16.3 / 19.6; down of 3072 x 8192
+// (192 workgroups) 70 rows 16.3 / 14.9, 96 rows 15.3 / 16.2.  Of 15 widths and 13 lengths none is more than 3 % slower than pf_choose's but O of 8192 x
+// 8192 at 97 and 105 rows (7 %).
+// Beyond five row tiles in seven slices at most: with eight, 256 workgroups, a launch takes 4 us more now and then, on some cards most of the time.  Down of
+// 4096 x 14336, us in the mean of 100 on two cards, eight slices / seven / tiles: 80 rows 29.0, 29.2 / 29.0, 29.5 / 31.1, 31.2; 97 rows 32.4, 34.5 / 31.9, 32.5 /
+// 32.6, 32.6; 112 rows 33.6, 36.7 / 33.0, 34.2 / 33.6, 33.7.
 // Gate/up beyond 256 rows: 10 or 12 row tiles x 14 columns where whole rounds of them cost less than pf_choose's best: us per k-tile 0.64 and 0.69
 // against 0.80 of 16 row tiles.  300 rows 102 -> 89, 600 rows 178 -> 160, 700 rows 208 -> 177.
 // QKV of 129 to 512 rows: a quarter of the rows and 6 columns a workgroup, while that is one round (7B and 12B shapes: 64 column groups).
@@ -131,12 +137,14 @@ inline int pf_qkv_rows(const PfProduct &p, int cus) {
   return p.M > 128 && p.M <= 512 && pf_up(rt, rows) * pf_up(p.n_tiles, PF_ROW_COLS_QKV) <= cus ? rows : 0;
 }
 inline int pf_part_rows(const PfProduct &p, int part_rows, int cus, int &S) {
-  const int groups = pf_up(p.n_tiles, PF_ROW_COLS_PART);
-  int k = cus / groups < PF_MAX_SPLIT ? cus / groups : PF_MAX_SPLIT;
+  const int groups = pf_up(p.n_tiles, PF_ROW_COLS_PART), rt = pf_up(p.M, 16), most = rt > 5 ? PF_MAX_SPLIT - 1 : PF_MAX_SPLIT;
+  int k = cus / groups < most ? cus / groups : most, tile, S_tile;
   while (k > 1 && (p.KT / k < 4 || (long long)k * p.M > part_rows)) --k;
   if (p.M <= LA_MAX_ROWS || p.M > 128 || k < 1 || 2 * groups * k <= cus) return 0;
+  pf_choose(p, PF_MAX_SPLIT, part_rows, cus, tile, S_tile);
+  if (tile == PF_SMALLEST) return 0;
   S = k;
-  return pf_up(p.M, 16);
+  return rt;
 }
 inline int pf_gateup_rows(const PfProduct &p, int cus) {
   const int rt = pf_up(p.M, 16);

@@ -62,6 +62,13 @@ def test_gate_up_is_cut_where_the_smallest_tiles_are_more_than_the_chip(rows):
                     assert g == (-(-M // 16) if cut else 0), (d, F, M)
 
 
+def test_o_and_down_are_cut_where_the_smallest_tiles_are_not_taken(rows):
+    for (d, qd, F), at in (((4096, 4096, 8192), [(77, 8, 8), (90, 0, 7), (128, 0, 7)]), ((5120, 4096, 14336), [(97, 6, 6), (112, 0, 6)]), ((3072, 3072, 8192), [(70, 0, 8), (96, 0, 0), (128, 0, 0)])):
+        t = {M: (So if o else 0, Sd if w else 0) for M, _, o, So, w, Sd, _, _ in rows(d, qd, 1024, F, 256)}
+        for M, So, Sd in at:  # slices, 0: not cut
+            assert t[M] == (So, Sd), (d, M)
+
+
 # 7B and 12B widths: QKV by 3 .. 8 row tiles (first and last length of each), gate/up by 10 and 12, one row into a row tile and a full one
 SIZES = [("mistral7b", "bf16", [(66, 1), (96, 0), (112, 33), (129, 0), (192, 5), (256, 0), (320, 64), (321, 0), (384, 7), (385, 0), (448, 1), (449, 0), (512, 31), (640, 0)]),
          ("mistral7b", "f16", [(80, 0), (310, 3)]),
