@@ -130,11 +130,18 @@ inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus
 // against 0.80 of 16 row tiles.  300 rows 102 -> 89, 600 rows 178 -> 160, 700 rows 208 -> 177.
 // QKV of 129 to 512 rows: a quarter of the rows and 6 columns a workgroup, while that is one round (7B and 12B shapes: 64 column groups).
 // 150 rows 33 -> 29, 200 rows 36.6 -> 32.0, 300 rows 51 -> 38, 400 rows 56 -> 45, 500 rows 59 -> 52.
+// Beyond 256 rows (five row tiles), where pf_choose takes its smallest tiles (fewer columns: the last layer's K and V, narrow models), only while the
+// contraction is short.  Time over the tiles' at 3 / 4 / 5 / 6 / 7 / 8 row tiles, K and V: 512 wide .75 / .80 / .92 / .97 / 1.09 / 1.16, 1024 wide .73 / .82 / .91 /
+// 1.00 / 1.12 / 1.21, 2048 wide .80 / .86 / .96 / 1.04 / 1.18 / 1.24, 3072 wide .87 / .87 / 1.04 / 1.03 / 1.26 / 1.23, 4096 wide .91 / .86 / 1.07 / 1.03 / 1.30 / 1.24,
+// 8192 wide 1.02 / .89 / 1.17 / 1.03 / 1.39 / 1.24; 4096 x 6144, more than one round of those tiles: .92 / .88 / .68 / .69 / .84 / .85.
 constexpr int PF_ROW_COLS_QKV = 6, PF_ROW_COLS_PART = 8, PF_ROW_COLS_GATEUP = 7;
 inline int pf_up(int a, int b) { return (a + b - 1) / b; }
 inline int pf_qkv_rows(const PfProduct &p, int cus) {
   const int rt = pf_up(p.M, 16), rows = pf_up(rt, 4);
-  return p.M > 128 && p.M <= 512 && pf_up(rt, rows) * pf_up(p.n_tiles, PF_ROW_COLS_QKV) <= cus ? rows : 0;
+  if (p.M <= 128 || p.M > 512 || pf_up(rt, rows) * pf_up(p.n_tiles, PF_ROW_COLS_QKV) > cus) return 0;
+  int tile, S;
+  pf_choose(p, 1, 0, cus, tile, S);
+  return rows <= 4 || tile != PF_SMALLEST || p.KT <= 32 * (7 - rows) ? rows : 0;
 }
 inline int pf_part_rows(const PfProduct &p, int part_rows, int cus, int &S) {
   const int groups = pf_up(p.n_tiles, PF_ROW_COLS_PART), rt = pf_up(p.M, 16), most = rt > 5 ? PF_MAX_SPLIT - 1 : PF_MAX_SPLIT;

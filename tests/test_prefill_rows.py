@@ -69,6 +69,15 @@ def test_o_and_down_are_cut_where_the_smallest_tiles_are_not_taken(rows):
             assert t[M] == (So, Sd), (d, M)
 
 
+def test_narrow_qkv_is_cut_beyond_256_rows_only_where_the_contraction_is_short(rows):
+    last = {64: 320, 128: 256, 32: 384, 16: 384}  # k-tiles: the last length that is cut (the last layer's K and V, all of a narrow model's QKV)
+    for KT, end in last.items():
+        for M, q, *_ in rows(32 * KT, 0, 1024, 32 * KT, 256):
+            assert (q != 0) == (128 < M <= end), (KT, M)
+    # more columns than one round of the smallest tiles
+    assert all((q != 0) == (128 < M <= 512) for M, q, *_ in rows(4096, 4096, 1024, 14336, 256))
+
+
 # 7B and 12B widths: QKV by 3 .. 8 row tiles (first and last length of each), gate/up by 10 and 12, one row into a row tile and a full one
 SIZES = [("mistral7b", "bf16", [(66, 1), (96, 0), (112, 33), (129, 0), (192, 5), (256, 0), (320, 64), (321, 0), (384, 7), (385, 0), (448, 1), (449, 0), (512, 31), (640, 0)]),
          ("mistral7b", "f16", [(80, 0), (310, 3)]),
