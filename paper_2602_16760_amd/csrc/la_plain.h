@@ -25,25 +25,22 @@ __device__ __forceinline__ float pl_load(__amdgpu_buffer_rsrc_t r, unsigned i) {
     return load_as_float<T>(&v);
   }
 }
-// Sixteen consecutive elements from element i (a multiple of 16).
+// Elements as they are stored, 16 bytes of them or one: turned into floats where they are used.  (Turned behind their load, a load under a condition is
+// waited for where the condition ends.)
 template <typename T>
-__device__ __forceinline__ void pl_load16(float *out, __amdgpu_buffer_rsrc_t r, unsigned i) {
-  constexpr int PER = 16 / sizeof(T);
-#pragma unroll
-  for (int n = 0; n < 16 / PER; ++n) {
-    const pl_u4 v = __builtin_bit_cast(pl_u4, __builtin_amdgcn_raw_buffer_load_b128(r, (i + (unsigned)(n * PER)) * (unsigned)sizeof(T), 0, 0));
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if constexpr (sizeof(T) == 4) {
-        out[n * PER + e] = __uint_as_float(v[e]);
-      } else {
-        const T h = __builtin_bit_cast(T, (uint16_t)(v[e >> 1] >> (16 * (e & 1))));
-        out[n * PER + e] = load_as_float<T>(&h);
-      }
-    }
+__device__ __forceinline__ float pl_value(unsigned bits) {
+  if constexpr (sizeof(T) == 4) {
+    return __uint_as_float(bits);
+  } else {
+    const T h = __builtin_bit_cast(T, (uint16_t)bits);
+    return load_as_float<T>(&h);
   }
 }
-
+template <typename T>
+__device__ __forceinline__ float pl_element(const pl_u4 *raw, int i) {
+  if constexpr (sizeof(T) == 4) return pl_value<T>(raw[i >> 2][i & 3]);
+  else return pl_value<T>(raw[i >> 3][(i >> 1) & 3] >> (16 * (i & 1)));
+}
 // A rotated channel (lower: of the lower half of its head); products and sum are rounded one by one wherever this is inlined.
 __device__ __forceinline__ float rotated(bool lower, float mine, float other, float c, float s) {
 #pragma clang fp contract(off)
@@ -274,8 +271,11 @@ __device__ __forceinline__ float pl_wave_sum(float v) {
 // behind the length, and waves then take more than one share each, so that the sums depend on the length alone.
 // Bound: a launch and two memory latencies for short contexts, a latency per 512 keys for long ones.
 // 17 rows, 4 heads of 64, us a layer (256 threads a workgroup, a key each, 256 keys in turn before): L = 47 6.7 -> 5.0, L = 1000
-// 28 -> 12, L = 4000 108 -> 41.  With K and V of the first piece requested beside q and the length (V waited for both before): L = 47 5.7 -> 5.0.
-template <typename T>
+// 28 -> 12, L = 4000 108 -> 41.
+// EARLY: K and V of a wave's first piece are requested beside q and the length (V waited for both before): L = 47 5.7 -> 5.0.  Only where every wave has a
+// piece: a captured launch has eight whatever the length, a long prompt's first rows see less than its last, and what such waves request costs
+// as much as what is used (captured steps of two layers 256 wide, L = 47: 4 heads, 17 rows 54 us, 64 with all eight pieces requested, 32 heads, 64 rows 168 and 230).
+template <typename T, bool EARLY>
 __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float *q, int ldq, int Hq, int Hkv, int dh, const T *Kc, const T *Vc, const int32_t *L_dev,
                                                                      int max_len, int Bp, const uint64_t *vis, float *out) {
   __shared__ __attribute__((aligned(16))) float qs[256], ps[PL_WAVES][64], os[PL_WAVES][64 + 2];
@@ -287,19 +287,26 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   const int L_mem = *L_dev;
   const uint64_t vb = vis ? vis[b] : 0ull;
   const float scale = 1.0f / sqrtf((float)dh);
-  float kv[64], vv[64];
+  constexpr int PER = 16 / sizeof(T);
+  pl_u4 kr[64 / PER];
+  unsigned vr[64];
   auto load_k = [&](int ck, int c0) {  // channels c0 .. c0 + 63 of this lane's key
     const unsigned at = (unsigned)((64 * ck + lane) * nkv + kvh * dh + c0);
 #pragma unroll
     for (int c = 0; c < 64; c += 16)
-      if (c0 + c < dh) pl_load16<T>(kv + c, rk, at + (unsigned)c);  // (head_dim is a multiple of 16)
+      if (c0 + c < dh) {  // (head_dim is a multiple of 16)
+#pragma unroll
+        for (int n = c / PER; n < (c + 16) / PER; ++n)
+          kr[n] = __builtin_bit_cast(pl_u4, __builtin_amdgcn_raw_buffer_load_b128(rk, (at + (unsigned)(n * PER)) * (unsigned)sizeof(T), 0, 0));
+      }
   };
   auto load_v = [&](int ck) {  // this lane's channel of the 64 keys
-    unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0));
+    unsigned at = (unsigned)(64 * ck * nkv + kvh * dh + (u0 + lane < dh ? u0 + lane : 0)) * (unsigned)sizeof(T);
 #pragma unroll
     for (int j = 0; j < 64; ++j) {
-      vv[j] = pl_load<T>(rv, at);
-      at += (unsigned)nkv;
+      if constexpr (sizeof(T) == 4) vr[j] = __builtin_amdgcn_raw_buffer_load_b32(rv, at, 0, 0);
+      else vr[j] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rv, at, 0, 0);
+      at += (unsigned)nkv * (unsigned)sizeof(T);
       asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
     }
   };
@@ -308,10 +315,12 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
 #pragma unroll
   for (int u = 0; u < 4; ++u) q_in[u] = (int)(threadIdx.x + u * blockDim.x) < dh ? q[(size_t)b * ldq + hq * dh + threadIdx.x + u * blockDim.x] : 0.f;
   __builtin_amdgcn_sched_barrier(0);
-  load_k(wave, 0);
-  __builtin_amdgcn_sched_barrier(0);
-  load_v(wave);
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (EARLY) {
+    load_k(wave, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(wave);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
   for (int u = 0; u < 4; ++u)
     if ((int)(threadIdx.x + u * blockDim.x) < dh) qs[threadIdx.x + u * blockDim.x] = q_in[u];
@@ -319,6 +328,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
   if (L < 0 || L + Bp > max_len) return;
   // a prompt (vis = NULL) is causal, and what is behind a row is not looked at: a piece that it sees nothing of adds nothing
   const int total = vis ? L + Bp : L + b + 1, seen = vis ? L : total, n_chunks = (total + 63) >> 6, n_shares = n_chunks < PL_WAVES ? n_chunks : PL_WAVES;
+  if (!EARLY && wave < n_shares) load_k(wave, 0);
   __syncthreads();
   for (int share = wave; share < n_shares; share += n_waves) {
     float m = -INFINITY, l = 0.f;
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
     if (share != wave) load_k(share, 0);
     for (int ck = share; ck < n_chunks; ck += PL_WAVES) {
       const int key = 64 * ck + lane;
-      if (ck != wave) load_v(ck);
+      if (!EARLY || ck != wave) load_v(ck);
       float s0 = 0.f, s1 = 0.f;
       for (int c0 = 0; c0 < dh; c0 += 64) {
         if (c0 > 0) load_k(ck, c0);
@@ -337,10 +347,10 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
 #pragma unroll
             for (int e = 0; e < 16; e += 4) {
               const pl_f4 qv = *reinterpret_cast<const pl_f4 *>(qs + c0 + c + e);
-              s0 = fmaf(qv[0], kv[c + e], s0);
-              s1 = fmaf(qv[1], kv[c + e + 1], s1);
-              s0 = fmaf(qv[2], kv[c + e + 2], s0);
-              s1 = fmaf(qv[3], kv[c + e + 3], s1);
+              s0 = fmaf(qv[0], pl_element<T>(kr, c + e), s0);
+              s1 = fmaf(qv[1], pl_element<T>(kr, c + e + 1), s1);
+              s0 = fmaf(qv[2], pl_element<T>(kr, c + e + 2), s0);
+              s1 = fmaf(qv[3], pl_element<T>(kr, c + e + 3), s1);
             }
           }
       }
@@ -363,7 +373,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
         if (j % 16 == 0) __builtin_amdgcn_sched_barrier(0);
         const pl_f4 pj = *reinterpret_cast<const pl_f4 *>(&ps[wave][j]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = fmaf(pj[e], pj[e] != 0.f ? vv[j + e] : 0.f, o[e]);
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(pj[e], pj[e] != 0.f ? pl_value<T>(vr[j + e]) : 0.f, o[e]);
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -392,9 +402,13 @@ static int plain_attention(const float *q, int ldq, const la_model_desc &d, cons
                            hipStream_t s) {
   ProfScope ps("plain_attention", s);
   // (a captured launch serves the lengths of its replays, and has every wave)
-  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && !stream_captures(s) ? pieces : PL_WAVES;
-  plain_attention_kernel<T><<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev,
-                                                                                                   kv->max_len, Bp, vis, out);
+  const bool captured = stream_captures(s);
+  const int pieces = ceil_div(kv->L_bound + Bp, 64), waves = pieces < PL_WAVES && !captured ? pieces : PL_WAVES;
+  auto run = [&](auto kernel) {
+    kernel<<<dim3(Bp, d.n_q_heads, ceil_div(d.head_dim, 64)), 64 * waves, 0, s>>>(q, ldq, d.n_q_heads, d.n_kv_heads, d.head_dim, Kc, Vc, kv->L_dev, kv->max_len, Bp, vis, out);
+  };
+  if (!captured && Bp <= LA_MAX_ROWS) run(plain_attention_kernel<T, true>);
+  else run(plain_attention_kernel<T, false>);
   LA_HIP(hipGetLastError());
   return LA_OK;
 }

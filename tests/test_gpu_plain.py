@@ -227,3 +227,33 @@ def test_a_row_does_not_depend_on_the_block_it_is_in(dims, dtype, attention):
             last = got
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("dims,dtype", [((1, 256, 4, 2, 64, 688, 50), "f32"), ((1, 256, 4, 2, 48, 688, 50), "bf16"), ((1, 256, 2, 1, 144, 688, 50), "f16")])
+def test_a_captured_block_waits_for_the_length_and_an_eager_one_does_not(dims, dtype):
+    """The attention has a kernel for either: the same bits at lengths around one piece of 64 keys, all waves' first pieces, and second ones."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    nl, d, hq, hkv, dh, F, V = dims
+    shape, rows, most = synth.ModelShape(f"early{dh}", nl, d, hq, hkv, dh, F, V, 1e-5, 1e4, dtype), 17, 1100
+    eng = gpu_engine(shape, most, seed=3)
+    try:
+        eng.fill_kv(0, *synth.kv_fill(shape, 0, most, 4))
+        B.la_kv_set_len(eng.kv, 0)
+        pos, vis = (B.to_device(a) for a in B.la_causal_layout(0, rows))
+        x = torch.from_numpy(np.ascontiguousarray(synth.hidden_block(shape, rows, 1), dtype=np.float32)).cuda()
+        h, stream, graph = x.clone(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        B.la_forward_layers(eng.model, 0, 1, h, pos, vis, eng.kv)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            h.copy_(x)
+            B.la_forward_layers(eng.model, 0, 1, h, pos, vis, eng.kv)
+        for L in (0, 46, 47, 48, 111, 112, 495, 496, 511, 512, 1000, 1083):
+            B.la_kv_set_len(eng.kv, L)
+            eager = x.clone()
+            B.la_forward_layers(eng.model, 0, 1, eager, pos, vis, eng.kv)
+            graph.replay()
+            assert torch.isfinite(eager).all() and torch.equal(h, eager), L
+    finally:
+        torch.cuda.synchronize()
+        eng.close()
