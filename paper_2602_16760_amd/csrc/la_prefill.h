@@ -19,8 +19,6 @@ namespace la {
 
 constexpr int PF_KEYS = 64;     // keys of a block of the attention
 
-enum PfMode { PF_QKV = 0, PF_PART = 1, PF_GATEUP = 2 };
-
 struct PfGemm {
   const uint8_t *wstream;
   size_t cu_bytes;
@@ -714,20 +712,12 @@ template <int MODE>
 static int pf_launch_gemm(PfGemm p, hipStream_t s, const char *name, int cus, int part_rows = 0, int *S = nullptr) {
   ProfScope ps(name, s);
   static_assert(R_NW == 4, "pf_qkv_few_kernel's waves take the k-tiles as they lie for four MFMA waves");
-  if (MODE == PF_QKV && pf_qkv_few(p.M, p.ntiles - p.t_first, cus)) return pf_launch_qkv_few(p, ceil_div(p.M, 16), s, false);
-  const PfProduct prod{p.RT, p.M, p.KT, p.ntiles - p.t_first, p.d};
-  int rows = 0;  // row tiles of a tile that is cut to the prompt's rows
-  if (MODE == PF_QKV) rows = pf_qkv_rows(prod, cus);
-  if (MODE == PF_PART) rows = pf_part_rows(prod, part_rows, cus, p.S);
-  if (MODE == PF_GATEUP) rows = pf_gateup_rows(prod, cus);
-  if (rows) {
-    if (S) *S = p.S;
-    return pf_launch_rows<MODE>(p, rows, s, false);
-  }
-  int tile;
-  pf_choose(prod, MODE == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, tile, p.S);
-  if (S) *S = p.S;
-  return pf_launch_tile<MODE>(tile, p, s, false);
+  const PfRoute r = pf_route((PfMode)MODE, PfProduct{p.RT, p.M, p.KT, p.ntiles - p.t_first, p.d}, part_rows, cus);
+  p.S = r.S;
+  if (S) *S = r.S;
+  if (MODE == PF_QKV && r.few) return pf_launch_qkv_few(p, r.few, s, false);
+  if (r.rows) return pf_launch_rows<MODE>(p, r.rows, s, false);
+  return pf_launch_tile<MODE>(r.tile, p, s, false);
 }
 
 static int pf_launch_norm(int S, float *x, const float *part, const float *gain, int M, int d, int RT, float *ss, uint16_t *A, hipStream_t s) {

@@ -79,6 +79,8 @@ constexpr PfTile PF_TILES[] = {
 };
 constexpr int PF_N_TILES = 6, PF_SMALLEST = 5;
 
+enum PfMode { PF_QKV = 0, PF_PART = 1, PF_GATEUP = 2 };
+
 struct PfProduct {
   int RT, M, KT, n_tiles, d;  // row tiles of the buffers, rows, k-tiles, column tiles wanted, row length of the products
 };
@@ -174,6 +176,23 @@ inline int pf_gateup_rows(const PfProduct &p, int cus) {
 // pass over the activations costs more than the tiles: 4096 x 12288 (384) 46 / 42, 52 / 43; 8192 x 10240 (320) 78 / 67, 93 / 67.
 // The last layer's 2048 columns of K and V: 16 / 37, 21 / 38.
 inline bool pf_qkv_few(int M, int n_tiles, int cus) { return M > LA_MAX_ROWS && M <= 128 && (n_tiles + 1) / 2 <= cus; }
+
+// The kernel that a product takes.
+struct PfRoute {
+  int few = 0;    // row tiles, by the kernel without tiles; 0: not by it
+  int rows = 0;   // row tiles of a tile that is cut to the prompt's rows; 0: not by one
+  int tile = -1;  // else: of PF_TILES
+  int S = 1;      // slices of the contraction
+};
+inline PfRoute pf_route(PfMode mode, const PfProduct &p, int part_rows, int cus) {
+  PfRoute r;
+  if (mode == PF_QKV && pf_qkv_few(p.M, p.n_tiles, cus)) r.few = pf_up(p.M, 16);
+  else if (mode == PF_QKV) r.rows = pf_qkv_rows(p, cus);
+  else if (mode == PF_PART) r.rows = pf_part_rows(p, part_rows, cus, r.S);
+  else r.rows = pf_gateup_rows(p, cus);
+  if (!r.few && !r.rows) pf_choose(p, mode == PF_PART ? PF_MAX_SPLIT : 1, part_rows, cus, r.tile, r.S);
+  return r;
+}
 
 static_assert(PF_PART_ROWS >= PF_ROWS, "one slice of a whole chunk");
 static_assert(PF_ROWS % PF_LONG == 0 && PF_MIN <= PF_LONG, "chunks halve down to the smaller set");

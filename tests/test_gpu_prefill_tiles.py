@@ -10,15 +10,15 @@ import synth
 from gpu_util import launch_names
 
 pytestmark = pytest.mark.gpu
-# (shape, dtype, [(tokens, start)]).  Every kernel that the pass picks from for these shapes between 65 and 2200 tokens runs at
-# one of these sizes: test_prefill_plan.py asserts it, without a GPU.
+# (shape, dtype, [(tokens, start)]).  Every kernel that the pass picks from for these shapes between 65 and 2200 tokens, and every number of slices of O
+# and of down with each, runs at one of these sizes or of test_prefill_rows.py's: test_prefill_plan.py asserts it, without a GPU.
 SIZES = [
-    ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (180, 3), (257, 0), (300, 31), (600, 0), (700, 5), (1023, 0),
-                           (1100, 32), (1300, 0), (1600, 0), (2200, 3)]),
+    ("mistral7b", "bf16", [(65, 0), (81, 20), (97, 3), (113, 0), (128, 1), (130, 37), (180, 3), (257, 0), (300, 31), (513, 0), (600, 0), (700, 5),
+                           (1023, 0), (1100, 32), (1300, 0), (1600, 0), (1601, 0), (2049, 3), (2200, 3)]),
     ("mistral7b", "f16", [(193, 33), (1025, 0)]),
-    ("nemo12b", "bf16", [(105, 0), (400, 64), (1024, 0)]),
+    ("nemo12b", "bf16", [(81, 0), (105, 0), (191, 5), (257, 0), (400, 64), (1024, 0), (1055, 0), (2049, 0)]),
     ("mistral7b/32 kv heads", "bf16", [(65, 0), (128, 9)]),  # (12288 columns of QKV: more than one round of the few-row product)
-    ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (2049, 100)]),
+    ("small64_bf16", "bf16", [(65, 7), (90, 33), (128, 0), (191, 0), (440, 0), (820, 33), (879, 0), (2049, 100)]),
 ]
 # max |got - want| over max |want| of a layer's cache rows: the bars of the prompt-pass parity tests (one storage
 # rounding of the rows on top of the hidden-state error of one layer)

@@ -5,6 +5,7 @@ import subprocess
 import pytest
 
 from test_gpu_prefill_tiles import SIZES, shape_of
+from test_prefill_rows import SIZES as ROW_SIZES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_16760_amd", "csrc")
@@ -25,23 +26,16 @@ int main(int, char **v) {
   if (!strcmp(v[1], "layout")) show(pf_layout(PfDims{num(2), num(3), num(4), num(5)}, (int)num(6)));
   if (!strcmp(v[1], "fit"))
     show(pf_fit(PfDims{num(2), num(3), num(4), num(5)}, PF_ROWS, PF_LONG, [&](size_t bytes) { return bytes <= num(6); }));
-  if (!strcmp(v[1], "routes")) {  // the products of every layer, then of the last one (its K and V columns): prompt lengths v[6] .. v[7]
+  if (!strcmp(v[1], "routes")) {  // product (QKV, O, gate/up, down, the last layer's K and V) by product: prompt lengths v[6] .. v[7]
     const int d = (int)num(2), qd = (int)num(3), kvd = (int)num(4), F = (int)num(5);
     for (int n = (int)num(6); n <= (int)num(7); ++n) {
       const int rows = n < PF_LONG ? PF_LONG : PF_ROWS, part_rows = pf_layout(PfDims{(size_t)d, (size_t)qd, 128, (size_t)F}, rows).part_rows;
       for (int done = 0; done < n; done += rows) {
         const int M = n - done < rows ? n - done : rows, RT = (M + 63) / 64 * 4;
-        int tile = 0, S = 0;
-        for (int cols : {qd + 2 * kvd, 2 * kvd}) {
-          pf_choose(PfProduct{RT, M, d / 32, cols / 16, d}, 1, part_rows, 256, tile, S);
-          if (pf_qkv_few(M, cols / 16, 256)) printf("0 %d %d %d\n", n, 100 + (M + 15) / 16, 1);
-          else printf("0 %d %d %d\n", n, tile, S);
-        }
-        pf_choose(PfProduct{RT, M, d / 32, 2 * F / 16, d}, 1, part_rows, 256, tile, S);
-        printf("2 %d %d %d\n", n, tile, S);
-        for (int K : {qd, F}) {
-          pf_choose(PfProduct{RT, M, K / 32, d / 16, d}, PF_MAX_SPLIT, part_rows, 256, tile, S);
-          printf("1 %d %d %d\n", n, tile, S);
+        const struct { PfMode mode; int K, cols; } products[] = {{PF_QKV, d, qd + 2 * kvd}, {PF_PART, qd, d}, {PF_GATEUP, d, 2 * F}, {PF_PART, F, d}, {PF_QKV, d, 2 * kvd}};
+        for (int i = 0; i < 5; ++i) {
+          const PfRoute r = pf_route(products[i].mode, PfProduct{RT, M, products[i].K / 32, products[i].cols / 16, d}, part_rows, 256);
+          printf("%d %d %d %d %d %d\n", i, n, products[i].mode, r.few ? 100 + r.few : r.rows ? 200 + r.rows : r.tile, r.S, r.S * M <= part_rows);
         }
       }
     }
@@ -98,19 +92,19 @@ def test_few_row_products_go_without_tiles_while_they_are_one_round(plan, rows, 
 
 
 def test_the_gpu_sizes_reach_every_kernel_the_pass_picks_from(plan):
-    """(product, tile or row tiles of the few-row kernel) and the numbers of slices, over all prompts of 65 to 2200 tokens of the
-    shapes that the GPU test runs, against those at its sizes."""
-    kernels, slices, have_kernels, have_slices = {}, {}, set(), set()
-    for name, dtype, cases in SIZES:
+    """By the function that the launches ask: of each kind of product every kernel, and of O and of down every kernel with every number of slices, over all prompts
+    of 65 to 2200 tokens of the shapes that the GPU tests run, against those at their sizes."""
+    want, have = {}, set()
+    for name, dtype, cases in SIZES + ROW_SIZES:
         sh = shape_of(name, dtype)
         tested = {n for n, _ in cases}
-        dims = (sh.d_model, sh.q_dim, sh.kv_dim, sh.d_ffn)
-        for mode, n, tile, S in plan("routes", *dims, 65, 2200):
-            kernels.setdefault((mode, tile), (name, n))
-            slices.setdefault(S, (name, n))
-            if n in tested:
-                have_kernels.add((mode, tile))
-                have_slices.add(S)
-    assert {k: at for k, at in kernels.items() if k not in have_kernels} == {}
-    assert {s: at for s, at in slices.items() if s not in have_slices} == {}
-    assert len(kernels) >= 3 * 6 + 4  # all six tiles of the three kinds of product, four heights of the few-row kernel
+        for product, n, mode, kernel, S, fits in plan("routes", sh.d_model, sh.q_dim, sh.kv_dim, sh.d_ffn, 65, 2200):
+            assert fits
+            for key in ((mode, kernel), (product, kernel, S))[:2 if mode == 1 else 1]:
+                want.setdefault(key, (name, n))
+                if n in tested:
+                    have.add(key)
+    assert {k: at for k, at in want.items() if k not in have} == {}
+    # all six tiles, the heights of the few-row kernel and of the cut tiles of the three kinds of product
+    assert {k for k in want if len(k) == 2} == {(m, t) for m in range(3) for t in range(6)} | {(0, 100 + r) for r in range(5, 9)} | \
+        {(0, 200 + r) for r in range(3, 9)} | {(1, 200 + r) for r in range(5, 9)} | {(2, 200 + r) for r in (5, 6, 7, 8, 10, 12)}
