@@ -53,7 +53,7 @@ enum PlKind { PL_QKV = 0, PL_RESID = 1, PL_GLU = 2, PL_STORE = 3, PL_QKV_FIRST =
 struct PlProduct {
   const float *A;     // [M][lda]
   int lda, M, K;
-  const float *gain;  // of the norm: A is x * gain, and the sums are multiplied by its row factor (NULL: A as it is)
+  const float *gain;  // of the norm: A is x * gain, and the sums are multiplied by its row factor (RESID: none, A as it is)
   float eps;
   const void *W;      // [K][ldw]
   int ldw, N;         // N: columns of the result (GLU: of gate, and as many of up behind them)
@@ -99,6 +99,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
   constexpr bool FIRST = KIND0 == PL_QKV_FIRST;
   constexpr int KIND = FIRST ? (int)PL_QKV : KIND0, PER = (MT + 1) / 2;  // elements of the result a thread finishes
   constexpr int WV = pl_waves(KIND0, NP0);
+  constexpr bool NORM = KIND != PL_RESID;
   constexpr int NP = WV > PL_WAVES ? NP0 / 2 : FIRST && MT > 2 && NP0 > 4 ? 4 : NP0;  // (QKV_FIRST: three waves on a SIMD, 168 registers)
   __shared__ __attribute__((aligned(16))) float part[PL_WAVES * MT * 256];  // [wave][row tile][lane][4]
   __shared__ float sqs[PL_WAVES * 64];
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
           for (int j = 0; j < 4; ++j) x[n][mt][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, k + j < K ? o + 4u * j : PL_OOB, 0, 0));
         }
       }
-      if (p.gain) {
+      if (NORM) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) g[n][j] = pl_load<float>(rg, (unsigned)(k + j));
       }
@@ -181,8 +182,8 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float v = x[n][mt][j];
-          if (p.gain) sq[mt] = fmaf(v, v, sq[mt]);
-          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(p.gain ? v * g[n][j] : v, b[n][j], acc[mt], 0, 0, 0);
+          if (NORM) sq[mt] = fmaf(v, v, sq[mt]);
+          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(NORM ? v * g[n][j] : v, b[n][j], acc[mt], 0, 0, 0);
         }
     }
   }
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     reinterpret_cast<pl_f4 *>(part)[(wave * MT + mt) * 64 + lane] = acc[mt];
-    if (p.gain) {
+    if (NORM) {
       sq[mt] += __shfl_xor(sq[mt], 16, 64);
       sq[mt] += __shfl_xor(sq[mt], 32, 64);
       if (q4 == 0) sqs[wave * 64 + 16 * mt + c16] = sq[mt];
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
     float v = pp[HALF * WS] + pp[0];
 #pragma unroll
     for (int w = 1; w < HALF; ++w) v += pp[(w + HALF) * WS] + pp[w * WS];
-    if (p.gain) {
+    if (NORM) {
       float q = sqs[row];
 #pragma unroll
       for (int w = 1; w < PL_WAVES; ++w) q += sqs[w * 64 + row];
