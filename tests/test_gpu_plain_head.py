@@ -49,8 +49,9 @@ def test_keys_behind_the_length_may_hold_anything():
         assert np.isfinite(got[True]).all() and np.array_equal(got[True], got[False])
 
 
-# columns around a tile of 16, a turn of 2048 and one round of 256 workgroups (4096 for the wide contraction), where the general product takes over
-@pytest.mark.parametrize("d,V", [(256, 1), (256, 15), (256, 17), (60, 257), (256, 2047), (257, 2049), (256, 4112), (257, 4096), (257, 4097)])
+# columns around a tile of 16, a turn of 2048 and the last that a rule takes before the general product does (two rounds of 256 workgroups for contractions
+# of at most 256, one for others, 2^24 weights)
+@pytest.mark.parametrize("d,V", [(256, 1), (256, 15), (256, 17), (60, 257), (256, 2047), (257, 2049), (256, 4112), (257, 4096), (257, 4097), (256, 8192), (256, 8193), (4096, 4096)])
 def test_unembedding_and_arg_max(d, V):
     """Logits are sums of d products of order 0.02, 1 and 1: bound d eps times the largest partial sum, 2^-24 * 16 d; ids where the margin is clear of
     it, and ties to the lowest index."""
@@ -85,3 +86,31 @@ def test_unembedding_and_arg_max(d, V):
     finally:
         torch.cuda.synchronize()
         B.la_free_model(model)
+
+
+@pytest.mark.parametrize("d,V", [(60, 8192), (256, 8192), (257, 4096), (1000, 4096), (4096, 4096)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_small_product_and_the_general_one_sum_alike(d, V, dtype, monkeypatch):
+    """The last size of either rule, and one column of zeros more: the same bits, since that column wins nowhere."""
+    import torch
+    from paper_2602_16760_amd import binding as B
+    monkeypatch.setenv("LA_FORCE_GENERIC", "1")
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(d + V)
+    u = (torch.randn(d, V, generator=g, device="cuda") * 0.02).to(t)
+    gain = torch.rand(d, generator=g, device="cuda") + 0.5
+    hidden = [torch.randn(rows, d, generator=g, device="cuda") for rows in (1, 17, 64)]
+    got = []
+    for columns in (V, V + 1):
+        shape = synth.ModelShape("head", 1, d, 1, 1, 16, 16, columns, 1e-5, 1e4, dtype)
+        model = B.la_init_model(shape, None, gain, torch.cat([u, torch.zeros(d, columns - V, dtype=t, device="cuda")], 1).contiguous())
+        try:
+            for h in hidden:
+                ids, top2 = torch.zeros(len(h), dtype=torch.int32, device="cuda"), torch.zeros(len(h), 2, device="cuda")
+                B.la_unembed_argmax(model, h, ids, top2)
+                got.append((ids, top2))
+        finally:
+            torch.cuda.synchronize()
+            B.la_free_model(model)
+    for (a, x), (b, y) in zip(got[:3], got[3:]):
+        assert (x > 0).all() and torch.equal(a, b) and torch.equal(x, y)
