@@ -399,17 +399,18 @@ static bool plain_heads(const la_model *m, const la_kv *kv) { return m->d.head_d
 static bool plain_attention_pays(const la_model *m, const la_kv *kv) {
   return plain_heads(m, kv) && m->d.n_q_heads * ceil_div(m->d.head_dim, 64) <= 16;
 }
-// Its products take layers that also fit 32-bit offsets, of up to 16 M weights, whose products are one round of the chip each: a workgroup
-// of eight waves with six slices of its operands on their way has a CU to itself, with two slices (contractions of at most 256)
-// there is room for two.  A second round reads all activations again and waits as long as the first.  Both sides of the lines, a forward of two
-// layers at 1 / 17 / 48 / 64 rows, L = 47, us, these products (the general ones):
-//   512 wide, 2048 of gate: bf16 68 / - / 109 / 127 (72 / - / 111 / 124), fp32 60 / - / 104 / 123 (71 / - / 111 / 125)
-//   512 wide, 2064 of gate: bf16 70 / - / 119 / 138 (73 / - / 110 / 122), fp32 62 / - / 114 / 135 (72 / - / 111 / 123)
-//   256 wide, 4096 of gate: bf16 80 / 102 / 127 / 149 (83 / 106 / 128 / 143), fp32 66 / 92 / 122 / 145 (81 / 103 / 126 / 142)
-//   256 wide, 8192 of gate: bf16 119 / 152 / 201 / 243 (125 / 157 / 192 / 220), fp32 94 / 135 / 184 / 225 (121 / 150 / 188 / 215)
-//   1024 wide, 2752 of gate: bf16 104 / 132 / - / 208 (99 / 125 / - / 175), fp32 92 / 124 / - / 205 (100 / 126 / - / 176)
-//   1536 wide, 2048 of gate (16.5 M): bf16 110 / - / 177 / 212 (110 / - / 182 / 210), fp32 109 / - / 167 / 200 (109 / - / 180 / 207)
-//   2048 wide, 2048 of gate (25 M): bf16 130 / - / 201 / 250 (129 / - / 213 / 250), fp32 137 / - / 206 / 249 (127 / - / 211 / 249)
+// Its products take layers that also fit 32-bit offsets, of up to 16 M weights, whose products are one round of the chip each: a workgroup of eight waves with
+// six slices of its operands on their way (sixteen with three into the residual stream) has a CU to itself, with two slices (contractions of at most 256) there
+// is room for two.  A second round reads all activations again and waits as long as the first.  Both sides of the lines, a forward of two layers at 1 / 17 / 48
+// / 64 rows, L = 47, heads of 64 channels, fp32 (bf16 the same or up to 7 % less, 13 % at one row), us, these products (the general ones):
+//   512 wide, 2048 of gate: 61 / 73 / 95 / 111 (74 / 92 / 111 / 125); 2064: 62 / 79 / 103 / 122 (77 / 94 / 111 / 123)
+//   256 wide, 4096 of gate: 66 / 81 / 110 / 130 (85 / 106 / 125 / 141); 8192: 87 / 114 / 165 / 202 (119 / 150 / 187 / 214)
+//   768 wide, 2064 of gate: 67 / 89 / 120 / 143 (81 / 99 / 123 / 138)
+//   1024 wide, 2752 of gate: 85 / 110 / 155 / 187 (100 / 124 / 154 / 176)
+//   1536 wide, 2048 of gate (16.5 M): 103 / 120 / 159 / 190 (113 / 144 / 181 / 207); 2064: 105 / 132 / 181 / 218 (113 / 143 / 180 / 205)
+//   2048 wide, 2048 of gate (25 M): 131 / 150 / 194 / 234 (131 / 167 / 211 / 250)
+// (The lines were drawn when these products took up to 15 % longer: a second round still loses at 64 rows where the activations are wide, but not 256 wide, and
+// layers of 25 M weights would gain.)
 // The rule does not ask for the rows: the two kinds of products round differently, and a row must not depend on the block it is in.
 constexpr size_t PL_LAYER_WEIGHTS = (size_t)1 << 24;
 static bool plain_round(int K, int workgroups) { return workgroups <= (K <= 2 * 16 * PL_WAVES ? 2 : 1) * 256; }

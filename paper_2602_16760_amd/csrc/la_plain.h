@@ -81,18 +81,22 @@ __device__ __forceinline__ void rotation(int pos, int i, int half, double theta,
   *s = (float)ds;
 }
 
-// One product.  A workgroup takes 16 columns and all rows of a block (64 rows of a prompt); its eight waves share the contraction, 16 deep at a time (the same order as
-// gemm_generic_kernel's), NP slices of it on their way at once, and their sums are added in gemm_generic_kernel's order, an element per thread.
+// One product.  A workgroup takes 16 columns and all rows of a block (64 rows of a prompt); its eight waves share the contraction, 16 deep at a time (the same
+// order as gemm_generic_kernel's), NP slices of it on their way at once, and their sums are added in gemm_generic_kernel's order, an element per thread (but
+// where sixteen waves share a contraction, below).
 //   QKV: eight channels of the lower half of a head and their rotation partners; rotates, and writes K and V to the cache.
 //   GLU: eight channels of gate and the same of up.
 //   STORE: the columns as they are (the unembedding).
 //   QKV_FIRST: QKV of the first layer of a call, where more waves make the rotation table meanwhile, each workgroup the pairs of its own tile
 //   (those of head 0 leave them for the layers behind it): a launch in front of the layers cost 2.9 us, the same work in front of the product 1.5.
+//   RESID: a contraction of more than 256 is shared by sixteen waves, three slices each on their way; the upper half's sums are added to the lower half's first.
 // Bound: a launch, the weights' way from memory (each is read by one wave) and the sums' through LDS.  Step of the tiny shape (256
-// wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below; -> 56.9 with the table, the unembedding and the arg-max in
+// wide, 2 layers, 17 rows): 76.0 -> 62.6 us with these and the attention below; -> 57.9 with the table, the unembedding and the arg-max in
 // products of this kind, what an epilogue adds to or rotates by requested with the operands, and K and V of the attention's first piece with q.
-// A wide contraction into the residual stream (down: 16 workgroups of the tiny shape, 36 loads a wave) is shared by sixteen waves, whose upper half's
-// sums are added to the lower half's first: tiny shape, 17 rows, 57.9 -> 56.1 us a step, 64 rows 81.1 -> 80.2, error against 64 bits 2.5e-7 -> 2.4e-7.
+// Eight waves / sixteen for RESID, a captured step of two fp32 layers, us at 17 and 64 rows: 688 channels of gate 52.1 / 52.1 and 73.8 / 74.2 (error against 64
+// bits 2.5e-7 / 2.4e-7), 512 wide and 2048 channels 85.5 / 83.8 and 136.7 / 131.8, 256 wide and 4096 channels 96.6 / 93.1 and 154.1 / 147.5.  That a product
+// has a norm is known when it is compiled: a test at run time cost registers (the sixteen waves' four row tiles 129 of 128, and scratch memory for the last)
+// and 3 to 7 % of these steps.
 constexpr int pl_waves(int kind, int np) { return kind == PL_RESID && np > 2 ? 2 * PL_WAVES : PL_WAVES; }
 template <typename T, int MT, int KIND0, int NP0>
 __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0)) void plain_product_kernel(PlProduct p) {

@@ -73,7 +73,8 @@ struct PfTile {
   int per_cu;
   float t_full, t_single;  // us per k-tile of a round that fills the chip, and of one with a workgroup per CU at most
 };
-// (from the products of the 7B shape at 77 .. 1023 rows, launch overhead included)
+// (from the products of the 7B shape at 77 .. 1023 rows, launch overhead included, before a step's requests were dealt out between its products: a launch takes
+// 5 to 20 % less now; what is chosen by them is measured below)
 constexpr PfTile PF_TILES[] = {
     {16, 14, 1, 0.85f, 0.85f}, {16, 10, 1, 0.66f, 0.66f}, {16, 8, 1, 0.57f, 0.57f}, {8, 12, 1, 0.50f, 0.50f}, {8, 8, 2, 0.70f, 0.45f}, {8, 4, 2, 0.52f, 0.30f},
 };
@@ -89,9 +90,9 @@ struct PfProduct {
 // XCDs evenly, so that the chip counts as one pool of CUs.)  Only
 // the projections that add to the residual stream are sliced: at 1023 rows a 4096-column matrix has 128 tiles of 256 x 128
 // for 256 CUs (down in one slice 182 us, in two 111 + 3 us more in pf_norm), at 77 rows 32 of 128 x 128 (eight slices).
-// Against every tile and number of slices, 17 lengths of 65 .. 2048 rows, 7B and 12B shapes: within 5 % of the best in 115 of 128
-// products; the others are O (at most 400 rows, up to 23 %: 32 us against 26) and down (at most 256 rows, 6 %), which would take
-// fewer slices of smaller tiles.
+// Against every tile, cut or not, and number of slices, 64 lengths of 65 .. 2047 rows, 7B and 12B shapes: what a product takes (pf_route) is within 5 % of the
+// best in 591 of 640; the others are O of at most 512 rows (up to 36 %: 21.9 us against 16.1), down of 129 to 160 (12 %) and the last layer's K and V of 1100
+// to 1200 (32 %).
 inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus, int &tile, int &S) {
   auto up = [](int a, int b) { return (a + b - 1) / b; };
   float best = 0.f;
@@ -128,8 +129,10 @@ inline float pf_choose(const PfProduct &p, int max_split, int part_rows, int cus
 // Beyond five row tiles in seven slices at most: with eight, 256 workgroups, a launch takes 4 us more now and then, on some cards most of the time.  Down of
 // 4096 x 14336, us in the mean of 100 on two cards, eight slices / seven / tiles: 80 rows 29.0, 29.2 / 29.0, 29.5 / 31.1, 31.2; 97 rows 32.4, 34.5 / 31.9, 32.5 /
 // 32.6, 32.6; 112 rows 33.6, 36.7 / 33.0, 34.2 / 33.6, 33.7.
-// Gate/up beyond 256 rows: 10 or 12 row tiles x 14 columns where whole rounds of them cost less than pf_choose's best: us per k-tile 0.64 and 0.69
-// against 0.80 of 16 row tiles.  300 rows 102 -> 89, 600 rows 178 -> 160, 700 rows 208 -> 177.
+// Gate/up beyond 128 rows: 10 or 12 row tiles x 14 columns where whole rounds of them cost less than pf_choose's best, at 0.64 and 0.69 us per k-tile against
+// PF_TILES' (the 16 row tiles of that width take 0.70 there, not 0.85, at 257 rows; the constants are kept because what they choose is right): 7B shape, 300
+// rows 91 -> 82, 600 rows 164 -> 143, 700 rows 176 -> 160, 1600 rows 374 -> 354.  Over 15 widths up to 512 rows and nine up to 2047 they take a slower kernel
+// only of 10240 channels at 257 and 288 rows (71 -> 75).
 // QKV of 129 to 512 rows: a quarter of the rows and 6 columns a workgroup, while that is one round (7B and 12B shapes: 64 column groups).
 // 150 rows 33 -> 29, 200 rows 36.6 -> 32.0, 300 rows 51 -> 38, 400 rows 56 -> 45, 500 rows 59 -> 52.
 // Beyond 256 rows (five row tiles), where pf_choose takes its smallest tiles (fewer columns: the last layer's K and V, narrow models), only while the
