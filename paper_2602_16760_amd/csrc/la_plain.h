@@ -96,7 +96,8 @@ __device__ __forceinline__ void rotation(int pos, int i, int half, double theta,
 // Eight waves / sixteen for RESID, a captured step of two fp32 layers, us at 17 and 64 rows: 688 channels of gate 52.1 / 52.1 and 73.8 / 74.2 (error against 64
 // bits 2.5e-7 / 2.4e-7), 512 wide and 2048 channels 85.5 / 83.8 and 136.7 / 131.8, 256 wide and 4096 channels 96.6 / 93.1 and 154.1 / 147.5.  That a product
 // has a norm is known when it is compiled: a test at run time cost registers (the sixteen waves' four row tiles 129 of 128, and scratch memory for the last)
-// and 3 to 7 % of these steps.
+// and 3 to 7 % of these steps.  A's rows are loaded 16 bytes at a time wherever they begin (word by word where a row was not a multiple of 16 bytes, or A not
+// aligned to them, the unembedding 1024 x 4096 of 64 rows took 39.8 us, 19.3 so, 22.5 with the general product; 254 x 777 11.9, 8.3 and 10.1).
 constexpr int pl_waves(int kind, int np) { return kind == PL_RESID && np > 2 ? 2 * PL_WAVES : PL_WAVES; }
 template <typename T, int MT, int KIND0, int NP0>
 __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST ? 64 * MT : 0)) void plain_product_kernel(PlProduct p) {
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
     return;
   }
   const __amdgpu_buffer_rsrc_t rw = pl_rsrc(p.W, (size_t)K * p.ldw * sizeof(T)), ra = pl_rsrc(p.A + (size_t)row0 * p.lda, (size_t)M * p.lda * 4), rg = pl_rsrc(p.gain, (size_t)K * 4);
-  const bool vec = (((uintptr_t)p.A | (size_t)p.lda * 4) % 16 == 0) && K % 4 == 0;
+  const bool quads = K % 4 == 0;
   constexpr bool LEN = KIND == PL_QKV || KIND == PL_RESID;
   int L = 0;
   if (LEN) L = *p.L_dev;
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(64 * pl_waves(KIND0, NP0) + (KIND0 == PL_QKV_FIRST 
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const unsigned o = (unsigned)((16 * mt + c16) * p.lda + k) * 4u;  // (rows past the end: zeros)
-        if (vec) {
+        if (quads || k0 + 16 * WV * n + 16 <= K) {  // (16 bytes from any element on: such loads want addresses in whole words)
           x[n][mt] = __builtin_bit_cast(pl_f4, __builtin_amdgcn_raw_buffer_load_b128(ra, k < K ? o : PL_OOB, 0, 0));
         } else {
 #pragma unroll

@@ -88,10 +88,11 @@ def test_unembedding_and_arg_max(d, V):
         B.la_free_model(model)
 
 
-@pytest.mark.parametrize("d,V", [(60, 8192), (256, 8192), (257, 4096), (1000, 4096), (4096, 4096)])
+@pytest.mark.parametrize("d,V", [(60, 8192), (255, 8192), (256, 8192), (257, 4096), (1000, 4096), (1002, 4096), (4096, 4096)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_the_small_product_and_the_general_one_sum_alike(d, V, dtype, monkeypatch):
-    """The last size of either rule, and one column of zeros more: the same bits, since that column wins nowhere."""
+@pytest.mark.parametrize("shift", [0, 1])
+def test_the_small_product_and_the_general_one_sum_alike(d, V, dtype, shift, monkeypatch):
+    """The last size of either rule, and one column of zeros more: the same bits, since that column wins nowhere.  Hidden states on any word."""
     import torch
     from paper_2602_16760_amd import binding as B
     monkeypatch.setenv("LA_FORCE_GENERIC", "1")
@@ -99,7 +100,7 @@ def test_the_small_product_and_the_general_one_sum_alike(d, V, dtype, monkeypatc
     g = torch.Generator(device="cuda").manual_seed(d + V)
     u = (torch.randn(d, V, generator=g, device="cuda") * 0.02).to(t)
     gain = torch.rand(d, generator=g, device="cuda") + 0.5
-    hidden = [torch.randn(rows, d, generator=g, device="cuda") for rows in (1, 17, 64)]
+    hidden = [torch.randn(rows * d + shift, generator=g, device="cuda")[shift:].view(rows, d) for rows in (1, 17, 64)]
     got = []
     for columns in (V, V + 1):
         shape = synth.ModelShape("head", 1, d, 1, 1, 16, 16, columns, 1e-5, 1e4, dtype)
