@@ -316,7 +316,7 @@ __global__ __launch_bounds__(PL_THREADS) void plain_attention_kernel(const float
       asm volatile("" : "+v"(at));  // (one register, not 64 offsets kept ahead)
     }
   };
-  // q, K and V of the first piece are requested together, q first (loads come back in order)
+  // q first: loads come back in order
   float q_in[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) q_in[u] = (int)(threadIdx.x + u * blockDim.x) < dh ? q[(size_t)b * ldq + hq * dh + threadIdx.x + u * blockDim.x] : 0.f;
