@@ -124,12 +124,15 @@ def _check(rc):
         raise LaError(rc, lib.la_last_error().decode())
 
 
+_torch = torch._C
+
+
 def _stream(stream=None):
     """Handle of `stream`, of the current stream without one.  (The stream object that torch.cuda.current_stream() makes for it
     costs 2.9 us, more than half of a launch, and torch.cuda.current_device() looks for the runtime's start first; a call of a small
     kernel waits for the host.  Both names are looked up here: a torch built without a GPU has neither, and the host functions need none.)"""
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return _torch._cuda_getCurrentRawStream(_torch._cuda_getDevice())
     return stream.cuda_stream
 
 
@@ -239,23 +242,19 @@ def la_free_pool(pool):
 
 
 @functools.lru_cache(maxsize=64)
-def _descriptor(W, N, G):
+def _lookahead(W, N, G):
+    """Reference to a descriptor, which the library only reads.  It is kept by three Python integers, the numbers that a call's arguments hold
+    (operator.index): an argument itself may change in place (a 0-d tensor, whose hash is its identity) or have no hash (a 0-d array)."""
     return C.byref(la_lookahead_desc(W, N, G))
 
 
-def _lookahead(W, N, G):
-    """Reference to a descriptor, which the library only reads.  It is kept by the numbers that the arguments hold at this call: an
-    argument itself may change in place (a 0-d tensor, whose hash is its identity) or have no hash (a 0-d array)."""
-    return _descriptor(index(W), index(N), index(G))
-
-
 def la_state_init(pool, kv, W, N, G, prompt, Bp, seed_pool, state, stream=None):
-    _check(lib.la_state_init(pool, kv, _lookahead(W, N, G), _ptr(prompt), prompt.shape[0], Bp, int(seed_pool), _ptr(state),
+    _check(lib.la_state_init(pool, kv, _lookahead(index(W), index(N), index(G)), _ptr(prompt), prompt.shape[0], Bp, int(seed_pool), _ptr(state),
                              _stream(stream)))
 
 
 def la_ngram_accept(pool, kv, W, N, G, ids, state, emitted, max_total, stream=None):
-    _check(lib.la_ngram_accept(pool, kv, _lookahead(W, N, G), _ptr(ids), _ptr(state), _ptr(emitted), max_total, _stream(stream)))
+    _check(lib.la_ngram_accept(pool, kv, _lookahead(index(W), index(N), index(G)), _ptr(ids), _ptr(state), _ptr(emitted), max_total, _stream(stream)))
 
 
 def la_prefill(model, kv, tok, L0=0, stream=None):
